@@ -215,8 +215,8 @@ def tolerance(case):
     if case["op"] == "encode":
         # codes are whole numbers with one right value; scales are float64 results stored in float32
         return {"rel": 1e-7, "max": 5e-7, "differ": 0.0}
-    # scores are float32 sums of d products (4e-8 to 1.8e-7 off float64) (fixed-point or float32 tables, float32 rotated queries);
-    # neighbours of a list may change places where their scores agree to rounding
+    # scores are sums of d products from float32 rotated queries, by fixed-point or float32 tables: 4e-8 to
+    # 1.8e-7 off float64; neighbours of a list may change places where their scores agree to rounding
     return {"rel": 8e-7, "max": 4e-6, "differ": 0.002}
 
 
