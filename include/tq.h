@@ -322,7 +322,11 @@ tq_status tq_search_postfilter(const tq_index *idx, const float *Q_dev,
 
 /* Scan path selection for tq_search_ex (section II-B step 5; the batched
  * path is this library's, not the paper's).
- *  TQ_PATH_AUTO  the single-query scan.
+ *  TQ_PATH_AUTO  whichever of the two is faster for the number of queries and
+ *                the size of the index; results are the single-query scan's.
+ *                Enqueues device work only (no synchronisation).  A workspace
+ *                with room for the single-query scan alone (the size of
+ *                TQ_PATH_LUT) is accepted and selects it.
  *  TQ_PATH_LUT   one pass over the code store per query, with the query's
  *                lookup table in LDS.
  *  TQ_PATH_MFMA  one pass per tile of 32 queries: approximate float16 scores
@@ -332,10 +336,11 @@ tq_status tq_search_postfilter(const tq_index *idx, const float *Q_dev,
  *                per-query certificate -- a rigorous bound on the
  *                approximation error -- proves that the exact top k lies
  *                among the candidates; queries without one are re-run on the
- *                LUT path (see tq_last_search_fallbacks).  Needs 4-bit codes,
+ *                LUT path by launches of the same call (see
+ *                tq_last_search_fallbacks).  Needs 4-bit codes,
  *                d % 256 == 0, d <= 1792, k <= 256 and n_tenants <= 4096,
  *                else TQ_EUNSUPPORTED.  Synchronises `stream` once per call, to
- *                read the certificates on the host. */
+ *                read the number of re-run queries on the host. */
 typedef enum {
     TQ_PATH_AUTO = 0,
     TQ_PATH_LUT = 1,

@@ -1099,6 +1099,26 @@ static int scan_grid() {
     return cus > 0 ? cus : 256;
 }
 
+// Whether TQ_PATH_AUTO answers nq queries on the batched path (same scores
+// and lists as the scan's, queries without a certificate re-run on the scan
+// within the call's launches).  The scan costs every query a pass over the
+// codes (about 6.2 TB/s) and 9 us of table build and merge; a tile of 32
+// queries costs one pass (about 5 TB/s) and 70 us of selection and rescoring,
+// once 20 us more per call.  Measured at d = 1536, 4 bits, k = 10, in us a
+// call, scan / batched: 10,000 vectors 63 / 90 for 4 queries, 100 / 92 for
+// 8, 1,331 / 233 for 128; 100,000 vectors 85 / 97 for 2, 125 / 99 for 4;
+// 1,000,000 vectors 170 / 248 for 1, 300 / 249 for 2, 17,185 / 811 for 128.
+static bool batch_pays(const ScanShape &sh, int64_t nq) {
+    const double bytes = (double)sh.nblk * sh.chunks * 1024.0;
+    const double tiles = (double)((nq + 31) / 32);
+    const double scan_us = (double)nq * (9.0 + bytes / 6.2e6);
+    return scan_us > 20.0 + tiles * (70.0 + bytes / 5.0e6);
+}
+
+static bool auto_batch(const tq_index *x, const ScanShape &sh, int64_t nq, int k) {
+    return !x->calibrated && mfma_search_supported(sh, k) && batch_matrix_fits(sh) && batch_pays(sh, nq);
+}
+
 static bool use_mfma(const ScanShape &sh, int k, int base) {
     return base == TQ_PATH_MFMA && mfma_search_supported(sh, k);
 }
@@ -1152,7 +1172,11 @@ tq_status tq_search_workspace_size(const tq_index *idx, int64_t nq, int32_t k, i
         return fail(TQ_EUNSUPPORTED, "matrix-core path does not take a TQ+ calibrated index");
     tq_status st = device_ready();
     if (st != TQ_OK) return st;
-    *bytes_out = search_bytes(shape_of(idx), nq, k, base, idx->calibrated);
+    const ScanShape sh = shape_of(idx);
+    size_t bytes = search_bytes(sh, nq, k, base, idx->calibrated);
+    if (base == TQ_PATH_AUTO && auto_batch(idx, sh, nq, k))
+        bytes = std::max(bytes, mfma_search_workspace_bytes(sh, nq, k, scan_grid()));
+    *bytes_out = bytes;
     return TQ_OK;
 }
 
@@ -1194,6 +1218,10 @@ tq_status tq_search_ex(const tq_index *idx, const float *Q_dev, int64_t nq, int3
     const size_t need = search_bytes(sh, nq, k, base, idx->calibrated);
     if (workspace_bytes < need)
         return fail(TQ_EINVAL, "workspace too small: need " + std::to_string(need) + " bytes");
+    // a workspace sized for the scan alone is still taken (by the scan)
+    const bool batched = use_mfma(sh, k, base) ||
+                         (base == TQ_PATH_AUTO && !filter.any() && auto_batch(idx, sh, nq, k) &&
+                          workspace_bytes >= mfma_search_workspace_bytes(sh, nq, k, grid));
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (idx->n == 0) {
         // nothing indexed: every slot is padding
@@ -1215,8 +1243,7 @@ tq_status tq_search_ex(const tq_index *idx, const float *Q_dev, int64_t nq, int3
         st = rotation_dev(&idx->rot, &R);
         if (st != TQ_OK) return st;
         float *qr = static_cast<float *>(workspace_dev);
-        int *bounds = use_mfma(sh, k, base) ? nullptr
-                                            : lut_search_bounds(sh, nq, k, grid, workspace_dev);
+        int *bounds = batched ? nullptr : lut_search_bounds(sh, nq, k, grid, workspace_dev);
         hipError_t e = rotate_rows_f32(Q_dev, nq, idx->d, R, qr, s, bounds, bounds ? nq : 0,
                                        kBoundInit);
         if (e != hipSuccess) return hip_fail(e, "query rotation");
@@ -1232,14 +1259,14 @@ tq_status tq_search_ex(const tq_index *idx, const float *Q_dev, int64_t nq, int3
         if (st != TQ_OK) return st;
         Qrot = qr;
     }
-    if (use_mfma(sh, k, base)) {
+    if (batched) {
         int n_fallback = 0;
         float cmax16 = 0.f, dmax = 0.f;
         centroid_half_bounds(idx, &cmax16, &dmax);
         hipError_t e = mfma_search(sh, idx->codes, idx->scales, scale_max_dev(idx), idx->tenants,
                                    idx->summ, idx->cents_dev, cmax16, dmax, Qrot, nq, k,
                                    allow_dev, grid, workspace_dev, ids_dev, scores_dev,
-                                   &n_fallback, s);
+                                   base == TQ_PATH_MFMA ? &n_fallback : nullptr, s);
         if (e != hipSuccess) return hip_fail(e, "matrix-core search");
         if (idx->idmap && (e = map_ids(ids_dev, nq * k, idx->ext, s)) != hipSuccess)
             return hip_fail(e, "id mapping");

@@ -26,8 +26,9 @@
 //     them, and a certificate: with E a rigorous bound on |approximate -
 //     exact| for every vector, a vector outside the candidates scores at
 //     most amin + E; if that is below the k-th exact score the top k is
-//     proven, otherwise the query is flagged and the caller re-runs it on
-//     the single-query scan.
+//     proven, otherwise the query's row joins the device list of queries
+//     that the single-query scan, launched behind the batched kernels,
+//     answers (it leaves at once when the list is empty: no host round trip).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -36,7 +37,6 @@
 #include <cstdint>
 #include <type_traits>
 #include <utility>
-#include <vector>
 
 #include "kernels.h"
 #include "lds_dma.h"
@@ -110,13 +110,16 @@ struct QInfo {
 // certificate is checked.
 __global__ void prep_kernel(const float *__restrict__ Q, int nq, int d, const float *smax_p,
                             float cmax16, float dmax, _Float16 *__restrict__ q16,
-                            QInfo *__restrict__ info, int *__restrict__ zero, int nzero) {
+                            QInfo *__restrict__ info, int *__restrict__ zero, int nzero,
+                            int *__restrict__ zero1) {
     __shared__ float red_m[SEL_THREADS / 64];
     __shared__ double red_1[SEL_THREADS / 64], red_2[SEL_THREADS / 64];
     const int q = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (q == 0)
+    if (q == 0) {
         for (int i = tid; i < nzero; i += SEL_THREADS) zero[i] = 0;   // the score kernel's tickets
+        if (zero1 && tid == 0) *zero1 = 0;                            // the search's uncertified count
+    }
     const float *row = Q + (int64_t)q * d;
     float m = 0.f;
     double s1 = 0.0, s2 = 0.0;
@@ -890,8 +893,17 @@ struct RescoreParams {
     const QInfo *info;
     int64_t *ids;              // [nqt][k]
     float *scores;
-    int *flags;                // [nqt]: 1 = not certified
     int d, bits, chunks, lut_words, k;
+    // queries whose top k is not proven, over all passes of the search:
+    // their number, rows, rotated queries, allowlists and global bounds
+    int *fb_count;
+    int *fb_rows;
+    float *fb_q;
+    uint64_t *fb_allow;
+    int *fb_bound;
+    const uint64_t *allow;     // [nqt][W] or null
+    int W;
+    int q0;                    // the pass's first row
 };
 
 // One workgroup per query, KC = 64 S candidate slots.
@@ -907,6 +919,9 @@ struct RescoreParams {
 //     most amin, so its exact score is at most amin + 2^-11 |amin| +
 //     2^-25 norm + err; if that is below the k-th exact score it cannot
 //     enter the top k.
+//  5. Without a certificate the workgroup appends the query's row, its
+//     rotated coordinates and allowlist to the list that the single-query
+//     scan takes.
 template <int S>
 __global__ __launch_bounds__(kTableThreads) void rescore_kernel(RescoreParams p) {
     constexpr int KC = 64 * S;
@@ -917,7 +932,7 @@ __global__ __launch_bounds__(kTableThreads) void rescore_kernel(RescoreParams p)
     int *sums = reinterpret_cast<int *>(red + 16);   // [KC]: integer sums, then ranks
     float *run_s = reinterpret_cast<float *>(sums + KC);
     int *run_i = reinterpret_cast<int *>(run_s + KC);
-    int *sh = run_i + KC;                   // [0] valid count, [1] k-th exact score
+    int *sh = run_i + KC;                   // [0] valid count, [1] k-th exact score, [2] list slot
     const int q = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int run = wave % S, slice = wave / S;
@@ -1026,8 +1041,23 @@ __global__ __launch_bounds__(kTableThreads) void rescore_kernel(RescoreParams p)
         const double amin = (double)amin_s * qi.norm;
         const double reach = amin + ldexp(1.0, -11) * fabs(amin) + ldexp(1.0, -25) * qi.norm +
                              (double)qi.err;
-        const bool cert = st == kSelAll || (st == kSelBound && reach < (double)ek);
-        p.flags[q] = cert ? 0 : 1;
+        // an error bound that is not finite (scales or queries that are not)
+        // proves nothing
+        const bool cert = qi.err < INFINITY &&
+                          (st == kSelAll || (st == kSelBound && reach < (double)ek));
+        sh[2] = cert ? -1 : atomicAdd(p.fb_count, 1);
+    }
+    __syncthreads();
+    const int slot = sh[2];
+    if (slot < 0) return;
+    for (int j = tid; j < p.d; j += kTableThreads)
+        p.fb_q[(int64_t)slot * p.d + j] = p.qrot[(int64_t)q * p.d + j];
+    if (p.allow)
+        for (int w = tid; w < p.W; w += kTableThreads)
+            p.fb_allow[(int64_t)slot * p.W + w] = p.allow[(int64_t)q * p.W + w];
+    if (tid == 0) {
+        p.fb_rows[slot] = p.q0 + q;
+        if (p.fb_bound) p.fb_bound[slot] = kBoundInit;
     }
 }
 
@@ -1728,41 +1758,11 @@ __global__ void fill_order_keys(int *p, int n) {
     for (int i = threadIdx.x; i < n * kBoundStride; i += blockDim.x) p[i] = fkey(-INFINITY);
 }
 
-__global__ void gather_allow(const uint64_t *__restrict__ src, const int *__restrict__ rows, int nr,
-                             int W, uint64_t *__restrict__ dst) {
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < (int64_t)nr * W;
-         e += (int64_t)gridDim.x * blockDim.x) {
-        const int r = (int)(e / W);
-        dst[e] = src[(int64_t)rows[r] * W + (e - (int64_t)r * W)];
-    }
-}
-
-__global__ void gather_rows(const float *__restrict__ src, const int *__restrict__ rows, int nr,
-                            int d, float *__restrict__ dst) {
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < (int64_t)nr * d;
-         e += (int64_t)gridDim.x * blockDim.x) {
-        const int r = (int)(e / d);
-        dst[e] = src[(int64_t)rows[r] * d + (e - (int64_t)r * d)];
-    }
-}
-
-__global__ void scatter_results(const int64_t *__restrict__ ci, const float *__restrict__ cs,
-                                const int *__restrict__ rows, int nr, int k,
-                                int64_t *__restrict__ ids, float *__restrict__ scores) {
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < (int64_t)nr * k;
-         e += (int64_t)gridDim.x * blockDim.x) {
-        const int r = (int)(e / k);
-        const int64_t dst = (int64_t)rows[r] * k + (e - (int64_t)r * k);
-        ids[dst] = ci[e];
-        scores[dst] = cs[e];
-    }
-}
-
 __global__ void scale_max_kernel(const float *__restrict__ s, int64_t n, int *smax_bits) {
     int m = 0;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
-        const int b = __float_as_int(s[i]);   // scales are >= 0: bit order is value order
+        const int b = __float_as_int(s[i]) & 0x7FFFFFFF;   // |s|: bit order is value order
         m = b > m ? b : m;
     }
     for (int o = 32; o > 0; o >>= 1) {
@@ -1795,8 +1795,8 @@ void with_slots(int KC, Fn fn) {
 }
 
 struct BatchLayout {
-    size_t q16, info, approx, bmax, cand_s, cand_i, top_i, amin, state, gbound, tickets, flags, rows, qc,
-        allow_c, ids_c, scores_c, lut, total;
+    size_t q16, info, approx, bmax, cand_s, cand_i, top_i, amin, state, gbound, tickets, count, rows, qc,
+        allow_c, lut, total;
     // wide passes
     size_t w_q16, w_info, w_qfrag, w_qf, w_pil, w_theta, w_pcn, w_pci, w_pcs, w_cs, w_ci, w_cn,
         w_top, w_amin, w_state;
@@ -1825,6 +1825,19 @@ WideGeom wide_geom(const ScanShape &s, int NG, int grid, int KC) {
     S = (S + 7) / 8 * 8;
     w.S = std::min(std::max(S, 16), 512);
     return w;
+}
+
+// Whether a pass over nq more queries takes the wide kernels: more queries
+// than two tiles, and an index of which the pilot (at most 65,536 vectors) is
+// large enough a part -- about KC ntiles / npil candidates per query must fit
+// the final selection and about 2 per + 16 a workgroup's list, with room for
+// chance; beyond that (N above 6.4M at k = 10, 1.6M at k = 100) most
+// queries would overflow and fall back.
+bool wide_pass(const ScanShape &s, int64_t nq, int KC, int grid) {
+    if (nq <= kWideMinQ || s.chunks < kWideMinChunks || grid > PS_THREADS) return false;
+    const WideGeom w = wide_geom(s, WD_NG, grid, KC);
+    const double part = (double)w.ntiles / (double)w.npil;
+    return KC * part <= 0.8 * kFinalMax && 2.0 * KC * part / grid + 16.0 <= 512.0;
 }
 
 // Query slots of a wide pass of nqt > kWideMinQ queries.
@@ -1860,21 +1873,17 @@ BatchLayout batch_layout(const ScanShape &s, int64_t nq, int k, int grid) {
     o += align256(kTile * kBoundStride * 4);
     L.tickets = o;
     o += align256((size_t)grid * kTicketStride * 4);
-    L.flags = o;
-    o += align256((size_t)nq * 4);
+    L.count = o;
+    o += align256(4);
     L.rows = o;
     o += align256((size_t)nq * 4);
     L.qc = o;
     o += align256((size_t)nq * s.d * sizeof(float));
     L.allow_c = o;
     o += align256((size_t)nq * s.W * sizeof(uint64_t));
-    L.ids_c = o;
-    o += align256((size_t)nq * k * 8);
-    L.scores_c = o;
-    o += align256((size_t)nq * k * 4);
     L.lut = o;
     o += lut_search_workspace_bytes(s, nq, k, grid);
-    if (nq > kWideMinQ && s.chunks >= kWideMinChunks && grid <= PS_THREADS) {
+    if (wide_pass(s, nq, batch_candidates(k), grid)) {
         const int KC = batch_candidates(k), PCM = 2 * KC;
         const int QP = wide_slots((int)std::min<int64_t>(nq, kWideMaxQ));
         const WideGeom w = wide_geom(s, WD_NG, grid, KC);
@@ -1944,6 +1953,11 @@ bool mfma_search_supported(const ScanShape &s, int k) {
            score_lds_bytes(s.d) <= 160 * 1024;
 }
 
+// The score matrix of a tile of 32 queries within 1 GiB (N up to 16.7M).
+bool batch_matrix_fits(const ScanShape &s) {
+    return (size_t)kTile * approx_row(s) * 2 <= (size_t)1 << 30;
+}
+
 size_t mfma_search_workspace_bytes(const ScanShape &s, int64_t nq, int k, int grid) {
     return batch_layout(s, nq, k, grid).total;
 }
@@ -1976,11 +1990,16 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
     int *state = reinterpret_cast<int *>(w8 + L.state);
     int *gbound = reinterpret_cast<int *>(w8 + L.gbound);
     int *tickets = reinterpret_cast<int *>(w8 + L.tickets);
-    int *flags = reinterpret_cast<int *>(w8 + L.flags);
+    int *count = reinterpret_cast<int *>(w8 + L.count);
+    int *rows = reinterpret_cast<int *>(w8 + L.rows);
+    float *qc = reinterpret_cast<float *>(w8 + L.qc);
+    uint64_t *allow_c = reinterpret_cast<uint64_t *>(w8 + L.allow_c);
+    void *lut_ws = w8 + L.lut;
+    int *lut_bounds = lut_search_bounds(s, nq, k, grid, lut_ws);
     const int64_t npad = approx_row(s);
     const size_t lds_scores = score_lds_bytes(s.d);
     const int KC = batch_candidates(k);   // candidates per query
-    // table, 16 floats, integer sums and sorted (score, id) runs, two counters
+    // table, 16 floats, integer sums and sorted (score, id) runs, three counters
     const size_t lds_rescore = (size_t)s.chunks * 2048 + 16 * 4 + (size_t)KC * 12 + 16;
     static bool attr_set = false;
     if (!attr_set) {
@@ -2017,7 +2036,14 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
         rp.info = qi;
         rp.ids = ids + q0 * k;
         rp.scores = scores + q0 * k;
-        rp.flags = flags + q0;
+        rp.fb_count = count;
+        rp.fb_rows = rows;
+        rp.fb_q = qc;
+        rp.fb_allow = allow_c;
+        rp.fb_bound = lut_bounds;
+        rp.allow = allow ? allow + q0 * s.W : nullptr;
+        rp.W = s.W;
+        rp.q0 = (int)q0;
         rp.d = s.d;
         rp.bits = s.bits;
         rp.chunks = s.chunks;
@@ -2030,7 +2056,7 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
         });
     };
     for (int64_t q0 = 0; q0 < nq;) {
-        if (nq - q0 > kWideMinQ && s.chunks >= kWideMinChunks && grid <= PS_THREADS) {
+        if (wide_pass(s, nq - q0, KC, grid)) {
             // a wide pass of up to kWideMaxQ queries
             const int nqt = (int)std::min<int64_t>(nq - q0, kWideMaxQ);
             const int QP = wide_slots(nqt);
@@ -2054,7 +2080,7 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
             const uint64_t *allow_p = allow ? allow + q0 * s.W : nullptr;
             hipLaunchKernelGGL(prep_kernel, dim3(nqt), dim3(SEL_THREADS), 0, stream,
                                Qrot + q0 * s.d, nqt, s.d, smax, cmax16, dmax, wq16, winfo,
-                               nullptr, 0);
+                               nullptr, 0, q0 == 0 ? count : nullptr);
             const int64_t fr = (int64_t)(s.d / 32) * QP * 4;
             hipLaunchKernelGGL(frag_kernel, dim3((int)std::min<int64_t>((fr + 255) / 256, 1024)),
                                dim3(256), 0, stream, wq16, winfo, nqt, QP, s.d, wqfrag, wqf);
@@ -2128,7 +2154,8 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
         }
         const int nqt = (int)std::min<int64_t>(nq - q0, kTile);
         hipLaunchKernelGGL(prep_kernel, dim3(nqt), dim3(SEL_THREADS), 0, stream, Qrot + q0 * s.d,
-                           nqt, s.d, smax, cmax16, dmax, q16, info, tickets, grid * kTicketStride);
+                           nqt, s.d, smax, cmax16, dmax, q16, info, tickets, grid * kTicketStride,
+                           q0 == 0 ? count : nullptr);
         ScoreParams sp{};
         sp.codes = reinterpret_cast<const uint4 *>(blocked);
         sp.scales = scales;
@@ -2189,39 +2216,17 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
         q0 += nqt;
     }
     // queries whose top k is not proven run on the single-query scan
-    std::vector<int> hf((size_t)nq);
-    hipError_t e = hipMemcpyAsync(hf.data(), flags, nq * sizeof(int), hipMemcpyDeviceToHost, stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(stream);
-    if (e != hipSuccess) return e;
-    std::vector<int> rows;
-    for (int64_t i = 0; i < nq; ++i)
-        if (hf[i]) rows.push_back((int)i);
-    *n_fallback = (int)rows.size();
-    if (rows.empty()) return hipSuccess;
-    const int nr = (int)rows.size();
-    int *rows_d = reinterpret_cast<int *>(w8 + L.rows);
-    float *qc = reinterpret_cast<float *>(w8 + L.qc);
-    int64_t *ids_c = reinterpret_cast<int64_t *>(w8 + L.ids_c);
-    float *scores_c = reinterpret_cast<float *>(w8 + L.scores_c);
-    e = hipMemcpyAsync(rows_d, rows.data(), nr * sizeof(int), hipMemcpyHostToDevice, stream);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(gather_rows, dim3(256), dim3(256), 0, stream, Qrot, rows_d, nr, s.d, qc);
-    uint64_t *allow_c = nullptr;
-    if (allow) {
-        allow_c = reinterpret_cast<uint64_t *>(w8 + L.allow_c);
-        hipLaunchKernelGGL(gather_allow, dim3(64), dim3(256), 0, stream, allow, rows_d, nr, s.W,
-                           allow_c);
-    }
     SearchFilter f;
-    f.allow = allow_c;
-    e = lut_search(s, blocked, scales, tenants, summaries, cents32, qc, nr, k, f, grid,
-                   w8 + L.lut, lut_search_workspace_bytes(s, nq, k, grid), ids_c, scores_c, stream);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(scatter_results, dim3(256), dim3(256), 0, stream, ids_c, scores_c, rows_d, nr,
-                       k, ids, scores);
-    e = hipGetLastError();
-    if (e == hipSuccess) e = hipStreamSynchronize(stream);   // host vectors above go out of scope
-    return e;
+    f.allow = allow ? allow_c : nullptr;
+    QueryRows qr;
+    qr.count = count;
+    qr.rows = rows;
+    hipError_t e = lut_search(s, blocked, scales, tenants, summaries, cents32, qc, nq, k, f, grid, lut_ws,
+                              lut_search_workspace_bytes(s, nq, k, grid), ids, scores, stream, nullptr,
+                              lut_bounds != nullptr, qr);
+    if (e != hipSuccess || !n_fallback) return e;
+    e = hipMemcpyAsync(n_fallback, count, sizeof(int), hipMemcpyDeviceToHost, stream);
+    return e == hipSuccess ? hipStreamSynchronize(stream) : e;
 }
 
 }  // namespace tq

@@ -138,15 +138,26 @@ struct SearchFilter {
     bool any() const { return allow || live || slot_allow; }
 };
 
+// Queries of a search whose number is known on the device only: *count of
+// them (at most the nq the search is launched for), query i's results going
+// to row rows[i] of the result lists.  base: queries of earlier launches.
+struct QueryRows {
+    const int *count = nullptr;
+    const int *rows = nullptr;
+    int base = 0;
+};
+
 // qconst: [nq] constant terms of TQ+ calibrated scores (Qrot then holds
 // kappa * q'), or null.  bounds_ready: the queries' global bounds (at
-// lut_search_bounds) already hold kBoundInit.
+// lut_search_bounds) already hold kBoundInit.  rows (k <= kMaxTopK): see
+// QueryRows.
 hipError_t lut_search(const ScanShape &s, const uint8_t *blocked, const float *scales,
                       const uint16_t *tenants, const uint64_t *summaries,
                       const float *cents32, const float *Qrot, int64_t nq, int k,
                       const SearchFilter &filter, int grid, void *ws, size_t ws_bytes,
                       int64_t *ids, float *scores, hipStream_t stream,
-                      const float *qconst = nullptr, bool bounds_ready = false);
+                      const float *qconst = nullptr, bool bounds_ready = false,
+                      const QueryRows &rows = QueryRows());
 // The order key of -inf: the value the global bounds of a top-k search
 // start from.
 constexpr int kBoundInit = (int)0x807FFFFFu;
@@ -163,10 +174,13 @@ int *lut_search_bounds(const ScanShape &s, int64_t nq, int k, int grid, void *ws
 // cmax16 = max |float16(c_l)|, dmax = max |float16(c_l) - c_l| over the
 // float32 centroids cents32.
 // Queries whose top k the certificate does not prove are re-run on the
-// single-query scan; their count goes to *n_fallback.  Synchronises
-// `stream` once to read the certificates.  `smax` is a device float: the
-// largest scale in the store.
+// single-query scan, from a list kept on the device.  With n_fallback their
+// count goes there and the call synchronises `stream` once to read it;
+// without, everything is asynchronous.  `smax` is a device float: the
+// largest |scale| in the store.
 bool mfma_search_supported(const ScanShape &s, int k);
+// Whether the workspace of the batched path stays moderate (about 1.1 GiB).
+bool batch_matrix_fits(const ScanShape &s);
 size_t mfma_search_workspace_bytes(const ScanShape &s, int64_t nq, int k, int grid);
 hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *scales,
                        const float *smax, const uint16_t *tenants, const uint64_t *summaries,
@@ -174,7 +188,7 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
                        int64_t nq, int k,
                        const uint64_t *allow, int grid, void *ws, int64_t *ids, float *scores,
                        int *n_fallback, hipStream_t stream);
-// *smax = max(*smax, max of scales[0..n)); scales are >= 0.
+// *smax = max(*smax, max of |scales[0..n)|).
 hipError_t update_scale_max(const float *scales, int64_t n, float *smax, hipStream_t stream);
 
 int device_cu_count();

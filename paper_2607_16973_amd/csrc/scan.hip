@@ -58,7 +58,18 @@ struct ScanParams {
     int64_t n, nblk;
     int d, bits, chunks, W, k, nq;
     int lut_words;              // 32-bit words of LDS used by the table
+    const int *nq_dev;          // queries in all launches of the search, or null: nq
+    int q_base;                 // queries of earlier launches (with nq_dev)
 };
+
+// Queries of this launch.  A search whose query count is only known on the
+// device (the queries that the batched path hands over) is launched for the
+// most there can be, nq, and leaves at once when there are none.
+__device__ inline int query_count(const ScanParams &p) {
+    if (!p.nq_dev) return p.nq;
+    const int left = *p.nq_dev - p.q_base;
+    return left < 0 ? 0 : (left < p.nq ? left : p.nq);
+}
 
 // Slots of block b that query qi may return: the live ones (all if no slot
 // was deleted), restricted to the query's allowed slots when slot-level
@@ -336,8 +347,9 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_kernel(ScanParams p) {
     const int64_t b0 = gb0 + (gb1 - gb0) * wave / SCAN_WAVES;
     const int64_t b1 = gb0 + (gb1 - gb0) * (wave + 1) / SCAN_WAVES;
 
+    const int nq = query_count(p);
     if (tid == 0) misc[2] = 0;
-    for (int qi = 0; qi < p.nq; ++qi) {
+    for (int qi = 0; qi < nq; ++qi) {
         const float cq = qconst_of(p, qi);
         const int sh = build_table<MODE>(lds, red, p, p.qrot + (int64_t)qi * p.d, cq);
         if (p.allow)
@@ -487,7 +499,9 @@ __global__ __launch_bounds__(SCAN_THREADS) void split_scan_kernel(ScanParams p) 
     const int NGq = nbq * GPB;                              // groups per query
     const int npass = (nbq + kPassBlocks - 1) / kPassBlocks;
     const int PG = kPassBlocks * GPB;                       // groups per full pass
-    const int total = p.nq * NGq;                           // work items (host-bounded)
+    const int nq = query_count(p);
+    if (nq == 0) return;
+    const int total = nq * NGq;                             // work items (host-bounded)
     const uint4 *wg_src = p.codes + gb0 * CH * 64;
     const char *lut = reinterpret_cast<const char *>(lds);
     // lane 0 takes a ticket; the wave reads it from lane 0 when it needs it
@@ -509,7 +523,6 @@ __global__ __launch_bounds__(SCAN_THREADS) void split_scan_kernel(ScanParams p) 
         misc[1] = 0;
         misc[2] = 0;
     }
-    if (p.nq == 0) return;
     QueryRegs<MODE> qv;
     load_query<MODE>(table_shape(p), p.qrot, qv);
     const float qc0 = qconst_of(p, 0);
@@ -533,7 +546,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void split_scan_kernel(ScanParams p) 
     }
     int sh = build_int_table<MODE>(lds, red, cents_s, table_shape(p), qv, qc0);
     __syncthreads();
-    for (int qi = 0; qi < p.nq; ++qi) {
+    for (int qi = 0; qi < nq; ++qi) {
         WaveTopK<S> top;
         top.reset();
         for (int ps = 0; ps < npass; ++ps) {
@@ -599,7 +612,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void split_scan_kernel(ScanParams p) 
         }
         // a wave that is done loads the next query's coordinates and |q'|
         // sum while the others finish (red was last read by this table's build)
-        const bool more = qi + 1 < p.nq;
+        const bool more = qi + 1 < nq;
         if (more) {
             load_query<MODE>(table_shape(p), p.qrot + (int64_t)(qi + 1) * p.d, qv);
             query_abs_sum<MODE>(red, qv);
@@ -657,6 +670,8 @@ __global__ __launch_bounds__(SCAN_THREADS) void split_filtered_kernel(ScanParams
     const int CH = p.chunks;          // multiple of 8
     const int GPB = CH >> 3;          // 8-chunk groups per block
     const int W = p.W;
+    const int nq = query_count(p);
+    if (nq == 0) return;
     const int64_t gb0 = p.nblk * g / G, gb1 = p.nblk * (g + 1) / G;
     const char *lut = reinterpret_cast<const char *>(lds);
     auto take = [&](int *ctr) {
@@ -673,7 +688,6 @@ __global__ __launch_bounds__(SCAN_THREADS) void split_filtered_kernel(ScanParams
         misc[2] = 0;
         misc[3] = 0;
     }
-    if (p.nq == 0) return;
     if (p.allow)
         for (int w = tid; w < W; w += SCAN_THREADS) allow_s[w] = p.allow[w];
     QueryRegs<MODE> qv;
@@ -682,7 +696,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void split_filtered_kernel(ScanParams
     __syncthreads();
     int sh = build_int_table<MODE>(lds, red, cents_s, table_shape(p), qv, qconst_of(p, 0));
     __syncthreads();
-    for (int qi = 0; qi < p.nq; ++qi) {
+    for (int qi = 0; qi < nq; ++qi) {
         WaveTopK<S> top;
         top.reset();
         int pass = 0;
@@ -786,7 +800,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void split_filtered_kernel(ScanParams
                 }
             }
         }
-        const bool more = qi + 1 < p.nq;
+        const bool more = qi + 1 < nq;
         if (more) {
             load_query<MODE>(table_shape(p), p.qrot + (int64_t)(qi + 1) * p.d, qv);
             query_abs_sum<MODE>(red, qv);
@@ -822,7 +836,8 @@ __global__ __launch_bounds__(256) void merge_kernel(const float *__restrict__ cs
                                                     const int *__restrict__ ci, int G, int k,
                                                     const int *__restrict__ gbound,
                                                     int64_t *__restrict__ ids,
-                                                    float *__restrict__ scores) {
+                                                    float *__restrict__ scores,
+                                                    QueryRows rows) {
     __shared__ float st_s[4 * 64 * S];
     __shared__ int st_i[4 * 64 * S];
     // survivors of the bound (k <= 64)
@@ -832,6 +847,8 @@ __global__ __launch_bounds__(256) void merge_kernel(const float *__restrict__ cs
     __shared__ int nsurv;
     __shared__ int lkey;
     const int q = blockIdx.x;
+    if (rows.count && rows.base + q >= *rows.count) return;
+    const int64_t orow = rows.rows ? rows.rows[rows.base + q] : q;   // the query's row of the results
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     // The k best score at least the final bound gbound[q] (a proven lower
@@ -911,8 +928,8 @@ __global__ __launch_bounds__(256) void merge_kernel(const float *__restrict__ cs
             wave_sort64(sv, iv, lane);
             for (int r = lane; r < k; r += 64) {
                 const bool empty = r >= 64 || !(sv > -INFINITY);
-                ids[(int64_t)q * k + r] = empty ? -1 : (int64_t)iv;
-                scores[(int64_t)q * k + r] = empty ? -INFINITY : sv;
+                ids[orow * k + r] = empty ? -1 : (int64_t)iv;
+                scores[orow * k + r] = empty ? -INFINITY : sv;
             }
         }
         return;
@@ -937,8 +954,8 @@ __global__ __launch_bounds__(256) void merge_kernel(const float *__restrict__ cs
             }
             if (lane < k) {
                 const bool empty = !(ls1[0] > -INFINITY);
-                ids[(int64_t)q * k + lane] = empty ? -1 : (int64_t)li1[0];
-                scores[(int64_t)q * k + lane] = empty ? -INFINITY : ls1[0];
+                ids[orow * k + lane] = empty ? -1 : (int64_t)li1[0];
+                scores[orow * k + lane] = empty ? -INFINITY : ls1[0];
             }
         }
         return;
@@ -994,8 +1011,8 @@ __global__ __launch_bounds__(256) void merge_kernel(const float *__restrict__ cs
             const int r = a * 64 + lane;
             if (r < k) {
                 const bool empty = !(ls[a] > -INFINITY);
-                ids[(int64_t)q * k + r] = empty ? -1 : (int64_t)li[a];
-                scores[(int64_t)q * k + r] = empty ? -INFINITY : ls[a];
+                ids[orow * k + r] = empty ? -1 : (int64_t)li[a];
+                scores[orow * k + r] = empty ? -INFINITY : ls[a];
             }
         }
     }
@@ -1327,7 +1344,8 @@ hipError_t lut_search(const ScanShape &s, const uint8_t *blocked, const float *s
                       const uint16_t *tenants, const uint64_t *summaries, const float *cents32,
                       const float *Qrot, int64_t nq, int k, const SearchFilter &filter, int grid,
                       void *ws, size_t ws_bytes, int64_t *ids, float *scores,
-                      hipStream_t stream, const float *qconst, bool bounds_ready) {
+                      hipStream_t stream, const float *qconst, bool bounds_ready,
+                      const QueryRows &rows) {
     const uint64_t *allow = filter.allow;
     const int64_t qc = query_chunk(s, nq, k, grid);
     uint8_t *p8 = static_cast<uint8_t *>(ws);
@@ -1408,6 +1426,13 @@ hipError_t lut_search(const ScanShape &s, const uint8_t *blocked, const float *s
         p.k = k;
         p.nq = (int)m;
         p.lut_words = lut_words_for(s);
+        p.nq_dev = rows.count;
+        p.q_base = (int)q0;
+        QueryRows rq = rows;
+        rq.base = (int)q0;
+        // with rows, results go to rows of the whole search's lists
+        int64_t *ids_q = rows.rows ? ids : ids + q0 * k;
+        float *scores_q = rows.rows ? scores : scores + q0 * k;
         const bool split = use_split(s) && lds_bytes_for(s, S, true, filter.any()) <= 160 * 1024;
         const size_t lds = lds_bytes_for(s, S, split, filter.any());
         hipError_t e = hipSuccess;
@@ -1425,13 +1450,13 @@ hipError_t lut_search(const ScanShape &s, const uint8_t *blocked, const float *s
         if (e != hipSuccess) return e;
         if (S == 1)
             hipLaunchKernelGGL(merge_kernel<1>, dim3(m), dim3(256), 0, stream, cand_s, cand_i,
-                               grid, k, gbound, ids + q0 * k, scores + q0 * k);
+                               grid, k, gbound, ids_q, scores_q, rq);
         else if (S == 2)
             hipLaunchKernelGGL(merge_kernel<2>, dim3(m), dim3(256), 0, stream, cand_s, cand_i,
-                               grid, k, gbound, ids + q0 * k, scores + q0 * k);
+                               grid, k, gbound, ids_q, scores_q, rq);
         else
             hipLaunchKernelGGL(merge_kernel<4>, dim3(m), dim3(256), 0, stream, cand_s, cand_i,
-                               grid, k, gbound, ids + q0 * k, scores + q0 * k);
+                               grid, k, gbound, ids_q, scores_q, rq);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

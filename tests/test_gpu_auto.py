@@ -1,0 +1,114 @@
+"""The default search path: whichever of the single-query scan and the batched
+path it takes, ids and scores are the scan's, bit for bit -- over sizes on
+both sides of the rule that chooses, with queries whose certificate fails
+(the scan answers them within the call), inside a captured graph, and with a
+workspace that only the scan fits."""
+import pytest
+
+import synth
+from tests.conftest import gpu_available
+
+pytestmark = pytest.mark.gpu
+if not gpu_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+import torch  # noqa: E402
+
+import paper_2607_16973_amd as tq  # noqa: E402
+
+_rot = {}
+
+
+def rotation(d):
+    if d not in _rot:
+        _rot[d] = tq.Rotation(d, 42)
+    return _rot[d]
+
+
+def corpus(n, d, seed):
+    return torch.from_numpy(synth.isotropic_mixture(n, d, seed=seed)).cuda()
+
+
+def queries(X, nq, seed):
+    return torch.from_numpy(synth.isotropic_queries(X.cpu().numpy(), nq, seed=seed)).cuda()
+
+
+def same(a, b):
+    assert torch.equal(a[0], b[0])
+    assert torch.equal(a[1], b[1])
+
+
+@pytest.mark.parametrize("n,nq,k", [(70, 40, 10), (1037, 7, 5), (1037, 33, 100), (20_011, 2, 10), (20_011, 64, 1),
+                                    (20_011, 130, 10), (20_011, 300, 256)])
+def test_default_equals_scan(n, nq, k):
+    d = 256
+    X = corpus(n, d, 5)
+    idx = tq.Index(tq.Codebook(d, 4), rotation(d))
+    idx.add(X)
+    Q = queries(X, min(nq, n), 6)
+    same(idx.search(Q, k), idx.search(Q, k, path="lut"))
+
+
+@pytest.mark.parametrize("nq", [12, 40, 100])
+def test_queries_without_certificate(nq):
+    # every score ties: no candidate set can be proven, every query goes to the scan
+    d = 256
+    X = corpus(1, d, 7).repeat(6000, 1)
+    idx = tq.Index(tq.Codebook(d, 4), rotation(d))
+    idx.add(X)
+    Q = queries(corpus(200, d, 8), nq, 9)
+    idx.search(Q, 10, path="mfma")
+    assert tq.last_search_fallbacks() == nq
+    ids, scores = idx.search(Q, 10)
+    same((ids, scores), idx.search(Q, 10, path="lut"))
+    assert torch.equal(ids, torch.arange(10, device="cuda").expand(nq, 10))
+
+
+def test_some_queries_without_certificate():
+    # copies of one row tie for the queries near it; the other queries are proven
+    d = 256
+    X = corpus(8000, d, 10)
+    X[1000:5000] = X[0]
+    idx = tq.Index(tq.Codebook(d, 4), rotation(d))
+    idx.add(X)
+    Q = torch.cat([queries(X[6000:], 30, 11), X[:1].repeat(3, 1), queries(X[6000:], 30, 12)])
+    idx.search(Q, 10, path="mfma")
+    assert 3 <= tq.last_search_fallbacks() < 63
+    same(idx.search(Q, 10), idx.search(Q, 10, path="lut"))
+
+
+def test_captured():
+    d, k = 256, 10
+    X = corpus(20_011, d, 13)
+    idx = tq.Index(tq.Codebook(d, 4), rotation(d))
+    idx.add(X)
+    Q = queries(X, 40, 14)
+    ws = torch.empty(idx.workspace_bytes(40, k), dtype=torch.uint8, device="cuda")
+    ids = torch.empty(40, k, dtype=torch.int64, device="cuda")
+    scores = torch.empty(40, k, device="cuda")
+    idx.search(Q, k, ids=ids, scores=scores, workspace=ws)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        idx.search(Q, k, ids=ids, scores=scores, workspace=ws)
+    for seed in (15, 16, 17):
+        Q.copy_(queries(X, 40, seed))
+        want = idx.search(Q, k, path="lut")
+        ids.fill_(-7)
+        g.replay()
+        torch.cuda.synchronize()
+        same((ids, scores), want)
+
+
+def test_scan_workspace_is_enough():
+    d, k = 256, 10
+    X = corpus(20_011, d, 18)
+    idx = tq.Index(tq.Codebook(d, 4), rotation(d))
+    idx.add(X)
+    Q = queries(X, 40, 19)
+    small = idx.workspace_bytes(40, k, path="lut")
+    assert small < idx.workspace_bytes(40, k)
+    ws = torch.empty(small, dtype=torch.uint8, device="cuda")
+    same(idx.search(Q, k, workspace=ws), idx.search(Q, k, path="lut"))
+    with pytest.raises(tq.TQError):
+        idx.search(Q, k, workspace=ws[:small // 2 // 256 * 256])
