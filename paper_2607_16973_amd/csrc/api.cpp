@@ -1101,22 +1101,25 @@ static int scan_grid() {
 
 // Whether TQ_PATH_AUTO answers nq queries on the batched path (same scores
 // and lists as the scan's, queries without a certificate re-run on the scan
-// within the call's launches).  The scan costs every query a pass over the
-// codes (about 6.2 TB/s) and 9 us of table build and merge; a tile of 32
-// queries costs one pass (about 5 TB/s) and 70 us of selection and rescoring,
-// once 20 us more per call.  Measured at d = 1536, 4 bits, k = 10, in us a
-// call, scan / batched: 10,000 vectors 63 / 90 for 4 queries, 100 / 92 for
-// 8, 1,331 / 233 for 128; 100,000 vectors 85 / 97 for 2, 125 / 99 for 4;
-// 1,000,000 vectors 170 / 248 for 1, 300 / 249 for 2, 17,185 / 811 for 128.
+// within the call's launches).  Both read the codes at about 5 TB/s: the scan
+// once per query, with 9 us (8 bits: 30 us) of table build and merge each;
+// the batched path once per tile of 32 queries, with 58 us (8 bits: 83 us)
+// of query preparation, selection and rescoring.  Measured at k = 10 in us a
+// call, scan / batched: d = 1536, 4 bits, 10,000 vectors 319 / 83 for 32
+// queries; 50,000 vectors 106 / 73 for 4, 174 / 74 for 8; 300,000 vectors
+// 140 / 118 for 2; 1,000,000 vectors 170 / 231 for 1, 300 / 229 for 2,
+// 8,537 / 450 for 64.  2 bits, 1,000,000 vectors 224 / 170 for 2; 3 bits
+// 309 / 223 for 2; 8 bits 530 / 382 for 2, 300,000 vectors 324 / 176 for 3.
+// d = 768, 4 bits, 100,000 vectors 222 / 62 for 8.
 static bool batch_pays(const ScanShape &sh, int64_t nq) {
-    const double bytes = (double)sh.nblk * sh.chunks * 1024.0;
+    const double pass_us = (double)sh.nblk * sh.chunks * 1024.0 / 5.0e6;
     const double tiles = (double)((nq + 31) / 32);
-    const double scan_us = (double)nq * (9.0 + bytes / 6.2e6);
-    return scan_us > 20.0 + tiles * (70.0 + bytes / 5.0e6);
+    const bool b8 = sh.bits == 8;
+    return (double)nq * ((b8 ? 30.0 : 9.0) + pass_us) > tiles * ((b8 ? 83.0 : 58.0) + pass_us);
 }
 
-static bool auto_batch(const tq_index *x, const ScanShape &sh, int64_t nq, int k) {
-    return !x->calibrated && mfma_search_supported(sh, k) && batch_matrix_fits(sh) && batch_pays(sh, nq);
+static bool auto_batch(const ScanShape &sh, int64_t nq, int k) {
+    return batch_search_supported(sh, k) && batch_matrix_fits(sh) && batch_pays(sh, nq);
 }
 
 static bool use_mfma(const ScanShape &sh, int k, int base) {
@@ -1127,6 +1130,15 @@ static bool use_mfma(const ScanShape &sh, int k, int base) {
 // terms at the end (calib_offset).
 static size_t calib_offset(const ScanShape &sh, int64_t nq, int k) {
     return (lut_search_workspace_bytes(sh, nq, k, scan_grid()) + 255) & ~(size_t)255;
+}
+
+// The same for the batched path.
+static size_t batch_calib_offset(const ScanShape &sh, int64_t nq, int k) {
+    return (mfma_search_workspace_bytes(sh, nq, k, scan_grid()) + 255) & ~(size_t)255;
+}
+
+static size_t batch_bytes(const ScanShape &sh, int64_t nq, int k, bool calibrated) {
+    return batch_calib_offset(sh, nq, k) + (calibrated ? (size_t)nq * sizeof(float) : 0);
 }
 
 static size_t search_bytes(const ScanShape &sh, int64_t nq, int k, int base, bool calibrated) {
@@ -1174,8 +1186,8 @@ tq_status tq_search_workspace_size(const tq_index *idx, int64_t nq, int32_t k, i
     if (st != TQ_OK) return st;
     const ScanShape sh = shape_of(idx);
     size_t bytes = search_bytes(sh, nq, k, base, idx->calibrated);
-    if (base == TQ_PATH_AUTO && auto_batch(idx, sh, nq, k))
-        bytes = std::max(bytes, mfma_search_workspace_bytes(sh, nq, k, scan_grid()));
+    if (base == TQ_PATH_AUTO && auto_batch(sh, nq, k))
+        bytes = std::max(bytes, batch_bytes(sh, nq, k, idx->calibrated));
     *bytes_out = bytes;
     return TQ_OK;
 }
@@ -1220,8 +1232,8 @@ tq_status tq_search_ex(const tq_index *idx, const float *Q_dev, int64_t nq, int3
         return fail(TQ_EINVAL, "workspace too small: need " + std::to_string(need) + " bytes");
     // a workspace sized for the scan alone is still taken (by the scan)
     const bool batched = use_mfma(sh, k, base) ||
-                         (base == TQ_PATH_AUTO && !filter.any() && auto_batch(idx, sh, nq, k) &&
-                          workspace_bytes >= mfma_search_workspace_bytes(sh, nq, k, grid));
+                         (base == TQ_PATH_AUTO && !filter.any() && auto_batch(sh, nq, k) &&
+                          workspace_bytes >= batch_bytes(sh, nq, k, idx->calibrated));
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (idx->n == 0) {
         // nothing indexed: every slot is padding
@@ -1253,7 +1265,8 @@ tq_status tq_search_ex(const tq_index *idx, const float *Q_dev, int64_t nq, int3
     float *qconst = nullptr;
     if (idx->calibrated) {
         uint8_t *w8 = static_cast<uint8_t *>(workspace_dev);
-        qconst = reinterpret_cast<float *>(w8 + calib_offset(sh, nq, k));
+        qconst = reinterpret_cast<float *>(
+            w8 + (batched ? batch_calib_offset(sh, nq, k) : calib_offset(sh, nq, k)));
         float *qr = static_cast<float *>(workspace_dev);
         st = prepare_calibrated(idx, Qrot, nq, qr, qconst, s);
         if (st != TQ_OK) return st;
@@ -1264,7 +1277,7 @@ tq_status tq_search_ex(const tq_index *idx, const float *Q_dev, int64_t nq, int3
         float cmax16 = 0.f, dmax = 0.f;
         centroid_half_bounds(idx, &cmax16, &dmax);
         hipError_t e = mfma_search(sh, idx->codes, idx->scales, scale_max_dev(idx), idx->tenants,
-                                   idx->summ, idx->cents_dev, cmax16, dmax, Qrot, nq, k,
+                                   idx->summ, idx->cents_dev, cmax16, dmax, Qrot, qconst, nq, k,
                                    allow_dev, grid, workspace_dev, ids_dev, scores_dev,
                                    base == TQ_PATH_MFMA ? &n_fallback : nullptr, s);
         if (e != hipSuccess) return hip_fail(e, "matrix-core search");

@@ -65,7 +65,6 @@ constexpr int kSelBound = 0;       // candidates + a bound amin on every other v
 constexpr int kSelOverflow = 1;    // no usable candidates: the query is not certified
 constexpr int kSelAll = 2;         // every vector is a candidate
 constexpr int MF_THREADS = 768;    // 12 waves: three per SIMD, 168 registers each
-constexpr int MF_RING = 8;         // chunk loads in flight per wave
 constexpr int kTableBytes = 256 * 32 * 4;   // byte table, 32 replicas
 constexpr int SEL_THREADS = 256;
 constexpr int SEL_GROUPS = 32;     // select workgroups per query
@@ -77,12 +76,22 @@ constexpr int kBufferWord3 = 0x00020000;
 constexpr int kBuf = 8 * 64 + 64;  // per-wave candidate buffer: one load of 8 scores per lane + a partial 64
 constexpr int kKeepVmemB = 0x1 | 0x2 | 0x4 | 0x8 | 0x80 | 0x100 | 0x200 | 0x400;
 
+// fn(std::integral_constant<int, i>) for i = 0 .. N-1.
+template <int N, class Fn, int... I>
+__device__ inline void static_for_impl(Fn &&fn, std::integer_sequence<int, I...>) {
+    (fn(std::integral_constant<int, I>()), ...);
+}
+template <int N, class Fn>
+__device__ inline void static_for(Fn &&fn) {
+    static_for_impl<N>(fn, std::make_integer_sequence<int, N>());
+}
+
 // Per-query constants written by prep_kernel.
 struct QInfo {
-    float f;      // stored approximate score = s_v * acc * f (acc: MFMA sum of the scaled query)
+    float f;      // stored approximate score = s_v (acc f + c) (acc: MFMA sum of the scaled query)
     float norm;   // approximate score = stored * norm  (s_max ||q'||_2)
     float err;    // bound on |approximate - exact| before the float16 storage
-    float pad;
+    float c;      // TQ+ constant term / norm (0 without calibration)
 };
 
 // ------------------------------------------------------------------- prep
@@ -93,22 +102,26 @@ struct QInfo {
 //   |acc / alpha - <c, q'>| <= dmax ||q'||_1 + cmax16 ||eps||_1 / alpha
 // plus the float32 accumulation of d products in any order,
 //   gamma_d cmax16 (||q'||_1 + ||eps||_1 / alpha),  gamma_d = d u / (1 - d u),
-// u = 2^-24, and two float32 roundings when scaling (2^-23 of the same
-// magnitude).  The exact score (the integer table of lut.h, d rows at
-// b = 4) differs from s_v <c, q'> by the table's rounding: each entry is
-// within 1/2 unit plus 2^-24 of its product, the integer sum is exact, and
-// its float conversion and the product with s_v add 2^-24 each.  The table
-// builder picks 2^sh > (2^31 - 1 - 2d) / (2 B'), B' = cmax tot (1 + 1e-5)
-// with tot its float sum of |q'_j| (within 1e-6 of ||q'||_1), so the d/2
-// units are below rho cmax ||q'||_1 in score units, rho = d (1 + 2e-5) /
-// (2^31 - 1 - 2d); with the 2^-24 terms the exact score is within
-// (rho + 4 * 2^-24) s_v cmax ||q'||_1 of s_v <c, q'> (cmax <= cmax16
-// (1 + 2^-10): float16 rounding moves a value by at most 2^-11 of it).
+// u = 2^-24, and a few float32 roundings when scaling and adding the
+// constant term C (4 * 2^-23 of the same magnitude and of |C|).
+// The exact score of b <= 4 (the integer tables of lut.h, at most d rows)
+// differs from s_v (<c, q'> + C) by the table's rounding: each entry is
+// within 1/2 unit plus 2 * 2^-24 of its products, the constant within 1/2
+// unit, the integer sum is exact, and its float conversion and the product
+// with s_v add 2^-24 each.  The table builder picks 2^sh > (2^31 - 1 - 2d) /
+// (2 B'), B' = (cmax tot + |C|) (1 + 1e-5) with tot its float sum of |q'_j|
+// (within 1e-6 of ||q'||_1), so the (d + 1)/2 units are below rho (cmax
+// ||q'||_1 + |C|) in score units, rho = (d + 1) (1 + 2e-5) / (2^31 - 1 - 2d);
+// with the 2^-24 terms the exact score is within (rho + 8 * 2^-24) s_v (cmax
+// ||q'||_1 + |C|) of s_v (<c, q'> + C) (cmax <= cmax16 (1 + 2^-10): float16
+// rounding moves a value by at most 2^-11 of it).  At b = 8 the exact score
+// is a float32 sum of d products from C on: gamma_{d+8} takes rho's place.
 // The sum of all terms times s_max is the error before storage (the factor
 // 1.1 is margin only); the float16 storage of the approximate score adds at
 // most 2^-11 of its magnitude plus 2^-25 norm, accounted for where the
 // certificate is checked.
-__global__ void prep_kernel(const float *__restrict__ Q, int nq, int d, const float *smax_p,
+__global__ void prep_kernel(const float *__restrict__ Q, const float *__restrict__ qconst, int nq,
+                            int d, int bits, const float *smax_p,
                             float cmax16, float dmax, _Float16 *__restrict__ q16,
                             QInfo *__restrict__ info, int *__restrict__ zero, int nzero,
                             int *__restrict__ zero1) {
@@ -170,26 +183,29 @@ __global__ void prep_kernel(const float *__restrict__ Q, int nq, int d, const fl
         const double u = ldexp(1.0, -24);
         const double gd = d * u / (1.0 - d * u);
         const double mag = (double)cmax16 * (s1 + se / alpha);
-        const double rho = d * (1.0 + 2e-5) / (2147483647.0 - 2.0 * d);
-        const double tab = (rho + 4 * u) * (double)cmax16 * (1.0 + ldexp(1.0, -10)) * s1;
+        const double rho = (d + 1) * (1.0 + 2e-5) / (2147483647.0 - 2.0 * d);
+        const double gx = (d + 8) * u / (1.0 - (d + 8) * u);
+        const double C = qconst ? (double)qconst[q] : 0.0;
+        const double tab = ((bits == 8 ? gx : rho) + 8 * u) *
+                           ((double)cmax16 * (1.0 + ldexp(1.0, -10)) * s1 + fabs(C));
         const double E = (double)dmax * s1 + (double)cmax16 * se / alpha + gd * mag +
-                         2 * ldexp(1.0, -23) * mag + tab;
+                         4 * ldexp(1.0, -23) * (mag + fabs(C)) + tab;
         QInfo qi;
         qi.f = (float)(1.0 / ((double)alpha * norm));
         qi.norm = (float)norm;
         qi.err = (float)(1.1 * smax * E);
-        qi.pad = 0.f;
+        qi.c = (float)(C / norm);
         info[q] = qi;
     }
 }
 
 // ------------------------------------------------------------ MFMA scores
 struct ScoreParams {
-    const uint4 *codes;        // blocked store (b = 4)
+    const uint4 *codes;        // blocked store
     const float *scales;
     const _Float16 *q16;       // [nqt][d]
     const QInfo *info;         // [nqt]
-    const float *cents;        // 16 levels
+    const float *cents;        // 2^b levels
     _Float16 *out;             // [kTile][npad] approximate scores / norm (rows >= nqt: 0)
     _Float16 *bmax;            // [kTile][nblk] per-block maximum of out (vectors < n)
     int *tickets;              // [grid * kTicketStride] block ticket counters, zero at launch
@@ -209,30 +225,124 @@ struct ScoreParams {
 //    canonical word and lb forms it (64 KiB of table).
 //  NR = 32: ((e << 7) | lb), lb = 4 * (lane mod 32), takes a shift or
 //    field extract and an and-or per lookup (32 KiB of table).
+// The other widths use tables of the same kind: an entry per pair of 2-bit
+// codes (16) or of 3-bit codes (64), or per 8-bit code (256, the centroid in
+// both halves).
+typedef __attribute__((address_space(3))) const uint32_t lds_u32;
+
+// Entry (byte B of w), for w whose bytes are entry numbers.
+template <int NR, int B>
+__device__ inline uint32_t table_byte(uint32_t w, uint32_t lb) {
+    if constexpr (NR == 64) {
+        // v_perm selector: byte 0 <- lb byte 0, byte 1 <- w byte B, bytes 2, 3 <- 0
+        return *(lds_u32 *)(uintptr_t)__builtin_amdgcn_perm(w, lb, 0x0C0C0400u + (B << 8));
+    } else {
+        const uint32_t at = B == 0 ? w << 7 : w >> (8 * B - 7);
+        return *(lds_u32 *)(uintptr_t)((at & 0x7F80u) | lb);
+    }
+}
+// Entry of the SH / 6-th 6-bit field of w (64 replicas).
+template <int SH>
+__device__ inline uint32_t table_six(uint32_t w, uint32_t lb) {
+    return *(lds_u32 *)(uintptr_t)((__builtin_amdgcn_ubfe(w, SH, 6) << 8) | lb);
+}
+// Low halves of two 8-bit entries as a pair.
+__device__ inline uint32_t pair_of(uint32_t a, uint32_t b) {
+    return __builtin_amdgcn_perm(b, a, 0x07060100u);   // bytes 0, 1 of a, bytes 2, 3 of b
+}
+
+union Half8 {
+    uint32_t u[4];
+    half8 h;
+};
+
 template <int NR>
 __device__ inline half8 dequant8_canonical(uint32_t cw, uint32_t lb) {
-    typedef __attribute__((address_space(3))) const uint32_t lds_u32;
-    union {
-        uint32_t u[4];
-        half8 h;
-    } r;
-    if constexpr (NR == 64) {
-        // v_perm selector: byte 0 <- lb byte 0, byte 1 <- cw byte b, bytes 2, 3 <- 0
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-            r.u[b] = *(lds_u32 *)(uintptr_t)__builtin_amdgcn_perm(cw, lb, 0x0C0C0400u + (b << 8));
-    } else {
-        r.u[0] = *(lds_u32 *)(uintptr_t)(((cw << 7) & 0x7F80u) | lb);
-        r.u[1] = *(lds_u32 *)(uintptr_t)(((cw >> 1) & 0x7F80u) | lb);
-        r.u[2] = *(lds_u32 *)(uintptr_t)(((cw >> 9) & 0x7F80u) | lb);
-        r.u[3] = *(lds_u32 *)(uintptr_t)(((cw >> 17) & 0x7F80u) | lb);
-    }
+    Half8 r;
+    r.u[0] = table_byte<NR, 0>(cw, lb);
+    r.u[1] = table_byte<NR, 1>(cw, lb);
+    r.u[2] = table_byte<NR, 2>(cw, lb);
+    r.u[3] = table_byte<NR, 3>(cw, lb);
     return r.h;
 }
 template <int NR>
 __device__ inline half8 dequant8(uint32_t w, uint32_t lb) {
     return dequant8_canonical<NR>(__builtin_amdgcn_alignbit(w, w, 2), lb);   // canonical word
 }
+
+// How the codes of one width are fed to the MFMAs (k = 32 per step).  The
+// lane exchanges leave lane row kq of a chunk with word kq of its vector;
+// U consecutive chunks give the lane U words, and ST steps of 8 of their
+// codes.  coord(u, st, kq, t): the coordinate that step st of unit u takes
+// in slot t of lane row kq (the queries are laid out alike).
+template <int BITS> struct Feed;
+template <> struct Feed<4> {
+    static constexpr int U = 1, ST = 1, ENTRIES = 256;
+    __host__ __device__ static int coord(int u, int, int kq, int t) { return 32 * u + 8 * kq + t; }
+};
+template <> struct Feed<2> {
+    static constexpr int U = 1, ST = 2, ENTRIES = 16;
+    __host__ __device__ static int coord(int u, int st, int kq, int t) {
+        return 64 * u + 16 * kq + 8 * st + t;
+    }
+};
+template <> struct Feed<8> {
+    static constexpr int U = 2, ST = 1, ENTRIES = 256;
+    __host__ __device__ static int coord(int u, int, int kq, int t) {
+        return 32 * u + 16 * (t >> 2) + 4 * kq + (t & 3);
+    }
+};
+// b = 3: ten codes per word, 40 per chunk; the lane's four words hold 20
+// pairs, four to a step (coordinates past d are zero in the queries).
+template <> struct Feed<3> {
+    static constexpr int U = 4, ST = 5, ENTRIES = 64;
+    __host__ __device__ static int coord(int u, int st, int kq, int t) {
+        const int p = 4 * st + (t >> 1);
+        return 160 * u + 40 * (p / 5) + 10 * kq + 2 * (p % 5) + (t & 1);
+    }
+};
+template <int BITS>
+__device__ inline uint32_t table_entry(const float *cents, int e) {
+    constexpr int M = (1 << BITS) - 1;
+    const float lo = cents[e & M], hi = BITS == 8 ? lo : cents[e >> BITS & M];
+    return (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)lo) |
+           (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)hi) << 16;
+}
+// B operand of step st from the lane's U words (w[0..U-1], as stored).
+template <int BITS, int NR, int ST>
+__device__ inline half8 feed_operand(const uint32_t *w, uint32_t lb) {
+    if constexpr (BITS == 4) {
+        return dequant8<NR>(w[0], lb);
+    } else if constexpr (BITS == 2) {
+        const uint32_t cw = __builtin_amdgcn_alignbit(w[0], w[0], 2);
+        const uint32_t lo = cw & 0x0F0F0F0Fu, hi = (cw >> 4) & 0x0F0F0F0Fu;
+        Half8 r;
+        r.u[0] = table_byte<NR, 2 * ST>(lo, lb);
+        r.u[1] = table_byte<NR, 2 * ST>(hi, lb);
+        r.u[2] = table_byte<NR, 2 * ST + 1>(lo, lb);
+        r.u[3] = table_byte<NR, 2 * ST + 1>(hi, lb);
+        return r.h;
+    } else if constexpr (BITS == 8) {
+        Half8 r;
+        r.u[0] = pair_of(table_byte<NR, 0>(w[0], lb), table_byte<NR, 1>(w[0], lb));
+        r.u[1] = pair_of(table_byte<NR, 2>(w[0], lb), table_byte<NR, 3>(w[0], lb));
+        r.u[2] = pair_of(table_byte<NR, 0>(w[1], lb), table_byte<NR, 1>(w[1], lb));
+        r.u[3] = pair_of(table_byte<NR, 2>(w[1], lb), table_byte<NR, 3>(w[1], lb));
+        return r.h;
+    } else {
+        Half8 r;
+        r.u[0] = table_six<(4 * ST + 0) % 5 * 6>(w[(4 * ST + 0) / 5], lb);
+        r.u[1] = table_six<(4 * ST + 1) % 5 * 6>(w[(4 * ST + 1) / 5], lb);
+        r.u[2] = table_six<(4 * ST + 2) % 5 * 6>(w[(4 * ST + 2) / 5], lb);
+        r.u[3] = table_six<(4 * ST + 3) % 5 * 6>(w[(4 * ST + 3) / 5], lb);
+        return r.h;
+    }
+}
+// Steps of a vector of `chunks` chunks.
+__host__ __device__ constexpr int feed_steps(int bits, int chunks) {
+    return bits == 4 ? chunks : bits == 2 ? 2 * chunks : bits == 8 ? chunks / 2 : chunks / 4 * 5;
+}
+__host__ __device__ constexpr int feed_entries(int bits) { return bits == 2 ? 16 : bits == 3 ? 64 : 256; }
 
 // Copies of a ring slot's four words into registers of their own.  The
 // exchanges below overwrite their operands in place; on the slot itself they
@@ -246,57 +356,81 @@ __device__ inline void copy4(const uint4 &v, uint32_t &a, uint32_t &b, uint32_t 
                  : "v"(v.x), "v"(v.y), "v"(v.z), "v"(v.w));
 }
 
-// Replicas of the score kernel's byte table: 64 where the table (64 KiB)
-// and the query tile (kTile x d float16) fit the 160 KiB of LDS together.
-__host__ __device__ constexpr int score_replicas(int d) {
-    return 64 * 1024 + kTile * d * 2 <= 160 * 1024 ? 64 : 32;
+// Replicas of the score kernel's table: 64 where the table (64 KiB at b = 4
+// and 8) and the query tile (2 KiB a step) fit the 160 KiB of LDS together.
+__host__ __device__ constexpr size_t score_lds(int bits, int chunks, int nr) {
+    return (size_t)feed_entries(bits) * nr * 4 + (size_t)feed_steps(bits, chunks) * 2048;
+}
+__host__ __device__ constexpr int score_replicas(int bits, int chunks) {
+    return score_lds(bits, chunks, 64) <= 160 * 1024 ? 64 : 32;
 }
 
-// One workgroup of 12 waves per compute unit.  The byte table and the query
+// One workgroup of 12 waves per compute unit.  The table and the query
 // tile stay in LDS; the tile is stored in the A-operand order of the MFMAs
-// (chunk c, row tile t: 64 lanes x 16 bytes, lane 16 kq + i holding row
-// 16 t + i, k = 32 c + 8 kq .. + 7), so each operand read is one 16-byte read
-// per lane at consecutive addresses.  Waves claim the workgroup's 64-vector
-// blocks one at a time from the workgroup's ticket counter in memory (one
-// ahead, so the ring of MF_RING chunk loads runs on into the next block).
-template <int NR>
+// (step, row tile t: 64 lanes x 16 bytes, lane 16 kq + i holding row
+// 16 t + i, slots 0..7 of lane row kq), so each operand read is one 16-byte
+// read per lane at consecutive addresses.  Waves claim the workgroup's
+// 64-vector blocks one at a time from the workgroup's ticket counter in
+// memory (one ahead, so the ring of RING chunk loads runs on into the next
+// block; RING = 4 for chunk counts that 8 does not divide).  The kernel is
+// bound by the code stream: 1,000,000 vectors at d = 1536 and 4 bits take
+// 152 to 178 us, 4.3 to 5.1 TB/s, whatever the number of queries in the tile.
+template <int BITS, int NR, int RING>
 __global__ __launch_bounds__(MF_THREADS) void mfma_scores_kernel(ScoreParams p) {
+    using F = Feed<BITS>;
+    static_assert(RING % F::U == 0 && (RING == 4 || RING == 8), "whole units in the ring");
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    uint32_t *T = reinterpret_cast<uint32_t *>(smem);                    // byte table, at 0
-    uint4 *Qf = reinterpret_cast<uint4 *>(smem + (size_t)NR * 256 * 4);   // [chunk][2][64]
+    uint32_t *T = reinterpret_cast<uint32_t *>(smem);                               // table, at 0
+    uint4 *Qf = reinterpret_cast<uint4 *>(smem + (size_t)NR * F::ENTRIES * 4);      // [step][2][64]
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int G = gridDim.x, g = blockIdx.x;
-    const int CH = p.chunks;   // multiple of 8
+    const int CH = p.chunks;   // multiple of RING
     const int64_t gb0 = p.nblk * g / G, gb1 = p.nblk * (g + 1) / G;
     const int nbw = (int)(gb1 - gb0);
 
     // query tile in operand order, zero rows past nqt
-    for (int e = tid; e < CH * 128; e += MF_THREADS) {
-        const int c = e >> 7, t = (e >> 6) & 1, l = e & 63;
-        const int r = 16 * t + (l & 15);
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (r < p.nqt)
-            v = *reinterpret_cast<const uint4 *>(p.q16 + (int64_t)r * p.d + 32 * c + 8 * (l >> 4));
-        Qf[e] = v;
+    for (int e = tid; e < feed_steps(BITS, CH) * 128; e += MF_THREADS) {
+        const int st = e >> 7, t = (e >> 6) & 1, l = e & 63;
+        const int r = 16 * t + (l & 15), kq = l >> 4;
+        union {
+            uint4 v;
+            _Float16 h[8];
+            uint2 w[2];
+        } q;
+        q.v = make_uint4(0, 0, 0, 0);
+        if (r < p.nqt) {
+            const _Float16 *row = p.q16 + (int64_t)r * p.d;
+            const int u = st / F::ST, sub = st % F::ST;
+            if constexpr (BITS == 8) {
+                q.w[0] = *reinterpret_cast<const uint2 *>(row + F::coord(u, sub, kq, 0));
+                q.w[1] = *reinterpret_cast<const uint2 *>(row + F::coord(u, sub, kq, 4));
+            } else if constexpr (BITS == 3) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const int j = F::coord(u, sub, kq, i);
+                    q.h[i] = j < p.d ? row[j] : (_Float16)0.f;
+                }
+            } else {
+                q.v = *reinterpret_cast<const uint4 *>(row + F::coord(u, sub, kq, 0));
+            }
+        }
+        Qf[e] = q.v;
     }
-    for (int e = tid; e < 256 * NR; e += MF_THREADS) {
-        const int v = e / NR;   // byte value; e % NR is the replica
-        const uint32_t lo = __builtin_bit_cast(uint16_t, (_Float16)p.cents[v & 15]);
-        const uint32_t hi = __builtin_bit_cast(uint16_t, (_Float16)p.cents[v >> 4]);
-        T[e] = lo | (hi << 16);
-    }
+    for (int e = tid; e < F::ENTRIES * NR; e += MF_THREADS)
+        T[e] = table_entry<BITS>(p.cents, e / NR);   // e % NR is the replica
     const uint32_t lb = (uint32_t)(lane & (NR - 1)) * 4;
     // per-lane query factors: tile t, rows 4*(lane/16) + r
-    float qf[2][4];
+    float qf[2][4], qc[2][4];
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int q = 16 * t + 4 * (lane >> 4) + r;
-            const float f = p.info[q < p.nqt ? q : 0].f;
-            qf[t][r] = q < p.nqt ? f : 0.f;
+            const QInfo qi = p.info[q < p.nqt ? q : 0];
+            qf[t][r] = q < p.nqt ? qi.f : 0.f;
+            qc[t][r] = q < p.nqt ? qi.c : 0.f;
         }
     __syncthreads();
 
@@ -316,18 +450,21 @@ __global__ __launch_bounds__(MF_THREADS) void mfma_scores_kernel(ScoreParams p) 
     const uint4 *bsrc = p.codes + (gb0 + cur) * CH * 64;   // uniform: the block's chunk 0
     // the ring: named registers (an array would end up in scratch)
     uint4 rb0, rb1, rb2, rb3, rb4, rb5, rb6, rb7;
-#define TQ_RING_LOAD(R, I)                          \
-    R = load_stream(bsrc + (I) * 64 + lane);        \
-    __builtin_amdgcn_sched_barrier(kKeepVmemB);
-    TQ_RING_LOAD(rb0, 0)
-    TQ_RING_LOAD(rb1, 1)
-    TQ_RING_LOAD(rb2, 2)
-    TQ_RING_LOAD(rb3, 3)
-    TQ_RING_LOAD(rb4, 4)
-    TQ_RING_LOAD(rb5, 5)
-    TQ_RING_LOAD(rb6, 6)
-    TQ_RING_LOAD(rb7, 7)
-#undef TQ_RING_LOAD
+    auto ring = [&](auto I) -> uint4 & {
+        constexpr int i = decltype(I)::value;
+        if constexpr (i == 0) return rb0;
+        else if constexpr (i == 1) return rb1;
+        else if constexpr (i == 2) return rb2;
+        else if constexpr (i == 3) return rb3;
+        else if constexpr (i == 4) return rb4;
+        else if constexpr (i == 5) return rb5;
+        else if constexpr (i == 6) return rb6;
+        else return rb7;
+    };
+    static_for<RING>([&](auto I) {
+        ring(I) = load_stream(bsrc + decltype(I)::value * 64 + lane);
+        __builtin_amdgcn_sched_barrier(kKeepVmemB);
+    });
     const uint4 *qa = Qf + lane;
     const int qrow = lane & 15, kq = lane >> 4;
     // a wave scores at most the workgroup's nbw blocks: the bound ends the
@@ -350,54 +487,63 @@ __global__ __launch_bounds__(MF_THREADS) void mfma_scores_kernel(ScoreParams p) 
         for (int t = 0; t < 2; ++t)
 #pragma unroll
             for (int m = 0; m < 4; ++m) acc[t][m] = float4v{0.f, 0.f, 0.f, 0.f};
-        // one chunk; the ring index is a compile-time constant at every call
-        auto chunk = [&](const int c, uint4 &slot) {
-            // W_q (row m) = word q of vector 16m+i.  permlane32_swap(a, b)
-            // exchanges a's rows 2, 3 with b's rows 0, 1; permlane16_swap(a, b)
-            // exchanges a's rows 1, 3 with b's rows 0, 2.  After both levels
-            // r[m] (row q) = W_q (row m): word q of vectors i, 16+i, 32+i,
-            // 48+i in lane 16q+i, the B operands (k = 8q..8q+7, column i) of
-            // the four 16-vector MFMAs.  The exchanges work on copies, and the
-            // slot is refilled right after the copy.
-            uint32_t cx, cy, cz, cw;
-            copy4(slot, cx, cy, cz, cw);
-            // refill MF_RING chunks ahead: this block, then the next one
-            {
-                const int nc = c + MF_RING;
-                slot = load_stream((nc < CH ? bsrc + nc * 64 : nsrc + (nc - CH) * 64) + lane);
-                __builtin_amdgcn_sched_barrier(kKeepVmemB);
-            }
-            const auto s02 = __builtin_amdgcn_permlane32_swap(cx, cz, false, false);
-            const auto s13 = __builtin_amdgcn_permlane32_swap(cy, cw, false, false);
-            const auto t01 = __builtin_amdgcn_permlane16_swap(s02[0], s13[0], false, false);
-            const auto t23 = __builtin_amdgcn_permlane16_swap(s02[1], s13[1], false, false);
-            const uint32_t r[4] = {t01[0], t01[1], t23[0], t23[1]};
-            const half8 a0 = __builtin_bit_cast(half8, qa[c * 128]);
-            const half8 a1 = __builtin_bit_cast(half8, qa[c * 128 + 64]);
+        // one unit of U chunks from c on, in ring slots I, I + 1, ...; the
+        // ring index is a compile-time constant at every call
+        auto unit = [&](const int c, auto I) {
+            constexpr int i0 = decltype(I)::value;
+            uint32_t w[4][F::U];   // [m][chunk]: this lane row's words of vector 16m + i
+            static_for<F::U>([&](auto J) {
+                constexpr int j = decltype(J)::value;
+                uint4 &slot = ring(std::integral_constant<int, i0 + j>());
+                // W_q (row m) = word q of vector 16m+i.  permlane32_swap(a, b)
+                // exchanges a's rows 2, 3 with b's rows 0, 1; permlane16_swap(a, b)
+                // exchanges a's rows 1, 3 with b's rows 0, 2.  After both levels
+                // w[m] (row q) = W_q (row m): word q of vectors i, 16+i, 32+i,
+                // 48+i in lane 16q+i, the B operands (lane row q, column i) of
+                // the four 16-vector MFMAs.  The exchanges work on copies, and
+                // the slot is refilled right after the copy.
+                uint32_t cx, cy, cz, cw;
+                copy4(slot, cx, cy, cz, cw);
+                // refill RING chunks ahead: this block, then the next one
+                {
+                    const int nc = c + j + RING;
+                    slot = load_stream((nc < CH ? bsrc + nc * 64 : nsrc + (nc - CH) * 64) + lane);
+                    __builtin_amdgcn_sched_barrier(kKeepVmemB);
+                }
+                const auto s02 = __builtin_amdgcn_permlane32_swap(cx, cz, false, false);
+                const auto s13 = __builtin_amdgcn_permlane32_swap(cy, cw, false, false);
+                const auto t01 = __builtin_amdgcn_permlane16_swap(s02[0], s13[0], false, false);
+                const auto t23 = __builtin_amdgcn_permlane16_swap(s02[1], s13[1], false, false);
+                w[0][j] = t01[0];
+                w[1][j] = t01[1];
+                w[2][j] = t23[0];
+                w[3][j] = t23[1];
+            });
+            const int s0 = c / F::U * F::ST;
+            static_for<F::ST>([&](auto S) {
+                constexpr int st = decltype(S)::value;
+                const half8 a0 = __builtin_bit_cast(half8, qa[(s0 + st) * 128]);
+                const half8 a1 = __builtin_bit_cast(half8, qa[(s0 + st) * 128 + 64]);
 #pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                const half8 b = dequant8<NR>(r[m], lb);
-                acc[0][m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, b, acc[0][m], 0, 0, 0);
-                acc[1][m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a1, b, acc[1][m], 0, 0, 0);
-            }
+                for (int m = 0; m < 4; ++m) {
+                    const half8 b = feed_operand<BITS, NR, st>(w[m], lb);
+                    acc[0][m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, b, acc[0][m], 0, 0, 0);
+                    acc[1][m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a1, b, acc[1][m], 0, 0, 0);
+                }
+            });
         };
-        static_assert(MF_RING == 8, "the chunk calls below assume a ring of 8");
-        for (int c0 = 0; c0 < CH; c0 += MF_RING) {
-            chunk(c0 + 0, rb0);
-            chunk(c0 + 1, rb1);
-            chunk(c0 + 2, rb2);
-            chunk(c0 + 3, rb3);
-            chunk(c0 + 4, rb4);
-            chunk(c0 + 5, rb5);
-            chunk(c0 + 6, rb6);
-            chunk(c0 + 7, rb7);
-        }
+        for (int c0 = 0; c0 < CH; c0 += RING)
+            static_for<RING / F::U>([&](auto I) {
+                constexpr int i = decltype(I)::value * F::U;
+                unit(c0 + i, std::integral_constant<int, i>());
+            });
         // lane holds vectors 16m + qrow, queries 16t + 4*kq + r.  The stores
         // are unconditional (rows past nqt are zero scores in rows that the
         // workspace holds and nothing reads; the 16 lanes of a row store the
         // same block maximum): a store under a branch leaves the wait-count
         // pass unsure of the loads in flight, and it then drains the chunk
-        // ring inside the chunk loop.
+        // ring inside the chunk loop.  Stored scores are at least -65504:
+        // -inf marks a vector that the query may not return.
         float mx[2][4];
 #pragma unroll
         for (int t = 0; t < 2; ++t)
@@ -412,7 +558,8 @@ __global__ __launch_bounds__(MF_THREADS) void mfma_scores_kernel(ScoreParams p) 
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int q = 16 * t + 4 * kq + r;
-                    const _Float16 h = (_Float16)(acc[t][m][r] * scl[m] * qf[t][r]);
+                    const float a = fmaf(acc[t][m][r], qf[t][r], qc[t][r]) * scl[m];
+                    const _Float16 h = (_Float16)fmaxf(a, -65504.f);
                     p.out[(int64_t)q * p.npad + v] = h;
                     mx[t][r] = fmaxf(mx[t][r], vin ? (float)h : -INFINITY);
                 }
@@ -616,6 +763,8 @@ __global__ __launch_bounds__(256) void select_merge_kernel(const float *__restri
 // ------------------------------------------- selection by block maxima
 // Order-preserving map of float16 bit patterns onto 16-bit keys.
 __device__ inline uint32_t hkey(uint32_t h) { return (h & 0x8000u) ? (~h & 0xFFFFu) : (h | 0x8000u); }
+// ... with 0 for -inf, the mark of vectors that the query may not return.
+__device__ inline uint32_t present_key(uint32_t h) { return h == 0xFC00u ? 0u : hkey(h); }
 __device__ inline float hkey_value(uint32_t key) {
     const uint32_t h = (key & 0x8000u) ? (key & 0x7FFFu) : (~key & 0xFFFFu);
     return (float)__builtin_bit_cast(_Float16, (uint16_t)h);
@@ -710,7 +859,7 @@ __global__ __launch_bounds__(BS_THREADS) void block_select_kernel(BlockSelParams
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t b = b0 + tid + (int64_t)u * BS_THREADS;
-            key[u] = b < p.nblk ? hkey(key[u]) : 0u;
+            key[u] = b < p.nblk ? present_key(key[u]) : 0u;
         }
     };
     // keys of vectors vv[u] (0 past the end) into key[0..U)
@@ -721,7 +870,7 @@ __global__ __launch_bounds__(BS_THREADS) void block_select_kernel(BlockSelParams
 #pragma unroll
         for (int u = 0; u < U; ++u) asm volatile("" : "+v"(key[u]));
 #pragma unroll
-        for (int u = 0; u < U; ++u) key[u] = vv[u] < p.n ? hkey(key[u]) : 0u;
+        for (int u = 0; u < U; ++u) key[u] = vv[u] < p.n ? present_key(key[u]) : 0u;
     };
     uint32_t bk[BB];
     if (breg) load_blocks(0, bk);
@@ -813,13 +962,14 @@ __global__ __launch_bounds__(BS_THREADS) void block_select_kernel(BlockSelParams
             p.state[q] = st;
         }
     };
-    // theta_a: the R-th largest block key (0, every block, when nblk <= R)
-    const bool all_blocks = p.nblk <= R;
+    // theta_a: the R-th largest block key (0, every block that holds a
+    // vector for the query, when there are fewer than R)
     uint32_t tha = 0;
-    if (!all_blocks) {
+    if (p.nblk > R) {
         int above;
         tha = kth(each_block, R, above);
     }
+    const bool all_blocks = tha == 0u;
     if (tid == 0) {
         sh[2] = 0;
         sh[3] = 0;
@@ -828,7 +978,7 @@ __global__ __launch_bounds__(BS_THREADS) void block_select_kernel(BlockSelParams
     }
     __syncthreads();
     each_block([&](int64_t b, uint32_t key) {
-        if (key >= tha) {
+        if (key != 0u && key >= tha) {
             const int pos = atomicAdd(&sh[2], 1);
             if (pos < kListMaxB) list[pos] = (int)b;
         }
@@ -842,13 +992,22 @@ __global__ __launch_bounds__(BS_THREADS) void block_select_kernel(BlockSelParams
         return;
     }
     load_listed(nl);
-    if (all_blocks && p.n <= KC) {
-        // every block listed and at most KC vectors: all are candidates
-        each_listed(nl, [&](int64_t v, uint32_t) { out_i[atomicAdd(&sh[3], 1)] = (int)v; });
+    if (all_blocks) {
+        // every vector for the query lies in a listed block: if at most KC,
+        // all are candidates
+        each_listed(nl, [&](int64_t v, uint32_t key) {
+            if (key != 0u) {
+                const int pos = atomicAdd(&sh[3], 1);
+                if (pos < KC) out_i[pos] = (int)v;
+            }
+        });
         __syncthreads();
-        for (int i = sh[3] + tid; i < KC; i += BS_THREADS) out_i[i] = INT_MAX;
-        finish(-INFINITY, kSelAll);
-        return;
+        const int c = sh[3];
+        if (c <= KC) {
+            for (int i = c + tid; i < KC; i += BS_THREADS) out_i[i] = INT_MAX;
+            finish(-INFINITY, kSelAll);
+            return;
+        }
     }
     if (!all_blocks) {
         // the vectors that reach theta_a (at least R)
@@ -886,6 +1045,7 @@ struct RescoreParams {
     const uint4 *codes;
     const float *scales;
     const float *qrot;         // [nqt][d] float32 rotated queries
+    const float *qconst;       // [nqt] TQ+ constant terms, or null
     const float *cents;
     const int *top_i;          // [nqt][KC] candidates (INT_MAX: none)
     const float *amin;         // [nqt] bound on the approximate score of non-candidates
@@ -899,6 +1059,7 @@ struct RescoreParams {
     int *fb_count;
     int *fb_rows;
     float *fb_q;
+    float *fb_const;
     uint64_t *fb_allow;
     int *fb_bound;
     const uint64_t *allow;     // [nqt][W] or null
@@ -911,7 +1072,9 @@ struct RescoreParams {
 //  2. Lane = candidate: wave w takes the 64 candidates of run w % S and the
 //     (w / S)-th of 16 / S slices of the chunks, so all lanes read the same
 //     table rows (as in the scan); partial integer sums meet in LDS (exact,
-//     order-free): bit-identical to the single-query scan's scores.
+//     order-free): bit-identical to the single-query scan's scores.  8-bit
+//     codes are summed in float32 in the scan's chunk order instead: waves
+//     0..S-1 take a run each over all chunks.
 //  3. Waves 0..S-1 sort their 64 exact scores; an entry's rank is its lane
 //     plus, in every other sorted run, the number of entries ahead of it
 //     (binary search); ranks below k are written.
@@ -922,7 +1085,7 @@ struct RescoreParams {
 //  5. Without a certificate the workgroup appends the query's row, its
 //     rotated coordinates and allowlist to the list that the single-query
 //     scan takes.
-template <int S>
+template <int MODE, int S>
 __global__ __launch_bounds__(kTableThreads) void rescore_kernel(RescoreParams p) {
     constexpr int KC = 64 * S;
     constexpr int SL = kTableWaves / S;    // chunk slices
@@ -936,7 +1099,8 @@ __global__ __launch_bounds__(kTableThreads) void rescore_kernel(RescoreParams p)
     const int q = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int run = wave % S, slice = wave / S;
-    const int c0 = p.chunks * slice / SL, c1 = p.chunks * (slice + 1) / SL;
+    const int c0 = MODE == BYTE ? 0 : p.chunks * slice / SL;
+    const int c1 = MODE != BYTE ? p.chunks * (slice + 1) / SL : slice == 0 ? p.chunks : 0;
     const TableShape ts{p.d, p.bits, p.lut_words};
     for (int i = tid; i < KC; i += kTableThreads) sums[i] = 0;
     if (tid == 0) {
@@ -947,8 +1111,10 @@ __global__ __launch_bounds__(kTableThreads) void rescore_kernel(RescoreParams p)
     // query's coordinates, this lane's candidate, the certificate inputs,
     // then the candidate's chunks, in flight while the table is built.
     // Every load is unconditional, from a clamped address.
-    float qv[2][4];
-    load_nibble_query(ts, p.qrot + (int64_t)q * p.d, qv);
+    QueryRegs<MODE> qv;
+    const float *qr = p.qrot + (int64_t)q * p.d;
+    if constexpr (MODE != BYTE) load_query<MODE>(ts, qr, qv);
+    const float C = p.qconst ? p.qconst[q] : 0.f;
     const int v = p.top_i[(int64_t)q * KC + run * 64 + lane];
     const QInfo qi = p.info[q];
     const float amin_s = p.amin[q];
@@ -966,9 +1132,16 @@ __global__ __launch_bounds__(kTableThreads) void rescore_kernel(RescoreParams p)
         }
     };
     load_chunks(c0);
-    nibble_abs_sum(red, qv);
-    __syncthreads();
-    const int shx = build_nibble_table(lds, red, p.cents, ts, qv);
+    int shx = 0;
+    float facc = C;
+    if constexpr (MODE == BYTE) {
+        for (int e = tid; e < kByteRepWords; e += kTableThreads) lds[e] = p.cents[e >> 5];
+        for (int e = tid; e < p.d; e += kTableThreads) lds[kByteRepWords + e] = qr[e];
+    } else {
+        query_abs_sum<MODE>(red, qv);
+        __syncthreads();
+        shx = build_int_table<MODE>(lds, red, p.cents, ts, qv, C);
+    }
     __syncthreads();
     const char *lut = reinterpret_cast<const char *>(lds);
     int acc = 0;
@@ -976,16 +1149,21 @@ __global__ __launch_bounds__(kTableThreads) void rescore_kernel(RescoreParams p)
         if (cb > c0) load_chunks(cb);
 #pragma unroll
         for (int r = 0; r < CB; ++r)
-            if (cb + r < c1) acc += nib_chunk(lut + (cb + r) * 2048, w[r]);
+            if (cb + r < c1) {
+                if constexpr (MODE == BYTE)
+                    facc += byte_chunk(lds, cb + r, w[r]);
+                else
+                    acc += int_chunk<MODE>(lut + (cb + r) * kChunkTableBytes<MODE>, w[r]);
+            }
     }
-    if (valid) atomicAdd(&sums[run * 64 + lane], acc);
+    if (MODE != BYTE && valid) atomicAdd(&sums[run * 64 + lane], acc);
     __syncthreads();
     // waves 0..S-1: sort their runs of 64 exact scores
     float s_ = -INFINITY;
     int i_ = INT_MAX;
     if (wave < S) {
         if (valid) {
-            s_ = ldexpf((float)sums[run * 64 + lane] * scl, -shx);
+            s_ = MODE == BYTE ? facc * scl : ldexpf((float)sums[run * 64 + lane] * scl, -shx);
             i_ = v;
         }
         wave_sort64(s_, i_, lane);
@@ -1052,6 +1230,7 @@ __global__ __launch_bounds__(kTableThreads) void rescore_kernel(RescoreParams p)
     if (slot < 0) return;
     for (int j = tid; j < p.d; j += kTableThreads)
         p.fb_q[(int64_t)slot * p.d + j] = p.qrot[(int64_t)q * p.d + j];
+    if (p.qconst && tid == 0) p.fb_const[slot] = p.qconst[q];
     if (p.allow)
         for (int w = tid; w < p.W; w += kTableThreads)
             p.fb_allow[(int64_t)slot * p.W + w] = p.allow[(int64_t)q * p.W + w];
@@ -1796,7 +1975,7 @@ void with_slots(int KC, Fn fn) {
 
 struct BatchLayout {
     size_t q16, info, approx, bmax, cand_s, cand_i, top_i, amin, state, gbound, tickets, count, rows, qc,
-        allow_c, lut, total;
+        qconst_c, allow_c, lut, total;
     // wide passes
     size_t w_q16, w_info, w_qfrag, w_qf, w_pil, w_theta, w_pcn, w_pci, w_pcs, w_cs, w_ci, w_cn,
         w_top, w_amin, w_state;
@@ -1834,7 +2013,7 @@ WideGeom wide_geom(const ScanShape &s, int NG, int grid, int KC) {
 // chance; beyond that (N above 6.4M at k = 10, 1.6M at k = 100) most
 // queries would overflow and fall back.
 bool wide_pass(const ScanShape &s, int64_t nq, int KC, int grid) {
-    if (nq <= kWideMinQ || s.chunks < kWideMinChunks || grid > PS_THREADS) return false;
+    if (s.bits != 4 || nq <= kWideMinQ || s.chunks < kWideMinChunks || grid > PS_THREADS) return false;
     const WideGeom w = wide_geom(s, WD_NG, grid, KC);
     const double part = (double)w.ntiles / (double)w.npil;
     return KC * part <= 0.8 * kFinalMax && 2.0 * KC * part / grid + 16.0 <= 512.0;
@@ -1879,6 +2058,8 @@ BatchLayout batch_layout(const ScanShape &s, int64_t nq, int k, int grid) {
     o += align256((size_t)nq * 4);
     L.qc = o;
     o += align256((size_t)nq * s.d * sizeof(float));
+    L.qconst_c = o;
+    o += align256((size_t)nq * sizeof(float));
     L.allow_c = o;
     o += align256((size_t)nq * s.W * sizeof(uint64_t));
     L.lut = o;
@@ -1912,6 +2093,70 @@ BatchLayout batch_layout(const ScanShape &s, int64_t nq, int k, int grid) {
     return L;
 }
 
+// Launches the score kernel of a tile.
+template <int BITS, int NR, int RING>
+hipError_t launch_scores_as(const ScoreParams &sp, int grid, size_t lds, hipStream_t stream) {
+    static bool attr = false;
+    if (!attr) {
+        const hipError_t e =
+            hipFuncSetAttribute((const void *)mfma_scores_kernel<BITS, NR, RING>,
+                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        if (e != hipSuccess) return e;
+        attr = true;
+    }
+    hipLaunchKernelGGL((mfma_scores_kernel<BITS, NR, RING>), dim3(grid), dim3(MF_THREADS), lds, stream, sp);
+    return hipGetLastError();
+}
+template <int BITS, int NR>
+hipError_t launch_scores_ring(const ScoreParams &sp, int grid, hipStream_t stream) {
+    const size_t lds = score_lds(BITS, sp.chunks, NR);
+    return sp.chunks % 8 == 0 ? launch_scores_as<BITS, NR, 8>(sp, grid, lds, stream)
+                              : launch_scores_as<BITS, NR, 4>(sp, grid, lds, stream);
+}
+hipError_t launch_scores(int bits, const ScoreParams &sp, int grid, hipStream_t stream) {
+    const bool r64 = score_replicas(bits, sp.chunks) == 64;
+    switch (bits) {
+    case 2: return launch_scores_ring<2, 64>(sp, grid, stream);
+    case 3: return launch_scores_ring<3, 64>(sp, grid, stream);
+    case 4:
+        return r64 ? launch_scores_ring<4, 64>(sp, grid, stream) : launch_scores_ring<4, 32>(sp, grid, stream);
+    default:
+        return r64 ? launch_scores_ring<8, 64>(sp, grid, stream) : launch_scores_ring<8, 32>(sp, grid, stream);
+    }
+}
+
+// LDS of the rescoring: the table, 16 floats, integer sums and sorted
+// (score, id) runs, three counters.
+int rescore_lut_words(const ScanShape &s) {
+    return s.bits == 8 ? kByteRepWords + s.d : s.bits == 3 ? s.chunks * 320 : s.chunks * 512;
+}
+size_t rescore_lds(const ScanShape &s, int KC) {
+    return (size_t)rescore_lut_words(s) * 4 + 16 * 4 + (size_t)KC * 12 + 16;
+}
+template <int MODE, int S>
+hipError_t launch_rescore_as(const RescoreParams &rp, int nqt, size_t lds, hipStream_t stream) {
+    static bool attr = false;
+    if (!attr) {
+        const hipError_t e = hipFuncSetAttribute((const void *)rescore_kernel<MODE, S>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        if (e != hipSuccess) return e;
+        attr = true;
+    }
+    hipLaunchKernelGGL((rescore_kernel<MODE, S>), dim3(nqt), dim3(kTableThreads), lds, stream, rp);
+    return hipGetLastError();
+}
+hipError_t launch_rescore(const ScanShape &s, int KC, const RescoreParams &rp, int nqt, hipStream_t stream) {
+    const size_t lds = rescore_lds(s, KC);
+    hipError_t e = hipSuccess;
+    with_slots(KC, [&](auto sc) {
+        constexpr int S = decltype(sc)::value;
+        e = s.bits == 8   ? launch_rescore_as<BYTE, S>(rp, nqt, lds, stream)
+            : s.bits == 3 ? launch_rescore_as<TRIBIT, S>(rp, nqt, lds, stream)
+                          : launch_rescore_as<NIBBLE, S>(rp, nqt, lds, stream);
+    });
+    return e;
+}
+
 // Launches wide_scores_kernel for a pass of QP query slots (QP / 2 queries
 // per wave).
 hipError_t launch_wide_scores(int QP, const WideParams &wp, int grid, hipStream_t stream) {
@@ -1943,14 +2188,17 @@ hipError_t launch_wide_scores(int QP, const WideParams &wp, int grid, hipStream_
 
 }  // namespace
 
-// LDS of the score kernel: replicated byte table and query tile.
-size_t score_lds_bytes(int d) {
-    return (size_t)score_replicas(d) * 256 * 4 + (size_t)kTile * d * 2;
+// The batched path's kernels take 2-, 3-, 4- and 8-bit codes in whole rings
+// of 4 chunks (d a multiple of 128, and of 256 at b = 2).
+bool batch_search_supported(const ScanShape &s, int k) {
+    return (s.bits == 2 || s.bits == 3 || s.bits == 4 || s.bits == 8) && s.chunks % 4 == 0 &&
+           k <= kMaxBatchK && s.W <= 64 &&
+           score_lds(s.bits, s.chunks, score_replicas(s.bits, s.chunks)) <= 160 * 1024 &&
+           rescore_lds(s, batch_candidates(k)) <= 160 * 1024;
 }
 
 bool mfma_search_supported(const ScanShape &s, int k) {
-    return s.bits == 4 && s.chunks % 8 == 0 && k <= kMaxBatchK && s.W <= 64 && s.d <= 1792 &&
-           score_lds_bytes(s.d) <= 160 * 1024;
+    return s.bits == 4 && s.chunks % 8 == 0 && s.d <= 1792 && batch_search_supported(s, k);
 }
 
 // The score matrix of a tile of 32 queries within 1 GiB (N up to 16.7M).
@@ -1974,7 +2222,7 @@ hipError_t update_scale_max(const float *scales, int64_t n, float *smax, hipStre
 hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *scales,
                        const float *smax, const uint16_t *tenants, const uint64_t *summaries,
                        const float *cents32, float cmax16, float dmax, const float *Qrot,
-                       int64_t nq, int k,
+                       const float *qconst, int64_t nq, int k,
                        const uint64_t *allow, int grid, void *ws, int64_t *ids, float *scores,
                        int *n_fallback, hipStream_t stream) {
     const BatchLayout L = batch_layout(s, nq, k, grid);
@@ -1993,30 +2241,17 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
     int *count = reinterpret_cast<int *>(w8 + L.count);
     int *rows = reinterpret_cast<int *>(w8 + L.rows);
     float *qc = reinterpret_cast<float *>(w8 + L.qc);
+    float *qconst_c = reinterpret_cast<float *>(w8 + L.qconst_c);
     uint64_t *allow_c = reinterpret_cast<uint64_t *>(w8 + L.allow_c);
     void *lut_ws = w8 + L.lut;
     int *lut_bounds = lut_search_bounds(s, nq, k, grid, lut_ws);
     const int64_t npad = approx_row(s);
-    const size_t lds_scores = score_lds_bytes(s.d);
     const int KC = batch_candidates(k);   // candidates per query
-    // table, 16 floats, integer sums and sorted (score, id) runs, three counters
-    const size_t lds_rescore = (size_t)s.chunks * 2048 + 16 * 4 + (size_t)KC * 12 + 16;
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)mfma_scores_kernel<64>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void *)mfma_scores_kernel<32>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        for (int S = 1; S <= 8 && e == hipSuccess; S *= 2)
-            with_slots(64 * S, [&](auto sc) {
-                e = hipFuncSetAttribute((const void *)rescore_kernel<decltype(sc)::value>,
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-            });
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void *)final_select_kernel,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)(kFinalMax * 8));
+        hipError_t e = hipFuncSetAttribute((const void *)final_select_kernel,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)(kFinalMax * 8));
         if (e == hipSuccess)
             e = hipFuncSetAttribute((const void *)pilot_select_kernel,
                                     hipFuncAttributeMaxDynamicSharedMemorySize, kPilotMax * 2);
@@ -2029,6 +2264,7 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
         rp.codes = reinterpret_cast<const uint4 *>(blocked);
         rp.scales = scales;
         rp.qrot = Qrot + q0 * s.d;
+        rp.qconst = qconst ? qconst + q0 : nullptr;
         rp.cents = cents32;
         rp.top_i = ti;
         rp.amin = am;
@@ -2039,6 +2275,7 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
         rp.fb_count = count;
         rp.fb_rows = rows;
         rp.fb_q = qc;
+        rp.fb_const = qconst_c;
         rp.fb_allow = allow_c;
         rp.fb_bound = lut_bounds;
         rp.allow = allow ? allow + q0 * s.W : nullptr;
@@ -2047,13 +2284,9 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
         rp.d = s.d;
         rp.bits = s.bits;
         rp.chunks = s.chunks;
-        rp.lut_words = s.chunks * 512;
+        rp.lut_words = rescore_lut_words(s);
         rp.k = k;
-        with_slots(KC, [&](auto sc) {
-            constexpr int S = decltype(sc)::value;
-            hipLaunchKernelGGL(rescore_kernel<S>, dim3(nqt), dim3(kTableThreads), lds_rescore, stream,
-                               rp);
-        });
+        return launch_rescore(s, KC, rp, nqt, stream);
     };
     for (int64_t q0 = 0; q0 < nq;) {
         if (wide_pass(s, nq - q0, KC, grid)) {
@@ -2079,7 +2312,8 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
             int *wstate = reinterpret_cast<int *>(w8 + L.w_state);
             const uint64_t *allow_p = allow ? allow + q0 * s.W : nullptr;
             hipLaunchKernelGGL(prep_kernel, dim3(nqt), dim3(SEL_THREADS), 0, stream,
-                               Qrot + q0 * s.d, nqt, s.d, smax, cmax16, dmax, wq16, winfo,
+                               Qrot + q0 * s.d, qconst ? qconst + q0 : nullptr, nqt, s.d, s.bits, smax,
+                               cmax16, dmax, wq16, winfo,
                                nullptr, 0, q0 == 0 ? count : nullptr);
             const int64_t fr = (int64_t)(s.d / 32) * QP * 4;
             hipLaunchKernelGGL(frag_kernel, dim3((int)std::min<int64_t>((fr + 255) / 256, 1024)),
@@ -2146,15 +2380,15 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
             fp.state = wstate;
             hipLaunchKernelGGL(final_select_kernel, dim3(nqt), dim3(PS_THREADS),
                                (size_t)kFinalMax * 8, stream, fp);
-            rescore(q0, nqt, wtop, wamin, wstate, winfo);
             e = hipGetLastError();
+            if (e == hipSuccess) e = rescore(q0, nqt, wtop, wamin, wstate, winfo);
             if (e != hipSuccess) return e;
             q0 += nqt;
             continue;
         }
         const int nqt = (int)std::min<int64_t>(nq - q0, kTile);
         hipLaunchKernelGGL(prep_kernel, dim3(nqt), dim3(SEL_THREADS), 0, stream, Qrot + q0 * s.d,
-                           nqt, s.d, smax, cmax16, dmax, q16, info, tickets, grid * kTicketStride,
+                           qconst ? qconst + q0 : nullptr, nqt, s.d, s.bits, smax, cmax16, dmax, q16, info, tickets, grid * kTicketStride,
                            q0 == 0 ? count : nullptr);
         ScoreParams sp{};
         sp.codes = reinterpret_cast<const uint4 *>(blocked);
@@ -2171,12 +2405,8 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
         sp.chunks = s.chunks;
         sp.nqt = nqt;
         sp.tickets = tickets;
-        if (score_replicas(s.d) == 64)
-            hipLaunchKernelGGL(mfma_scores_kernel<64>, dim3(grid), dim3(MF_THREADS), lds_scores,
-                               stream, sp);
-        else
-            hipLaunchKernelGGL(mfma_scores_kernel<32>, dim3(grid), dim3(MF_THREADS), lds_scores,
-                               stream, sp);
+        hipError_t e = launch_scores(s.bits, sp, grid, stream);
+        if (e != hipSuccess) return e;
         if (allow) {
             // the block maxima ignore the allowlist: select over every allowed score
             hipLaunchKernelGGL(fill_order_keys, dim3(1), dim3(64), 0, stream, gbound, nqt);
@@ -2210,8 +2440,8 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
             bp.KC = KC;
             hipLaunchKernelGGL(block_select_kernel, dim3(nqt), dim3(BS_THREADS), 0, stream, bp);
         }
-        rescore(q0, nqt, top_i, amin, state, info);
-        hipError_t e = hipGetLastError();
+        e = hipGetLastError();
+        if (e == hipSuccess) e = rescore(q0, nqt, top_i, amin, state, info);
         if (e != hipSuccess) return e;
         q0 += nqt;
     }
@@ -2222,7 +2452,8 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
     qr.count = count;
     qr.rows = rows;
     hipError_t e = lut_search(s, blocked, scales, tenants, summaries, cents32, qc, nq, k, f, grid, lut_ws,
-                              lut_search_workspace_bytes(s, nq, k, grid), ids, scores, stream, nullptr,
+                              lut_search_workspace_bytes(s, nq, k, grid), ids, scores, stream,
+                              qconst ? qconst_c : nullptr,
                               lut_bounds != nullptr, qr);
     if (e != hipSuccess || !n_fallback) return e;
     e = hipMemcpyAsync(n_fallback, count, sizeof(int), hipMemcpyDeviceToHost, stream);

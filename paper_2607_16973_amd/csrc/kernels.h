@@ -168,9 +168,10 @@ constexpr int kBoundInit = (int)0x807FFFFFu;
 // without a launch of its own in between.
 int *lut_search_bounds(const ScanShape &s, int64_t nq, int k, int grid, void *ws);
 
-// Batched search of a tile of queries on the matrix cores with exact
-// rescoring (b = 4, chunks % 8 == 0, d <= 1792, k <= 256, at most 4096
-// tenants).
+// Batched search on the matrix cores with exact rescoring.
+// batch_search_supported: the shapes its kernels take; mfma_search_supported:
+// those that TQ_PATH_MFMA is documented to take (b = 4, d % 256 == 0,
+// d <= 1792, k <= 256, at most 4096 tenants).
 // cmax16 = max |float16(c_l)|, dmax = max |float16(c_l) - c_l| over the
 // float32 centroids cents32.
 // Queries whose top k the certificate does not prove are re-run on the
@@ -178,6 +179,7 @@ int *lut_search_bounds(const ScanShape &s, int64_t nq, int k, int grid, void *ws
 // count goes there and the call synchronises `stream` once to read it;
 // without, everything is asynchronous.  `smax` is a device float: the
 // largest |scale| in the store.
+bool batch_search_supported(const ScanShape &s, int k);
 bool mfma_search_supported(const ScanShape &s, int k);
 // Whether the workspace of the batched path stays moderate (about 1.1 GiB).
 bool batch_matrix_fits(const ScanShape &s);
@@ -185,7 +187,7 @@ size_t mfma_search_workspace_bytes(const ScanShape &s, int64_t nq, int k, int gr
 hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *scales,
                        const float *smax, const uint16_t *tenants, const uint64_t *summaries,
                        const float *cents32, float cmax16, float dmax, const float *Qrot,
-                       int64_t nq, int k,
+                       const float *qconst, int64_t nq, int k,
                        const uint64_t *allow, int grid, void *ws, int64_t *ids, float *scores,
                        int *n_fallback, hipStream_t stream);
 // *smax = max(*smax, max of |scales[0..n)|).

@@ -1,6 +1,6 @@
 // Per-query lookup tables for 4-bit fields of the code stream (b in
-// {1, 2, 4}) and for 3-bit codes (b = 3), and the integer scoring that uses
-// them (device code, shared by the single-query scan and the exact
+// {1, 2, 4}) and for 3-bit codes (b = 3) with the integer scoring that uses
+// them, and the float32 scoring of 8-bit codes (device code, shared by the single-query scan and the exact
 // rescoring of the batched search).
 //
 // One row of 16 int32 entries per 4-bit field of the code stream (row r
@@ -242,6 +242,84 @@ __device__ inline int tri10(const char *__restrict__ Lb, uint32_t w) {
 // bytes of table rows.
 __device__ inline int tri_chunk(const char *__restrict__ Lb, uint4 v) {
     return (tri10(Lb, v.x) + tri10(Lb + 320, v.y)) + (tri10(Lb + 640, v.z) + tri10(Lb + 960, v.w));
+}
+
+// ---------------------------------------------------------------- b = 8
+// The 256 float32 centroids, each repeated 32 times, followed by q'.
+// Centroid e of lane l is at byte 128 e + 4 (l % 32): the 32 lanes of a
+// half-wave always read 32 different banks, whatever their codes.  A
+// vector's sum starts at C and adds its chunks in order.
+constexpr int kByteRepWords = 256 * 32;
+
+// Sum over the four codes of word w of c[code] q'_j; rep is the repeated
+// centroids, lo = 4 (lane % 32).  Each address is a bit-field extract and a
+// shift-add (the empty asm keeps the compiler from re-forming them).
+__device__ inline float byte4(const char *__restrict__ rep, const float *__restrict__ q,
+                              uint32_t w, uint32_t lo) {
+    uint32_t e0 = __builtin_amdgcn_ubfe(w, 0, 8), e1 = __builtin_amdgcn_ubfe(w, 8, 8);
+    uint32_t e2 = __builtin_amdgcn_ubfe(w, 16, 8), e3 = w >> 24;
+    asm volatile("" : "+v"(e0), "+v"(e1), "+v"(e2), "+v"(e3));
+    const float c0 = *reinterpret_cast<const float *>(rep + (e0 << 7) + lo);
+    const float c1 = *reinterpret_cast<const float *>(rep + (e1 << 7) + lo);
+    const float c2 = *reinterpret_cast<const float *>(rep + (e2 << 7) + lo);
+    const float c3 = *reinterpret_cast<const float *>(rep + (e3 << 7) + lo);
+    float a = c0 * q[0];
+    float b = c1 * q[1];
+    a = fmaf(c2, q[2], a);
+    b = fmaf(c3, q[3], b);
+    return a + b;
+}
+
+// The 16 codes of chunk c.
+__device__ inline float byte_chunk(const float *__restrict__ lds, int c, uint4 v) {
+    const char *rep = reinterpret_cast<const char *>(lds);
+    const float *q = lds + kByteRepWords + c * 16;
+    const uint32_t lo = (threadIdx.x & 31u) << 2;
+    return (byte4(rep, q, v.x, lo) + byte4(rep, q + 4, v.y, lo)) +
+           (byte4(rep, q + 8, v.z, lo) + byte4(rep, q + 12, v.w, lo));
+}
+
+// Kind of table: b in {1, 2, 4}, b = 3, b = 8.
+enum Mode { NIBBLE = 0, TRIBIT = 1, BYTE = 2 };
+
+// The integer-table modes: the query coordinates a thread loads ahead of
+// the build, and the bytes of table per 16-byte chunk of codes.
+template <int MODE> struct QueryRegs { float v[2][4]; };
+template <> struct QueryRegs<TRIBIT> { float v[kTriRowsPerThread]; };
+template <int MODE> constexpr int kChunkTableBytes = MODE == TRIBIT ? 1280 : 2048;
+
+template <int MODE>
+__device__ inline void load_query(const TableShape &t, const float *__restrict__ q,
+                                  QueryRegs<MODE> &r) {
+    if constexpr (MODE == TRIBIT)
+        load_tribit_query(t, q, r.v);
+    else
+        load_nibble_query(t, q, r.v);
+}
+
+template <int MODE>
+__device__ inline void query_abs_sum(float *red, const QueryRegs<MODE> &r) {
+    if constexpr (MODE == TRIBIT)
+        tribit_abs_sum(red, r.v);
+    else
+        nibble_abs_sum(red, r.v);
+}
+
+template <int MODE>
+__device__ inline int build_int_table(float *lds, const float *red, const float *cents,
+                                      const TableShape &t, const QueryRegs<MODE> &r, float C) {
+    if constexpr (MODE == TRIBIT)
+        return build_tribit_table(lds, red, cents, t, r.v, C);
+    else
+        return build_nibble_table(lds, red, cents, t, r.v, C);
+}
+
+template <int MODE>
+__device__ inline int int_chunk(const char *__restrict__ Lb, uint4 v) {
+    if constexpr (MODE == TRIBIT)
+        return tri_chunk(Lb, v);
+    else
+        return nib_chunk(Lb, v);
 }
 
 }  // namespace tq

@@ -39,8 +39,6 @@ constexpr int SCAN_WAVES = SCAN_THREADS / 64;
 // instructions may move across, memory loads and stores to HBM may not.
 constexpr int kKeepVmem = 0x1 | 0x2 | 0x4 | 0x8 | 0x80 | 0x100 | 0x200 | 0x400;
 
-enum Mode { NIBBLE = 0, TRIBIT = 1, BYTE = 2 };
-
 struct ScanParams {
     const uint4 *codes;
     const float *scales;
@@ -93,70 +91,7 @@ __device__ inline TableShape table_shape(const ScanParams &p) {
 // b in {1,2,4}: int32 fixed-point rows of 16 entries per 4-bit field (lut.h).
 // b = 3: int32 fixed-point rows of 8 entries per coordinate (lut.h).
 // b = 8: the 256 float32 centroids, each repeated 32 times, followed by q'
-// (multiplied on the fly).  Centroid e of lane l is at byte 128 e + 4 (l % 32):
-// the 32 lanes of a half-wave always read 32 different banks, whatever
-// their codes.
-
-constexpr int kByteRepWords = 256 * 32;
-
-// Sum over the four codes of word w of c[code] q'_j; rep is the repeated
-// centroids, lo = 4 (lane % 32).  Each address is a bit-field extract and a
-// shift-add (the empty asm keeps the compiler from re-forming them).
-__device__ inline float byte4(const char *__restrict__ rep, const float *__restrict__ q,
-                              uint32_t w, uint32_t lo) {
-    uint32_t e0 = __builtin_amdgcn_ubfe(w, 0, 8), e1 = __builtin_amdgcn_ubfe(w, 8, 8);
-    uint32_t e2 = __builtin_amdgcn_ubfe(w, 16, 8), e3 = w >> 24;
-    asm volatile("" : "+v"(e0), "+v"(e1), "+v"(e2), "+v"(e3));
-    const float c0 = *reinterpret_cast<const float *>(rep + (e0 << 7) + lo);
-    const float c1 = *reinterpret_cast<const float *>(rep + (e1 << 7) + lo);
-    const float c2 = *reinterpret_cast<const float *>(rep + (e2 << 7) + lo);
-    const float c3 = *reinterpret_cast<const float *>(rep + (e3 << 7) + lo);
-    float a = c0 * q[0];
-    float b = c1 * q[1];
-    a = fmaf(c2, q[2], a);
-    b = fmaf(c3, q[3], b);
-    return a + b;
-}
-
-// The integer-table modes: the query coordinates a thread loads ahead of
-// the build, and the bytes of table per 16-byte chunk of codes.
-template <int MODE> struct QueryRegs { float v[2][4]; };
-template <> struct QueryRegs<TRIBIT> { float v[kTriRowsPerThread]; };
-template <int MODE> constexpr int kChunkTableBytes = MODE == TRIBIT ? 1280 : 2048;
-
-template <int MODE>
-__device__ inline void load_query(const TableShape &t, const float *__restrict__ q,
-                                  QueryRegs<MODE> &r) {
-    if constexpr (MODE == TRIBIT)
-        load_tribit_query(t, q, r.v);
-    else
-        load_nibble_query(t, q, r.v);
-}
-
-template <int MODE>
-__device__ inline void query_abs_sum(float *red, const QueryRegs<MODE> &r) {
-    if constexpr (MODE == TRIBIT)
-        tribit_abs_sum(red, r.v);
-    else
-        nibble_abs_sum(red, r.v);
-}
-
-template <int MODE>
-__device__ inline int build_int_table(float *lds, const float *red, const float *cents,
-                                      const TableShape &t, const QueryRegs<MODE> &r, float C) {
-    if constexpr (MODE == TRIBIT)
-        return build_tribit_table(lds, red, cents, t, r.v, C);
-    else
-        return build_nibble_table(lds, red, cents, t, r.v, C);
-}
-
-template <int MODE>
-__device__ inline int int_chunk(const char *__restrict__ Lb, uint4 v) {
-    if constexpr (MODE == TRIBIT)
-        return tri_chunk(Lb, v);
-    else
-        return nib_chunk(Lb, v);
-}
+// (multiplied on the fly; lut.h).
 
 template <int MODE> struct AccOf { typedef int type; };
 template <> struct AccOf<BYTE> { typedef float type; };
@@ -164,11 +99,7 @@ template <> struct AccOf<BYTE> { typedef float type; };
 template <int MODE>
 __device__ inline typename AccOf<MODE>::type chunk_sum(const float *__restrict__ lds, int c, uint4 v) {
     if constexpr (MODE == BYTE) {
-        const char *rep = reinterpret_cast<const char *>(lds);
-        const float *q = lds + kByteRepWords + c * 16;
-        const uint32_t lo = (threadIdx.x & 31u) << 2;
-        return (byte4(rep, q, v.x, lo) + byte4(rep, q + 4, v.y, lo)) +
-               (byte4(rep, q + 8, v.z, lo) + byte4(rep, q + 12, v.w, lo));
+        return byte_chunk(lds, c, v);
     } else {
         return int_chunk<MODE>(reinterpret_cast<const char *>(lds) + c * kChunkTableBytes<MODE>, v);
     }

@@ -49,6 +49,25 @@ def test_default_equals_scan(n, nq, k):
     same(idx.search(Q, k), idx.search(Q, k, path="lut"))
 
 
+# every width of the batched kernels' feeds: rings of 4 and of 8 chunks, 64
+# and 32 table replicas (d = 2048), the shortest vectors, ragged n and tiles
+@pytest.mark.parametrize("d,bits,n,nq,k", [
+    (256, 2, 20_011, 33, 10), (768, 2, 20_011, 12, 10), (1536, 2, 9_001, 40, 100),
+    (128, 3, 20_011, 33, 10), (768, 3, 9_001, 70, 20), (2048, 3, 9_001, 20, 10),
+    (128, 4, 20_011, 33, 10), (384, 4, 20_011, 40, 10), (2048, 4, 9_001, 20, 10),
+    (64, 8, 20_011, 33, 10), (768, 8, 9_001, 70, 100), (2048, 8, 5_001, 20, 256)])
+@pytest.mark.parametrize("plus", [False, True])
+def test_widths(d, bits, n, nq, k, plus):
+    X = corpus(n, d, 30)
+    idx = tq.Index(tq.Codebook(d, bits), rotation(d))
+    if plus:
+        idx.calibrate(X[:2000])
+    idx.add(X)
+    Q = queries(X, nq, 31)
+    assert idx.workspace_bytes(nq, k) > idx.workspace_bytes(nq, k, path="lut")   # the batched path's
+    same(idx.search(Q, k), idx.search(Q, k, path="lut"))
+
+
 @pytest.mark.parametrize("nq", [12, 40, 100])
 def test_queries_without_certificate(nq):
     # every score ties: no candidate set can be proven, every query goes to the scan
