@@ -1118,6 +1118,14 @@ static bool batch_pays(const ScanShape &sh, int64_t nq) {
     return (double)nq * ((b8 ? 30.0 : 9.0) + pass_us) > tiles * ((b8 ? 83.0 : 58.0) + pass_us);
 }
 
+// With tenant allowlists the scan skips blocks query by query and may be the
+// faster one whatever the sizes; the device decides, at the price of the
+// pass's launches (about 20 us) when it is the scan.  From 6 queries on the
+// pass has been the faster one even for the most selective lists: one tenant
+// of 1,000 per query, 1,000,000 vectors, scan / batched 82 / 91 us for 4
+// queries, 124 / 98 for 8, 410 / 170 for 32 (one of 10: 1,082 / 250 for 8).
+constexpr int64_t kBatchFiltered = 6;
+
 static bool auto_batch(const ScanShape &sh, int64_t nq, int k) {
     return batch_search_supported(sh, k) && batch_matrix_fits(sh) && batch_pays(sh, nq);
 }
@@ -1232,7 +1240,8 @@ tq_status tq_search_ex(const tq_index *idx, const float *Q_dev, int64_t nq, int3
         return fail(TQ_EINVAL, "workspace too small: need " + std::to_string(need) + " bytes");
     // a workspace sized for the scan alone is still taken (by the scan)
     const bool batched = use_mfma(sh, k, base) ||
-                         (base == TQ_PATH_AUTO && !filter.any() && auto_batch(sh, nq, k) &&
+                         (base == TQ_PATH_AUTO && !filter.slot_allow &&
+                          (!filter.allow || nq >= kBatchFiltered) && auto_batch(sh, nq, k) &&
                           workspace_bytes >= batch_bytes(sh, nq, k, idx->calibrated));
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (idx->n == 0) {
@@ -1278,7 +1287,7 @@ tq_status tq_search_ex(const tq_index *idx, const float *Q_dev, int64_t nq, int3
         centroid_half_bounds(idx, &cmax16, &dmax);
         hipError_t e = mfma_search(sh, idx->codes, idx->scales, scale_max_dev(idx), idx->tenants,
                                    idx->summ, idx->cents_dev, cmax16, dmax, Qrot, qconst, nq, k,
-                                   allow_dev, grid, workspace_dev, ids_dev, scores_dev,
+                                   filter, grid, workspace_dev, ids_dev, scores_dev,
                                    base == TQ_PATH_MFMA ? &n_fallback : nullptr, s);
         if (e != hipSuccess) return hip_fail(e, "matrix-core search");
         if (idx->idmap && (e = map_ids(ids_dev, nq * k, idx->ext, s)) != hipSuccess)

@@ -18,9 +18,12 @@
 //     maximum reaches it: a radix selection over the block maxima lists
 //     those blocks, and their vectors that reach it are the candidates
 //     (about R when vectors sit at random positions; if more than KC, a
-//     radix selection over the listed scores keeps the KC best).  Filtered
-//     (the block maxima ignore the allowlist): select_kernel +
-//     select_merge_kernel, the KC best allowed scores.
+//     radix selection over the listed scores keeps the KC best).
+//     Filtered: filter_kernel lists the blocks that some query of the tile
+//     may need (tenant summary against the union of the allowlists, live
+//     slots) and turns the allowlists into a bit mask over the tile's queries
+//     per tenant; only listed blocks are read, and a vector that a query may
+//     not return scores -inf for it.
 //  4. rescore_kernel: the exact score of each candidate with the
 //     single-query scan's integer table (bit-identical scores), the top k of
 //     them, and a certificate: with E a rigorous bound on |approximate -
@@ -67,13 +70,10 @@ constexpr int kSelAll = 2;         // every vector is a candidate
 constexpr int MF_THREADS = 768;    // 12 waves: three per SIMD, 168 registers each
 constexpr int kTableBytes = 256 * 32 * 4;   // byte table, 32 replicas
 constexpr int SEL_THREADS = 256;
-constexpr int SEL_GROUPS = 32;     // select workgroups per query
-constexpr int kBoundStride = 32;  // ints between the global bounds of two queries
 constexpr int kTicketStride = 32;  // ints between two workgroups' ticket counters (own 128 B line)
 // Last word of a raw buffer resource (stride 0, byte offsets): 32-bit data
 // format, so untyped loads, stores and atomics are bounds-checked by bytes.
 constexpr int kBufferWord3 = 0x00020000;
-constexpr int kBuf = 8 * 64 + 64;  // per-wave candidate buffer: one load of 8 scores per lane + a partial 64
 constexpr int kKeepVmemB = 0x1 | 0x2 | 0x4 | 0x8 | 0x80 | 0x100 | 0x200 | 0x400;
 
 // fn(std::integral_constant<int, i>) for i = 0 .. N-1.
@@ -199,6 +199,120 @@ __global__ void prep_kernel(const float *__restrict__ Q, const float *__restrict
     }
 }
 
+// ----------------------------------------------------------------- filters
+// Whether the single-query scan answers a pass's queries faster: it skips
+// blocks by each query's own allowlist, the batched kernels by the union
+// (tiles) or not at all (wide passes).  counts[0]: blocks of the union,
+// counts[1]: blocks over all queries, from every kSampleB-th block.  The
+// kernels of the pass leave at once then and the rescoring hands every query
+// over.  Decided on the device: the host does not know the allowlists.
+constexpr int kSampleB = 8;
+struct Gate {
+    const int *counts;         // null: never
+    float scan_us, block_us;   // scan: per query, per block
+    float pass_us, read_us;    // batched: per pass, per union block
+};
+__device__ inline bool scan_is_faster(const Gate &g, int nqt) {
+    if (!g.counts) return false;
+    return (float)nqt * g.scan_us + (float)g.counts[1] * (float)kSampleB * g.block_us <
+           g.pass_us + (float)g.counts[0] * g.read_us;
+}
+
+struct FilterParams {
+    const uint64_t *allow;     // [nqt][W] or null
+    const uint64_t *live;      // [nblk] or null
+    const uint64_t *summaries; // [nblk][W]
+    int64_t nblk;
+    int W, nqt;
+    int words;                 // 32-query words per tenant
+    uint32_t *tmask;           // [64 W][words]: bit q of a tenant's mask: query q admits it
+    int *counts;               // see Gate; zero at launch
+    int *list;                 // tiles: union blocks (order not fixed), or null
+    uint16_t *bmax;            // tiles: [32][nblk], -inf for blocks that are not listed
+};
+
+// Workgroups of one thread per (tenant, mask word), then of one thread per
+// block.  The latter stage the allowlists in LDS, 32 queries at a time
+// (their words read one by one from L2 made the kernel 40 us at 1,000
+// tenants), and share out the (sampled block, query) tests.
+constexpr int FK_THREADS = 256;
+constexpr int FK_SAMPLES = FK_THREADS / kSampleB;
+__global__ __launch_bounds__(FK_THREADS) void filter_kernel(FilterParams p) {
+    __shared__ uint64_t allow_s[32 * 64];            // [query][W] of 32 queries
+    __shared__ uint64_t sum_s[FK_SAMPLES * 64];      // [sampled block][W]
+    __shared__ unsigned long long any_s[64];         // union of the allowlists (W <= 64)
+    const int tid = threadIdx.x, lane = tid & 63, W = p.W;
+    const int mask_items = 64 * W * p.words;
+    const int mask_wgs = (mask_items + FK_THREADS - 1) / FK_THREADS;
+    if ((int)blockIdx.x < mask_wgs) {
+        const int e = blockIdx.x * FK_THREADS + tid;
+        if (e < mask_items) {
+            const int t = e / p.words, q0 = e % p.words * 32;
+            uint32_t m = p.allow ? 0u : ~0u;
+            if (p.allow) {
+#pragma unroll
+                for (int i = 0; i < 32; ++i) {
+                    const int q = q0 + i < p.nqt ? q0 + i : 0;
+                    const uint64_t a = p.allow[(int64_t)q * W + (t >> 6)] >> (t & 63);
+                    m |= q0 + i < p.nqt ? (uint32_t)(a & 1ull) << i : 0u;
+                }
+            }
+            p.tmask[e] = m;
+        }
+        return;
+    }
+    const int64_t b0 = (int64_t)(blockIdx.x - mask_wgs) * FK_THREADS;
+    const int64_t b = b0 + tid;
+    bool hit = b < p.nblk && (!p.live || p.live[b] != 0);
+    int sum = 0;
+    if (!p.allow) {
+        sum = hit && b % kSampleB == 0 ? p.nqt : 0;
+    } else {
+        // summaries of the sampled blocks (b0 + kSampleB i), zero where dead
+        for (int e = tid; e < FK_SAMPLES * W; e += FK_THREADS) {
+            const int64_t sb = b0 + kSampleB * (e / W);
+            const bool in = sb < p.nblk && (!p.live || p.live[sb] != 0);
+            sum_s[e] = in ? p.summaries[sb * W + e % W] : 0ull;
+        }
+        if (tid < 64) any_s[tid] = 0;
+        for (int q0 = 0; q0 < p.nqt; q0 += 32) {
+            const int nq = p.nqt - q0 < 32 ? p.nqt - q0 : 32;
+            __syncthreads();   // the previous queries' rows have been read
+            for (int e = tid; e < nq * W; e += FK_THREADS) {
+                const uint64_t a = p.allow[(int64_t)q0 * W + e];
+                allow_s[e] = a;
+                if (a) atomicOr(&any_s[e % W], (unsigned long long)a);
+            }
+            __syncthreads();
+            for (int e = tid; e < FK_SAMPLES * nq; e += FK_THREADS) {
+                const uint64_t *sm = sum_s + e / nq * W, *al = allow_s + e % nq * W;
+                bool h = false;
+                for (int w = 0; w < W; ++w) h |= (sm[w] & al[w]) != 0;
+                sum += h;
+            }
+        }
+        if (hit) {
+            const uint64_t *sm = p.summaries + b * W;
+            hit = false;
+            for (int w = 0; w < W; ++w) hit |= (sm[w] & any_s[w]) != 0;
+        }
+    }
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    const uint64_t m = __ballot(hit);
+    int at = 0;
+    if (lane == 0) {
+        if (sum) atomicAdd(p.counts + 1, sum);
+        if (m) at = atomicAdd(p.counts, (int)__popcll(m));
+    }
+    if (!p.list) return;
+    at = __shfl(at, 0, 64);
+    if (hit) {
+        p.list[at + __popcll(m & ((1ull << lane) - 1))] = (int)b;
+    } else if (b < p.nblk) {
+        for (int q = 0; q < kTile; ++q) p.bmax[(int64_t)q * p.nblk + b] = 0xFC00u;   // -inf
+    }
+}
+
 // ------------------------------------------------------------ MFMA scores
 struct ScoreParams {
     const uint4 *codes;        // blocked store
@@ -211,6 +325,13 @@ struct ScoreParams {
     int *tickets;              // [grid * kTicketStride] block ticket counters, zero at launch
     int64_t n, nblk, npad;
     int d, chunks, nqt;
+    // filtered tiles
+    const int *list;           // blocks to score, counts[0] of them
+    const int *counts;
+    const uint32_t *tmask;     // [tenant] queries that admit it
+    const uint16_t *tenants;
+    const uint64_t *live;      // [nblk] or null
+    Gate gate;
 };
 
 // Float16 centroids of the 8 4-bit fields of a stored word w (the canonical
@@ -358,8 +479,12 @@ __device__ inline void copy4(const uint4 &v, uint32_t &a, uint32_t &b, uint32_t 
 
 // Replicas of the score kernel's table: 64 where the table (64 KiB at b = 4
 // and 8) and the query tile (2 KiB a step) fit the 160 KiB of LDS together.
+// At b = 2 and 3 the table leaves room for the queries' factors in LDS; the
+// feeds of these widths leave no registers for them.
+__host__ __device__ constexpr bool factors_in_lds(int bits) { return bits == 2 || bits == 3; }
 __host__ __device__ constexpr size_t score_lds(int bits, int chunks, int nr) {
-    return (size_t)feed_entries(bits) * nr * 4 + (size_t)feed_steps(bits, chunks) * 2048;
+    return (size_t)feed_entries(bits) * nr * 4 + (size_t)feed_steps(bits, chunks) * 2048 +
+           (factors_in_lds(bits) ? 2 * kTile * 4 : 0);
 }
 __host__ __device__ constexpr int score_replicas(int bits, int chunks) {
     return score_lds(bits, chunks, 64) <= 160 * 1024 ? 64 : 32;
@@ -375,7 +500,10 @@ __host__ __device__ constexpr int score_replicas(int bits, int chunks) {
 // block; RING = 4 for chunk counts that 8 does not divide).  The kernel is
 // bound by the code stream: 1,000,000 vectors at d = 1536 and 4 bits take
 // 152 to 178 us, 4.3 to 5.1 TB/s, whatever the number of queries in the tile.
-template <int BITS, int NR, int RING>
+// FILT: the blocks of p.list, with the tile's allowlists and the live slots
+// applied to the stored scores.  A block's tenant ids are loaded a block
+// ahead and its query masks at its start, so neither wait drains the ring.
+template <int BITS, int NR, int RING, bool FILT>
 __global__ __launch_bounds__(MF_THREADS) void mfma_scores_kernel(ScoreParams p) {
     using F = Feed<BITS>;
     static_assert(RING % F::U == 0 && (RING == 4 || RING == 8), "whole units in the ring");
@@ -387,8 +515,18 @@ __global__ __launch_bounds__(MF_THREADS) void mfma_scores_kernel(ScoreParams p) 
     const int lane = tid & 63;
     const int G = gridDim.x, g = blockIdx.x;
     const int CH = p.chunks;   // multiple of RING
-    const int64_t gb0 = p.nblk * g / G, gb1 = p.nblk * (g + 1) / G;
+    if (FILT && scan_is_faster(p.gate, p.nqt)) return;
+    const int64_t nb = FILT ? (int64_t)*p.counts : p.nblk;
+    const int64_t gb0 = nb * g / G, gb1 = nb * (g + 1) / G;
     const int nbw = (int)(gb1 - gb0);
+    if (FILT && nbw == 0) return;
+    // the block of this workgroup's share entry i (scalar loads of the list)
+    typedef const __attribute__((address_space(4))) int *const_int;
+    typedef const __attribute__((address_space(4))) uint64_t *const_u64;
+    auto block_of = [&](int i) -> int64_t {
+        if constexpr (FILT) return ((const_int)(uintptr_t)p.list)[gb0 + i];
+        else return gb0 + i;
+    };
 
     // query tile in operand order, zero rows past nqt
     for (int e = tid; e < feed_steps(BITS, CH) * 128; e += MF_THREADS) {
@@ -422,16 +560,26 @@ __global__ __launch_bounds__(MF_THREADS) void mfma_scores_kernel(ScoreParams p) 
         T[e] = table_entry<BITS>(p.cents, e / NR);   // e % NR is the replica
     const uint32_t lb = (uint32_t)(lane & (NR - 1)) * 4;
     // per-lane query factors: tile t, rows 4*(lane/16) + r
+    constexpr bool FL = factors_in_lds(BITS);
     float qf[2][4], qc[2][4];
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int q = 16 * t + 4 * (lane >> 4) + r;
-            const QInfo qi = p.info[q < p.nqt ? q : 0];
-            qf[t][r] = q < p.nqt ? qi.f : 0.f;
-            qc[t][r] = q < p.nqt ? qi.c : 0.f;
+    float *fl = reinterpret_cast<float *>(Qf + feed_steps(BITS, CH) * 128);   // [2][32]: f, c
+    if constexpr (FL) {
+        if (tid < kTile) {
+            const QInfo qi = p.info[tid < p.nqt ? tid : 0];
+            fl[tid] = tid < p.nqt ? qi.f : 0.f;
+            fl[kTile + tid] = tid < p.nqt ? qi.c : 0.f;
         }
+    } else {
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int q = 16 * t + 4 * (lane >> 4) + r;
+                const QInfo qi = p.info[q < p.nqt ? q : 0];
+                qf[t][r] = q < p.nqt ? qi.f : 0.f;
+                qc[t][r] = q < p.nqt ? qi.c : 0.f;
+            }
+    }
     __syncthreads();
 
     // The ticket is a buffer atomic issued by every lane, of which only lane
@@ -447,7 +595,18 @@ __global__ __launch_bounds__(MF_THREADS) void mfma_scores_kernel(ScoreParams p) 
     int cur = __builtin_amdgcn_readfirstlane(take());
     if (cur >= nbw) return;
     int nxt = __builtin_amdgcn_readfirstlane(take());
-    const uint4 *bsrc = p.codes + (gb0 + cur) * CH * 64;   // uniform: the block's chunk 0
+    int64_t blk = block_of(cur);
+    const uint4 *bsrc = p.codes + blk * CH * 64;   // uniform: the block's chunk 0
+    const int qrow = lane & 15, kq = lane >> 4;
+    int ten[4] = {0, 0, 0, 0};   // filtered: tenants of the current block's vectors 16m + qrow
+    auto load_tenants = [&](int64_t b) {
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            const int64_t v = b * 64 + 16 * m + qrow;
+            ten[m] = p.tenants[v < p.n ? v : 0];
+        }
+    };
+    if (FILT) load_tenants(blk);
     // the ring: named registers (an array would end up in scratch)
     uint4 rb0, rb1, rb2, rb3, rb4, rb5, rb6, rb7;
     auto ring = [&](auto I) -> uint4 & {
@@ -466,14 +625,19 @@ __global__ __launch_bounds__(MF_THREADS) void mfma_scores_kernel(ScoreParams p) 
         __builtin_amdgcn_sched_barrier(kKeepVmemB);
     });
     const uint4 *qa = Qf + lane;
-    const int qrow = lane & 15, kq = lane >> 4;
     // a wave scores at most the workgroup's nbw blocks: the bound ends the
     // loop even if the tickets were to stop advancing
     for (int iter = 1;; ++iter) {
-        const int64_t blk = gb0 + cur;
         // the block after this one (or this one again past the end: cache hits)
-        const uint4 *nsrc = nxt < nbw ? p.codes + (gb0 + nxt) * CH * 64 : bsrc;
+        const int64_t nblk_ = nxt < nbw ? block_of(nxt) : blk;
+        const uint4 *nsrc = p.codes + nblk_ * CH * 64;
         const int ticket = take();
+        uint32_t ok[4] = {0u, 0u, 0u, 0u};   // filtered: queries that may return vector 16m + qrow
+        if constexpr (FILT) {
+#pragma unroll
+            for (int m = 0; m < 4; ++m) ok[m] = p.tmask[ten[m]];
+            load_tenants(nblk_);
+        }
         // unconditional loads (clamped index): a load under a branch makes the
         // wait-count pass drain the chunk ring in the loop below
         float scl[4];
@@ -537,6 +701,15 @@ __global__ __launch_bounds__(MF_THREADS) void mfma_scores_kernel(ScoreParams p) 
                 constexpr int i = decltype(I)::value * F::U;
                 unit(c0 + i, std::integral_constant<int, i>());
             });
+        if constexpr (FILT) {
+            const uint64_t lv = p.live ? ((const_u64)(uintptr_t)p.live)[blk] : ~0ull;
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                const int64_t v = blk * 64 + 16 * m + qrow;
+                const bool may = v < p.n && ((lv >> (16 * m + qrow)) & 1ull);
+                ok[m] = may ? ok[m] >> (4 * kq) : 0u;   // bit 16t + r: query 16t + 4kq + r
+            }
+        }
         // lane holds vectors 16m + qrow, queries 16t + 4*kq + r.  The stores
         // are unconditional (rows past nqt are zero scores in rows that the
         // workspace holds and nothing reads; the 16 lanes of a row store the
@@ -544,6 +717,15 @@ __global__ __launch_bounds__(MF_THREADS) void mfma_scores_kernel(ScoreParams p) 
         // pass unsure of the loads in flight, and it then drains the chunk
         // ring inside the chunk loop.  Stored scores are at least -65504:
         // -inf marks a vector that the query may not return.
+        if constexpr (FL) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    qf[t][r] = fl[16 * t + 4 * kq + r];
+                    qc[t][r] = fl[kTile + 16 * t + 4 * kq + r];
+                }
+        }
         float mx[2][4];
 #pragma unroll
         for (int t = 0; t < 2; ++t)
@@ -559,9 +741,11 @@ __global__ __launch_bounds__(MF_THREADS) void mfma_scores_kernel(ScoreParams p) 
                 for (int r = 0; r < 4; ++r) {
                     const int q = 16 * t + 4 * kq + r;
                     const float a = fmaf(acc[t][m][r], qf[t][r], qc[t][r]) * scl[m];
-                    const _Float16 h = (_Float16)fmaxf(a, -65504.f);
+                    float c = fmaxf(a, -65504.f);
+                    if constexpr (FILT) c = (ok[m] >> (16 * t + r)) & 1u ? c : -INFINITY;
+                    const _Float16 h = (_Float16)c;
                     p.out[(int64_t)q * p.npad + v] = h;
-                    mx[t][r] = fmaxf(mx[t][r], vin ? (float)h : -INFINITY);
+                    mx[t][r] = fmaxf(mx[t][r], FILT || vin ? (float)h : -INFINITY);
                 }
         }
         // block maxima: the 16 lanes of a DPP row hold the block's 64 vectors
@@ -579,187 +763,13 @@ __global__ __launch_bounds__(MF_THREADS) void mfma_scores_kernel(ScoreParams p) 
                 p.bmax[(int64_t)q * p.nblk + blk] = (_Float16)x;
             }
         if (nxt >= nbw || iter >= nbw) break;
-        cur = nxt;
+        blk = nblk_;
         nxt = __builtin_amdgcn_readfirstlane(ticket);
         bsrc = nsrc;
     }
 }
 
 // -------------------------------------------------------------- selection
-struct SelectParams {
-    const _Float16 *approx;    // [nqt][npad]
-    const uint16_t *tenants;
-    const uint64_t *allow;     // [nqt][W] or null
-    float *cand_s;             // [nqt][SEL_GROUPS][KC]
-    int *cand_i;
-    int *gbound;               // [nqt * kBoundStride] order keys
-    int64_t n, npad;
-    int W;
-};
-
-// The KC = 64 S best allowed approximate scores of one query over
-// 1/SEL_GROUPS of the vectors; each lane reads 8 consecutive scores per load.  A wave
-// keeps its best kCand in registers; scores that pass its current bound are
-// first appended to a per-wave LDS buffer, and the buffer is sorted into
-// the list only when 64 have gathered -- a sort per 64 real candidates
-// rather than per 64 scores read.
-template <int S>
-__global__ __launch_bounds__(SEL_THREADS) void select_kernel(SelectParams p) {
-    constexpr int NW = SEL_THREADS / 64;
-    constexpr int kCand = 64 * S, kCandS = S;
-    __shared__ float st_s[NW * kCand];
-    __shared__ int st_i[NW * kCand];
-    __shared__ float buf_s[NW * kBuf];
-    __shared__ int buf_i[NW * kBuf];
-    __shared__ int wg_key;
-    __shared__ uint64_t allow_s[64];
-    const int g = blockIdx.x, q = blockIdx.y;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const bool filtered = p.allow != nullptr;
-    if (tid == 0) wg_key = fkey(-INFINITY);
-    if (filtered)
-        for (int w = tid; w < p.W && w < 64; w += SEL_THREADS) allow_s[w] = p.allow[(int64_t)q * p.W + w];
-    __syncthreads();
-    int *gb = p.gbound + q * kBoundStride;
-    float *bs = buf_s + wave * kBuf;
-    int *bi = buf_i + wave * kBuf;
-    int cnt = 0;   // wave-uniform
-    const uint64_t below = (1ull << lane) - 1;
-    // ranges of 512 vectors (one load per lane per wave)
-    const int64_t units = p.npad / 512;
-    const int64_t u0 = units * g / SEL_GROUPS, u1 = units * (g + 1) / SEL_GROUPS;
-    WaveTopK<kCandS> top;
-    top.reset();
-    const uint4 *row = reinterpret_cast<const uint4 *>(p.approx + (int64_t)q * p.npad);
-    for (int64_t u = u0 + wave; u < u1; u += NW) {
-        const uint4 w = row[u * 64 + lane];
-        // the global bound is read on every 4th load (each read is a trip to L2)
-        const int gk = ((u - u0 - wave) & (4 * NW - 1)) == 0
-                           ? __hip_atomic_load(gb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                           : top.seen_g;
-        const int bk = max(max(gk, wg_key), max(top.seen_g, fkey(top.th_s)));
-        const float thr = unfkey(bk);
-        const _Float16 *h = reinterpret_cast<const _Float16 *>(&w);
-        // append the 8 scores of each lane that pass the bound
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int64_t v = u * 512 + lane * 8 + e;
-            bool ok = v < p.n;
-            if (ok && filtered) {
-                const int t = p.tenants[v];
-                ok = (t >> 6) < p.W && ((allow_s[t >> 6] >> (t & 63)) & 1ull);
-            }
-            const float val = (float)h[e];
-            const bool cand = ok && !(val < thr);
-            const uint64_t m = __ballot(cand);
-            if (cand) {
-                const int pos = cnt + __popcll(m & below);
-                bs[pos] = val;
-                bi[pos] = (int)v;
-            }
-            cnt += __popcll(m);
-        }
-        __builtin_amdgcn_wave_barrier();
-        // sort them in, 64 at a time (one copy of the sort in the code)
-        while (cnt >= 64) {
-            cnt -= 64;
-            const float sc = bs[cnt + lane];
-            const int id = bi[cnt + lane];
-            __builtin_amdgcn_wave_barrier();
-            top.offer_seen(sc, id, lane, kCand, &wg_key, gb, gk);
-        }
-    }
-    if (cnt > 0) {
-        const float sc = lane < cnt ? bs[lane] : -INFINITY;
-        const int id = lane < cnt ? bi[lane] : INT_MAX;
-        top.offer_seen(sc, id, lane, kCand, &wg_key, gb, top.seen_g);
-    }
-    // merge the wave lists
-#pragma unroll
-    for (int a = 0; a < kCandS; ++a) {
-        st_s[wave * kCand + a * 64 + lane] = top.ls[a];
-        st_i[wave * kCand + a * 64 + lane] = top.li[a];
-    }
-    __syncthreads();
-    if (wave == 0) {
-        for (int w = 1; w < NW; ++w) {
-            float os[kCandS];
-            int oi[kCandS];
-#pragma unroll
-            for (int a = 0; a < kCandS; ++a) {
-                os[a] = st_s[w * kCand + a * 64 + lane];
-                oi[a] = st_i[w * kCand + a * 64 + lane];
-            }
-            merge_lists<kCandS>(top.ls, top.li, os, oi, lane);
-        }
-        const int64_t base = ((int64_t)q * SEL_GROUPS + g) * kCand;
-#pragma unroll
-        for (int a = 0; a < kCandS; ++a) {
-            p.cand_s[base + a * 64 + lane] = top.ls[a];
-            p.cand_i[base + a * 64 + lane] = top.li[a];
-        }
-    }
-}
-
-// The KC = 64 S best of the SEL_GROUPS lists of each query: their ids, the
-// approximate score of the KC-th, and the selection state (every allowed
-// vector a candidate when fewer than KC).
-template <int S>
-__global__ __launch_bounds__(256) void select_merge_kernel(const float *__restrict__ cs,
-                                                           const int *__restrict__ ci,
-                                                           int *__restrict__ top_i,
-                                                           float *__restrict__ amin,
-                                                           int *__restrict__ state) {
-    constexpr int kCand = 64 * S, kCandS = S;
-    __shared__ float st_s[4 * kCand];
-    __shared__ int st_i[4 * kCand];
-    const int q = blockIdx.x;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    float ls[kCandS];
-    int li[kCandS];
-#pragma unroll
-    for (int a = 0; a < kCandS; ++a) {
-        ls[a] = -INFINITY;
-        li[a] = INT_MAX;
-    }
-    for (int g = wave; g < SEL_GROUPS; g += 4) {
-        const int64_t base = ((int64_t)q * SEL_GROUPS + g) * kCand;
-        float os[kCandS];
-        int oi[kCandS];
-#pragma unroll
-        for (int a = 0; a < kCandS; ++a) {
-            os[a] = cs[base + a * 64 + lane];
-            oi[a] = ci[base + a * 64 + lane];
-        }
-        merge_lists<kCandS>(ls, li, os, oi, lane);
-    }
-#pragma unroll
-    for (int a = 0; a < kCandS; ++a) {
-        st_s[wave * kCand + a * 64 + lane] = ls[a];
-        st_i[wave * kCand + a * 64 + lane] = li[a];
-    }
-    __syncthreads();
-    if (wave == 0) {
-        for (int w = 1; w < 4; ++w) {
-            float os[kCandS];
-            int oi[kCandS];
-#pragma unroll
-            for (int a = 0; a < kCandS; ++a) {
-                os[a] = st_s[w * kCand + a * 64 + lane];
-                oi[a] = st_i[w * kCand + a * 64 + lane];
-            }
-            merge_lists<kCandS>(ls, li, os, oi, lane);
-        }
-#pragma unroll
-        for (int a = 0; a < kCandS; ++a) top_i[(int64_t)q * kCand + a * 64 + lane] = li[a];
-        const bool full = __shfl(li[kCandS - 1], 63, 64) != INT_MAX;
-        if (lane == 63) {
-            amin[q] = ls[kCandS - 1];
-            state[q] = full ? kSelBound : kSelAll;
-        }
-    }
-}
-
 // ------------------------------------------- selection by block maxima
 // Order-preserving map of float16 bit patterns onto 16-bit keys.
 __device__ inline uint32_t hkey(uint32_t h) { return (h & 0x8000u) ? (~h & 0xFFFFu) : (h | 0x8000u); }
@@ -816,9 +826,11 @@ struct BlockSelParams {
     int *state;                // [nqt] kSel*
     int64_t n, nblk, npad;
     int KC;
+    int nqt;
+    Gate gate;
 };
 
-// One workgroup per query (unfiltered), as described at the top of the
+// One workgroup per query, as described at the top of the
 // file.  Keys are the float16 bit patterns mapped by hkey; a radix
 // selection takes the high byte, then the low byte, with LDS histograms.
 __global__ __launch_bounds__(BS_THREADS) void block_select_kernel(BlockSelParams p) {
@@ -826,6 +838,7 @@ __global__ __launch_bounds__(BS_THREADS) void block_select_kernel(BlockSelParams
     __shared__ int list[kListMaxB];
     __shared__ int sh[8];
     const int q = blockIdx.x;
+    if (scan_is_faster(p.gate, p.nqt)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int KC = p.KC, R = KC - 32;
     const uint16_t *bm = p.bmax + (int64_t)q * p.nblk;
@@ -1065,6 +1078,8 @@ struct RescoreParams {
     const uint64_t *allow;     // [nqt][W] or null
     int W;
     int q0;                    // the pass's first row
+    int nqt;
+    Gate gate;
 };
 
 // One workgroup per query, KC = 64 S candidate slots.
@@ -1085,6 +1100,25 @@ struct RescoreParams {
 //  5. Without a certificate the workgroup appends the query's row, its
 //     rotated coordinates and allowlist to the list that the single-query
 //     scan takes.
+// Appends the query of this workgroup to the list that the single-query scan
+// answers; *slot_s is a word of LDS.
+__device__ inline void hand_over(const RescoreParams &p, int q, int *slot_s) {
+    const int tid = threadIdx.x;
+    if (tid == 0) *slot_s = atomicAdd(p.fb_count, 1);
+    __syncthreads();
+    const int slot = *slot_s;
+    for (int j = tid; j < p.d; j += kTableThreads)
+        p.fb_q[(int64_t)slot * p.d + j] = p.qrot[(int64_t)q * p.d + j];
+    if (p.qconst && tid == 0) p.fb_const[slot] = p.qconst[q];
+    if (p.allow)
+        for (int w = tid; w < p.W; w += kTableThreads)
+            p.fb_allow[(int64_t)slot * p.W + w] = p.allow[(int64_t)q * p.W + w];
+    if (tid == 0) {
+        p.fb_rows[slot] = p.q0 + q;
+        if (p.fb_bound) p.fb_bound[slot] = kBoundInit;
+    }
+}
+
 template <int MODE, int S>
 __global__ __launch_bounds__(kTableThreads) void rescore_kernel(RescoreParams p) {
     constexpr int KC = 64 * S;
@@ -1095,8 +1129,12 @@ __global__ __launch_bounds__(kTableThreads) void rescore_kernel(RescoreParams p)
     int *sums = reinterpret_cast<int *>(red + 16);   // [KC]: integer sums, then ranks
     float *run_s = reinterpret_cast<float *>(sums + KC);
     int *run_i = reinterpret_cast<int *>(run_s + KC);
-    int *sh = run_i + KC;                   // [0] valid count, [1] k-th exact score, [2] list slot
+    int *sh = run_i + KC;                   // [0] valid count, [1] k-th exact score, [2] certified, [3] list slot
     const int q = blockIdx.x;
+    if (scan_is_faster(p.gate, p.nqt)) {
+        hand_over(p, q, sh + 3);
+        return;
+    }
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int run = wave % S, slice = wave / S;
     const int c0 = MODE == BYTE ? 0 : p.chunks * slice / SL;
@@ -1223,21 +1261,10 @@ __global__ __launch_bounds__(kTableThreads) void rescore_kernel(RescoreParams p)
         // proves nothing
         const bool cert = qi.err < INFINITY &&
                           (st == kSelAll || (st == kSelBound && reach < (double)ek));
-        sh[2] = cert ? -1 : atomicAdd(p.fb_count, 1);
+        sh[2] = cert;
     }
     __syncthreads();
-    const int slot = sh[2];
-    if (slot < 0) return;
-    for (int j = tid; j < p.d; j += kTableThreads)
-        p.fb_q[(int64_t)slot * p.d + j] = p.qrot[(int64_t)q * p.d + j];
-    if (p.qconst && tid == 0) p.fb_const[slot] = p.qconst[q];
-    if (p.allow)
-        for (int w = tid; w < p.W; w += kTableThreads)
-            p.fb_allow[(int64_t)slot * p.W + w] = p.allow[(int64_t)q * p.W + w];
-    if (tid == 0) {
-        p.fb_rows[slot] = p.q0 + q;
-        if (p.fb_bound) p.fb_bound[slot] = kBoundInit;
-    }
+    if (!sh[2]) hand_over(p, q, sh + 3);
 }
 
 // ============================================================ wide passes
@@ -1258,8 +1285,8 @@ __global__ __launch_bounds__(kTableThreads) void rescore_kernel(RescoreParams p)
 //     allowed pilot vectors that reach it as candidates.  At least KC
 //     vectors of the store score theta or more.
 //  4. wide_scores_kernel, main launch: every other tile; a vector whose
-//     score reaches its query's theta (and whose tenant the query allows) is
-//     appended to the workgroup's list for that query.
+//     score reaches its query's theta (and that is live and whose tenant the
+//     query allows) is appended to the workgroup's list for that query.
 //  5. final_select_kernel: the KC best of the pilot's and the workgroups'
 //     candidates, and amin = the KC-th one's score.  A vector that is not
 //     taken scores below theta <= amin (never appended) or at most amin
@@ -1310,24 +1337,29 @@ __global__ void frag_kernel(const _Float16 *__restrict__ q16, const QInfo *__res
         qfrag[e] = v;
     }
     for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < QP;
-         q += (int64_t)gridDim.x * blockDim.x)
+         q += (int64_t)gridDim.x * blockDim.x) {
         qf[q] = q < nqt ? info[q].f : 0.f;
+        qf[QP + q] = q < nqt ? info[q].c : 0.f;
+    }
 }
 
 struct WideParams {
     const uint4 *codes;        // blocked store (b = 4)
     const float *scales;
     const uint4 *qfrag;        // [chunks][QP * 4] query pieces
-    const float *qf;           // [QP] score factor (0 for unused slots)
+    const float *qf;           // [QP] score factors (0 for unused slots), then [QP] constant terms
     const float *cents;        // 16 levels
     int64_t n, nblk, ntiles;   // tiles of NG blocks
     int chunks, pstride, npil; // pilot tiles: i * pstride, i < npil
     int pilot;                 // 1: pilot launch, 0: main launch (selects the kernel)
     float *pil;                // pilot: [QP][npil * 64 NG] scores
     const float *theta;        // main: [nqt] thresholds
-    const uint16_t *tenants;   // main, filtered
-    const uint64_t *allow;     // main: [nqt][W] allowlists, or null
-    int W, nqt;
+    // main, filtered
+    const uint16_t *tenants;
+    const uint32_t *tmask;     // [tenant][QP / 32] queries that admit it (null: not filtered)
+    const uint64_t *live;      // [nblk] or null
+    Gate gate;
+    int nqt;
     float *cand_s;             // main: [grid][QP][S] appended scores and ids
     int *cand_i;
     int *cand_n;               // main: [grid][QP] appended per workgroup and query
@@ -1355,12 +1387,12 @@ struct WideShape {
     static constexpr int NB = QW == 128 ? 5 : 7;       // slab buffers
     static constexpr int PD = NB - 1;                  // slabs requested ahead
     static constexpr size_t lds = kTableBytes + (size_t)NB * SU * 16 + 2 * 1024 +
-                                  3 * (size_t)QP * 4;
+                                  4 * (size_t)QP * 4;
     // uint4 offset of piece i within a slab
     static constexpr int pos(int i) { return ((i % WD_WAVES) * DW + i / WD_WAVES) * 64; }
 };
 
-template <int QW, bool PILOT>
+template <int QW, bool PILOT, bool FILT>
 __global__ __launch_bounds__(WD_THREADS) void wide_scores_kernel(WideParams p) {
     using WS = WideShape<QW>;
     constexpr int QP = WS::QP, QF = WS::QF, NI = WS::NI, SU = WS::SU, NB = WS::NB, PD = WS::PD;
@@ -1378,6 +1410,8 @@ __global__ __launch_bounds__(WD_THREADS) void wide_scores_kernel(WideParams p) {
     float *fq = sclv + 512;                                            // [QP]
     float *th = fq + QP;                                               // [QP]
     int *cnt = reinterpret_cast<int *>(th + QP);                       // [QP]
+    float *cq = reinterpret_cast<float *>(cnt + QP);                   // [QP]
+    if (scan_is_faster(p.gate, p.nqt)) return;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: scalar branches
@@ -1402,6 +1436,7 @@ __global__ __launch_bounds__(WD_THREADS) void wide_scores_kernel(WideParams p) {
     }
     for (int q = tid; q < QP; q += WD_THREADS) {
         fq[q] = p.qf[q];
+        cq[q] = p.qf[QP + q];
         th[q] = (!PILOT && q < p.nqt) ? p.theta[q] : INFINITY;
         cnt[q] = 0;
     }
@@ -1525,10 +1560,11 @@ __global__ __launch_bounds__(WD_THREADS) void wide_scores_kernel(WideParams p) {
 #pragma unroll
                     for (int e = 0; e < 16; ++e) {
                         const int q = hq + 32 * t + 8 * (e >> 2) + (e & 3);
-                        const float f = fq[q];
+                        const float f = fq[q], k = cq[q];
 #pragma unroll
                         for (int m = 0; m < 2; ++m)
-                            p.pil[q * prow + pcol + 32 * m] = vin[m] ? acc[t][m][e] * scl[m] * f : -INFINITY;
+                            p.pil[q * prow + pcol + 32 * m] =
+                                vin[m] ? fmaf(acc[t][m][e], f, k) * scl[m] : -INFINITY;
                     }
             } else {
                 // which entries reach their query's threshold, without
@@ -1541,16 +1577,44 @@ __global__ __launch_bounds__(WD_THREADS) void wide_scores_kernel(WideParams p) {
                     for (int i = 0; i < 4; ++i) {
                         // four queries' factors and thresholds, read together
                         const float4 f4 = *reinterpret_cast<const float4 *>(fq + hq + 32 * t + 8 * i);
+                        const float4 k4 = *reinterpret_cast<const float4 *>(cq + hq + 32 * t + 8 * i);
                         const float4 t4 = *reinterpret_cast<const float4 *>(th + hq + 32 * t + 8 * i);
                         const float fr[4] = {f4.x, f4.y, f4.z, f4.w}, tr[4] = {t4.x, t4.y, t4.z, t4.w};
+                        const float kr[4] = {k4.x, k4.y, k4.z, k4.w};
 #pragma unroll
                         for (int j = 0; j < 4; ++j) {
                             const int e = 4 * i + j;
-                            hb |= (vin[0] && acc[t][0][e] * scl[0] * fr[j] >= tr[j]) ? 1u << (2 * e) : 0u;
-                            hb |= (vin[1] && acc[t][1][e] * scl[1] * fr[j] >= tr[j]) ? 2u << (2 * e) : 0u;
+                            hb |= (vin[0] && fmaf(acc[t][0][e], fr[j], kr[j]) * scl[0] >= tr[j]) ? 1u << (2 * e) : 0u;
+                            hb |= (vin[1] && fmaf(acc[t][1][e], fr[j], kr[j]) * scl[1] >= tr[j]) ? 2u << (2 * e) : 0u;
                         }
                     }
                     hit[t] = hb;
+                }
+                // ... restricted to the vectors that a query may return (bit
+                // 8i + j of a mask word past the lane half's shift: entry
+                // e = 4i + j)
+                if constexpr (FILT) {
+                    // loads without branches: an absent live mask reads the
+                    // tenant masks instead, unused
+                    const uint64_t *lp = p.live ? p.live : reinterpret_cast<const uint64_t *>(p.tmask);
+                    const uint64_t all = p.live ? 0ull : ~0ull;
+                    const int sh = 4 * (lane >> 5);
+#pragma unroll
+                    for (int m = 0; m < 2; ++m) {
+                        int v = vin[m] ? (int)vb + 32 * m : 0;
+                        asm volatile("" : "+v"(v));   // formed here, not held across the steps
+                        const uint64_t lv = lp[p.live ? v >> 6 : 0] | all;
+                        const uint32_t may = (lv >> (v & 63)) & 1ull ? ~0u : 0u;
+                        const uint32_t *tw = p.tmask + p.tenants[v] * (QP / 32) + h * QT;
+#pragma unroll
+                        for (int t = 0; t < QT; ++t) {
+                            uint32_t x = (tw[t] >> sh) & may & 0x0F0F0F0Fu;
+                            x = (x | (x << 2)) & 0x33333333u;
+                            x = (x | (x << 1)) & 0x55555555u;
+                            hit[t] &= (x << m) | (0xAAAAAAAAu >> m);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
                 }
                 // ... then append those (rare): one entry per lane and round,
                 // its value picked out of the accumulators by its bit index
@@ -1587,21 +1651,12 @@ __global__ __launch_bounds__(WD_THREADS) void wide_scores_kernel(WideParams p) {
                                     a = (bt == t && bb == 2 * e + m) ? acc[t][m][e] : a;
                         const int e = bb >> 1, m = bb & 1;
                         const int q = hq + 32 * bt + 8 * (e >> 2) + (e & 3);
-                        const float val = a * scl[m] * fq[q];
-                        const int64_t v = vb + 32 * m;
-                        bool ok = true;
-                        if (p.allow) {
-                            const int tn = p.tenants[v];
-                            ok = (tn >> 6) < p.W &&
-                                 ((p.allow[(int64_t)q * p.W + (tn >> 6)] >> (tn & 63)) & 1ull);
-                        }
-                        if (ok) {
-                            const int slot = atomicAdd(&cnt[q], 1);
-                            if (slot < p.S) {
-                                const int64_t o = ((int64_t)wg * QP + q) * p.S + slot;
-                                p.cand_s[o] = val;
-                                p.cand_i[o] = (int)v;
-                            }
+                        const float val = fmaf(a, fq[q], cq[q]) * scl[m];
+                        const int slot = atomicAdd(&cnt[q], 1);
+                        if (slot < p.S) {
+                            const int64_t o = ((int64_t)wg * QP + q) * p.S + slot;
+                            p.cand_s[o] = val;
+                            p.cand_i[o] = (int)(vb + 32 * m);
                         }
                     }
                 }
@@ -1726,6 +1781,9 @@ struct PilotParams {
     int64_t n;
     const uint16_t *tenants;
     const uint64_t *allow;     // [nqt][W] or null
+    const uint64_t *live;      // [nblk] or null
+    Gate gate;
+    int nqt;
     int W, KC, PCM;
     float *theta;              // [nqt]
     int *pc_n;                 // [nqt] pilot candidates (may exceed PCM: overflow)
@@ -1744,6 +1802,7 @@ __global__ __launch_bounds__(PS_THREADS) void pilot_select_kernel(PilotParams p)
     __shared__ int hist[kHistCopies * kHistStride];
     __shared__ int sh[8];
     const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    if (scan_is_faster(p.gate, p.nqt)) return;
     const int npv = (int)p.npv;
     const float *row = p.pil + (int64_t)q * p.npv;
     const uint64_t *arow = p.allow ? p.allow + (int64_t)q * p.W : nullptr;
@@ -1771,7 +1830,8 @@ __global__ __launch_bounds__(PS_THREADS) void pilot_select_kernel(PilotParams p)
 #pragma unroll
             for (int u = 0; u < R; ++u) {
                 const int e = e0 + tid + u * PS_THREADS;
-                tn[u] = p.tenants[vec_of(e < npv ? e : 0)];
+                const int64_t v = vec_of(e < npv ? e : 0);
+                tn[u] = p.tenants[v < p.n ? v : 0];
             }
         }
 #pragma unroll
@@ -1781,6 +1841,10 @@ __global__ __launch_bounds__(PS_THREADS) void pilot_select_kernel(PilotParams p)
                 bool ok = val[u] > -INFINITY;
                 if (arow)
                     ok = ok && (tn[u] >> 6) < p.W && ((allow_s[tn[u] >> 6] >> (tn[u] & 63)) & 1ull);
+                if (p.live) {
+                    const int64_t v = vec_of(e);
+                    ok = ok && ((p.live[v < p.n ? v >> 6 : 0] >> (v & 63)) & 1ull);
+                }
                 k16[e] = ok ? (uint16_t)(ukey(val[u]) >> 16) : (uint16_t)0;   // a finite key's top half is >= 0x80
                 cnt += ok;
             }
@@ -1823,6 +1887,8 @@ struct FinalParams {
     const int *cand_i;
     const int *cand_n;         // [G][QP]
     int G, QP, S, KC;
+    int nqt;
+    Gate gate;
     int *top_i;                // [nqt][KC] (INT_MAX: none)
     float *amin;
     int *state;
@@ -1837,6 +1903,7 @@ __global__ __launch_bounds__(PS_THREADS) void final_select_kernel(FinalParams p)
     __shared__ int hist[kHistCopies * kHistStride];
     __shared__ int sh[8];
     const int q = blockIdx.x, tid = threadIdx.x;
+    if (scan_is_faster(p.gate, p.nqt)) return;
     int *out = p.top_i + (int64_t)q * p.KC;
     __shared__ int goff[1025];                  // exclusive offsets of the workgroup lists
     __shared__ int wsum[PS_THREADS / 64];
@@ -1929,14 +1996,6 @@ __global__ __launch_bounds__(PS_THREADS) void final_select_kernel(FinalParams p)
     }
 }
 
-// ------------------------------------------------------ fallback helpers
-// Global bounds are kept one 128-byte line apart (kBoundStride ints): every
-// wave of a query's selection reads and raises its query's bound, and bounds
-// of different queries sharing a line serialise each other.
-__global__ void fill_order_keys(int *p, int n) {
-    for (int i = threadIdx.x; i < n * kBoundStride; i += blockDim.x) p[i] = fkey(-INFINITY);
-}
-
 __global__ void scale_max_kernel(const float *__restrict__ s, int64_t n, int *smax_bits) {
     int m = 0;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
@@ -1974,7 +2033,7 @@ void with_slots(int KC, Fn fn) {
 }
 
 struct BatchLayout {
-    size_t q16, info, approx, bmax, cand_s, cand_i, top_i, amin, state, gbound, tickets, count, rows, qc,
+    size_t q16, info, approx, bmax, top_i, amin, state, tickets, count, rows, qc, tmask, list,
         qconst_c, allow_c, lut, total;
     // wide passes
     size_t w_q16, w_info, w_qfrag, w_qf, w_pil, w_theta, w_pcn, w_pci, w_pcs, w_cs, w_ci, w_cn,
@@ -2038,20 +2097,18 @@ BatchLayout batch_layout(const ScanShape &s, int64_t nq, int k, int grid) {
     o += align256((size_t)kTile * npad * 2);
     L.bmax = o;
     o += align256((size_t)kTile * s.nblk * 2);
-    L.cand_s = o;
-    o += align256((size_t)kTile * SEL_GROUPS * kCandMax * 4);
-    L.cand_i = o;
-    o += align256((size_t)kTile * SEL_GROUPS * kCandMax * 4);
     L.top_i = o;
     o += align256((size_t)kTile * kCandMax * 4);
     L.amin = o;
     o += align256((size_t)kTile * 4);
     L.state = o;
     o += align256((size_t)kTile * 4);
-    L.gbound = o;
-    o += align256(kTile * kBoundStride * 4);
     L.tickets = o;
-    o += align256((size_t)grid * kTicketStride * 4);
+    o += align256(((size_t)grid * kTicketStride + 2) * 4);   // ... and the filter counts
+    L.tmask = o;
+    o += align256((size_t)s.W * 64 * (kWideMaxQ / 32) * 4);
+    L.list = o;
+    o += align256((size_t)s.nblk * 4);
     L.count = o;
     o += align256(4);
     L.rows = o;
@@ -2076,7 +2133,7 @@ BatchLayout batch_layout(const ScanShape &s, int64_t nq, int k, int grid) {
         L.w_q16 = take((size_t)QP * s.d * 2);
         L.w_info = take((size_t)QP * sizeof(QInfo));
         L.w_qfrag = take((size_t)QP * s.d * 2);
-        L.w_qf = take((size_t)QP * 4);
+        L.w_qf = take((size_t)QP * 2 * 4);
         L.w_pil = take((size_t)QP * w.npil * w.tilev * 4);
         L.w_theta = take((size_t)QP * 4);
         L.w_pcn = take((size_t)QP * 4);
@@ -2094,24 +2151,27 @@ BatchLayout batch_layout(const ScanShape &s, int64_t nq, int k, int grid) {
 }
 
 // Launches the score kernel of a tile.
-template <int BITS, int NR, int RING>
+template <int BITS, int NR, int RING, bool FILT>
 hipError_t launch_scores_as(const ScoreParams &sp, int grid, size_t lds, hipStream_t stream) {
     static bool attr = false;
     if (!attr) {
         const hipError_t e =
-            hipFuncSetAttribute((const void *)mfma_scores_kernel<BITS, NR, RING>,
+            hipFuncSetAttribute((const void *)mfma_scores_kernel<BITS, NR, RING, FILT>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (e != hipSuccess) return e;
         attr = true;
     }
-    hipLaunchKernelGGL((mfma_scores_kernel<BITS, NR, RING>), dim3(grid), dim3(MF_THREADS), lds, stream, sp);
+    hipLaunchKernelGGL((mfma_scores_kernel<BITS, NR, RING, FILT>), dim3(grid), dim3(MF_THREADS), lds, stream, sp);
     return hipGetLastError();
 }
 template <int BITS, int NR>
 hipError_t launch_scores_ring(const ScoreParams &sp, int grid, hipStream_t stream) {
     const size_t lds = score_lds(BITS, sp.chunks, NR);
-    return sp.chunks % 8 == 0 ? launch_scores_as<BITS, NR, 8>(sp, grid, lds, stream)
-                              : launch_scores_as<BITS, NR, 4>(sp, grid, lds, stream);
+    if (sp.list)
+        return sp.chunks % 8 == 0 ? launch_scores_as<BITS, NR, 8, true>(sp, grid, lds, stream)
+                                  : launch_scores_as<BITS, NR, 4, true>(sp, grid, lds, stream);
+    return sp.chunks % 8 == 0 ? launch_scores_as<BITS, NR, 8, false>(sp, grid, lds, stream)
+                              : launch_scores_as<BITS, NR, 4, false>(sp, grid, lds, stream);
 }
 hipError_t launch_scores(int bits, const ScoreParams &sp, int grid, hipStream_t stream) {
     const bool r64 = score_replicas(bits, sp.chunks) == 64;
@@ -2126,7 +2186,7 @@ hipError_t launch_scores(int bits, const ScoreParams &sp, int grid, hipStream_t 
 }
 
 // LDS of the rescoring: the table, 16 floats, integer sums and sorted
-// (score, id) runs, three counters.
+// (score, id) runs, four words.
 int rescore_lut_words(const ScanShape &s) {
     return s.bits == 8 ? kByteRepWords + s.d : s.bits == 3 ? s.chunks * 320 : s.chunks * 512;
 }
@@ -2160,29 +2220,28 @@ hipError_t launch_rescore(const ScanShape &s, int KC, const RescoreParams &rp, i
 // Launches wide_scores_kernel for a pass of QP query slots (QP / 2 queries
 // per wave).
 hipError_t launch_wide_scores(int QP, const WideParams &wp, int grid, hipStream_t stream) {
-    static bool attr[6] = {false, false, false, false, false, false};
     hipError_t err = hipSuccess;
-    auto go = [&](int slot, auto kern, size_t lds) {
-        if (!attr[slot]) {
-            err = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      (int)lds);
+    auto go = [&](auto qw, auto pilot, auto filt) {
+        constexpr int QW = decltype(qw)::value;
+        constexpr bool P = decltype(pilot)::value, F = decltype(filt)::value;
+        static bool attr = false;
+        if (!attr) {
+            err = hipFuncSetAttribute((const void *)wide_scores_kernel<QW, P, F>,
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)WideShape<QW>::lds);
             if (err != hipSuccess) return;
-            attr[slot] = true;
+            attr = true;
         }
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(WD_THREADS), lds, stream, wp);
+        hipLaunchKernelGGL((wide_scores_kernel<QW, P, F>), dim3(grid), dim3(WD_THREADS), WideShape<QW>::lds,
+                           stream, wp);
         err = hipGetLastError();
     };
-    const int pl = wp.pilot ? 1 : 0;
-    switch (QP) {
-    case 128:
-        if (pl) go(1, wide_scores_kernel<64, true>, WideShape<64>::lds);
-        else go(4, wide_scores_kernel<64, false>, WideShape<64>::lds);
-        break;
-    default:
-        if (pl) go(2, wide_scores_kernel<128, true>, WideShape<128>::lds);
-        else go(5, wide_scores_kernel<128, false>, WideShape<128>::lds);
-        break;
-    }
+    auto go_width = [&](auto qw) {
+        if (wp.pilot) go(qw, std::true_type(), std::false_type());
+        else if (wp.tmask) go(qw, std::false_type(), std::true_type());
+        else go(qw, std::false_type(), std::false_type());
+    };
+    if (QP == 128) go_width(std::integral_constant<int, 64>());
+    else go_width(std::integral_constant<int, 128>());
     return err;
 }
 
@@ -2223,21 +2282,23 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
                        const float *smax, const uint16_t *tenants, const uint64_t *summaries,
                        const float *cents32, float cmax16, float dmax, const float *Qrot,
                        const float *qconst, int64_t nq, int k,
-                       const uint64_t *allow, int grid, void *ws, int64_t *ids, float *scores,
+                       const SearchFilter &filter, int grid, void *ws, int64_t *ids, float *scores,
                        int *n_fallback, hipStream_t stream) {
+    const uint64_t *allow = filter.allow, *live = filter.live;
+    const bool filtered = filter.any();
     const BatchLayout L = batch_layout(s, nq, k, grid);
     uint8_t *w8 = static_cast<uint8_t *>(ws);
     _Float16 *q16 = reinterpret_cast<_Float16 *>(w8 + L.q16);
     QInfo *info = reinterpret_cast<QInfo *>(w8 + L.info);
     _Float16 *approx = reinterpret_cast<_Float16 *>(w8 + L.approx);
     _Float16 *bmax = reinterpret_cast<_Float16 *>(w8 + L.bmax);
-    float *cand_s = reinterpret_cast<float *>(w8 + L.cand_s);
-    int *cand_i = reinterpret_cast<int *>(w8 + L.cand_i);
     int *top_i = reinterpret_cast<int *>(w8 + L.top_i);
     float *amin = reinterpret_cast<float *>(w8 + L.amin);
     int *state = reinterpret_cast<int *>(w8 + L.state);
-    int *gbound = reinterpret_cast<int *>(w8 + L.gbound);
     int *tickets = reinterpret_cast<int *>(w8 + L.tickets);
+    int *counts = tickets + (size_t)grid * kTicketStride;
+    uint32_t *tmask = filtered ? reinterpret_cast<uint32_t *>(w8 + L.tmask) : nullptr;
+    int *list = reinterpret_cast<int *>(w8 + L.list);
     int *count = reinterpret_cast<int *>(w8 + L.count);
     int *rows = reinterpret_cast<int *>(w8 + L.rows);
     float *qc = reinterpret_cast<float *>(w8 + L.qc);
@@ -2258,8 +2319,45 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
         if (e != hipSuccess) return e;
         attr_set = true;
     }
+    // the scan of a pass's queries against the pass (see Gate; the explicit
+    // path always runs the pass): the scan reads at about 5 TB/s, a tile too
+    // (unions only), a wide pass multiplies 1.0 to 1.35 MB of codes a us
+    const double block_bytes = s.chunks * 1024.0;
+    auto gate_of = [&](int QP) {
+        Gate g{};
+        if (!allow || n_fallback) return g;
+        g.counts = counts;
+        g.scan_us = s.bits == 8 ? 30.f : 9.f;
+        g.block_us = (float)(block_bytes / 5.0e6);
+        if (QP == kTile) {
+            g.pass_us = s.bits == 8 ? 83.f : 58.f;
+            g.read_us = g.block_us;
+        } else {
+            g.pass_us = (float)(230.0 + (double)s.nblk * block_bytes / (QP == 256 ? 1.0e6 : 1.35e6));
+        }
+        return g;
+    };
+    auto apply_filter = [&](int64_t q0, int nqt, int QP) {
+        FilterParams fp{};
+        fp.allow = allow ? allow + q0 * s.W : nullptr;
+        fp.live = live;
+        fp.summaries = summaries;
+        fp.nblk = s.nblk;
+        fp.W = s.W;
+        fp.nqt = nqt;
+        fp.words = QP / 32;
+        fp.tmask = tmask;
+        fp.counts = counts;
+        if (QP == kTile) {
+            fp.list = list;
+            fp.bmax = reinterpret_cast<uint16_t *>(bmax);
+        }
+        const int64_t mask_wgs = (64 * (int64_t)s.W * fp.words + FK_THREADS - 1) / FK_THREADS;
+        hipLaunchKernelGGL(filter_kernel, dim3((unsigned)(mask_wgs + (s.nblk + FK_THREADS - 1) / FK_THREADS)),
+                           dim3(FK_THREADS), 0, stream, fp);
+    };
     auto rescore = [&](int64_t q0, int nqt, const int *ti, const float *am, const int *st,
-                       const QInfo *qi) {
+                       const QInfo *qi, const Gate &gate) {
         RescoreParams rp{};
         rp.codes = reinterpret_cast<const uint4 *>(blocked);
         rp.scales = scales;
@@ -2281,6 +2379,8 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
         rp.allow = allow ? allow + q0 * s.W : nullptr;
         rp.W = s.W;
         rp.q0 = (int)q0;
+        rp.nqt = nqt;
+        rp.gate = gate;
         rp.d = s.d;
         rp.bits = s.bits;
         rp.chunks = s.chunks;
@@ -2311,10 +2411,12 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
             float *wamin = reinterpret_cast<float *>(w8 + L.w_amin);
             int *wstate = reinterpret_cast<int *>(w8 + L.w_state);
             const uint64_t *allow_p = allow ? allow + q0 * s.W : nullptr;
+            const Gate gate = gate_of(QP);
             hipLaunchKernelGGL(prep_kernel, dim3(nqt), dim3(SEL_THREADS), 0, stream,
                                Qrot + q0 * s.d, qconst ? qconst + q0 : nullptr, nqt, s.d, s.bits, smax,
                                cmax16, dmax, wq16, winfo,
-                               nullptr, 0, q0 == 0 ? count : nullptr);
+                               counts, 2, q0 == 0 ? count : nullptr);
+            if (filtered) apply_filter(q0, nqt, QP);
             const int64_t fr = (int64_t)(s.d / 32) * QP * 4;
             hipLaunchKernelGGL(frag_kernel, dim3((int)std::min<int64_t>((fr + 255) / 256, 1024)),
                                dim3(256), 0, stream, wq16, winfo, nqt, QP, s.d, wqfrag, wqf);
@@ -2333,8 +2435,9 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
             wp.pil = wpil;
             wp.theta = wtheta;
             wp.tenants = tenants;
-            wp.allow = allow_p;
-            wp.W = s.W;
+            wp.tmask = tmask;
+            wp.live = live;
+            wp.gate = gate;
             wp.nqt = nqt;
             wp.cand_s = wcs;
             wp.cand_i = wci;
@@ -2350,6 +2453,9 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
             pp.n = s.n;
             pp.tenants = tenants;
             pp.allow = allow_p;
+            pp.live = live;
+            pp.gate = gate;
+            pp.nqt = nqt;
             pp.W = s.W;
             pp.KC = KC;
             pp.PCM = PCM;
@@ -2375,21 +2481,25 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
             fp.QP = QP;
             fp.S = w.S;
             fp.KC = KC;
+            fp.nqt = nqt;
+            fp.gate = gate;
             fp.top_i = wtop;
             fp.amin = wamin;
             fp.state = wstate;
             hipLaunchKernelGGL(final_select_kernel, dim3(nqt), dim3(PS_THREADS),
                                (size_t)kFinalMax * 8, stream, fp);
             e = hipGetLastError();
-            if (e == hipSuccess) e = rescore(q0, nqt, wtop, wamin, wstate, winfo);
+            if (e == hipSuccess) e = rescore(q0, nqt, wtop, wamin, wstate, winfo, gate);
             if (e != hipSuccess) return e;
             q0 += nqt;
             continue;
         }
         const int nqt = (int)std::min<int64_t>(nq - q0, kTile);
         hipLaunchKernelGGL(prep_kernel, dim3(nqt), dim3(SEL_THREADS), 0, stream, Qrot + q0 * s.d,
-                           qconst ? qconst + q0 : nullptr, nqt, s.d, s.bits, smax, cmax16, dmax, q16, info, tickets, grid * kTicketStride,
-                           q0 == 0 ? count : nullptr);
+                           qconst ? qconst + q0 : nullptr, nqt, s.d, s.bits, smax, cmax16, dmax, q16, info, tickets,
+                           grid * kTicketStride + 2, q0 == 0 ? count : nullptr);
+        const Gate gate = gate_of(kTile);
+        if (filtered) apply_filter(q0, nqt, kTile);
         ScoreParams sp{};
         sp.codes = reinterpret_cast<const uint4 *>(blocked);
         sp.scales = scales;
@@ -2405,49 +2515,38 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
         sp.chunks = s.chunks;
         sp.nqt = nqt;
         sp.tickets = tickets;
+        if (filtered) {
+            sp.list = list;
+            sp.counts = counts;
+            sp.tmask = tmask;
+            sp.tenants = tenants;
+            sp.live = live;
+            sp.gate = gate;
+        }
         hipError_t e = launch_scores(s.bits, sp, grid, stream);
         if (e != hipSuccess) return e;
-        if (allow) {
-            // the block maxima ignore the allowlist: select over every allowed score
-            hipLaunchKernelGGL(fill_order_keys, dim3(1), dim3(64), 0, stream, gbound, nqt);
-            SelectParams sl{};
-            sl.approx = approx;
-            sl.tenants = tenants;
-            sl.allow = allow + q0 * s.W;
-            sl.cand_s = cand_s;
-            sl.cand_i = cand_i;
-            sl.gbound = gbound;
-            sl.n = s.n;
-            sl.npad = npad;
-            sl.W = s.W;
-            with_slots(KC, [&](auto sc) {
-                constexpr int S = decltype(sc)::value;
-                hipLaunchKernelGGL(select_kernel<S>, dim3(SEL_GROUPS, nqt), dim3(SEL_THREADS), 0,
-                                   stream, sl);
-                hipLaunchKernelGGL(select_merge_kernel<S>, dim3(nqt), dim3(256), 0, stream, cand_s,
-                                   cand_i, top_i, amin, state);
-            });
-        } else {
-            BlockSelParams bp{};
-            bp.approx = reinterpret_cast<const uint16_t *>(approx);
-            bp.bmax = reinterpret_cast<const uint16_t *>(bmax);
-            bp.top_i = top_i;
-            bp.amin = amin;
-            bp.state = state;
-            bp.n = s.n;
-            bp.nblk = s.nblk;
-            bp.npad = npad;
-            bp.KC = KC;
-            hipLaunchKernelGGL(block_select_kernel, dim3(nqt), dim3(BS_THREADS), 0, stream, bp);
-        }
+        BlockSelParams bp{};
+        bp.approx = reinterpret_cast<const uint16_t *>(approx);
+        bp.bmax = reinterpret_cast<const uint16_t *>(bmax);
+        bp.top_i = top_i;
+        bp.amin = amin;
+        bp.state = state;
+        bp.n = s.n;
+        bp.nblk = s.nblk;
+        bp.npad = npad;
+        bp.KC = KC;
+        bp.nqt = nqt;
+        bp.gate = gate;
+        hipLaunchKernelGGL(block_select_kernel, dim3(nqt), dim3(BS_THREADS), 0, stream, bp);
         e = hipGetLastError();
-        if (e == hipSuccess) e = rescore(q0, nqt, top_i, amin, state, info);
+        if (e == hipSuccess) e = rescore(q0, nqt, top_i, amin, state, info, gate);
         if (e != hipSuccess) return e;
         q0 += nqt;
     }
     // queries whose top k is not proven run on the single-query scan
     SearchFilter f;
     f.allow = allow ? allow_c : nullptr;
+    f.live = live;
     QueryRows qr;
     qr.count = count;
     qr.rows = rows;

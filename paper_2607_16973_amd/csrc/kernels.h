@@ -177,7 +177,9 @@ int *lut_search_bounds(const ScanShape &s, int64_t nq, int k, int grid, void *ws
 // Queries whose top k the certificate does not prove are re-run on the
 // single-query scan, from a list kept on the device.  With n_fallback their
 // count goes there and the call synchronises `stream` once to read it;
-// without, everything is asynchronous.  `smax` is a device float: the
+// without, everything is asynchronous, and a filtered pass whose queries the
+// scan answers faster is left to it (decided on the device).  The filter has
+// no slot allowlists.  `smax` is a device float: the
 // largest |scale| in the store.
 bool batch_search_supported(const ScanShape &s, int k);
 bool mfma_search_supported(const ScanShape &s, int k);
@@ -188,7 +190,7 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
                        const float *smax, const uint16_t *tenants, const uint64_t *summaries,
                        const float *cents32, float cmax16, float dmax, const float *Qrot,
                        const float *qconst, int64_t nq, int k,
-                       const uint64_t *allow, int grid, void *ws, int64_t *ids, float *scores,
+                       const SearchFilter &filter, int grid, void *ws, int64_t *ids, float *scores,
                        int *n_fallback, hipStream_t stream);
 // *smax = max(*smax, max of |scales[0..n)|).
 hipError_t update_scale_max(const float *scales, int64_t n, float *smax, hipStream_t stream);

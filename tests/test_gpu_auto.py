@@ -68,6 +68,39 @@ def test_widths(d, bits, n, nq, k, plus):
     same(idx.search(Q, k), idx.search(Q, k, path="lut"))
 
 
+# filtered: tenants allowed per query (0: none for some queries), few and many
+# tenants, tiles and wide passes, with and without deletions; the device gate
+# leaves the most selective passes to the scan
+@pytest.mark.parametrize("bits,d", [(4, 256), (2, 256), (3, 128), (8, 128)])
+@pytest.mark.parametrize("T,allowed,nq,k", [(5, 1, 33, 10), (100, 1, 40, 10), (100, 10, 130, 100), (100, 0, 20, 10),
+                                            (1000, 1, 150, 10), (4096, 400, 70, 20), (3000, 1, 10, 10)])
+@pytest.mark.parametrize("deleted", [False, True])
+def test_filtered(bits, d, T, allowed, nq, k, deleted):
+    n = 20_011
+    X = corpus(n, d, 40)
+    g = torch.Generator(device="cuda").manual_seed(41)
+    # a third of the rows belongs to one tenant, the others are spread
+    ten = torch.where(torch.rand(n, generator=g, device="cuda") < 0.3, 0,
+                      torch.randint(T, (n,), generator=g, device="cuda")).to(torch.int16)
+    cls = tq.IdMapIndex if deleted else tq.Index
+    idx = cls(tq.Codebook(d, bits), rotation(d), T)
+    if deleted:
+        idx.add(X, range(10 ** 12, 10 ** 12 + n), ten)
+        idx.remove([10 ** 12 + i for i in range(0, n, 3)])
+        idx.remove(range(10 ** 12 + 640, 10 ** 12 + 1100))   # whole blocks
+    else:
+        idx.add(X, ten)
+    words = (T + 63) // 64
+    allow = torch.zeros(nq, words * 64, dtype=torch.bool, device="cuda")
+    for q in range(nq):
+        if allowed or q % 3:
+            allow[q, torch.randint(T, (max(allowed, 1),), generator=g, device="cuda")] = True
+    bits64 = (allow.view(nq, words, 64).long() << torch.arange(64, device="cuda")).sum(dim=2).contiguous()
+    Q = queries(X, nq, 42)
+    for al in (bits64, None):
+        same(idx.search(Q, k, allow=al), idx.search(Q, k, allow=al, path="lut"))
+
+
 @pytest.mark.parametrize("nq", [12, 40, 100])
 def test_queries_without_certificate(nq):
     # every score ties: no candidate set can be proven, every query goes to the scan
