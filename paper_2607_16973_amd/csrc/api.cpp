@@ -85,11 +85,19 @@ tq_status rotation_dev(const tq_rotation *rot, const float **out) {
         (void)hipFree(rot->R_dev);
         rot->R_dev = nullptr;
     }
+    // the matrix, then its parts for the encoder
     const size_t bytes = sizeof(float) * rot->R.size();
-    e = hipMalloc(&rot->R_dev, bytes);
+    float *R = nullptr;
+    e = hipMalloc(&R, bytes + split_rotation_bytes(rot->d));
     if (e != hipSuccess) return hip_fail(e, "hipMalloc(rotation)");
-    e = hipMemcpy(rot->R_dev, rot->R.data(), bytes, hipMemcpyHostToDevice);
-    if (e != hipSuccess) return hip_fail(e, "hipMemcpy(rotation)");
+    e = hipMemcpy(R, rot->R.data(), bytes, hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = split_rotation(R, rot->d, R + rot->R.size(), nullptr);
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+    if (e != hipSuccess) {
+        (void)hipFree(R);
+        return hip_fail(e, "rotation upload");
+    }
+    rot->R_dev = R;
     rot->R_dev_device = dev;
     *out = rot->R_dev;
     return TQ_OK;
@@ -393,15 +401,13 @@ tq_status tq_rotate_quantize(const tq_codebook *cb, const tq_rotation *rot, cons
     fill_codebook_dev(cb->t, &cd);
     const int d = rot->d;
     AsyncBuf ws;
-    hipError_t e = ws.alloc(encode_workspace_bytes(d) + 256, s);
+    hipError_t e = ws.alloc(encode_workspace_bytes(n, d) + 256, s);
     if (e != hipSuccess) return hip_fail(e, "hipMallocAsync(encode workspace)");
-    int *status = reinterpret_cast<int *>(static_cast<uint8_t *>(ws.p) + encode_workspace_bytes(d));
-    e = hipMemsetAsync(status, 0, sizeof(int), s);
-    if (e != hipSuccess) return hip_fail(e, "hipMemsetAsync");
+    int *status = reinterpret_cast<int *>(static_cast<uint8_t *>(ws.p) + encode_workspace_bytes(n, d));
     EncodeOut out;
     out.canonical = codes_dev;
     out.scales = scales_dev;
-    e = encode_rows(X_dev, n, d, R, cd, out, ws.p, status, s);
+    e = encode_rows(X_dev, n, d, R, R + (size_t)d * d, cd, out, ws.p, status, s);
     if (e != hipSuccess) return hip_fail(e, "encode");
     int h = 0;
     st = read_status(status, s, &h);
@@ -486,10 +492,8 @@ static tq_status add_vectors(tq_index *idx, const float *X_dev, const uint16_t *
     st = rotation_dev(&idx->rot, &R);
     if (st != TQ_OK) return st;
     AsyncBuf ws;
-    hipError_t e = ws.alloc(encode_workspace_bytes(idx->d), s);
+    hipError_t e = ws.alloc(encode_workspace_bytes(n, idx->d), s);
     if (e != hipSuccess) return hip_fail(e, "hipMallocAsync(encode workspace)");
-    e = hipMemsetAsync(idx->status, 0, sizeof(int), s);
-    if (e != hipSuccess) return hip_fail(e, "hipMemsetAsync");
     EncodeOut out;
     out.blocked = idx->codes;
     out.blocked_scales = idx->scales;
@@ -499,7 +503,7 @@ static tq_status add_vectors(tq_index *idx, const float *X_dev, const uint16_t *
         cal.athr = idx->athr;
         cal.ysq = idx->ysq;
     }
-    e = encode_rows(X_dev, n, idx->d, R, idx->cbdev, out, ws.p, idx->status, s, cal);
+    e = encode_rows(X_dev, n, idx->d, R, R + (size_t)idx->d * idx->d, idx->cbdev, out, ws.p, idx->status, s, cal);
     if (e != hipSuccess) return hip_fail(e, "encode");
     int h = 0;
     st = read_status(idx->status, s, &h);

@@ -1,27 +1,39 @@
 // Rotation + quantisation of float32 rows on gfx950 (section II-B, steps 1-5).
 //
 // Pipeline per chunk of rows:
-//  0. row_norm_kernel: the exact row norm n = sqrt(sum_k x_k^2) (sequential
-//     float64 over k) and a report of non-finite inputs.
-//  1. encode_gemm: Y = X R^T on the matrix cores (v_mfma_f32_32x32x2f32),
-//     with each 32-wide slab of k accumulated in float32 and then added into
-//     float64 accumulators.  The epilogue turns every y into a code by
-//     comparing it with fl64(t_i * n) and flags the coordinate when y lies
+//  0. split_rows_kernel: the exact row norm n = sqrt(sum_k x_k^2) (sequential
+//     float64 over k), a report of non-finite inputs, and every row scaled by
+//     a power of two 2^e (n 2^e in [2^15, 2^16) / 1.02) and split into two
+//     float16 parts, x 2^e = xh + xl (1 + eps).  The rotation is split the
+//     same way once, R 2^15 = Rh + Rl (1 + eps).
+//  1. encode_gemm: Y = X R^T on the float16 matrix cores
+//     (v_mfma_f32_32x32x16_f16, sixteen times the float32 rate): xh Rh, xh Rl
+//     and xl Rh, whose products are exact in float32.  The xh Rh partials of
+//     each 32-wide slab of k are rounded into 32-bit integer accumulators, the
+//     two small sums stay in float32.  The epilogue turns every y into a code
+//     by comparing it with fl64(t_i * n) and flags the coordinate when y lies
 //     within tau of a threshold, where tau bounds |y - S| for S the float64
-//     sequential dot product of the definition:
-//       per slab, float32 MFMA accumulation of 32 products from 0, in any
-//       order:
-//         |err| <= gamma_33 * sum|R_jk x_k|   (gamma_m = m u / (1 - m u),
-//                                              u = 2^-24; doubled for margin)
-//       float64 sum of 48 slab partials and the float64 reference itself:
-//         < 2e-13 * n;  flushed denormal products: < 2e-35 absolute.
-//     With ||R_j|| <= 1 + 1e-6 this gives tau = 4.0e-6 * n + 1e-30.
+//     sequential dot product of the definition.  With u = 2^-23 (twice the
+//     unit roundoff, for additions that truncate), ||R_j|| <= 1 + 1e-6 and
+//     A = sum_k |R_jk x_k| <= n (1 + 1e-6), relative to n:
+//       xh Rh: 32 products per slab, added from 0 in any order: 33 u A
+//              (1 + 2^-10)^2; rounded to the integer unit, at most 2^-30 n,
+//              once per slab: d/32 2^-31;
+//       xh Rl + xl Rh: 2d products of which the absolute sum is at most
+//              2^-10 A (1 + 2^-10), in any order: (2d + 1) u 2^-10 (1 + 2^-9);
+//       xl Rl left out, and xl and Rl rounded: 2^-22 A each;
+//       parts below the smallest normal float16 (2^-14, 2^-29 relative to
+//              the scales) if the matrix cores flush them: 4 sqrt(d) 2^-29;
+//       the float64 reference itself: < 3e-13; the float32 arithmetic of
+//              the epilogue: 5 2^-24.
+//     tau_rel sums these: 5.7e-6 at d = 1536.
 //  2. fixup: every flagged coordinate is recomputed as the sequential float64
 //     sum sum_{k=0}^{d-1} R[j][k] x_k (every product of two float32 values is
-//     exact in float64) and re-coded.  Flags are kept per output tile; with
-//     few flags per tile (b <= 4) one thread per flag reads its rows from
-//     memory, with many (b = 8, about 2% of coordinates) each tile stages
-//     its X and R slabs in LDS once for all of its flags.
+//     exact in float64) and re-coded.  Flags are kept per list tile; with
+//     few flags per tile (b <= 4) one wave per flag sums in parallel and only
+//     falls back to the sequential order where that decides the code, with
+//     many (b = 8, about 3% of coordinates) each tile stages its X and R
+//     slabs in LDS once for all of its flags.
 //  3. pack: per row, scale = n / sqrt(sum_j fl64(c_code_j^2)) (sequential
 //     float64 over j) and the codes are written in the canonical bitstream
 //     and/or the index's blocked layout.
@@ -31,6 +43,7 @@
 // computed on the host in float64 and passed in (CalibDev).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <type_traits>
@@ -48,8 +61,18 @@ constexpr int BN = 128;                 // rows of R (output columns) per workgr
 constexpr int KB = 32;                  // k per slab
 constexpr int LDS_STRIDE = KB + 4;      // floats per staged row (conflict-free b128 reads)
 constexpr int GEMM_THREADS = 512;       // 8 waves: 2 along rows x 4 along columns
-constexpr double kTauRel = 4.0e-6;
-constexpr double kTauAbs = 1e-30;
+constexpr int RC_PANEL = 32;            // rows of a split panel (an MFMA tile)
+
+// The bound tau / n above.
+double tau_rel(int d) {
+    const double u = std::ldexp(1.0, -23);
+    const double hh = 33 * u * (1 + std::ldexp(1.0, -10)) * (1 + std::ldexp(1.0, -10)) +
+                      (d / 32) * std::ldexp(1.0, -31);
+    const double small = (2 * d + 1) * u * std::ldexp(1.0, -10) * (1 + std::ldexp(1.0, -9));
+    const double rest = 3 * std::ldexp(1.0, -22) + 4 * std::sqrt((double)d) * std::ldexp(1.0, -29) + 3e-13 +
+                        5 * std::ldexp(1.0, -24);
+    return (hh + small + rest) * (1 + 3e-6);
+}
 
 struct QuantArgs {
     const double *bounds;   // device copy of the thresholds t_i (levels-1)
@@ -58,10 +81,11 @@ struct QuantArgs {
     const double *athr;
     int levels;
     uint8_t *codes_tmp;     // [rows][d] unpacked codes of this chunk
-    double *norms;          // [rows] exact row norms (written by column tile 0)
-    uint32_t *flags;        // per output tile, BM * BN slots: flagged (local row << 7 | local col)
-    unsigned int *tile_count;   // flags of each output tile
-    int *status;            // set non-zero on a non-finite input
+    const float *inv;       // [rows] 1 / (n 2^(e + 15)): y / n per unit of the products; 0 for a zero row
+    float tau;              // bound on |y - S| relative to the norm
+    double bin_width;       // of the epilogue's table
+    uint16_t *flags;        // per list tile, one slot per output: flagged (local row << 7 | local col)
+    unsigned int *tile_count;   // flags of each list tile
 };
 
 // XCD-aware tile order: the d/BN column tiles of one row tile go to the same
@@ -196,343 +220,456 @@ __global__ __launch_bounds__(GEMM_THREADS) void rot_gemm(
         }
 }
 
-// ------------------------------------------------------------- row norms
-// n = sqrt(sum_k x_k^2) of every row of the chunk: one thread per row adds
-// the squares in k order in float64 (x^2 is exact in float64, so the fused
-// multiply-add rounds exactly as add(fl(x^2))).  A wave takes 64 rows in
-// slabs of RN_KS coordinates: every load instruction reads the 256-byte
-// slabs of 4 rows, the slab passes through LDS (rows padded to 17 pieces, so
-// the summing lanes read distinct banks), and lane r adds row r's squares;
-// two slabs are in registers while one is summed.  A non-finite input makes
-// the sum non-finite (x^2 of a finite float32 cannot overflow float64),
-// which sets *status.
-constexpr int RN_KS = 64;               // coordinates per slab (d is a multiple of 64)
-constexpr int RN_PQ = RN_KS / 4;        // 16-byte pieces of a row slab
-constexpr int RN_LD = 64 * RN_PQ / 64;  // load instructions per slab (4 rows each)
+// ------------------------------------------------------ norms and splitting
+// Split panels: 32 rows of a matrix in the operand order of
+// v_mfma_f32_32x32x16_f16, [panel][k / 16][part][lane] with 16 bytes (8
+// float16) per lane: lane l holds row 32 panel + (l & 31), k = 16 (k / 16) +
+// 8 (l >> 5) .. +7; part 0 is the high part, part 1 the low one.  A panel's
+// k-step is 2 KiB.
+__device__ inline int64_t split_at(int64_t row, int ks, int h, int part, int d) {
+    return (((row >> 5) * (d / 16) + ks) * 2 + part) * 64 + 32 * h + (row & 31);
+}
+// Splits the 8 values v (scaled by 2^e) and stores both parts.
+__device__ inline void split_store(const f4 &v0, const f4 &v1, int e, uint4 *planes, int64_t at) {
+    union {
+        _Float16 f[8];
+        uint4 u;
+    } hi, lo;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const float x = ldexpf(i < 4 ? v0[i & 3] : v1[i & 3], e);
+        hi.f[i] = (_Float16)x;
+        lo.f[i] = (_Float16)(x - (float)hi.f[i]);   // the difference is exact
+    }
+    planes[at] = hi.u;
+    planes[at + 64] = lo.u;
+}
 
-struct RnSlab {
-    f4 v[RN_LD];
-};
+constexpr int kRotScale = 15;           // R is scaled by 2^15
 
-__global__ __launch_bounds__(64) void row_norm_kernel(const float *__restrict__ X, int64_t m,
-                                                      int d, double *__restrict__ norms,
-                                                      int *__restrict__ status) {
-    constexpr int PS = RN_PQ + 1;
-    __shared__ f4 xs[64 * PS];
-    const int lane = threadIdx.x;
-    const int64_t r0 = (int64_t)blockIdx.x * 64;
-    const int ns = d / RN_KS;
-    // load i: lanes 16 g .. 16 g + 15 read row 4 i + g (rows past m: the last)
-    auto row_ptr = [&](int i) {
-        int64_t r = r0 + 4 * i + (lane >> 4);
-        r = r < m ? r : m - 1;
-        return X + r * d + 4 * (lane & 15);
-    };
-    auto load = [&](int sl, RnSlab &b) {
+__global__ __launch_bounds__(256) void split_rotation_kernel(const float *__restrict__ R, int d,
+                                                             uint4 *__restrict__ planes) {
+    // consecutive threads: 8 rows of one 8-wide piece (128 bytes of a plane)
+    const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const int64_t per8 = 8 * (d / 8);
+    if (e >= (int64_t)d / 8 * per8) return;
+    const int64_t row = e / per8 * 8 + (e & 7);
+    const int piece = (int)(e % per8 >> 3);
+    const f4 *src = reinterpret_cast<const f4 *>(R + row * d + piece * 8);
+    split_store(src[0], src[1], kRotScale, planes, split_at(row, piece >> 1, piece & 1, 0, d));
+}
+
+// Norms and split panels of 8 rows per workgroup (rows m .. up to a multiple
+// of 32: zeros).  The rows are read once into LDS (padded by one 16-byte
+// piece, so that the 8 rows' pieces lie in distinct banks); two rows per
+// wave are summed in parallel for the row's exponent e, then lanes 0..7 of
+// wave 0 add the squares in k order in float64 (x^2 is exact in float64, so
+// the fused multiply-add rounds exactly as add(fl(x^2))) while the other
+// waves split.  Three workgroups fit a compute unit, so one workgroup's sequential
+// sums (about 5 us at d = 1536) overlap the others' loads.  A non-finite
+// input makes the sum non-finite (x^2 of a finite float32 cannot overflow
+// float64), which sets *status.
+constexpr int SR_ROWS = 8;
+constexpr int SR_THREADS = 256;
+__global__ __launch_bounds__(SR_THREADS) void split_rows_kernel(
+    const float *__restrict__ X, int64_t m, int d, uint4 *__restrict__ planes,
+    double *__restrict__ norms, float *__restrict__ inv, int *__restrict__ status) {
+    extern __shared__ __attribute__((aligned(16))) float xs[];   // [SR_ROWS][d + 4]
+    __shared__ int exps[SR_ROWS];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t r0 = (int64_t)blockIdx.x * SR_ROWS;
+    const int ps = d + 4, pq = d / 4;   // LDS row stride; 16-byte pieces of a row
+    constexpr int LD = SR_ROWS * (2048 / 4) / SR_THREADS;   // loads per thread, d <= 2048
+    {
+        f4 v[LD];
+        const int total = SR_ROWS * pq;
 #pragma unroll
-        for (int i = 0; i < RN_LD; ++i)
-            b.v[i] = *reinterpret_cast<const f4 *>(row_ptr(i) + sl * RN_KS);
-    };
-    // the barriers order the lanes' LDS accesses (a lane sums what other
-    // lanes staged) and leave the loads in flight
-    auto stage = [&](const RnSlab &b) {
-        lds_barrier();
+        for (int u = 0; u < LD; ++u) {
+            const int e = tid + u * SR_THREADS;
+            const int r = e / pq;
+            v[u] = f4{0.f, 0.f, 0.f, 0.f};
+            if (e < total && r0 + r < m)
+                v[u] = *reinterpret_cast<const f4 *>(X + (r0 + r) * d + (e - r * pq) * 4);
+        }
 #pragma unroll
-        for (int i = 0; i < RN_LD; ++i) xs[(4 * i + (lane >> 4)) * PS + (lane & 15)] = b.v[i];
-        lds_barrier();
-        // the refill of these registers stays after the writes: moved ahead,
-        // it would take other registers and the loop would copy them back
-        // at its back edge, waiting for every load in flight
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    double s2 = 0.0;
-    auto sum = [&]() {
+        for (int u = 0; u < LD; ++u) {
+            const int e = tid + u * SR_THREADS;
+            const int r = e / pq;
+            if (e < total) *reinterpret_cast<f4 *>(xs + r * ps + (e - r * pq) * 4) = v[u];
+        }
+    }
+    __syncthreads();
 #pragma unroll
-        for (int q = 0; q < RN_PQ; ++q) {
-            const f4 v = xs[lane * PS + q];
+    for (int i = 0; i < 2; ++i) {
+        const int r = 2 * wave + i;
+        double s = 0.0;
+        for (int q = lane; q < pq; q += 64) {
+            const f4 v = *reinterpret_cast<const f4 *>(xs + r * ps + 4 * q);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const double x = (double)v[c];
-                s2 = __builtin_fma(x, x, s2);
+            for (int c = 0; c < 4; ++c) s = __builtin_fma((double)v[c], (double)v[c], s);
+        }
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+        if (lane == 0) {
+            const double n = std::sqrt(s);   // within 1e-13 of the norm
+            const bool ok = n > 0.0 && std::isfinite(n);
+            const int e = ok ? 15 - ilogb(n * 1.02) : 0;
+            exps[r] = e;
+            if (r0 + r < m) inv[r0 + r] = ok ? (float)(1.0 / ldexp(n, e + kRotScale)) : 0.f;
+        }
+    }
+    __syncthreads();
+    if (wave == 0) {
+        if (lane < SR_ROWS) {
+            const float *x = xs + lane * ps;
+            // 8 pieces in registers while the 8 before are summed (pq is a
+            // multiple of 16); the last read is of the last pieces again
+            f4 va[8], vb[8];
+            auto load = [&](int q, f4(&v)[8]) {
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const f4 *>(x + 4 * (q + u));
+            };
+            double s2 = 0.0;
+            auto sum = [&](const f4(&v)[8]) {
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) s2 = __builtin_fma((double)v[u][c], (double)v[u][c], s2);
+            };
+            load(0, va);
+            for (int q = 0; q < pq; q += 16) {
+                load(q + 8, vb);
+                __builtin_amdgcn_sched_barrier(0);
+                sum(va);
+                load(q + 16 < pq ? q + 16 : q + 8, va);
+                __builtin_amdgcn_sched_barrier(0);
+                sum(vb);
+            }
+            if (r0 + lane < m) {
+                norms[r0 + lane] = std::sqrt(s2);
+                if (!std::isfinite(s2)) atomicOr(status, 1);
             }
         }
-    };
-    RnSlab b0, b1;
-    load(0, b0);
-    __builtin_amdgcn_sched_barrier(0);   // b0's loads all ahead of b1's
-    load(ns > 1 ? 1 : 0, b1);
-    for (int sl = 0; sl < ns; sl += 2) {
-        stage(b0);
-        load(sl + 2 < ns ? sl + 2 : ns - 1, b0);
-        sum();
-        if (sl + 1 < ns) stage(b1);
-        load(sl + 3 < ns ? sl + 3 : ns - 1, b1);
-        if (sl + 1 < ns) sum();
-    }
-    const int64_t r = r0 + lane;
-    if (r < m) {
-        norms[r] = std::sqrt(s2);
-        if (!std::isfinite(s2)) atomicOr(status, 1);
+    } else {
+        for (int e = tid - 64; e < SR_ROWS * (d / 8); e += SR_THREADS - 64) {
+            const int r = e & 7, piece = e >> 3;
+            const f4 *x = reinterpret_cast<const f4 *>(xs + r * ps + piece * 8);
+            split_store(x[0], x[1], exps[r], planes, split_at(r0 + r, piece >> 1, piece & 1, 0, d));
+        }
     }
 }
 
 // ------------------------------------------------------------- encode_gemm
-// Y = X R^T with the quantiser epilogue, for the encode.  Same tiles and
-// workgroup shape as rot_gemm (128 x 128, k-slabs of 32, 8 waves of 64 x 32),
-// but built for throughput:
-//  - v_mfma_f32_32x32x2f32 (two 32 x 32 tiles per wave), which keeps the
-//    matrix pipe busier than 16x16x4 at two waves per SIMD;
-//  - a four-stage LDS ring filled by direct global -> LDS loads three slabs
-//    ahead, one barrier per slab, and each k-group's operands read from LDS
-//    one group ahead, so that no load or LDS latency sits between a barrier
-//    and the next MFMA;
-//  - two sets of float32 accumulators: the float64 fold of slab s-1 is
-//    interleaved with the MFMAs of slab s;
-//  - the row norms come from row_norm_kernel (float64 vector work in this
-//    loop does not overlap the matrix pipe).
-// Slab s covers k in [32s, 32s+32); group g of it k in [32s+8g, 32s+8g+8).
-// Lane l (h = l / 32) of a wave feeds k = 32s + 8g + 4h + t to step t of
-// group g, so one 16-byte LDS read per operand and group serves 4 MFMAs.
-// The float32 partial of a slab sums its 32 products in an order of the
-// matrix core's choosing; the error bound behind tau (any order of a
-// 32-term float32 sum from zero) is the same as for rot_gemm.
-constexpr int EG_STAGES = 4;
-constexpr int EG_OPER_B = BM * KB * 4;   // bytes of one operand tile of a slab (16 KiB)
-constexpr int EG_STAGE_B = 2 * EG_OPER_B;  // A then B
-
-// Operand tiles are stored unpadded in four planes, one per k-group g:
-// plane g holds, for each of the 128 rows, the row's floats 8g .. 8g+7 of
-// the slab as two 16-byte pieces, piece h at byte 4096 g + 32 r +
-// 16 (h ^ eg_swz(r)).  A read of piece h of 16 consecutive rows (8, with
-// 32 banks) then meets distinct banks, and the group index is an immediate
-// offset.
-__device__ inline int eg_swz(int r) { return ((r >> 2) ^ (r >> 3)) & 1; }
+// Y = X R^T with the quantiser epilogue, for the encode.  WR x WC waves of TM
+// x TN tiles of 32 x 32 outputs:
+//  - both operands are split panels, staged by direct global -> LDS loads of
+//    1 KiB pieces into a ring of ST k-steps of 16, four k-steps ahead,
+//    one barrier per k-step; operand reads are 16 bytes per lane at
+//    consecutive addresses;
+//  - three products per tile and k-step.  The integer fold of the previous
+//    slab's xh Rh partials (round, convert, add) is interleaved with them and
+//    is hidden behind them: 24 products and the fold of four tiles run at the
+//    rate of the products alone (2.0 to 2.1 PFLOP/s in a register-only loop),
+//    which a fold into float64 does not (it has twice the registers).
+// Large shape (TM = TN = 2, 2 x 2 waves, 128 x 128 outputs, two workgroups per
+// compute unit): 224 registers of accumulators and operands leave two waves
+// per SIMD.  Each operand register is read again for the next k-step as soon as
+// its last product is issued; the column order alternates so that the next
+// k-step starts with the pair that was read first.  32,768 rows at d = 1536
+// take 530 us, 870 TFLOP/s of products (1,409 us with float32 products); of
+// the time, without the loads into LDS it would be 160 us less, without the
+// reads from it 70 us, without the fold 45 us.  256 x 128 outputs and one
+// workgroup of 8 waves move a quarter less through the L2 and take as long,
+// but 83 instead of 56 us where one round of tiles is all there is.
+// Small shape (TM = TN = 1, 2 x 2 waves, 64 x 64 outputs) for row counts
+// whose large tiles would leave compute units idle: see kEncodeSmallOutputs.
+//
+// The epilogue's table of the thresholds t_0 .. t_{L-2}: EG_BINS bins of equal
+// width over [t_0, t_{L-2}] (values outside take the end ones), each with the
+// threshold next to its centre and the number of thresholds below that one.
+// Two thresholds are at least 1/519 of the range apart (over all dimensions
+// and widths, at b = 8), almost two bins, so that no other threshold lies in
+// the bin or within tau of it.
+constexpr int EG_BINS = 1024;
 
 typedef float f16v __attribute__((ext_vector_type(16)));
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 
-__global__ __launch_bounds__(GEMM_THREADS) void encode_gemm(
-    const float *__restrict__ X, int64_t m, const float *__restrict__ R, int d,
-    int n_row_tiles, QuantArgs qa) {
-    __shared__ __attribute__((aligned(1024))) char stg[EG_STAGES * EG_STAGE_B];
-    __shared__ double norm_s[BM];
-    __shared__ double bnd_s[255];
-    __shared__ double athr_s[15 * BN];   // TQ+ thresholds of the tile's columns, b <= 4
-    __shared__ unsigned int nflag_s;
+template <int TM, int TN, int WR, int WC, int ST>
+struct EgShape {
+    static constexpr int STAGES = ST;
+    static constexpr int WAVES = WR * WC;
+    static constexpr int THREADS = 64 * WAVES;
+    static constexpr int RP = TM * WR, CP = TN * WC;     // panels of rows and columns
+    static constexpr int ROWS = 32 * RP, COLS = 32 * CP;
+    static constexpr int PIECES = 2 * (RP + CP);         // 1 KiB pieces of a k-step
+    static constexpr int PW = PIECES / WAVES;            // of which a wave loads
+    static constexpr int STEP_B = PIECES * 1024;
+    static constexpr int SIDE = COLS;                    // list tiles are COLS x COLS
+    static constexpr int LISTS = ROWS / SIDE;            // of a workgroup
+    static constexpr size_t lds = (size_t)ST * STEP_B + ROWS * 4 + EG_BINS * 8 + 8;
+    static_assert(PIECES % WAVES == 0, "whole pieces per wave");
+};
+using EgLarge = EgShape<2, 2, 2, 2, 4>;
+using EgSmall = EgShape<1, 1, 2, 2, 6>;
 
-    const int ncol = (d + BN - 1) / BN;
+template <int TM, int TN, int WR, int WC, int ST>
+__global__ __launch_bounds__(64 * WR * WC, 2) void encode_gemm(
+    const uint4 *__restrict__ Xp, int64_t m, const uint4 *__restrict__ Rp, int d, int n_row_tiles,
+    QuantArgs qa) {
+    using S = EgShape<TM, TN, WR, WC, ST>;
+    static_assert((TM == 1 && TN == 1) || (TM == 2 && TN == 2), "operand schedules below");
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    char *stg = smem;
+    float *inv_s = reinterpret_cast<float *>(smem + ST * S::STEP_B);      // [ROWS]
+    float2 *bin_s = reinterpret_cast<float2 *>(inv_s + S::ROWS);                 // [EG_BINS]
+    unsigned int *nflag_s = reinterpret_cast<unsigned int *>(bin_s + EG_BINS);   // [LISTS]
+
+    const int ncol = (d + S::COLS - 1) / S::COLS;
     int rt, ct;
     tile_of(blockIdx.x, ncol, rt, ct);
     if (rt >= n_row_tiles) return;
-    const int64_t row0 = (int64_t)rt * BM;
-    const int col0 = ct * BN;
+    const int64_t row0 = (int64_t)rt * S::ROWS;
+    const int col0 = ct * S::COLS;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wr = wave >> 2;     // 0..1 : 64-row half
-    const int wc = wave & 3;      // 0..3 : 32-column quarter
+    const int wr = wave / WC, wc = wave % WC;
     const int l32 = lane & 31;
     const int h = lane >> 5;
-    const int nslab = d / KB;     // even: d is a multiple of 64
+    const int KS = d / 16;        // even: d is a multiple of 64
 
-    // This wave's loads of a slab: pieces 128 wave + 64 j + lane (j = 0, 1)
-    // of the A tile and of the B tile.  Rows of X past m and rows of R past
-    // d are clamped to the last one: they only feed outputs the epilogue
-    // drops.
-    // This wave's loads of a slab: 1 KiB pieces 2 wave + j (j = 0, 1) of the
-    // A tile and of the B tile, i.e. plane wave / 2, rows 32 ((2 wave + j) & 3)
-    // + lane / 2.  Rows of X past m and rows of R past d are clamped to the
-    // last one: they only feed outputs that the epilogue drops.
-    uint32_t off_a[2], off_b[2];   // byte offsets of the lane's pieces in slab 0
+    // This wave's pieces of a k-step: piece p is part p & 1 of row panel
+    // p >> 1 (p < 2 RP), then of the column panels.  Panels past the last row
+    // or column are clamped to the last one: they only feed outputs that the
+    // epilogue drops.
+    const int64_t last_rp = (m - 1) >> 5;
+    const int last_cp = (d >> 5) - 1;
+    const char *src[S::PW];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int i = 2 * wave + j;
-        const int row = 32 * (i & 3) + (lane >> 1);
-        const int k = 8 * (i >> 2) + 4 * ((lane & 1) ^ eg_swz(row));
-        const int64_t ar = row0 + row < m ? row0 + row : m - 1;
-        const int br = col0 + row < d ? col0 + row : d - 1;
-        off_a[j] = (uint32_t)((ar * d + k) * 4);
-        off_b[j] = (uint32_t)(((int64_t)br * d + k) * 4);
+    for (int j = 0; j < S::PW; ++j) {
+        const int p = wave * S::PW + j;
+        const bool is_r = p < 2 * S::RP;
+        int64_t panel = is_r ? (row0 >> 5) + (p >> 1) : (col0 >> 5) + ((p - 2 * S::RP) >> 1);
+        const int64_t last = is_r ? last_rp : last_cp;
+        panel = panel < last ? panel : last;
+        src[j] = reinterpret_cast<const char *>(is_r ? Xp : Rp) + panel * KS * 2048 + (p & 1) * 1024;
     }
     const uint32_t stg_lds = (uint32_t)(uintptr_t)stg;
-    // slab s into stage ST: 4 loads per wave (uniform base + 32-bit lane offset)
-    auto request = [&](int s, auto ST) {
-        constexpr uint32_t stage = decltype(ST)::value;
-        const uint32_t base = stg_lds + stage * EG_STAGE_B + (uint32_t)wave * 2048;
-        const float *xa = X + s * KB;
-        const float *rb = R + s * KB;
-        lds_dma16_s(off_a[0], xa, base);
-        lds_dma16_s(off_a[1], xa, base + 1024);
-        lds_dma16_s(off_b[0], rb, base + EG_OPER_B);
-        lds_dma16_s(off_b[1], rb, base + EG_OPER_B + 1024);
-    };
-    // operands of group g: A rows of the wave's two 32-row tiles, B columns
-    const int pz = 16 * (h ^ eg_swz(l32));   // eg_swz(row) of every row this lane reads
-    const int a_base = (wr * 64 + l32) * 32 + pz;
-    const int b_base = EG_OPER_B + (wc * 32 + l32) * 32 + pz;
-    auto opread = [&](auto ST, int g, f4 &a0, f4 &a1, f4 &b) {
-        constexpr int stage = decltype(ST)::value;
-        const char *S = stg + stage * EG_STAGE_B + 4096 * g;
-        a0 = *reinterpret_cast<const f4 *>(S + a_base);
-        a1 = *reinterpret_cast<const f4 *>(S + a_base + 32 * 32);
-        b = *reinterpret_cast<const f4 *>(S + b_base);
+    int rq = 0, rq_st = 0;        // next k-step to request (the last one again past the end), its stage
+    auto request = [&]() {
+        const uint32_t base = stg_lds + rq_st * S::STEP_B + wave * (S::PW * 1024);
+        const int64_t off = (int64_t)(rq < KS ? rq : KS - 1) * 2048;
+#pragma unroll
+        for (int j = 0; j < S::PW; ++j) lds_dma16_s((uint32_t)lane * 16, src[j] + off, base + j * 1024);
+        ++rq;
+        rq_st = rq_st + 1 == ST ? 0 : rq_st + 1;
     };
 
+    const int L = qa.levels;
     if (!qa.athr)
-        for (int i = tid; i < qa.levels - 1; i += GEMM_THREADS) bnd_s[i] = qa.bounds[i];
-    const bool athr_lds = qa.athr && qa.levels <= 16;
-    if (athr_lds)
-        for (int e = tid; e < (qa.levels - 1) * BN; e += GEMM_THREADS) {
-            const int i = e / BN, c = col0 + e % BN;
-            athr_s[e] = c < d ? qa.athr[(int64_t)i * d + c] : 0.0;
+        for (int e = tid; e < EG_BINS; e += S::THREADS) {
+            const double centre = qa.bounds[0] + (e + 0.5) * qa.bin_width;
+            int c = 0;   // thresholds at most the centre
+            for (int step = L / 2; step >= 1; step >>= 1) c += qa.bounds[c + step - 1] <= centre ? step : 0;
+            const bool up = c == 0 || (c < L - 1 && qa.bounds[c] - centre < centre - qa.bounds[c - 1]);
+            const int i = up ? c : c - 1;
+            bin_s[e] = make_float2((float)qa.bounds[i], __int_as_float(i));
         }
-    if (tid == 0) nflag_s = 0;
-    if (tid < BM) norm_s[tid] = row0 + tid < m ? qa.norms[row0 + tid] : 0.0;
-
-    // prologue: slabs 0, 1 and 2 requested, 0 and 1 landed
-    using I0 = std::integral_constant<int, 0>;
-    using I1 = std::integral_constant<int, 1>;
-    using I2 = std::integral_constant<int, 2>;
-    using I3 = std::integral_constant<int, 3>;
-    request(0, I0());
-    request(1, I1());
-    if (nslab > 2) {
-        request(2, I2());
-        wait_vmem<4>();
-    } else {
-        wait_vmem<0>();
-    }
-    lds_barrier();
+    if (tid < S::LISTS) nflag_s[tid] = 0;
+    for (int r = tid; r < S::ROWS; r += S::THREADS) inv_s[r] = row0 + r < m ? qa.inv[row0 + r] : 0.f;
+    wait_vmem<0>();   // the counts below are of the pieces alone
+#pragma unroll
+    for (int i = 0; i < ST - 1; ++i) request();
 
     const f16v zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f,
                        0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    f16v acc[2][2];     // [set][tile]: float32 partials of slab s (set s & 1)
-    double accd[2][16]; // [tile][i]
+    f16v hh[TM][TN], sm[TM][TN];   // xh Rh of the current slab; xh Rl + xl Rh
+    int tot[TM][TN][16];           // xh Rh of the slabs before
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        acc[1][t] = zero;
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) accd[t][i] = 0.0;
-    }
-    // operands: set g & 1 feeds group g while group g + 1's are read into
-    // the other set (static indices once unrolled: no register copies)
-    f4 op[2][3];
-    opread(I0(), 0, op[0][0], op[0][1], op[0][2]);
-
-    // slab s, held in stage ST (static, so that every LDS address is an
-    // offset from a fixed register)
-    auto slab = [&](int s, auto ST, f16v(&cur)[2], const f16v(&prv)[2]) {
-        using Next = std::integral_constant<int, (decltype(ST)::value + 1) % EG_STAGES>;
-        using Far = std::integral_constant<int, (decltype(ST)::value + 3) % EG_STAGES>;
+        for (int j = 0; j < TN; ++j) {
+            hh[i][j] = zero;
+            sm[i][j] = zero;
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            f4(&c)[3] = op[g & 1];
-            f4(&n)[3] = op[(g + 1) & 1];
-            if (g < 3)
-                opread(ST, g + 1, n[0], n[1], n[2]);
-            else if (s + 1 < nslab)
-                opread(Next(), 0, n[0], n[1], n[2]);
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                cur[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(c[0][t], c[2][t],
-                                                              (g == 0 && t == 0) ? zero : cur[0], 0, 0, 0);
-                cur[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(c[1][t], c[2][t],
-                                                              (g == 0 && t == 0) ? zero : cur[1], 0, 0, 0);
-            }
-            // fold a quarter of slab s-1's partials (zeros before slab 0)
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                accd[g >> 1][(g & 1) * 8 + i] += (double)prv[g >> 1][(g & 1) * 8 + i];
-            if (g == 1) {
-                // slab s+1 has landed (this wave's loads; the barrier makes it
-                // every wave's), and every wave is past slab s-1, whose stage,
-                // (s+3) % 4, takes slab s+3
-                if (s + 2 < nslab)
-                    wait_vmem<4>();
-                else
-                    wait_vmem<0>();
-                lds_barrier();
-                if (s + 3 < nslab) request(s + 3, Far());
-            }
+            for (int e = 0; e < 16; ++e) tot[i][j][e] = 0;
         }
+    // operands [set][tile][part]; the small shape has two sets in turn
+    constexpr int SETS = TM == 1 ? 2 : 1;
+    half8 a[SETS][TM][2], b[SETS][TN][2];
+    int rd_st = 0;                // stage of the operands read next
+    const char *a_at = stg + wr * TM * 2048 + lane * 16;
+    const char *b_at = stg + S::RP * 2048 + wc * TN * 2048 + lane * 16;
+    auto load_a = [&](int set, int i) {
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+            a[set][i][p] = *reinterpret_cast<const half8 *>(a_at + rd_st * S::STEP_B + i * 2048 + p * 1024);
     };
-    int s0 = 0;
-    for (; s0 + 4 <= nslab; s0 += 4) {
-        slab(s0, I0(), acc[0], acc[1]);
-        slab(s0 + 1, I1(), acc[1], acc[0]);
-        slab(s0 + 2, I2(), acc[0], acc[1]);
-        slab(s0 + 3, I3(), acc[1], acc[0]);
-    }
-    if (s0 < nslab) {   // nslab = 2 mod 4: two more, in stages 0 and 1
-        slab(s0, I0(), acc[0], acc[1]);
-        slab(s0 + 1, I1(), acc[1], acc[0]);
+    auto load_b = [&](int set, int j) {
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+            b[set][j][p] = *reinterpret_cast<const half8 *>(b_at + rd_st * S::STEP_B + j * 2048 + p * 1024);
+    };
+    auto fold = [&](int i, int j, int half) {
+#pragma unroll
+        for (int e = 8 * half; e < 8 * half + 8; ++e) tot[i][j][e] += (int)__builtin_rintf(hh[i][j][e]);
+    };
+    // the three products of tile (i, j); an even k-step starts a slab
+    auto products = [&](int set, int i, int j, bool even) {
+        sm[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[set][i][1], b[set][j][0], sm[i][j], 0, 0, 0);
+        if (even) {
+            __builtin_amdgcn_sched_barrier(0);
+            fold(i, j, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        sm[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[set][i][0], b[set][j][1], sm[i][j], 0, 0, 0);
+        if (even) {
+            __builtin_amdgcn_sched_barrier(0);
+            fold(i, j, 1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        hh[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[set][i][0], b[set][j][0], even ? zero : hh[i][j],
+                                                          0, 0, 0);
+    };
+    // Publishes the k-step after the current one (own pieces landed, then
+    // everyone's) and requests the k-step five ahead into the stage of the
+    // previous one, which every wave is past.  Operand reads in flight need
+    // not complete here: their stage is not written before the next
+    // publication but one.
+    auto publish = [&]() {
+        wait_vmem<(ST - 3) * S::PW>();
+        asm volatile("s_barrier" ::: "memory");
+        request();
+    };
+    wait_vmem<(ST - 2) * S::PW>();
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < TM; ++i) load_a(0, i);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) load_b(0, j);
+    rd_st = 1;
+    auto step = [&](auto PAR) {
+        constexpr int par = decltype(PAR)::value;
+        constexpr bool even = par == 0;
+        if constexpr (TM == 1) {
+            publish();
+            load_a(par ^ 1, 0);
+            load_b(par ^ 1, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            products(par, 0, 0, even);
+        } else {
+            constexpr int c0 = par, c1 = par ^ 1;   // column order
+            products(0, 0, c0, even);
+            __builtin_amdgcn_sched_barrier(0);
+            publish();
+            __builtin_amdgcn_sched_barrier(0);
+            products(0, 0, c1, even);
+            __builtin_amdgcn_sched_barrier(0);
+            load_a(0, 0);
+            products(0, 1, c1, even);
+            __builtin_amdgcn_sched_barrier(0);
+            load_b(0, c1);
+            products(0, 1, c0, even);
+            __builtin_amdgcn_sched_barrier(0);
+            load_a(0, 1);
+            load_b(0, c0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        rd_st = rd_st + 1 == ST ? 0 : rd_st + 1;
+    };
+    for (int ks = 0; ks < KS; ks += 2) {
+        step(std::integral_constant<int, 0>());
+        step(std::integral_constant<int, 1>());
     }
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) accd[t][i] += (double)acc[1][t][i];
+        for (int j = 0; j < TN; ++j) {
+            fold(i, j, 0);
+            fold(i, j, 1);
+        }
+    wait_vmem<0>();    // the pieces requested past the end have landed:
+    __syncthreads();   // the stages are free
+    // TQ+ thresholds of the tile's columns, b <= 4, in the stages
+    float *athr_s = reinterpret_cast<float *>(stg);
+    const bool athr_lds = qa.athr && qa.levels <= 16;
+    if (athr_lds) {
+        for (int e = tid; e < (qa.levels - 1) * S::COLS; e += S::THREADS) {
+            const int i = e / S::COLS, c = col0 + e % S::COLS;
+            athr_s[e] = c < d ? (float)qa.athr[(int64_t)i * d + c] : 0.f;
+        }
+        __syncthreads();
+    }
 
-    const int L = qa.levels;
-    const int64_t tile = (int64_t)rt * ncol + ct;
-    uint32_t *tflags = qa.flags + tile * (BM * BN);
-    const int lc = wc * 32 + l32;
-    const int col = col0 + lc;
-    // Code and flag of the lane's 32 outputs (one column, 32 rows).  thr(q)
-    // is threshold q of this column before scaling by n.  The binary search
-    // runs level by level over a tile's 16 outputs, so that their threshold
-    // reads are independent (L is a power of two: c + step - 1 <= L - 2).
-    auto epilogue = [&](auto thr) {
+    const int lrow = wr * 32 * TM;                 // the wave's first row in the workgroup's tile
+    const int list = lrow / S::SIDE;
+    const int64_t tile = ((int64_t)rt * S::LISTS + list) * ncol + ct;
+    uint16_t *tflags = qa.flags + tile * (S::SIDE * S::SIDE);
+    // Code and flag of the lane's 16 outputs of a tile (one column, 16 rows),
+    // from z = y / n in float32: the float32 rounding of the two sums, of
+    // 1 / n, of the product and of the threshold is at most 4 2^-24 (|z| <= 1
+    // up to tau), part of tau.  find(lc, z, c, flag) gives the number c of
+    // thresholds at most z and whether one lies within tau of z.
+    const bool whole = row0 + S::ROWS <= m && col0 + S::COLS <= d;
+    uint8_t *cbase = qa.codes_tmp + row0 * d + col0;
+    auto epilogue = [&](int ti, int tj, auto find) {
+        const int lc = wc * 32 * TN + tj * 32 + l32;
+        const int r0 = lrow + ti * 32 + 4 * h;   // row of output i: r0 + 8 (i >> 2) + (i & 3)
+        const uint32_t at = (uint32_t)(r0 * d + lc);
+        uint32_t flagged = 0u;   // bit i: output i
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            int c[16];
-            double nr[16];
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                c[i] = 0;
-                nr[i] = norm_s[wr * 64 + t * 32 + 8 * (i >> 2) + 4 * h + (i & 3)];
-            }
-            for (int step = L / 2; step >= 1; step >>= 1) {
-#pragma unroll
-                for (int i = 0; i < 16; ++i)
-                    c[i] += (thr(c[i] + step - 1) * nr[i] <= accd[t][i]) ? step : 0;
-            }
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int lr = wr * 64 + t * 32 + 8 * (i >> 2) + 4 * h + (i & 3);
-                const int64_t gr = row0 + lr;
-                const double y = accd[t][i];
-                const double nrm = nr[i];
-                const double tau = kTauRel * nrm + kTauAbs;
-                const int ci = c[i];
-                const double lo = thr(ci > 0 ? ci - 1 : 0) * nrm;
-                const double hi = thr(ci < L - 1 ? ci : L - 2) * nrm;
-                bool flag = !std::isfinite(y) || (ci > 0 && y - lo <= tau) ||
-                            (ci < L - 1 && hi - y <= tau);
-                int code = ci;
-                if (nrm == 0.0) {
-                    code = L / 2;
-                    flag = false;
-                }
-                if (gr < m && col < d) {
-                    qa.codes_tmp[gr * d + col] = (uint8_t)code;
-                    if (flag) {
-                        // a slot of this tile's list (an LDS counter)
-                        const unsigned int slot = atomicAdd(&nflag_s, 1u);
-                        tflags[slot] = ((uint32_t)lr << 7) | (uint32_t)lc;
-                    }
-                }
-            }
+        for (int i = 0; i < 16; ++i) {
+            const int dr = 8 * (i >> 2) + (i & 3);
+            const float z = ((float)tot[ti][tj][i] + sm[ti][tj][i]) * inv_s[r0 + dr];
+            int c;
+            bool flag;
+            find(lc, z, c, flag);
+            flagged |= flag ? 1u << i : 0u;
+            if (whole || (row0 + r0 + dr < m && col0 + lc < d)) cbase[at + (uint32_t)(dr * d)] = (uint8_t)c;
+        }
+        while (flagged) {   // rare: a slot of this tile's list each (an LDS counter)
+            const int i = __builtin_ctz(flagged);
+            flagged &= flagged - 1u;
+            const int r = r0 + 8 * (i >> 2) + (i & 3);
+            if (row0 + r >= m || col0 + lc >= d) continue;
+            if (inv_s[r] == 0.f)   // a zero row
+                cbase[(uint32_t)(r * d + lc)] = (uint8_t)(L / 2);
+            else
+                tflags[atomicAdd(&nflag_s[list], 1u)] = (uint16_t)(((r - list * S::SIDE) << 7) | lc);
         }
     };
     if (!qa.athr) {
-        epilogue([&](int q) { return bnd_s[q]; });
-    } else if (athr_lds) {
-        epilogue([&](int q) { return athr_s[q * BN + lc]; });
+        const float t0 = (float)qa.bounds[0], inv_w = (float)(1.0 / qa.bin_width);
+        auto find = [&](int, float z, int &c, bool &flag) {
+            const float x = fminf(fmaxf((z - t0) * inv_w, 0.f), (float)(EG_BINS - 1));
+            const float2 b = bin_s[(int)x];
+            c = __float_as_int(b.y) + (b.x <= z ? 1 : 0);
+            flag = fabsf(z - b.x) <= qa.tau;
+        };
+#pragma unroll
+        for (int ti = 0; ti < TM; ++ti)
+#pragma unroll
+            for (int tj = 0; tj < TN; ++tj) epilogue(ti, tj, find);
     } else {
-        const double *ac = qa.athr + (col < d ? col : d - 1);
-        epilogue([&](int q) { return ac[(int64_t)q * d]; });
+        // TQ+: a binary search of the column's own thresholds (L is a power
+        // of two: c + step - 1 <= L - 2); zero rows may lie away from all of
+        // them and are always flagged
+        auto find = [&](int lc, float z, int &c, bool &flag) {
+            const int col = col0 + lc < d ? col0 + lc : d - 1;
+            auto thr = [&](int q) { return athr_lds ? athr_s[q * S::COLS + lc] : (float)qa.athr[(int64_t)q * d + col]; };
+            c = 0;
+            for (int step = L / 2; step >= 1; step >>= 1) c += thr(c + step - 1) <= z ? step : 0;
+            flag = fabsf(z - thr(c > 0 ? c - 1 : 0)) <= qa.tau ||
+                   fabsf(thr(c < L - 1 ? c : L - 2) - z) <= qa.tau || z == 0.f;
+        };
+#pragma unroll
+        for (int ti = 0; ti < TM; ++ti)
+#pragma unroll
+            for (int tj = 0; tj < TN; ++tj) epilogue(ti, tj, find);
     }
     __syncthreads();
-    if (tid == 0) qa.tile_count[tile] = nflag_s;
+    if (tid < S::LISTS && row0 + tid * S::SIDE < m)
+        qa.tile_count[((int64_t)rt * S::LISTS + tid) * ncol + ct] = nflag_s[tid];
 }
 
 // The code of coordinate j of a row with norm nrm whose exact sum is S.
@@ -546,132 +683,95 @@ __device__ inline int exact_code(double S, double nrm, int j, int d, const doubl
     return c;
 }
 
-// Exact recomputation of flagged coordinates (b <= 4): the sequential
-// float64 sum of the definition (products of float32 values are exact in
-// float64, so fused and unfused multiply-adds agree).  One wave per output
-// tile takes the tile's flags in batches of FX_FB, and for each slab of FX_KS
-// coordinates every lane loads 16-byte pieces of the batch's X rows and R
-// rows (one load instruction reads the 256-byte slabs of 4 flags' rows).
-// The slabs are staged in LDS and lane f adds its flag's products in k
-// order.  Two slabs are in registers while one is summed.
-constexpr int FX_FB = 16;                    // flags per batch
-constexpr int FX_KS = 64;                    // coordinates per slab (d is a multiple of 64)
-constexpr int FX_PQ = FX_KS / 4;             // 16-byte pieces of a row slab
-constexpr int FX_LD = FX_FB * FX_PQ / 64;    // load instructions per operand and slab
+// Exact recomputation of flagged coordinates (b <= 4).  One wave per flag
+// (the list tile's flags w, w + 4, ... for wave w) adds the coordinate's
+// products in float64 in parallel: every product is exact, so that sum and
+// the definition's sequential one differ by at most 2 gamma_d n < 1e-12 n.
+// If no threshold lies that close, both give the same code; otherwise (about
+// one flag in a million) the wave repeats the sum in k order from its
+// registers.  Bound by the 12 KiB of X and R a flag reads (68,000 flags of
+// 32,768 rows at d = 1536: 128 us, 6.4 TB/s); one lane per flag summing in k
+// order took 47 us for 400 flags, this takes 11.
+constexpr int FX_WAVES = 4;
+constexpr int FX_PC = 2048 / 256;            // 16-byte pieces of a row per lane at most
 
-struct FxSlab {
-    f4 x[FX_LD], r[FX_LD];
-};
-
-__global__ __launch_bounds__(64) void fixup_batch_kernel(
-    const float *__restrict__ X, const float *__restrict__ R, int d, int ncol,
+__global__ __launch_bounds__(FX_WAVES * 64) void fixup_flag_kernel(
+    const float *__restrict__ X, const float *__restrict__ R, int d, int side, int nrow, int ncol,
     const double *__restrict__ bounds, const double *__restrict__ athr, int levels,
     const double *__restrict__ norms,
-    const uint32_t *__restrict__ flags, const unsigned int *__restrict__ tile_count,
+    const uint16_t *__restrict__ flags, const unsigned int *__restrict__ tile_count,
     uint8_t *__restrict__ codes_tmp) {
-    // flag f's slab at [f][FX_PQ + 1]: the padding puts the 16 summing
-    // lanes' reads of one piece 17 pieces apart, in distinct banks
-    constexpr int PS = FX_PQ + 1;
-    __shared__ f4 xs[FX_FB * PS], rs[FX_FB * PS];
-    const int tile = blockIdx.x;
-    const int lane = threadIdx.x;
-    const int64_t row0 = (int64_t)(tile / ncol) * BM;
-    const int col0 = (tile % ncol) * BN;
+    int rt, ct;   // the column tiles of a row tile on one XCD: they share X rows
+    tile_of(blockIdx.x, ncol, rt, ct);
+    if (rt >= nrow) return;
+    const int tile = rt * ncol + ct;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t row0 = (int64_t)rt * side;
+    const int col0 = ct * side;
     const int cnt = (int)tile_count[tile];
-    const uint32_t *tflags = flags + (int64_t)tile * (BM * BN);
-    const int ns = d / FX_KS;
-    for (int e0 = 0; e0 < cnt; e0 += FX_FB) {
-        const int nb = cnt - e0 < FX_FB ? cnt - e0 : FX_FB;
-        // load i of a slab: lanes 16 g .. 16 g + 15 read the 256 contiguous
-        // bytes of flag 4 i + g's row slab (piece lane mod 16)
-        const float *xrow[FX_LD], *rrow[FX_LD];
+    const uint16_t *tflags = flags + (int64_t)tile * (side * side);
+    const int pq = d / 4;
+    for (int f = wave; f < cnt; f += FX_WAVES) {
+        const uint32_t fl = tflags[f];
+        const int64_t row = row0 + (fl >> 7);
+        const int j = col0 + (int)(fl & 127);
+        const float *xr = X + row * d, *rr = R + (int64_t)j * d;
+        f4 x[FX_PC], r[FX_PC];
 #pragma unroll
-        for (int i = 0; i < FX_LD; ++i) {
-            const int f = 4 * i + (lane >> 4);
-            const uint32_t fl = tflags[e0 + (f < nb ? f : nb - 1)];
-            xrow[i] = X + (row0 + (fl >> 7)) * d + 4 * (lane & 15);
-            rrow[i] = R + (int64_t)(col0 + (int)(fl & 127)) * d + 4 * (lane & 15);
+        for (int u = 0; u < FX_PC; ++u) {
+            const int q = lane + 64 * u;
+            x[u] = r[u] = f4{0.f, 0.f, 0.f, 0.f};
+            if (q < pq) {
+                x[u] = *reinterpret_cast<const f4 *>(xr + 4 * q);
+                r[u] = *reinterpret_cast<const f4 *>(rr + 4 * q);
+            }
         }
-        const bool act = lane < nb;
-        const uint32_t mf = tflags[e0 + (act ? lane : 0)];
-        auto load = [&](int sl, FxSlab &b) {
-#pragma unroll
-            for (int i = 0; i < FX_LD; ++i) {
-                b.x[i] = *reinterpret_cast<const f4 *>(xrow[i] + sl * FX_KS);
-                b.r[i] = *reinterpret_cast<const f4 *>(rrow[i] + sl * FX_KS);
-            }
-        };
-        // the barriers order the lanes' LDS accesses (a lane sums pieces
-        // that other lanes staged): the previous slab's reads, the writes,
-        // then the reads of the new slab; they leave the loads in flight
-        auto stage = [&](const FxSlab &b) {
-            lds_barrier();
-#pragma unroll
-            for (int i = 0; i < FX_LD; ++i) {
-                const int at = (4 * i + (lane >> 4)) * PS + (lane & 15);
-                xs[at] = b.x[i];
-                rs[at] = b.r[i];
-            }
-            lds_barrier();
-            // the refill of these registers stays after the writes: moved
-            // ahead, it would take other registers and the loop would copy
-            // them back at its back edge, waiting for every load in flight
-            __builtin_amdgcn_sched_barrier(0);
-        };
+        const double nrm = norms[row];
         double S = 0.0;
-        auto sum = [&]() {
-            if (act) {
 #pragma unroll
-                for (int q = 0; q < FX_PQ; ++q) {
-                    const f4 a = rs[lane * PS + q];
-                    const f4 b = xs[lane * PS + q];
+        for (int u = 0; u < FX_PC; ++u)
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const double prod = (double)a[c] * (double)b[c];
-                        S = S + prod;
-                    }
-                }
+            for (int c = 0; c < 4; ++c) S = __builtin_fma((double)r[u][c], (double)x[u][c], S);
+        for (int o = 32; o > 0; o >>= 1) S += __shfl_xor(S, o, 64);
+        const double eps = 1e-12 * nrm;
+        int code = exact_code(S + eps, nrm, j, d, bounds, athr, levels);
+        if (code != exact_code(S - eps, nrm, j, d, bounds, athr, levels) || !std::isfinite(S)) {
+            double T = 0.0;
+#pragma unroll
+            for (int u = 0; u < FX_PC; ++u) {
+                double p[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) p[c] = (double)r[u][c] * (double)x[u][c];
+                const int nl = pq - 64 * u < 64 ? pq - 64 * u : 64;
+                for (int l = 0; l < nl; ++l)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) T = T + __shfl(p[c], l, 64);
             }
-        };
-        // the loads are unconditional (clamped slab), so the waits count
-        // them exactly
-        FxSlab b0, b1;
-        load(0, b0);
-        __builtin_amdgcn_sched_barrier(0);   // b0's loads all ahead of b1's
-        load(ns > 1 ? 1 : 0, b1);
-        for (int sl = 0; sl < ns; sl += 2) {
-            stage(b0);
-            load(sl + 2 < ns ? sl + 2 : ns - 1, b0);
-            sum();
-            if (sl + 1 < ns) stage(b1);
-            load(sl + 3 < ns ? sl + 3 : ns - 1, b1);
-            if (sl + 1 < ns) sum();
+            code = exact_code(T, nrm, j, d, bounds, athr, levels);
         }
-        if (act) {
-            const int64_t row = row0 + (mf >> 7);
-            const int j = col0 + (int)(mf & 127);
-            codes_tmp[row * d + j] = (uint8_t)exact_code(S, norms[row], j, d, bounds, athr, levels);
-        }
+        if (lane == 0) codes_tmp[row * d + j] = (uint8_t)code;
     }
 }
 
 // The same recomputation for tiles with many flags: the tile's X rows and R
 // rows pass through LDS in slabs of KB (once per 512 flags), and each
-// thread adds its flag's products in k order from there.
+// thread adds its flag's products in k order from there.  List tiles have
+// `side` rows and columns (128 or 64).
 __global__ __launch_bounds__(GEMM_THREADS) void fixup_tile_kernel(
-    const float *__restrict__ X, int64_t m, const float *__restrict__ R, int d, int ncol,
+    const float *__restrict__ X, int64_t m, const float *__restrict__ R, int d, int side, int ncol,
     const double *__restrict__ bounds, const double *__restrict__ athr, int levels,
     const double *__restrict__ norms,
-    const uint32_t *__restrict__ flags, const unsigned int *__restrict__ tile_count,
+    const uint16_t *__restrict__ flags, const unsigned int *__restrict__ tile_count,
     uint8_t *__restrict__ codes_tmp) {
     __shared__ __attribute__((aligned(16))) float As[BM * LDS_STRIDE];
     __shared__ __attribute__((aligned(16))) float Bs[BN * LDS_STRIDE];
     const int tile = blockIdx.x;
-    const int64_t row0 = (int64_t)(tile / ncol) * BM;
-    const int col0 = (tile % ncol) * BN;
+    const int64_t row0 = (int64_t)(tile / ncol) * side;
+    const int col0 = (tile % ncol) * side;
     const unsigned int cnt = tile_count[tile];
     if (cnt == 0) return;
-    const uint32_t *tflags = flags + (int64_t)tile * (BM * BN);
+    const uint16_t *tflags = flags + (int64_t)tile * (side * side);
     const int tid = threadIdx.x;
     for (unsigned int e0 = 0; e0 < cnt; e0 += GEMM_THREADS) {
         const unsigned int e = e0 + tid;
@@ -686,6 +786,7 @@ __global__ __launch_bounds__(GEMM_THREADS) void fixup_tile_kernel(
                 const int q = tid + r * GEMM_THREADS;
                 const int row = q >> 3;
                 const int kq = (q & 7) * 4;
+                if (row >= side) continue;
                 const int64_t gr = row0 + row;
                 const f4 a = gr < m ? *reinterpret_cast<const f4 *>(X + gr * d + k0 + kq)
                                     : f4{0.f, 0.f, 0.f, 0.f};
@@ -727,7 +828,7 @@ __global__ __launch_bounds__(GEMM_THREADS) void fixup_tile_kernel(
 // definition in j order, and writes the chunk's 16 bytes to the canonical
 // and blocked layouts.  Every row of a chunk of rows is in flight at once,
 // so the sequential sums (one dependent float64 add per code) overlap; the
-// next chunk's codes are loaded while one is summed.
+// next 64 codes and more are loaded while as many are summed.
 template <int BITS>
 __global__ __launch_bounds__(64) void pack_rows_kernel(
     const uint8_t *__restrict__ codes_tmp, int64_t m, int d,
@@ -740,6 +841,7 @@ __global__ __launch_bounds__(64) void pack_rows_kernel(
     constexpr int CPC = 128 / BITS;   // codes per chunk
     constexpr int LPC = CPC / 16;     // 16-byte loads of one-byte codes per chunk
     constexpr int PER = 32 / BITS;    // codes per word
+    constexpr int G = LPC >= 4 ? 1 : 4 / LPC;
     __shared__ double csq_s[L];
     const int lane = threadIdx.x;
     for (int i = lane; i < L; i += 64) csq_s[i] = ysq ? 0.0 : cent_sq[i];
@@ -753,13 +855,16 @@ __global__ __launch_bounds__(64) void pack_rows_kernel(
     double h2 = 0.0;
     auto run = [&](auto cal_t) {
         constexpr bool CAL = decltype(cal_t)::value;
-        uint4 cur[LPC], nxt[LPC];
+        uint4 buf[2][G][LPC];   // a group of G chunks is loaded while one is summed
+        auto load = [&](int c0, uint4(&b)[G][LPC]) {
 #pragma unroll
-        for (int i = 0; i < LPC; ++i) cur[i] = src[i];
-        for (int ch = 0; ch < chunks; ++ch) {
-            const int cn = ch + 1 < chunks ? ch + 1 : ch;
+            for (int g = 0; g < G; ++g) {
+                const int c = c0 + g < chunks ? c0 + g : chunks - 1;
 #pragma unroll
-            for (int i = 0; i < LPC; ++i) nxt[i] = src[cn * LPC + i];
+                for (int i = 0; i < LPC; ++i) b[g][i] = src[c * LPC + i];
+            }
+        };
+        auto chunk = [&](int ch, const uint4(&cur)[LPC]) {
             uint32_t w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
             for (int t = 0; t < CPC; ++t) {
@@ -781,8 +886,20 @@ __global__ __launch_bounds__(64) void pack_rows_kernel(
                     for (int u = 0; u < 4; ++u) w[u] = rotl2(w[u]);
                 *reinterpret_cast<uint4 *>(bdst + ch * 1024) = make_uint4(w[0], w[1], w[2], w[3]);
             }
+        };
+        auto group = [&](int c0, const uint4(&b)[G][LPC]) {
 #pragma unroll
-            for (int i = 0; i < LPC; ++i) cur[i] = nxt[i];
+            for (int g = 0; g < G; ++g)
+                if (c0 + g < chunks) chunk(c0 + g, b[g]);
+        };
+        load(0, buf[0]);
+        for (int c0 = 0; c0 < chunks; c0 += 2 * G) {
+            load(c0 + G, buf[1]);
+            __builtin_amdgcn_sched_barrier(0);
+            group(c0, buf[0]);
+            load(c0 + 2 * G, buf[0]);
+            __builtin_amdgcn_sched_barrier(0);
+            group(c0 + G, buf[1]);
         }
     };
     if (ysq)
@@ -984,76 +1101,159 @@ __global__ __launch_bounds__(SPLIT_WAVES * 64) void rot_small_kernel(
 
 }  // namespace
 
-// Output tiles of one chunk of rows.
-size_t encode_tiles(int d) {
-    return (size_t)(kEncodeChunkRows / BM) * (size_t)((d + BN - 1) / BN);
+// Workspace of a chunk of `rows` rows.
+struct EncodeLayout {
+    size_t codes, planes, norms, inv, flags, counts, bounds, total;
+};
+static EncodeLayout encode_layout(int64_t rows, int d) {
+    EncodeLayout L{};
+    size_t o = 0;
+    auto take = [&](size_t bytes) {
+        const size_t at = o;
+        o += (bytes + 255) & ~(size_t)255;
+        return at;
+    };
+    const size_t r = (size_t)((rows + EgLarge::ROWS - 1) / EgLarge::ROWS * EgLarge::ROWS);
+    const size_t c = (size_t)((d + BN - 1) / BN * BN);
+    L.codes = take(r * (size_t)d);                // unpacked codes
+    L.planes = take(r * (size_t)d * 4);           // split rows
+    L.norms = take(r * sizeof(double));
+    L.inv = take(r * sizeof(float));
+    L.flags = take(r * c * sizeof(uint16_t));     // worst case: every coordinate
+    L.counts = take(r / EgSmall::SIDE * (c / EgSmall::SIDE) * sizeof(unsigned int));
+    L.bounds = take(255 * sizeof(double) + 256 * sizeof(double));   // bounds, cent_sq
+    L.total = o;
+    return L;
 }
 
-size_t encode_workspace_bytes(int d) {
-    const size_t rows = kEncodeChunkRows;
-    size_t b = 0;
-    b += rows * (size_t)d;                    // unpacked codes
-    b = (b + 255) & ~(size_t)255;
-    b += rows * sizeof(double);               // norms
-    b = (b + 255) & ~(size_t)255;
-    b += encode_tiles(d) * BM * BN * sizeof(uint32_t);   // flags (worst case: every coordinate)
-    b = (b + 255) & ~(size_t)255;
-    b += encode_tiles(d) * sizeof(unsigned int);          // flags per tile
-    b = (b + 255) & ~(size_t)255;
-    b += 255 * sizeof(double) + 256 * sizeof(double);   // bounds, cent_sq
-    b = (b + 255) & ~(size_t)255;
-    return b;
+// Rows of the next chunk of n: a last chunk of few rows, which would leave
+// most compute units idle through five launches (113 us for 1,696 rows at
+// d = 1536, 34 a thousand for full ones), joins the one before.
+static int64_t chunk_rows(int64_t n) {
+    return n <= kEncodeChunkRows + kEncodeChunkSlack ? n : kEncodeChunkRows;
 }
 
-hipError_t encode_rows(const float *X, int64_t n, int d, const float *R,
+// Rows that any chunk of n holds at most.
+static int64_t layout_rows(int64_t n) {
+    return n <= kEncodeChunkRows ? n : kEncodeChunkRows + kEncodeChunkSlack;
+}
+
+size_t encode_workspace_bytes(int64_t n, int d) {
+    return encode_layout(layout_rows(n), d).total;
+}
+
+size_t split_rotation_bytes(int d) { return (size_t)d * d * 4; }
+
+hipError_t split_rotation(const float *R, int d, void *planes, hipStream_t stream) {
+    const int64_t items = (int64_t)d * (d / 8);
+    hipLaunchKernelGGL(split_rotation_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, stream, R, d,
+                       static_cast<uint4 *>(planes));
+    return hipGetLastError();
+}
+
+// Outputs of a chunk up to which the small tiles are faster: 257, 1,696 and
+// 4,096 rows at d = 1536 take 25, 53 and 106 us with small tiles, 56, 62 and
+// 92 with large ones.
+constexpr int64_t kEncodeSmallOutputs = 3 << 20;
+
+// The tables of codebooks of up to 16 levels travel as kernel arguments (a
+// copy from pageable host memory costs the stream about 10 us each), with
+// the status word's reset.
+struct SmallTables {
+    double bounds[16], cent_sq[16];
+};
+__global__ void small_tables_kernel(SmallTables t, double *bounds, double *cent_sq, int *status) {
+    const int i = threadIdx.x;
+    if (i < 16) {
+        bounds[i] = t.bounds[i];
+        cent_sq[i] = t.cent_sq[i];
+    }
+    if (i == 0) *status = 0;
+}
+
+template <int TM, int TN, int WR, int WC, int ST>
+static hipError_t launch_encode_gemm(const uint4 *Xp, int64_t m, const uint4 *Rp, int d, const QuantArgs &qa,
+                                     hipStream_t stream) {
+    using S = EgShape<TM, TN, WR, WC, ST>;
+    static bool attr = false;
+    if (!attr) {
+        const hipError_t e = hipFuncSetAttribute((const void *)encode_gemm<TM, TN, WR, WC, ST>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::lds);
+        if (e != hipSuccess) return e;
+        attr = true;
+    }
+    const int nrt = (int)((m + S::ROWS - 1) / S::ROWS);
+    const int ncol = (d + S::COLS - 1) / S::COLS;
+    hipLaunchKernelGGL((encode_gemm<TM, TN, WR, WC, ST>), dim3((nrt + 7) / 8 * 8 * ncol), dim3(S::THREADS), S::lds,
+                       stream, Xp, m, Rp, d, nrt, qa);
+    return hipGetLastError();
+}
+
+hipError_t encode_rows(const float *X, int64_t n, int d, const float *R, const void *Rsplit,
                        const CodebookDev &cb, const EncodeOut &out, void *ws,
                        int *status_dev, hipStream_t stream, const CalibDev &calib) {
-    const size_t rows = kEncodeChunkRows;
+    const EncodeLayout L = encode_layout(layout_rows(n), d);
     uint8_t *p = static_cast<uint8_t *>(ws);
-    uint8_t *codes_tmp = p;
-    p += (rows * (size_t)d + 255) & ~(size_t)255;
-    double *norms = reinterpret_cast<double *>(p);
-    p += (rows * sizeof(double) + 255) & ~(size_t)255;
-    uint32_t *flags = reinterpret_cast<uint32_t *>(p);
-    p += (encode_tiles(d) * BM * BN * sizeof(uint32_t) + 255) & ~(size_t)255;
-    unsigned int *tile_count = reinterpret_cast<unsigned int *>(p);
-    p += (encode_tiles(d) * sizeof(unsigned int) + 255) & ~(size_t)255;
-    double *bounds = reinterpret_cast<double *>(p);
+    uint8_t *codes_tmp = p + L.codes;
+    uint4 *planes = reinterpret_cast<uint4 *>(p + L.planes);
+    double *norms = reinterpret_cast<double *>(p + L.norms);
+    float *inv = reinterpret_cast<float *>(p + L.inv);
+    uint16_t *flags = reinterpret_cast<uint16_t *>(p + L.flags);
+    unsigned int *tile_count = reinterpret_cast<unsigned int *>(p + L.counts);
+    double *bounds = reinterpret_cast<double *>(p + L.bounds);
     double *cent_sq = bounds + 255;
 
-    hipError_t e = hipMemcpyAsync(bounds, cb.bounds, sizeof(double) * (cb.levels - 1),
-                                  hipMemcpyHostToDevice, stream);
-    if (e != hipSuccess) return e;
-    e = hipMemcpyAsync(cent_sq, cb.cent_sq, sizeof(double) * cb.levels,
-                       hipMemcpyHostToDevice, stream);
+    hipError_t e;
+    if (cb.levels <= 16) {
+        SmallTables t{};
+        std::copy(cb.bounds, cb.bounds + cb.levels - 1, t.bounds);
+        std::copy(cb.cent_sq, cb.cent_sq + cb.levels, t.cent_sq);
+        hipLaunchKernelGGL(small_tables_kernel, dim3(1), dim3(64), 0, stream, t, bounds, cent_sq, status_dev);
+        e = hipGetLastError();
+    } else {
+        e = hipMemsetAsync(status_dev, 0, sizeof(int), stream);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(bounds, cb.bounds, sizeof(double) * (cb.levels - 1), hipMemcpyHostToDevice, stream);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(cent_sq, cb.cent_sq, sizeof(double) * cb.levels, hipMemcpyHostToDevice, stream);
+    }
     if (e != hipSuccess) return e;
 
     const int chunks = chunks_per_vector(d, cb.bits);
-    const int ncol = (d + BN - 1) / BN;
-    for (int64_t r0 = 0; r0 < n; r0 += rows) {
-        const int64_t m = (n - r0) < (int64_t)rows ? (n - r0) : (int64_t)rows;
-        const int nrt = (int)((m + BM - 1) / BM);
-        const int groups = (nrt + 7) / 8;
-        // every output tile of the chunk writes its flag count
-        QuantArgs qa{bounds, calib.athr, cb.levels, codes_tmp, norms, flags, tile_count, status_dev};
-        // one wave per 64 rows, spread over the CUs
-        hipLaunchKernelGGL(row_norm_kernel, dim3((unsigned)((m + 63) / 64)), dim3(64), 0, stream,
-                           X + r0 * d, m, d, norms, status_dev);
+    const size_t split_lds = (size_t)SR_ROWS * (d + 4) * sizeof(float);
+    static bool attr = false;
+    if (!attr) {
+        e = hipFuncSetAttribute((const void *)split_rows_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                SR_ROWS * (2048 + 4) * (int)sizeof(float));
+        if (e != hipSuccess) return e;
+        attr = true;
+    }
+    for (int64_t r0 = 0, m; r0 < n; r0 += m) {
+        m = chunk_rows(n - r0);
+        // every list tile of the chunk's rows gets its flag count
+        QuantArgs qa{bounds, calib.athr, cb.levels, codes_tmp, inv, (float)tau_rel(d),
+                     (cb.bounds[cb.levels - 2] - cb.bounds[0]) / EG_BINS, flags, tile_count};
+        hipLaunchKernelGGL(split_rows_kernel, dim3((unsigned)((m + 31) / 32 * (32 / SR_ROWS))), dim3(SR_THREADS),
+                           split_lds, stream, X + r0 * d, m, d, planes, norms, inv, status_dev);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(encode_gemm, dim3(groups * 8 * ncol), dim3(GEMM_THREADS), 0,
-                           stream, X + r0 * d, m, R, d, nrt, qa);
-        e = hipGetLastError();
+        const bool large = m * (int64_t)d > kEncodeSmallOutputs;
+        const int side = large ? EgLarge::SIDE : EgSmall::SIDE;
+        const uint4 *Rp = static_cast<const uint4 *>(Rsplit);
+        e = large ? launch_encode_gemm<2, 2, 2, 2, 4>(planes, m, Rp, d, qa, stream)
+                  : launch_encode_gemm<1, 1, 2, 2, 6>(planes, m, Rp, d, qa, stream);
         if (e != hipSuccess) return e;
-        // 8-bit codes flag about 2% of coordinates (thresholds ~4e-4 apart
+        const int ncol = (d + side - 1) / side;
+        const int nrow = (int)((m + side - 1) / side);
+        // 8-bit codes flag about 3% of coordinates (thresholds ~4e-4 apart
         // at d = 1536): tiles then share their staged rows
         if (cb.levels > 16)
-            hipLaunchKernelGGL(fixup_tile_kernel, dim3(nrt * ncol), dim3(GEMM_THREADS), 0, stream,
-                               X + r0 * d, m, R, d, ncol, bounds, calib.athr, cb.levels, norms,
+            hipLaunchKernelGGL(fixup_tile_kernel, dim3(nrow * ncol), dim3(GEMM_THREADS), 0, stream,
+                               X + r0 * d, m, R, d, side, ncol, bounds, calib.athr, cb.levels, norms,
                                flags, tile_count, codes_tmp);
         else
-            hipLaunchKernelGGL(fixup_batch_kernel, dim3(nrt * ncol), dim3(64), 0, stream, X + r0 * d,
-                               R, d, ncol, bounds, calib.athr, cb.levels, norms, flags, tile_count,
+            hipLaunchKernelGGL(fixup_flag_kernel, dim3((nrow + 7) / 8 * 8 * ncol), dim3(FX_WAVES * 64), 0, stream,
+                               X + r0 * d, R, d, side, nrow, ncol, bounds, calib.athr, cb.levels, norms, flags, tile_count,
                                codes_tmp);
         e = hipGetLastError();
         if (e != hipSuccess) return e;

@@ -20,7 +20,12 @@ struct CodebookDev {
 // ------------------------------------------------------------------ encode
 // Rows per encode chunk and the workspace it needs.
 constexpr int kEncodeChunkRows = 32768;
-size_t encode_workspace_bytes(int d);
+constexpr int kEncodeChunkSlack = 4096;   // more rows that the last chunk may take
+size_t encode_workspace_bytes(int64_t n, int d);
+// The rotation's float16 parts in the encoder's operand order, made once
+// from R [d][d] on the device.
+size_t split_rotation_bytes(int d);
+hipError_t split_rotation(const float *R, int d, void *planes, hipStream_t stream);
 
 // Output layout selector for the encode pipeline.
 struct EncodeOut {
@@ -31,9 +36,9 @@ struct EncodeOut {
     int64_t base = 0;               // index position of row 0 (blocked only)
 };
 
-// Encodes X [n][d] (float32, row-major) with R [d][d] on `stream`.
-// `ws` must hold encode_workspace_bytes(d); `status_dev` is an int32 that the
-// kernels set non-zero on a non-finite input.
+// Encodes X [n][d] (float32, row-major) with R [d][d] and its parts on
+// `stream`.  `ws` must hold encode_workspace_bytes(n, d); `status_dev` is an int32 that the
+// kernels set to zero, or non-zero on a non-finite input.
 // TQ+ calibration tables on the device (null: plain TurboQuant):
 // athr [(levels-1)][d] per-coordinate thresholds mu_j + kappa_j t_i and ysq
 // [d][levels] squares of the reconstructions mu_j + kappa_j c_c (float64).
@@ -42,7 +47,7 @@ struct CalibDev {
     const double *ysq = nullptr;
 };
 
-hipError_t encode_rows(const float *X, int64_t n, int d, const float *R,
+hipError_t encode_rows(const float *X, int64_t n, int d, const float *R, const void *Rsplit,
                        const CodebookDev &cb, const EncodeOut &out, void *ws,
                        int *status_dev, hipStream_t stream,
                        const CalibDev &calib = CalibDev());

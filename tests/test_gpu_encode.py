@@ -182,3 +182,47 @@ def test_codes_of_rows_built_on_thresholds(rot_pair, bits):
     print("coordinates within 1e-15 of a threshold: %d" % int((gap <= 1e-15).sum()), flush=True)
     assert_codes_equal(codes.cpu().numpy(), c_or, bits)
     assert_scales_close(scales.cpu().numpy(), s_or)
+
+
+@pytest.fixture(scope="module")
+def edge_rows(rot_pair):
+    """2,200 rows with special ones among them, and the oracle's codes."""
+    _, R32 = rot_pair
+    rng = np.random.default_rng(77)
+    X = rng.standard_normal((2200, D)).astype(np.float32)
+    X[0] = 0
+    X[30, :] = 0
+    X[30, 11] = -3.0                      # the whole norm in one coordinate
+    X[63] *= np.float32(2.0) ** -130      # subnormal coordinates
+    X[64] *= np.float32(1e37)
+    X[127, 1:] *= np.float32(1e-12)       # parts far below the row's largest
+    X[2047] = np.where(rng.random(D) < 0.5, np.float32(2.0) ** 15, np.float32(2.0) ** -15)
+    X[2048] = np.float32(65504.0)
+    cb = tq.Codebook(D, 4)
+    c_or, _, s_or = oracle.encode(X, R32, oracle_tables(cb))
+    return X, cb, c_or, s_or
+
+
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 64, 65, 129, 2047, 2048, 2049, 2200])
+def test_codes_at_the_edges_of_tiles(edge_rows, rot_pair, n):
+    """Row counts around the panels (32), the small and large tiles (64, 128)
+    and the switch between them (2,048 rows at d = 1536)."""
+    X, cb, c_or, s_or = edge_rows
+    print("rotate_quantize edges n=%d" % n, flush=True)
+    codes, scales = tq.rotate_quantize(cb, rot_pair[0], torch.from_numpy(X[:n]).cuda())
+    assert_codes_equal(codes.cpu().numpy(), c_or[:n], 4)
+    assert_scales_close(scales.cpu().numpy(), s_or[:n])
+
+
+@pytest.mark.parametrize("n", [32769, 36864, 36865])
+def test_codes_do_not_depend_on_the_chunks(n):
+    """Rows are encoded in chunks of 32,768; a last chunk of at most 4,096
+    rows joins the one before."""
+    print("rotate_quantize chunks n=%d" % n, flush=True)
+    d = 64
+    rot, cb = tq.Rotation(d, 3), tq.Codebook(d, 4)
+    X = torch.from_numpy(np.random.default_rng(n).standard_normal((n, d)).astype(np.float32)).cuda()
+    codes, scales = tq.rotate_quantize(cb, rot, X)
+    for a in range(0, n, 5000):
+        c, s = tq.rotate_quantize(cb, rot, X[a:a + 5000].contiguous())
+        assert torch.equal(c, codes[a:a + 5000]) and torch.equal(s, scales[a:a + 5000]), a
