@@ -212,10 +212,17 @@ struct Gate {
     float scan_us, block_us;   // scan: per query, per block
     float pass_us, read_us;    // batched: per pass, per union block
 };
-__device__ inline bool scan_is_faster(const Gate &g, int nqt) {
+// tile: of the group (counts per tile), nqt: its queries.
+__device__ inline bool scan_is_faster(const Gate &g, int tile, int nqt) {
     if (!g.counts) return false;
-    return (float)nqt * g.scan_us + (float)g.counts[1] * (float)kSampleB * g.block_us <
-           g.pass_us + (float)g.counts[0] * g.read_us;
+    const int *c = g.counts + 2 * tile;
+    return (float)nqt * g.scan_us + (float)c[1] * (float)kSampleB * g.block_us <
+           g.pass_us + (float)c[0] * g.read_us;
+}
+// The same for query q of a launch of nqt queries in passes of tq queries.
+__device__ inline bool scan_is_faster_for(const Gate &g, int q, int nqt, int tq) {
+    const int t = q / tq;
+    return scan_is_faster(g, t, nqt - t * tq < tq ? nqt - t * tq : tq);
 }
 
 struct FilterParams {
@@ -229,6 +236,15 @@ struct FilterParams {
     int *counts;               // see Gate; zero at launch
     int *list;                 // tiles: union blocks (order not fixed), or null
     uint16_t *bmax;            // tiles: [32][nblk], -inf for blocks that are not listed
+    // Tile blockIdx.y of a group: its queries and its part of every output.
+    __device__ void to_tile(int t) {
+        if (allow) allow += (int64_t)t * kTile * W;
+        nqt = nqt - t * kTile < kTile ? nqt - t * kTile : kTile;
+        tmask += (int64_t)t * 64 * W * words;
+        counts += 2 * t;
+        list += t * nblk;
+        bmax += (int64_t)t * kTile * nblk;
+    }
 };
 
 // Workgroups of one thread per (tenant, mask word), then of one thread per
@@ -242,6 +258,7 @@ __global__ __launch_bounds__(FK_THREADS) void filter_kernel(FilterParams p) {
     __shared__ uint64_t sum_s[FK_SAMPLES * 64];      // [sampled block][W]
     __shared__ unsigned long long any_s[64];         // union of the allowlists (W <= 64)
     const int tid = threadIdx.x, lane = tid & 63, W = p.W;
+    if (p.list) p.to_tile(blockIdx.y);
     const int mask_items = 64 * W * p.words;
     const int mask_wgs = (mask_items + FK_THREADS - 1) / FK_THREADS;
     if ((int)blockIdx.x < mask_wgs) {
@@ -322,16 +339,28 @@ struct ScoreParams {
     const float *cents;        // 2^b levels
     _Float16 *out;             // [kTile][npad] approximate scores / norm (rows >= nqt: 0)
     _Float16 *bmax;            // [kTile][nblk] per-block maximum of out (vectors < n)
-    int *tickets;              // [grid * kTicketStride] block ticket counters, zero at launch
+    int *tickets;              // [workgroup * kTicketStride] block ticket counters, zero at launch
     int64_t n, nblk, npad;
     int d, chunks, nqt;
+    int tiles;                 // of the group; the arrays above and below hold one part per tile
     // filtered tiles
     const int *list;           // blocks to score, counts[0] of them
     const int *counts;
     const uint32_t *tmask;     // [tenant] queries that admit it
     const uint16_t *tenants;
     const uint64_t *live;      // [nblk] or null
+    int W;
     Gate gate;
+    __device__ void to_tile(int t) {
+        q16 += (int64_t)t * kTile * d;
+        info += t * kTile;
+        out += (int64_t)t * kTile * npad;
+        bmax += (int64_t)t * kTile * nblk;
+        nqt = nqt - t * kTile < kTile ? nqt - t * kTile : kTile;
+        list += t * nblk;
+        counts += 2 * t;
+        tmask += (int64_t)t * 64 * W;
+    }
 };
 
 // Float16 centroids of the 8 4-bit fields of a stored word w (the canonical
@@ -513,9 +542,18 @@ __global__ __launch_bounds__(MF_THREADS) void mfma_scores_kernel(ScoreParams p) 
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int G = gridDim.x, g = blockIdx.x;
+    // G workgroups per tile; the tiles' workgroups of one share of the codes
+    // are 8 apart, on one XCD, where G allows
+    const int G = gridDim.x / p.tiles;
+    int g = blockIdx.x / p.tiles, tile = blockIdx.x % p.tiles;
+    if (G % 8 == 0) {
+        const int r = blockIdx.x >> 3;
+        tile = r % p.tiles;
+        g = r / p.tiles * 8 + (blockIdx.x & 7);
+    }
+    p.to_tile(tile);
     const int CH = p.chunks;   // multiple of RING
-    if (FILT && scan_is_faster(p.gate, p.nqt)) return;
+    if (FILT && scan_is_faster(p.gate, tile, p.nqt)) return;
     const int64_t nb = FILT ? (int64_t)*p.counts : p.nblk;
     const int64_t gb0 = nb * g / G, gb1 = nb * (g + 1) / G;
     const int nbw = (int)(gb1 - gb0);
@@ -588,7 +626,7 @@ __global__ __launch_bounds__(MF_THREADS) void mfma_scores_kernel(ScoreParams p) 
     // leaves the wait-count pass unsure of the loads in flight, and it then
     // drains the chunk ring inside the chunk loop.
     const __amdgpu_buffer_rsrc_t trs =
-        __builtin_amdgcn_make_buffer_rsrc(p.tickets + g * kTicketStride, 0, 4, kBufferWord3);
+        __builtin_amdgcn_make_buffer_rsrc(p.tickets + (tile * G + g) * kTicketStride, 0, 4, kBufferWord3);
     auto take = [&]() {
         return __builtin_amdgcn_raw_ptr_buffer_atomic_add_i32(1, trs, lane == 0 ? 0 : 4, 0, 0);
     };
@@ -838,7 +876,7 @@ __global__ __launch_bounds__(BS_THREADS) void block_select_kernel(BlockSelParams
     __shared__ int list[kListMaxB];
     __shared__ int sh[8];
     const int q = blockIdx.x;
-    if (scan_is_faster(p.gate, p.nqt)) return;
+    if (scan_is_faster_for(p.gate, q, p.nqt, kTile)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int KC = p.KC, R = KC - 32;
     const uint16_t *bm = p.bmax + (int64_t)q * p.nblk;
@@ -1078,7 +1116,7 @@ struct RescoreParams {
     const uint64_t *allow;     // [nqt][W] or null
     int W;
     int q0;                    // the pass's first row
-    int nqt;
+    int nqt, tile_q;           // queries, and those of a tile or pass
     Gate gate;
 };
 
@@ -1131,7 +1169,7 @@ __global__ __launch_bounds__(kTableThreads) void rescore_kernel(RescoreParams p)
     int *run_i = reinterpret_cast<int *>(run_s + KC);
     int *sh = run_i + KC;                   // [0] valid count, [1] k-th exact score, [2] certified, [3] list slot
     const int q = blockIdx.x;
-    if (scan_is_faster(p.gate, p.nqt)) {
+    if (scan_is_faster_for(p.gate, q, p.nqt, p.tile_q)) {
         hand_over(p, q, sh + 3);
         return;
     }
@@ -1411,7 +1449,7 @@ __global__ __launch_bounds__(WD_THREADS) void wide_scores_kernel(WideParams p) {
     float *th = fq + QP;                                               // [QP]
     int *cnt = reinterpret_cast<int *>(th + QP);                       // [QP]
     float *cq = reinterpret_cast<float *>(cnt + QP);                   // [QP]
-    if (scan_is_faster(p.gate, p.nqt)) return;
+    if (scan_is_faster(p.gate, 0, p.nqt)) return;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: scalar branches
@@ -1802,7 +1840,7 @@ __global__ __launch_bounds__(PS_THREADS) void pilot_select_kernel(PilotParams p)
     __shared__ int hist[kHistCopies * kHistStride];
     __shared__ int sh[8];
     const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
-    if (scan_is_faster(p.gate, p.nqt)) return;
+    if (scan_is_faster(p.gate, 0, p.nqt)) return;
     const int npv = (int)p.npv;
     const float *row = p.pil + (int64_t)q * p.npv;
     const uint64_t *arow = p.allow ? p.allow + (int64_t)q * p.W : nullptr;
@@ -1903,7 +1941,7 @@ __global__ __launch_bounds__(PS_THREADS) void final_select_kernel(FinalParams p)
     __shared__ int hist[kHistCopies * kHistStride];
     __shared__ int sh[8];
     const int q = blockIdx.x, tid = threadIdx.x;
-    if (scan_is_faster(p.gate, p.nqt)) return;
+    if (scan_is_faster(p.gate, 0, p.nqt)) return;
     int *out = p.top_i + (int64_t)q * p.KC;
     __shared__ int goff[1025];                  // exclusive offsets of the workgroup lists
     __shared__ int wsum[PS_THREADS / 64];
@@ -2032,7 +2070,12 @@ void with_slots(int KC, Fn fn) {
     }
 }
 
+// Tiles of a group: as many as the queries need, at most kGroupTiles and
+// 256 MiB of scores (a tile of 1,000,000 vectors has 64 MiB).
+constexpr int kGroupTiles = 8;
+
 struct BatchLayout {
+    int tiles;
     size_t q16, info, approx, bmax, top_i, amin, state, tickets, count, rows, qc, tmask, list,
         qconst_c, allow_c, lut, total;
     // wide passes
@@ -2089,26 +2132,31 @@ BatchLayout batch_layout(const ScanShape &s, int64_t nq, int k, int grid) {
     BatchLayout L{};
     size_t o = align256((size_t)nq * s.d * sizeof(float));   // rotated queries
     const int64_t npad = approx_row(s);
+    // after wide passes at most kWideMinQ queries are left for tiles
+    const int64_t tile_q = wide_pass(s, nq, batch_candidates(k), grid) ? std::min<int64_t>(nq, kWideMinQ) : nq;
+    const int64_t need = (tile_q + kTile - 1) / kTile, fit = ((int64_t)256 << 20) / (kTile * npad * 2 + 1);
+    L.tiles = (int)std::max<int64_t>(1, std::min<int64_t>({need, fit, kGroupTiles, grid}));
+    const size_t gq = (size_t)L.tiles * kTile;   // queries of a group
     L.q16 = o;
-    o += align256((size_t)kTile * s.d * 2);
+    o += align256(gq * s.d * 2);
     L.info = o;
-    o += align256(kTile * sizeof(QInfo));
+    o += align256(gq * sizeof(QInfo));
     L.approx = o;
-    o += align256((size_t)kTile * npad * 2);
+    o += align256(gq * npad * 2);
     L.bmax = o;
-    o += align256((size_t)kTile * s.nblk * 2);
+    o += align256(gq * s.nblk * 2);
     L.top_i = o;
-    o += align256((size_t)kTile * kCandMax * 4);
+    o += align256(gq * kCandMax * 4);
     L.amin = o;
-    o += align256((size_t)kTile * 4);
+    o += align256(gq * 4);
     L.state = o;
-    o += align256((size_t)kTile * 4);
+    o += align256(gq * 4);
     L.tickets = o;
-    o += align256(((size_t)grid * kTicketStride + 2) * 4);   // ... and the filter counts
+    o += align256(((size_t)grid * kTicketStride + 2 * kGroupTiles) * 4);   // ... and the filter counts
     L.tmask = o;
-    o += align256((size_t)s.W * 64 * (kWideMaxQ / 32) * 4);
+    o += align256((size_t)s.W * 64 * (kWideMaxQ / 32) * 4);   // as many words for a group of 8 tiles
     L.list = o;
-    o += align256((size_t)s.nblk * 4);
+    o += align256((size_t)L.tiles * s.nblk * 4);
     L.count = o;
     o += align256(4);
     L.rows = o;
@@ -2323,14 +2371,14 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
     // path always runs the pass): the scan reads at about 5 TB/s, a tile too
     // (unions only), a wide pass multiplies 1.0 to 1.35 MB of codes a us
     const double block_bytes = s.chunks * 1024.0;
-    auto gate_of = [&](int QP) {
+    auto gate_of = [&](int QP, int tiles) {
         Gate g{};
         if (!allow || n_fallback) return g;
         g.counts = counts;
         g.scan_us = s.bits == 8 ? 30.f : 9.f;
         g.block_us = (float)(block_bytes / 5.0e6);
         if (QP == kTile) {
-            g.pass_us = s.bits == 8 ? 83.f : 58.f;
+            g.pass_us = (s.bits == 8 ? 83.f : 58.f) / tiles + (tiles > 1 ? 8.f : 0.f);
             g.read_us = g.block_us;
         } else {
             g.pass_us = (float)(230.0 + (double)s.nblk * block_bytes / (QP == 256 ? 1.0e6 : 1.35e6));
@@ -2353,11 +2401,13 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
             fp.bmax = reinterpret_cast<uint16_t *>(bmax);
         }
         const int64_t mask_wgs = (64 * (int64_t)s.W * fp.words + FK_THREADS - 1) / FK_THREADS;
-        hipLaunchKernelGGL(filter_kernel, dim3((unsigned)(mask_wgs + (s.nblk + FK_THREADS - 1) / FK_THREADS)),
+        const unsigned tiles = QP == kTile ? (nqt + kTile - 1) / kTile : 1;
+        hipLaunchKernelGGL(filter_kernel,
+                           dim3((unsigned)(mask_wgs + (s.nblk + FK_THREADS - 1) / FK_THREADS), tiles),
                            dim3(FK_THREADS), 0, stream, fp);
     };
     auto rescore = [&](int64_t q0, int nqt, const int *ti, const float *am, const int *st,
-                       const QInfo *qi, const Gate &gate) {
+                       const QInfo *qi, const Gate &gate, int tile_q) {
         RescoreParams rp{};
         rp.codes = reinterpret_cast<const uint4 *>(blocked);
         rp.scales = scales;
@@ -2380,6 +2430,7 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
         rp.W = s.W;
         rp.q0 = (int)q0;
         rp.nqt = nqt;
+        rp.tile_q = tile_q;
         rp.gate = gate;
         rp.d = s.d;
         rp.bits = s.bits;
@@ -2411,7 +2462,7 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
             float *wamin = reinterpret_cast<float *>(w8 + L.w_amin);
             int *wstate = reinterpret_cast<int *>(w8 + L.w_state);
             const uint64_t *allow_p = allow ? allow + q0 * s.W : nullptr;
-            const Gate gate = gate_of(QP);
+            const Gate gate = gate_of(QP, 1);
             hipLaunchKernelGGL(prep_kernel, dim3(nqt), dim3(SEL_THREADS), 0, stream,
                                Qrot + q0 * s.d, qconst ? qconst + q0 : nullptr, nqt, s.d, s.bits, smax,
                                cmax16, dmax, wq16, winfo,
@@ -2489,16 +2540,22 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
             hipLaunchKernelGGL(final_select_kernel, dim3(nqt), dim3(PS_THREADS),
                                (size_t)kFinalMax * 8, stream, fp);
             e = hipGetLastError();
-            if (e == hipSuccess) e = rescore(q0, nqt, wtop, wamin, wstate, winfo, gate);
+            if (e == hipSuccess) e = rescore(q0, nqt, wtop, wamin, wstate, winfo, gate, QP);
             if (e != hipSuccess) return e;
             q0 += nqt;
             continue;
         }
-        const int nqt = (int)std::min<int64_t>(nq - q0, kTile);
+        // a group of tiles
+        const int nqt = (int)std::min<int64_t>(nq - q0, (int64_t)L.tiles * kTile);
+        const int tiles = (nqt + kTile - 1) / kTile;
+        // its workgroups, as many for each tile: the tiles read the codes at
+        // the same time, one of them from HBM and the others from the caches
+        int per_tile = grid / tiles;
+        if (per_tile > 8) per_tile &= ~7;
         hipLaunchKernelGGL(prep_kernel, dim3(nqt), dim3(SEL_THREADS), 0, stream, Qrot + q0 * s.d,
                            qconst ? qconst + q0 : nullptr, nqt, s.d, s.bits, smax, cmax16, dmax, q16, info, tickets,
-                           grid * kTicketStride + 2, q0 == 0 ? count : nullptr);
-        const Gate gate = gate_of(kTile);
+                           grid * kTicketStride + 2 * kGroupTiles, q0 == 0 ? count : nullptr);
+        const Gate gate = gate_of(kTile, tiles);
         if (filtered) apply_filter(q0, nqt, kTile);
         ScoreParams sp{};
         sp.codes = reinterpret_cast<const uint4 *>(blocked);
@@ -2515,6 +2572,8 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
         sp.chunks = s.chunks;
         sp.nqt = nqt;
         sp.tickets = tickets;
+        sp.tiles = tiles;
+        sp.W = s.W;
         if (filtered) {
             sp.list = list;
             sp.counts = counts;
@@ -2523,7 +2582,7 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
             sp.live = live;
             sp.gate = gate;
         }
-        hipError_t e = launch_scores(s.bits, sp, grid, stream);
+        hipError_t e = launch_scores(s.bits, sp, per_tile * tiles, stream);
         if (e != hipSuccess) return e;
         BlockSelParams bp{};
         bp.approx = reinterpret_cast<const uint16_t *>(approx);
@@ -2539,7 +2598,7 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
         bp.gate = gate;
         hipLaunchKernelGGL(block_select_kernel, dim3(nqt), dim3(BS_THREADS), 0, stream, bp);
         e = hipGetLastError();
-        if (e == hipSuccess) e = rescore(q0, nqt, top_i, amin, state, info, gate);
+        if (e == hipSuccess) e = rescore(q0, nqt, top_i, amin, state, info, gate, kTile);
         if (e != hipSuccess) return e;
         q0 += nqt;
     }
