@@ -1099,6 +1099,75 @@ __global__ __launch_bounds__(SPLIT_WAVES * 64) void rot_small_kernel(
     }
 }
 
+// Y = X R^T for kSmallRows < m <= kMidRows rows, again with exactly the
+// arithmetic of rot_gemm (the same products in the same order per output).
+// Tiles of 32 x 32 outputs, four waves with a 16 x 16 block each, so that a few
+// hundred rows fill the chip: 256 rows at d = 1536 are 384 workgroups instead
+// of 24.  Slabs of 32 k come by direct global -> LDS loads into a ring of
+// RM_STAGES, four slabs ahead, one barrier per slab.  A 1 KiB piece holds 8
+// rows of 8 16-byte quads, quad q of row r at place q ^ r, so that a read of
+// one quad of 8 consecutive rows meets distinct banks.
+constexpr int kMidRows = 2048;
+constexpr int RM_STAGES = 6;
+constexpr int RM_STAGE_B = 8 * 1024;     // four pieces of X, four of R
+
+__global__ __launch_bounds__(256) void rot_mid_kernel(const float *__restrict__ X, int64_t m,
+                                                      const float *__restrict__ R, int d,
+                                                      float *__restrict__ Y) {
+    __shared__ __attribute__((aligned(1024))) char stg[RM_STAGES * RM_STAGE_B];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, g4 = lane >> 4;
+    const int wr = wave >> 1, wc = wave & 1;
+    const int64_t row0 = (int64_t)blockIdx.y * 32;
+    const int col0 = blockIdx.x * 32;
+    const int nslab = d / KB;   // even
+    // piece `wave` of X and of R: row 8 wave + lane / 8, quad (lane & 7) ^ (row & 7)
+    const int pr = 8 * wave + (lane >> 3), pq = (lane & 7) ^ (lane >> 3);
+    const int64_t xr = row0 + pr < m ? row0 + pr : m - 1;   // rows past m feed dropped outputs
+    const uint32_t xo = (uint32_t)((xr * d + pq * 4) * 4);
+    const uint32_t ro = (uint32_t)(((col0 + pr) * d + pq * 4) * 4);
+    const uint32_t stg_lds = (uint32_t)(uintptr_t)stg + wave * 1024;
+    int rq = 0, rq_st = 0;      // next slab to request (the last one again past the end), its stage
+    auto request = [&]() {
+        const int s = rq < nslab ? rq : nslab - 1;
+        lds_dma16_s(xo, X + s * KB, stg_lds + rq_st * RM_STAGE_B);
+        lds_dma16_s(ro, R + s * KB, stg_lds + rq_st * RM_STAGE_B + 4096);
+        ++rq;
+        rq_st = rq_st + 1 == RM_STAGES ? 0 : rq_st + 1;
+    };
+#pragma unroll
+    for (int i = 0; i < RM_STAGES - 1; ++i) request();
+    // this lane's quads of a slab: row 16 wr (or column 16 wc) + l16, quad 4 sub + g4
+    const char *ab = stg + (16 * wr + l16) * 128, *bb = stg + 4096 + (16 * wc + l16) * 128;
+    const int q0 = (g4 ^ (l16 & 7)) * 16, q1 = ((4 + g4) ^ (l16 & 7)) * 16;
+    double accd[4] = {0.0, 0.0, 0.0, 0.0};
+    int st = 0;
+    for (int s = 0; s < nslab; ++s) {
+        wait_vmem<(RM_STAGES - 2) * 2>();   // slab s, then everyone's
+        lds_barrier();                      // ... and every wave is past slab s - 1
+        request();                          // slab s + 5, into its stage
+        const char *A = ab + st * RM_STAGE_B, *B = bb + st * RM_STAGE_B;
+        const f4 a[2] = {*reinterpret_cast<const f4 *>(A + q0), *reinterpret_cast<const f4 *>(A + q1)};
+        const f4 b[2] = {*reinterpret_cast<const f4 *>(B + q0), *reinterpret_cast<const f4 *>(B + q1)};
+        f4 acc = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[sub][t], b[sub][t], acc, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) accd[v] += (double)acc[v];
+        st = st + 1 == RM_STAGES ? 0 : st + 1;
+    }
+    wait_vmem<0>();   // the slabs requested past the end
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int64_t gr = row0 + 16 * wr + 4 * g4 + v;
+        if (gr < m) Y[gr * d + col0 + 16 * wc + l16] = (float)accd[v];
+    }
+}
+
 }  // namespace
 
 // Workspace of a chunk of `rows` rows.
@@ -1309,6 +1378,11 @@ hipError_t rotate_rows_f32(const float *X, int64_t m, int d, const float *R, flo
         if (e != hipSuccess) return e;
     }
     if (m <= 0) return hipSuccess;
+    if (m <= kMidRows) {
+        hipLaunchKernelGGL(rot_mid_kernel, dim3((unsigned)(d / 32), (unsigned)((m + 31) / 32)), dim3(256), 0,
+                           stream, X, m, R, d, Y);
+        return hipGetLastError();
+    }
     const int ncol = (d + BN - 1) / BN;
     const int nrt = (int)((m + BM - 1) / BM);
     const int groups = (nrt + 7) / 8;

@@ -67,6 +67,17 @@ def test_query_rotation_does_not_depend_on_the_batch(d):
         assert torch.equal(part, full[a:b]), (a, b)
 
 
+@pytest.mark.parametrize("d", [1536, 64, 192, 2048])
+def test_query_rotation_by_every_kernel(d):
+    """Up to 64, up to 2,048 and more rows take kernels of their own."""
+    print("query rotation kernels d=%d" % d, flush=True)
+    rot = tq.Rotation(d, 9)
+    Q = torch.from_numpy(np.random.default_rng(d).standard_normal((2100, d)).astype(np.float32)).cuda()
+    full = tq.rotate_queries(rot, Q)
+    for n in [33, 64, 65, 96, 97, 2048]:
+        assert torch.equal(tq.rotate_queries(rot, Q[:n].contiguous()), full[:n]), n
+
+
 @pytest.mark.parametrize("bits", [4, 2, 8, 3, 1])
 def test_codes_bit_exact(small, rot_pair, bits):
     X, _ = small
