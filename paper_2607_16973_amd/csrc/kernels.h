@@ -130,6 +130,8 @@ struct ScanShape {
 // vector and selects per query.
 constexpr int kMaxTopK = 256;
 constexpr int kMaxK = 4096;
+// Workspace of the large-k selection, per query of a launch.
+constexpr size_t kSelectStateBytes = 98560;
 
 size_t lut_search_workspace_bytes(const ScanShape &s, int64_t nq, int k, int grid);
 // Which slots a search may return: tenant allowlists [nq][W] (null: every

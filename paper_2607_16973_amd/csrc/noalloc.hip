@@ -15,15 +15,18 @@
 #include <mutex>
 #include <string>
 
+#include "kernels.h"
 #include "tq_internal.h"
 
 namespace tq {
 namespace {
 
-constexpr size_t kScratchBytes = TQ_NOALLOC_SCRATCH_BYTES;
+// Searches with k > kMaxTopK may also use room for one query's selection
+// state, which does not count against the limit.
+constexpr size_t kArrayBytes = TQ_NOALLOC_SCRATCH_BYTES + kSelectStateBytes;
 constexpr int kMaxDevices = 64;
 
-static __device__ __align__(256) uint8_t scratch[kScratchBytes];
+static __device__ __align__(256) uint8_t scratch[kArrayBytes];
 
 std::mutex g_scratch_mu;
 void *g_scratch_ptr[kMaxDevices];   // scratch's address on each device
@@ -103,26 +106,27 @@ extern "C" tq_status tq_search_noalloc(const tq_index *idx, const float *Q_dev, 
                                "(it is uploaded by the first tq_index_add, tq_index_calibrate or "
                                "allocating search on the index)");
     // queries per tq_search_ex call whose workspace fits in the scratch array
+    const size_t room = k > kMaxTopK ? kArrayBytes : TQ_NOALLOC_SCRATCH_BYTES;
     size_t need = 0;
     st = tq_search_workspace_size(idx, 1, k, TQ_PATH_LUT, &need);
     if (st != TQ_OK) return st;
-    if (need > kScratchBytes)
+    if (need > room)
         return fail(TQ_EUNSUPPORTED, "tq_search_noalloc: one query needs " + std::to_string(need) +
                                          " bytes of scratch, more than the " +
-                                         std::to_string(kScratchBytes) + " the library holds");
+                                         std::to_string(room) + " the library holds");
     int64_t qb = nq;
     for (;;) {
         st = tq_search_workspace_size(idx, qb, k, TQ_PATH_LUT, &need);
         if (st != TQ_OK) return st;
-        if (need <= kScratchBytes) break;
-        const int64_t next = (int64_t)((double)qb * ((double)kScratchBytes / (double)need));
+        if (need <= room) break;
+        const int64_t next = (int64_t)((double)qb * ((double)room / (double)need));
         qb = next < qb ? (next > 1 ? next : 1) : qb - 1;
     }
     const int64_t words = (n_tenants + 63) / 64;
     for (int64_t q0 = 0; q0 < nq; q0 += qb) {
         const int64_t m = (nq - q0) < qb ? (nq - q0) : qb;
         st = tq_search_ex(idx, Q_dev + q0 * d, m, k, allow_dev ? allow_dev + q0 * words : nullptr,
-                          TQ_PATH_LUT, ws, kScratchBytes, ids_dev + q0 * k, scores_dev + q0 * k,
+                          TQ_PATH_LUT, ws, room, ids_dev + q0 * k, scores_dev + q0 * k,
                           stream);
         if (st != TQ_OK) return st;
     }

@@ -951,74 +951,206 @@ __global__ __launch_bounds__(256) void merge_kernel(const float *__restrict__ cs
 
 // ---------------------------------------------------------------- large k
 // Top k (kMaxK >= k > kMaxTopK) of a query's n scores by radix selection:
-// scores map to order-preserving unsigned keys (larger score, larger key);
-// three histogram passes over 11, 11 and 10 key bits find the key T of the
-// k-th best; the vectors with a larger key and, in id order, the first ones
-// with key T make up the k best (ties broken by id, as everywhere); a
-// bitonic sort in LDS orders them by (score descending, id ascending).
-// One workgroup of 1024 threads per query.  Entries of score -inf (vectors
-// the filter dropped) become padding (-1, -inf).
+// scores map to order-preserving unsigned keys (larger score, larger key).
+//  1. sel_count_kernel<0>, <1>: histograms of the top 12 key bits, then, within
+//     the k-th best key's class, of the next 12, by sel_parts workgroups per query
+//     (LDS histograms, added to the query's in memory).  The 24-bit prefix T
+//     of the k-th best key remains, and its rank within that class.
+//  2. sel_gather_kernel: the keys whose prefix is T or more go to the query's
+//     candidate list (at least k of them; few more than k unless many scores
+//     agree to 15 bits of their mantissa).
+//  3. sel_sort_kernel: a bitonic sort of the candidates in LDS by (score
+//     descending, id ascending), of which the first k are the result.  If
+//     the list overflowed (kSelCand), one workgroup selects over all scores
+//     instead, as follows: 8 more key bits find the exact k-th key, the
+//     vectors with a larger key and, in id order, the first ones equal to it
+//     make up the k best.
+// Entries of score -inf (vectors the filter dropped) are left out; missing
+// entries are padding (-1, -inf).  One workgroup per query for the three passes took 308 us for 4
+// queries of 200,000 scores, k = 1,000, on 4 of 256 compute units.
 constexpr int SEL_T = 1024;
+constexpr int kSelBits = 12;
+constexpr int kSelBins = 1 << kSelBits;
+constexpr int kSelCand = 2 * kMaxK;
+constexpr uint32_t kSelNone = 0x007FFFFFu;   // the key of -inf: dropped vectors, never a result
+
+// Selection state of a query.
+struct SelState {
+    uint64_t cand[kSelCand];      // (key << 32) | (0xFFFFFFFF - id)
+    uint32_t hist[2][kSelBins];
+    uint32_t prefix[2];           // after pass p: the class of the k-th key
+    uint32_t need[2];             // rank of the k-th key within the class
+    uint32_t ncand;
+    uint32_t k;                   // entries to find
+    uint32_t kk;                  // of which there are (scores that are not -inf)
+};
+
+static_assert(sizeof(SelState) <= kSelectStateBytes && kSelectStateBytes % 256 == 0, "the size that the workspace counts");
 
 __device__ inline uint32_t ukey(float f) { return (uint32_t)fkey(f) ^ 0x80000000u; }
 __device__ inline float unukey(uint32_t u) { return unfkey((int)(u ^ 0x80000000u)); }
 
-__global__ __launch_bounds__(SEL_T) void select_topk_kernel(const float *__restrict__ scores,
-                                                           int64_t n, int k,
-                                                           int64_t *__restrict__ ids_out,
-                                                           float *__restrict__ scores_out) {
-    __shared__ uint32_t hist[2048];
-    __shared__ uint64_t cand[kMaxK];          // (key << 32) | (0xFFFFFFFF - id)
+__global__ __launch_bounds__(SEL_T) void sel_clear_kernel(SelState *__restrict__ sel, int64_t n, int k) {
+    SelState &q = sel[blockIdx.x];
+    for (int i = threadIdx.x; i < 2 * kSelBins; i += SEL_T) (&q.hist[0][0])[i] = 0;
+    if (threadIdx.x == 0) {
+        q.ncand = 0;
+        q.k = (uint32_t)((int64_t)k < n ? k : n);
+    }
+}
+
+// Workgroups per query: two per compute unit over all queries, of at least
+// 4 rounds of their threads.
+int sel_parts(int64_t n, int64_t nq) {
+    const int64_t want = (512 + nq - 1) / nq, most = (n + 4 * SEL_T - 1) / (4 * SEL_T);
+    return (int)std::max<int64_t>(1, std::min(want, most));
+}
+
+// By one wave: of BINS bins in LDS, with need lowered to the number of keys
+// and returned in out[2], the bin b with (#keys above it) < need <= (#keys
+// from it on); out[0] = b, out[1] = need - #keys above; without keys BINS, 0.
+template <int BINS>
+__device__ inline void find_bin(const uint32_t *hist, uint32_t need, uint32_t *out) {
+    constexpr int PER = BINS / 64;
+    const int lane = threadIdx.x & 63;
+    uint32_t sum = 0;
+    for (int j = 0; j < PER; ++j) sum += hist[lane * PER + j];
+    uint32_t from = sum;   // keys in the bins of lanes >= this one
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t t = __shfl_down(from, o, 64);
+        if (lane + o < 64) from += t;
+    }
+    const uint32_t total = (uint32_t)__shfl((int)from, 0);
+    need = need < total ? need : total;
+    if (need == 0) {
+        if (lane == 0) {
+            out[0] = BINS;
+            out[1] = out[2] = 0;
+        }
+        return;
+    }
+    const uint64_t ge = __ballot(from >= need);
+    if (lane == 63 - __builtin_clzll(ge)) {
+        uint32_t above = from - sum;
+        int b = lane * PER + PER - 1;
+        for (; b > lane * PER; --b) {
+            if (above + hist[b] >= need) break;
+            above += hist[b];
+        }
+        out[0] = (uint32_t)b;
+        out[1] = need - above;
+        out[2] = need;
+    }
+}
+
+// The class of the k-th key after pass p, found by every workgroup from the
+// pass's counts (the launch order makes them complete; a last-workgroup
+// scheme inside the pass took 50 us for its device-wide fences); hist: room
+// for kSelBins counts.  Workgroup 0 of the query keeps it for the sort.
+__device__ inline uint32_t sel_class(SelState &q, int p, uint32_t *hist) {
+    __shared__ uint32_t out[3];
+    for (int b = threadIdx.x; b < kSelBins; b += SEL_T) hist[b] = q.hist[p][b];
+    __syncthreads();
+    if (threadIdx.x < 64) find_bin<kSelBins>(hist, p ? q.need[0] : q.k, out);
+    __syncthreads();
+    const uint32_t c = p ? q.prefix[0] << kSelBits | out[0] : out[0];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        q.prefix[p] = c;
+        q.need[p] = out[1];
+        if (p == 0) q.kk = out[2];
+    }
+    return c;
+}
+
+template <int PASS>
+__global__ __launch_bounds__(SEL_T) void sel_count_kernel(const float *__restrict__ scores, int64_t n,
+                                                         SelState *sel) {
+    __shared__ uint32_t hist[kSelBins];
+    SelState &q = sel[blockIdx.y];
+    const int tid = threadIdx.x;
+    const float *sc = scores + (int64_t)blockIdx.y * n;
+    constexpr int SHIFT = 32 - kSelBits * (PASS + 1);
+    const uint32_t prefix = PASS ? sel_class(q, 0, hist) : 0u;
+    for (int b = tid; b < kSelBins; b += SEL_T) hist[b] = 0;
+    __syncthreads();
+    // the first pass's keys mostly share a few bins: the lanes of a wave that
+    // agree with its first one add once
+    for (int64_t i0 = (int64_t)blockIdx.x * SEL_T; i0 < n; i0 += (int64_t)gridDim.x * SEL_T) {
+        const int64_t i = i0 + tid;
+        const uint32_t u = i < n ? ukey(sc[i]) : 0u;
+        const bool act = i < n && u > kSelNone && (PASS == 0 || u >> (32 - kSelBits) == prefix);
+        const uint32_t b = (u >> SHIFT) & (kSelBins - 1);
+        const uint64_t live = __ballot(act);
+        if (!live) continue;
+        const int leader = __builtin_ctzll(live);
+        const bool same = act && b == (uint32_t)__shfl((int)b, leader);
+        const uint64_t sm = __ballot(same);
+        if ((tid & 63) == leader) atomicAdd(&hist[b], (uint32_t)__popcll(sm));
+        else if (act && !same) atomicAdd(&hist[b], 1u);
+    }
+    __syncthreads();
+    for (int b = tid; b < kSelBins; b += SEL_T)
+        if (hist[b]) atomicAdd(&q.hist[PASS][b], hist[b]);
+}
+
+__global__ __launch_bounds__(SEL_T) void sel_gather_kernel(const float *__restrict__ scores, int64_t n,
+                                                          SelState *sel) {
+    SelState &q = sel[blockIdx.y];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const float *sc = scores + (int64_t)blockIdx.y * n;
+    __shared__ uint32_t hist[kSelBins];
+    const uint32_t T = sel_class(q, 1, hist);
+    for (int64_t i0 = (int64_t)blockIdx.x * SEL_T; i0 < n; i0 += (int64_t)gridDim.x * SEL_T) {
+        const int64_t i = i0 + tid;
+        const uint32_t u = i < n ? ukey(sc[i]) : 0u;
+        const bool take = i < n && u > kSelNone && u >> (32 - 2 * kSelBits) >= T;
+        const uint64_t m = __ballot(take);
+        if (!m) continue;
+        uint32_t at = 0;
+        if (lane == 0) at = atomicAdd(&q.ncand, (uint32_t)__popcll(m));
+        at = __shfl((int)at, 0) + __popcll(m & ((1ull << lane) - 1));
+        if (take && at < kSelCand) q.cand[at] = ((uint64_t)u << 32) | (0xFFFFFFFFu - (uint32_t)i);
+    }
+}
+
+__global__ __launch_bounds__(SEL_T) void sel_sort_kernel(const float *__restrict__ scores, int64_t n, int k,
+                                                        const SelState *__restrict__ sel,
+                                                        int64_t *__restrict__ ids_out,
+                                                        float *__restrict__ scores_out) {
+    __shared__ uint64_t cand[kSelCand];
+    __shared__ uint32_t hist[256];
     __shared__ int wave_eq[SEL_T / 64];
-    __shared__ uint32_t sel[4];               // [0] prefix, [1] still needed, [2] candidates
+    __shared__ uint32_t out[3];
+    const SelState &q = sel[blockIdx.x];
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const float *sc = scores + (int64_t)blockIdx.x * n;
-    const int kk = (int64_t)k < n ? k : (int)n;       // entries to return
-    uint32_t prefix = 0, pmask = 0;
-    uint32_t need = (uint32_t)kk;
-    if (kk > 0) {
-        for (int pass = 0; pass < 3; ++pass) {
-            const int shift = pass == 0 ? 21 : (pass == 1 ? 10 : 0);
-            const int bins = pass == 2 ? 1024 : 2048;
-            for (int b = tid; b < 2048; b += SEL_T) hist[b] = 0;
-            __syncthreads();
-            for (int64_t i = tid; i < n; i += SEL_T) {
-                const uint32_t u = ukey(sc[i]);
-                if ((u & pmask) == prefix) atomicAdd(&hist[(u >> shift) & (bins - 1)], 1u);
-            }
-            __syncthreads();
-            if (tid == 0) {
-                // bin of the need-th largest key within the prefix class
-                uint32_t above = 0;
-                int b = bins - 1;
-                for (; b > 0; --b) {
-                    if (above + hist[b] >= need) break;
-                    above += hist[b];
-                }
-                sel[0] = prefix | ((uint32_t)b << shift);
-                sel[1] = need - above;
-            }
-            __syncthreads();
-            prefix = sel[0];
-            need = sel[1];
-            pmask |= (uint32_t)(bins - 1) << shift;
-            __syncthreads();
+    const int kk = (int)q.kk;
+    int nc = (int)q.ncand;
+    if (nc <= kSelCand) {
+        for (int e = tid; e < nc; e += SEL_T) cand[e] = q.cand[e];
+    } else {
+        // the last 8 bits of the k-th key, from the keys of its class
+        for (int b = tid; b < 256; b += SEL_T) hist[b] = 0;
+        __syncthreads();
+        for (int64_t i = tid; i < n; i += SEL_T) {
+            const uint32_t u = ukey(sc[i]);
+            if (u >> 8 == q.prefix[1]) atomicAdd(&hist[u & 255u], 1u);
         }
-    }
-    // prefix is now the key T of the kk-th best; `need` of the keys equal to
-    // T are taken, the ones with the smallest ids
-    const uint32_t T = prefix;
-    const int64_t len = ((n + SEL_T / 64 - 1) / (SEL_T / 64) + 63) / 64 * 64;   // per wave
-    const int64_t w0 = wave * len, w1 = w0 + len < n ? w0 + len : n;
-    int eq = 0;
-    if (kk > 0)
+        __syncthreads();
+        if (wave == 0) find_bin<256>(hist, q.need[1], out);
+        __syncthreads();
+        const uint32_t T = q.prefix[1] << 8 | out[0];
+        const int need = (int)out[1];   // of the keys equal to T, the ones with the smallest ids
+        __syncthreads();
+        if (tid == 0) out[0] = 0;
+        const int64_t len = ((n + SEL_T / 64 - 1) / (SEL_T / 64) + 63) / 64 * 64;   // per wave
+        const int64_t w0 = wave * len, w1 = w0 + len < n ? w0 + len : n;
+        int eq = 0;
         for (int64_t i = w0 + lane; i < w1; i += 64) eq += ukey(sc[i]) == T;
-    for (int m = 32; m > 0; m >>= 1) eq += __shfl_xor(eq, m, 64);
-    if (lane == 0) wave_eq[wave] = eq;
-    if (tid == 0) sel[2] = 0;
-    __syncthreads();
-    if (kk > 0) {
+        for (int m = 32; m > 0; m >>= 1) eq += __shfl_xor(eq, m, 64);
+        if (lane == 0) wave_eq[wave] = eq;
+        __syncthreads();
         int before = 0;
         for (int w = 0; w < wave; ++w) before += wave_eq[w];
         for (int64_t i0 = w0; i0 < w1; i0 += 64) {
@@ -1027,19 +1159,17 @@ __global__ __launch_bounds__(SEL_T) void select_topk_kernel(const float *__restr
             const bool is_eq = i < w1 && u == T;
             const uint64_t m = __ballot(is_eq);
             const int rank = before + __popcll(m & ((1ull << lane) - 1));
-            const bool take = (i < w1 && u > T) || (is_eq && rank < (int)need);
-            if (take) {
-                const uint32_t at = atomicAdd(&sel[2], 1u);
-                cand[at] = ((uint64_t)u << 32) | (0xFFFFFFFFu - (uint32_t)i);
-            }
+            const bool take = (i < w1 && u > T) || (is_eq && rank < need);
+            if (take) cand[atomicAdd(&out[0], 1u)] = ((uint64_t)u << 32) | (0xFFFFFFFFu - (uint32_t)i);
             before += __popcll(m);
         }
+        nc = kk;
     }
     __syncthreads();
     // pad to a power of two and sort descending
     int P = 1;
-    while (P < kk) P <<= 1;
-    for (int e = kk + tid; e < P; e += SEL_T) cand[e] = 0;
+    while (P < nc) P <<= 1;
+    for (int e = nc + tid; e < P; e += SEL_T) cand[e] = 0;
     __syncthreads();
     for (int size = 2; size <= P; size <<= 1) {
         for (int stride = size >> 1; stride > 0; stride >>= 1) {
@@ -1229,21 +1359,26 @@ int device_cu_count() {
     return cus;
 }
 
-// Queries per launch of the large-k path: their scores (n floats each) fill
-// at most 256 MiB.
+// Queries per launch of the large-k path: their scores (n floats each) and
+// selection states fill at most 256 MiB.
 int64_t all_scores_chunk(const ScanShape &s, int64_t nq) {
-    const int64_t per = (s.n > 0 ? s.n : 1) * (int64_t)sizeof(float);
+    const int64_t per = (s.n > 0 ? s.n : 1) * (int64_t)sizeof(float) + (int64_t)kSelectStateBytes;
     int64_t qc = ((int64_t)256 << 20) / per;
     if (qc < 1) qc = 1;
     return nq < qc ? nq : qc;
+}
+
+static size_t all_scores_bytes(const ScanShape &s, int64_t nq) {
+    const size_t b = (size_t)all_scores_chunk(s, nq) * (s.n > 0 ? s.n : 1) * sizeof(float);
+    return (b + 255) & ~(size_t)255;
 }
 
 size_t lut_search_workspace_bytes(const ScanShape &s, int64_t nq, int k, int grid) {
     if (k > kMaxTopK) {
         size_t b = (size_t)nq * s.d * sizeof(float);
         b = (b + 255) & ~(size_t)255;
-        b += (size_t)all_scores_chunk(s, nq) * (s.n > 0 ? s.n : 1) * sizeof(float);
-        b = (b + 255) & ~(size_t)255;
+        b += all_scores_bytes(s, nq);
+        b += (size_t)all_scores_chunk(s, nq) * kSelectStateBytes;
         return b + 256;
     }
     const int64_t qc = query_chunk(s, nq, k, grid);
@@ -1289,6 +1424,7 @@ hipError_t lut_search(const ScanShape &s, const uint8_t *blocked, const float *s
         // every score, then a radix selection per query
         float *all = reinterpret_cast<float *>(p8);
         const int64_t qa = all_scores_chunk(s, nq);
+        SelState *sel = reinterpret_cast<SelState *>(p8 + all_scores_bytes(s, nq));
         const size_t lds = lds_bytes_for(s, 1, false, filter.any());
         for (int64_t q0 = 0; q0 < nq; q0 += qa) {
             const int64_t m = (nq - q0) < qa ? (nq - q0) : qa;
@@ -1315,6 +1451,7 @@ hipError_t lut_search(const ScanShape &s, const uint8_t *blocked, const float *s
             p.lut_words = lut_words_for(s);
             hipLaunchKernelGGL(fill_keys, dim3(1024), dim3(256), 0, stream,
                                reinterpret_cast<int *>(all), m * s.n, (int)0xFF800000u);   // -inf
+            hipLaunchKernelGGL(sel_clear_kernel, dim3((unsigned)m), dim3(SEL_T), 0, stream, sel, s.n, k);
             hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
             if (s.bits == 8)
@@ -1324,8 +1461,13 @@ hipError_t lut_search(const ScanShape &s, const uint8_t *blocked, const float *s
             else
                 e = launch_scan_all<NIBBLE>(p, grid, lds, stream);
             if (e != hipSuccess) return e;
-            hipLaunchKernelGGL(select_topk_kernel, dim3((unsigned)m), dim3(SEL_T), 0, stream, all,
-                               s.n, k, ids + q0 * k, scores + q0 * k);
+            const int parts = sel_parts(s.n, m);
+            const dim3 sg((unsigned)parts, (unsigned)m);
+            hipLaunchKernelGGL(sel_count_kernel<0>, sg, dim3(SEL_T), 0, stream, all, s.n, sel);
+            hipLaunchKernelGGL(sel_count_kernel<1>, sg, dim3(SEL_T), 0, stream, all, s.n, sel);
+            hipLaunchKernelGGL(sel_gather_kernel, sg, dim3(SEL_T), 0, stream, all, s.n, sel);
+            hipLaunchKernelGGL(sel_sort_kernel, dim3((unsigned)m), dim3(SEL_T), 0, stream, all, s.n, k, sel,
+                               ids + q0 * k, scores + q0 * k);
             e = hipGetLastError();
             if (e != hipSuccess) return e;
         }

@@ -93,6 +93,33 @@ def test_large_k_other_bit_widths(env, bits):
                ref_i, ref_s, n=n)
 
 
+@pytest.mark.parametrize("n,live,k", [(300, 300, 257), (4096, 4096, 4096), (20000, 20000, 600),
+                                      (20000, 9000, 4096), (20000, 500, 600), (20000, 0, 300),
+                                      (70001, 70001, 4096)])
+def test_large_k_ties_and_few_vectors(env, n, live, k):
+    """Every vector the same code: all scores tie, more of them than the
+    selection's list holds (8,192) from n = 20,000 on, and the first k live
+    ids in order are the result; fewer live vectors than k leave padding."""
+    print("large k ties n=%d live=%d k=%d" % (n, live, k), flush=True)
+    idx = tq.Index(env.cb, env.rot, n_tenants=2)
+    codes = np.repeat(oracle.pack_codes(env.codes[:1], 4), n, axis=0)
+    ten = np.ones(n, dtype=np.uint16)
+    ids_live = np.sort(np.random.default_rng(n + live).choice(n, live, replace=False))
+    ten[ids_live] = 0
+    idx.add_codes(torch.from_numpy(codes).cuda(), torch.full((n,), float(env.scales[0])).cuda(),
+                  torch.from_numpy(ten.view(np.int16)).cuda())
+    allow = torch.ones(3, 1, dtype=torch.int64, device="cuda")   # tenant 0
+    ids, sc = idx.search(env.Qd[:3].contiguous(), k, allow=allow)
+    one, s1 = idx.search(env.Qd[:3].contiguous(), 1, allow=allow)
+    want = np.full(k, -1, dtype=np.int64)
+    want[:min(k, live)] = ids_live[:k]
+    assert np.array_equal(ids.cpu().numpy(), np.tile(want, (3, 1)))
+    sc = sc.cpu().numpy()
+    assert np.array_equal(np.isinf(sc), np.tile(want < 0, (3, 1)))
+    if live:
+        assert np.all(sc[:, :min(k, live)] == s1.cpu().numpy())
+
+
 @pytest.mark.parametrize("T,overfetch", [(10, 1), (100, 10), (1000, 100), (100, 3)])
 def test_postfilter_matches_oracle(env, T, overfetch):
     print("post-filter T=%d overfetch=%d" % (T, overfetch), flush=True)
