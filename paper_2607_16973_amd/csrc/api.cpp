@@ -1106,20 +1106,21 @@ static int scan_grid() {
 // Whether TQ_PATH_AUTO answers nq queries on the batched path (same scores
 // and lists as the scan's, queries without a certificate re-run on the scan
 // within the call's launches).  Both read the codes at about 5 TB/s: the scan
-// once per query, with 9 us (8 bits: 30 us) of table build and merge each;
-// the batched path once per tile of 32 queries, with 58 us (8 bits: 83 us)
-// of query preparation, selection and rescoring.  Measured at k = 10 in us a
-// call, scan / batched: d = 1536, 4 bits, 10,000 vectors 319 / 83 for 32
-// queries; 50,000 vectors 106 / 73 for 4, 174 / 74 for 8; 300,000 vectors
-// 140 / 118 for 2; 1,000,000 vectors 170 / 231 for 1, 300 / 229 for 2,
-// 8,537 / 450 for 64.  2 bits, 1,000,000 vectors 224 / 170 for 2; 3 bits
-// 309 / 223 for 2; 8 bits 530 / 382 for 2, 300,000 vectors 324 / 176 for 3.
-// d = 768, 4 bits, 100,000 vectors 222 / 62 for 8.
+// once per query, with 9 us (8 bits: 15 us) of table build and merge each and
+// about 20 us more for the first; the batched path once per tile of 32
+// queries, with 55 us of query preparation, selection and rescoring for a
+// group of 8 tiles.  Measured at k = 10 in us a call, scan / batched: d =
+// 1536, 4 bits, 20,000 vectors 58 / 65 for 3 queries, 69 / 65 for 4; 100,000
+// vectors 82 / 77 for 2, 102 / 77 for 3; 1,000,000 vectors 170 / 231 for 1,
+// 300 / 229 for 2.  d = 256, 30,000 vectors 44 / 49 for 3, 67 / 49 for 6.
+// 2 bits, 500,000 vectors 160 / 114 for 2; 3 bits, d = 256, 350,000 vectors
+// 116 / 58 for 2.
 static bool batch_pays(const ScanShape &sh, int64_t nq) {
     const double pass_us = (double)sh.nblk * sh.chunks * 1024.0 / 5.0e6;
     const double tiles = (double)((nq + 31) / 32);
     const bool b8 = sh.bits == 8;
-    return (double)nq * ((b8 ? 30.0 : 9.0) + pass_us) > tiles * ((b8 ? 83.0 : 58.0) + pass_us);
+    const double groups = (double)((nq + 255) / 256);
+    return 20.0 + (double)nq * ((b8 ? 15.0 : 9.0) + pass_us) > groups * 55.0 + tiles * pass_us;
 }
 
 // With tenant allowlists the scan skips blocks query by query and may be the

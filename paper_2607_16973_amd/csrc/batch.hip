@@ -860,6 +860,7 @@ struct BlockSelParams {
     const uint16_t *approx;    // [nqt][npad] float16 bit patterns
     const uint16_t *bmax;      // [nqt][nblk]
     int *top_i;                // [nqt][KC] candidate ids (INT_MAX: none)
+    float *top_s;              // [nqt][KC] and stored scores
     float *amin;               // [nqt] bound on the approximate score of non-candidates
     int *state;                // [nqt] kSel*
     int64_t n, nblk, npad;
@@ -882,6 +883,11 @@ __global__ __launch_bounds__(BS_THREADS) void block_select_kernel(BlockSelParams
     const uint16_t *bm = p.bmax + (int64_t)q * p.nblk;
     const uint16_t *row = p.approx + (int64_t)q * p.npad;
     int *out_i = p.top_i + (int64_t)q * KC;
+    float *out_s = p.top_s + (int64_t)q * KC;
+    auto put = [&](int pos, int64_t v, uint32_t key) {
+        out_i[pos] = (int)v;
+        out_s[pos] = hkey_value(key);
+    };
     int *hc = hist + (lane & 3) * kHistStride;
     auto clear_hist = [&]() {
         for (int i = tid; i < kHistCopies * kHistStride; i += BS_THREADS) hist[i] = 0;
@@ -1049,7 +1055,7 @@ __global__ __launch_bounds__(BS_THREADS) void block_select_kernel(BlockSelParams
         each_listed(nl, [&](int64_t v, uint32_t key) {
             if (key != 0u) {
                 const int pos = atomicAdd(&sh[3], 1);
-                if (pos < KC) out_i[pos] = (int)v;
+                if (pos < KC) put(pos, v, key);
             }
         });
         __syncthreads();
@@ -1065,7 +1071,7 @@ __global__ __launch_bounds__(BS_THREADS) void block_select_kernel(BlockSelParams
         each_listed(nl, [&](int64_t v, uint32_t key) {
             if (key >= tha) {
                 const int pos = atomicAdd(&sh[3], 1);
-                if (pos < KC) out_i[pos] = (int)v;
+                if (pos < KC) put(pos, v, key);
             }
         });
         __syncthreads();
@@ -1082,10 +1088,10 @@ __global__ __launch_bounds__(BS_THREADS) void block_select_kernel(BlockSelParams
     const int need_eq = KC - n_gt;   // keys equal to theta_b to take (>= 1)
     each_listed(nl, [&](int64_t v, uint32_t key) {
         if (key > thb) {
-            out_i[atomicAdd(&sh[4], 1)] = (int)v;
+            put(atomicAdd(&sh[4], 1), v, key);
         } else if (key == thb) {
             const int e = atomicAdd(&sh[5], 1);
-            if (e < need_eq) out_i[n_gt + e] = (int)v;
+            if (e < need_eq) put(n_gt + e, v, key);
         }
     });
     finish(hkey_value(thb), kSelBound);
@@ -1099,6 +1105,7 @@ struct RescoreParams {
     const float *qconst;       // [nqt] TQ+ constant terms, or null
     const float *cents;
     const int *top_i;          // [nqt][KC] candidates (INT_MAX: none)
+    const float *top_s;        // [nqt][KC] their stored (approximate) scores
     const float *amin;         // [nqt] bound on the approximate score of non-candidates
     const int *state;          // [nqt] kSel*
     const QInfo *info;
@@ -1122,13 +1129,20 @@ struct RescoreParams {
 
 // One workgroup per query, KC = 64 S candidate slots.
 //  1. The query's integer table (as the single-query scan builds it).
-//  2. Lane = candidate: wave w takes the 64 candidates of run w % S and the
-//     (w / S)-th of 16 / S slices of the chunks, so all lanes read the same
+//  0. The candidates that may be among the top k: with a the k-th largest
+//     stored score and e(.) the error of a stored score (see 4), k vectors
+//     score at least a - e(a), and a candidate whose b + e(b) is less is out.
+//     At k = 10 about 15 of 128 remain, in R runs of 64 (R a power of two up
+//     to S); each of a candidate's chunks is a line of memory, and reading
+//     all of them took 44 us for 256 queries (25 now) and 26 for 32.
+//  2. Lane = candidate: wave w takes the 64 candidates of run w % R and the
+//     (w / R)-th of 16 / R slices of the chunks, so all lanes read the same
 //     table rows (as in the scan); partial integer sums meet in LDS (exact,
 //     order-free): bit-identical to the single-query scan's scores.  8-bit
-//     codes are summed in float32 in the scan's chunk order instead: waves
-//     0..S-1 take a run each over all chunks.
-//  3. Waves 0..S-1 sort their 64 exact scores; an entry's rank is its lane
+//     codes are summed in float32 chunk by chunk: for one run after the
+//     other, the waves compute the sums of every sixteenth chunk, which wave 0
+//     then adds in the scan's order (a wave per run over all chunks took 41 us).
+//  3. Waves 0..R-1 sort their 64 exact scores; an entry's rank is its lane
 //     plus, in every other sorted run, the number of entries ahead of it
 //     (binary search); ranks below k are written.
 //  4. Certificate: a vector outside the candidates has a stored score at
@@ -1160,56 +1174,114 @@ __device__ inline void hand_over(const RescoreParams &p, int q, int *slot_s) {
 template <int MODE, int S>
 __global__ __launch_bounds__(kTableThreads) void rescore_kernel(RescoreParams p) {
     constexpr int KC = 64 * S;
-    constexpr int SL = kTableWaves / S;    // chunk slices
     constexpr int CB = 12;                 // chunk loads of a lane in flight at once
     extern __shared__ __attribute__((aligned(16))) float lds[];
     float *red = lds + p.lut_words;         // 16
-    int *sums = reinterpret_cast<int *>(red + 16);   // [KC]: integer sums, then ranks
+    int *sums = reinterpret_cast<int *>(red + 16);   // [KC]: ranks, integer sums, then ranks
     float *run_s = reinterpret_cast<float *>(sums + KC);
     int *run_i = reinterpret_cast<int *>(run_s + KC);
-    int *sh = run_i + KC;                   // [0] valid count, [1] k-th exact score, [2] certified, [3] list slot
+    int *kept = run_i + KC;                 // [KC] candidates that may be in the top k
+    // [0] sorted entries, [1] k-th exact score, [2] certified, [3] list slot,
+    // [4] key of the k-th largest stored score, [5] kept, [6] candidates
+    int *sh = kept + KC;
     const int q = blockIdx.x;
     if (scan_is_faster_for(p.gate, q, p.nqt, p.tile_q)) {
         hand_over(p, q, sh + 3);
         return;
     }
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int run = wave % S, slice = wave / S;
-    const int c0 = MODE == BYTE ? 0 : p.chunks * slice / SL;
-    const int c1 = MODE != BYTE ? p.chunks * (slice + 1) / SL : slice == 0 ? p.chunks : 0;
     const TableShape ts{p.d, p.bits, p.lut_words};
-    for (int i = tid; i < KC; i += kTableThreads) sums[i] = 0;
-    if (tid == 0) {
-        sh[0] = 0;
-        sh[1] = __float_as_int(-INFINITY);
-    }
     // Loads in the order they are needed (completion is in order): the
-    // query's coordinates, this lane's candidate, the certificate inputs,
-    // then the candidate's chunks, in flight while the table is built.
+    // candidates and the certificate inputs, the query's coordinates, then
+    // the kept candidates' chunks, in flight while the table is built.
     // Every load is unconditional, from a clamped address.
+    const int ce = tid % KC;
+    const int cv = p.top_i[(int64_t)q * KC + ce];
+    const float cs = p.top_s[(int64_t)q * KC + ce];
+    const QInfo qi = p.info[q];
+    const float amin_s = p.amin[q];
+    const int st = p.state[q];
     QueryRegs<MODE> qv;
     const float *qr = p.qrot + (int64_t)q * p.d;
     if constexpr (MODE != BYTE) load_query<MODE>(ts, qr, qv);
     const float C = p.qconst ? p.qconst[q] : 0.f;
-    const int v = p.top_i[(int64_t)q * KC + run * 64 + lane];
-    const QInfo qi = p.info[q];
-    const float amin_s = p.amin[q];
-    const int st = p.state[q];
-    const bool valid = v != INT_MAX;
-    const int vc = valid ? v : 0;
-    const uint4 *src = p.codes + ((int64_t)(vc >> 6) * p.chunks) * 64 + (vc & 63);
-    const float scl = p.scales[vc];
+    const float own = cv == INT_MAX ? -INFINITY : cs;
+    if (tid < KC) {
+        run_s[ce] = own;
+        sums[ce] = 0;
+    }
+    if (tid == 0) {
+        sh[0] = 0;
+        sh[1] = __float_as_int(-INFINITY);
+        sh[4] = INT_MAX;
+        sh[5] = 0;
+        sh[6] = 0;
+    }
+    __syncthreads();
+    {
+        constexpr int LEN = KC * KC / kTableThreads;   // entries that a thread compares its own with
+        const int j0 = tid / KC * LEN;
+        int ahead = 0;
+#pragma unroll 4
+        for (int j = 0; j < LEN; ++j) ahead += run_s[j0 + j] > own;
+        if (ahead) atomicAdd(&sums[ce], ahead);
+    }
+    __syncthreads();
+    if (tid < KC) {
+        const uint64_t there = __ballot(cv != INT_MAX);
+        if (lane == 0 && there) atomicAdd(&sh[6], (int)__popcll(there));
+        if (cv != INT_MAX && sums[ce] < p.k) atomicMin(&sh[4], fkey(own));
+    }
+    __syncthreads();
+    // largest error of a stored score x / norm
+    auto stored_err = [&](double x) {
+        return ldexp(1.0, -11) * fabs(x) + ldexp(1.0, -25) * qi.norm + (double)qi.err;
+    };
+    if (tid < KC) {
+        bool keep = cv != INT_MAX;
+        if (qi.err < INFINITY && sh[6] >= p.k) {
+            const double kth = (double)unfkey(sh[4]) * qi.norm, x = (double)own * qi.norm;
+            keep = keep && x + stored_err(x) >= kth - stored_err(kth);
+        }
+        const uint64_t m = __ballot(keep);
+        int at = 0;
+        if (lane == 0 && m) at = atomicAdd(&sh[5], (int)__popcll(m));
+        at = __shfl(at, 0) + (int)__popcll(m & ((1ull << lane) - 1));
+        if (keep) kept[at] = cv;
+        sums[ce] = 0;
+        run_s[ce] = -INFINITY;
+        run_i[ce] = INT_MAX;
+    }
+    __syncthreads();
+    const int nk = sh[5];
+    int R = 1;                             // runs of 64 kept candidates
+    while (R < S && 64 * R < nk) R *= 2;
+    const int run = wave % R, slice = wave / R, SL = kTableWaves / R;
+    const int c0 = MODE == BYTE ? wave : p.chunks * slice / SL;
+    const int c1 = MODE == BYTE ? p.chunks : p.chunks * (slice + 1) / SL;
+    constexpr int CS = MODE == BYTE ? kTableWaves : 1;   // step of a wave's chunks
     uint4 w[CB];
+    const uint4 *src;
+    auto take_run = [&](int r) {           // the lane's candidate of run r
+        const int e = r * 64 + lane;
+        const int v = e < nk ? kept[e] : INT_MAX;
+        const int vc = v != INT_MAX ? v : 0;
+        src = p.codes + ((int64_t)(vc >> 6) * p.chunks) * 64 + (vc & 63);
+        return v;
+    };
     auto load_chunks = [&](int cb) {
 #pragma unroll
         for (int r = 0; r < CB; ++r) {
-            const int c = cb + r < c1 ? cb + r : c0;
+            const int c = cb + CS * r < c1 ? cb + CS * r : cb;
             w[r] = src[(int64_t)c * 64];
         }
     };
-    load_chunks(c0);
+    const int v = take_run(MODE == BYTE ? 0 : run);
+    const bool valid = v != INT_MAX;
+    const float scl = p.scales[valid ? v : 0];
+    const bool any = c0 < c1 && __ballot(valid) != 0;
+    if (any) load_chunks(c0);
     int shx = 0;
-    float facc = C;
     if constexpr (MODE == BYTE) {
         for (int e = tid; e < kByteRepWords; e += kTableThreads) lds[e] = p.cents[e >> 5];
         for (int e = tid; e < p.d; e += kTableThreads) lds[kByteRepWords + e] = qr[e];
@@ -1219,34 +1291,51 @@ __global__ __launch_bounds__(kTableThreads) void rescore_kernel(RescoreParams p)
         shx = build_int_table<MODE>(lds, red, p.cents, ts, qv, C);
     }
     __syncthreads();
-    const char *lut = reinterpret_cast<const char *>(lds);
-    int acc = 0;
-    for (int cb = c0; cb < c1; cb += CB) {
-        if (cb > c0) load_chunks(cb);
-#pragma unroll
-        for (int r = 0; r < CB; ++r)
-            if (cb + r < c1) {
-                if constexpr (MODE == BYTE)
-                    facc += byte_chunk(lds, cb + r, w[r]);
-                else
-                    acc += int_chunk<MODE>(lut + (cb + r) * kChunkTableBytes<MODE>, w[r]);
-            }
-    }
-    if (MODE != BYTE && valid) atomicAdd(&sums[run * 64 + lane], acc);
-    __syncthreads();
-    // waves 0..S-1: sort their runs of 64 exact scores
-    float s_ = -INFINITY;
-    int i_ = INT_MAX;
-    if (wave < S) {
-        if (valid) {
-            s_ = MODE == BYTE ? facc * scl : ldexpf((float)sums[run * 64 + lane] * scl, -shx);
-            i_ = v;
-        }
+    // waves 0..R-1 sort their runs of 64 exact scores
+    auto sort_run = [&](int r, float s_, int i_) {
         wave_sort64(s_, i_, lane);
-        run_s[wave * 64 + lane] = s_;
-        run_i[wave * 64 + lane] = i_;
+        run_s[r * 64 + lane] = s_;
+        run_i[r * 64 + lane] = i_;
         const int c = __popcll(__ballot(i_ != INT_MAX));
         if (lane == 0 && c) atomicAdd(&sh[0], c);
+    };
+    if constexpr (MODE == BYTE) {
+        float *part = lds + kByteRepWords + p.d;   // [chunk][64]
+        for (int r = 0; r < R; ++r) {
+            const int vr = r == 0 ? v : take_run(r);
+            if (c0 < c1) {
+                if (r > 0) load_chunks(c0);
+                for (int cb = c0; cb < c1; cb += CS * CB) {
+                    if (cb > c0) load_chunks(cb);
+#pragma unroll
+                    for (int u = 0; u < CB; ++u)
+                        if (cb + CS * u < c1)
+                            part[(cb + CS * u) * 64 + lane] = byte_chunk(lds, cb + CS * u, w[u]);
+                }
+            }
+            __syncthreads();
+            if (wave == 0) {
+                float facc = C;
+                for (int c = 0; c < p.chunks; ++c) facc += part[c * 64 + lane];
+                const bool in = vr != INT_MAX;
+                sort_run(r, in ? facc * p.scales[vr] : -INFINITY, vr);
+            }
+            __syncthreads();   // the sums have been read
+        }
+    } else {
+        const char *lut = reinterpret_cast<const char *>(lds);
+        int acc = 0;
+        if (any)
+            for (int cb = c0; cb < c1; cb += CB) {
+                if (cb > c0) load_chunks(cb);
+#pragma unroll
+                for (int r = 0; r < CB; ++r)
+                    if (cb + r < c1) acc += int_chunk<MODE>(lut + (cb + r) * kChunkTableBytes<MODE>, w[r]);
+            }
+        if (valid) atomicAdd(&sums[run * 64 + lane], acc);
+        __syncthreads();
+        if (wave < R)   // slice 0: the run's own candidates
+            sort_run(wave, valid ? ldexpf((float)sums[wave * 64 + lane] * scl, -shx) : -INFINITY, v);
     }
     __syncthreads();
     // rank of entry e = its place in its run + the entries ahead of it in
@@ -1293,8 +1382,7 @@ __global__ __launch_bounds__(kTableThreads) void rescore_kernel(RescoreParams p)
     if (tid == 0) {
         const float ek = __int_as_float(sh[1]);
         const double amin = (double)amin_s * qi.norm;
-        const double reach = amin + ldexp(1.0, -11) * fabs(amin) + ldexp(1.0, -25) * qi.norm +
-                             (double)qi.err;
+        const double reach = amin + stored_err(amin);
         // an error bound that is not finite (scales or queries that are not)
         // proves nothing
         const bool cert = qi.err < INFINITY &&
@@ -1306,9 +1394,8 @@ __global__ __launch_bounds__(kTableThreads) void rescore_kernel(RescoreParams p)
 }
 
 // ============================================================ wide passes
-// Passes of 65 to 256 queries (QP = 128 or 256 query slots) read the code
-// store once per pass and keep no score matrix (passes of at most 64 queries
-// take tiles of 32, which are faster there):
+// Passes of up to 256 queries (QP = 256 query slots) read the code store once
+// per pass and keep no score matrix (taken where wide_pass says so):
 //  1. prep_kernel, then frag_kernel: the float16 queries in the A operand
 //     order of v_mfma_f32_32x32x16_f16.  Piece (c, f, l) (16 bytes) holds
 //     coordinates 32c + 16(f & 1) + 8(l >> 5) .. +7 of query
@@ -1344,7 +1431,7 @@ constexpr int PS_THREADS = 1024;               // pilot_select_kernel, final_sel
 constexpr int kPilotMax = 65536;               // pilot vectors per query (16-bit keys in 128 KiB of LDS)
 constexpr int kFinalMax = 16384;               // candidates a query's final selection gathers
 constexpr int kWideMaxQ = 256;
-constexpr int kWideMinQ = 64;                 // passes of more queries take the wide path (fewer: tiles of 32)
+constexpr int64_t kWideWork = 1000000;       // see wide_pass
 constexpr int kWideMinChunks = 8;            // chunks per vector of a wide pass: more than its slabs ahead
 
 // Order-preserving map of float32 onto uint32; 0 marks an absent entry
@@ -1422,7 +1509,7 @@ struct WideShape {
     static constexpr int NI = QF + WD_NG;              // 1 KiB pieces of a slab
     static constexpr int DW = (NI + WD_WAVES - 1) / WD_WAVES;
     static constexpr int SU = WD_WAVES * DW * 64;      // uint4 of a slab
-    static constexpr int NB = QW == 128 ? 5 : 7;       // slab buffers
+    static constexpr int NB = 5;                       // slab buffers
     static constexpr int PD = NB - 1;                  // slabs requested ahead
     static constexpr size_t lds = kTableBytes + (size_t)NB * SU * 16 + 2 * 1024 +
                                   4 * (size_t)QP * 4;
@@ -1830,10 +1917,13 @@ struct PilotParams {
 };
 
 // One workgroup per query.  The selection runs on 16-bit keys, the top half
-// of the order-preserving key of each allowed pilot score, held in LDS: the
-// KC-th largest such key kt gives theta = the smallest float whose key starts
-// with kt, so at least KC allowed pilot vectors score theta or more, and a
-// pilot vector reaches theta exactly when its 16-bit key reaches kt.
+// of the order-preserving key of each allowed pilot score, held in LDS: with
+// kt a key that at least KC allowed pilot vectors reach, theta = the smallest
+// float whose key starts with kt, and a pilot vector reaches theta exactly when
+// its 16-bit key reaches kt.  kt is the KC-th largest of the threads' largest
+// keys, each over up to 64 vectors 1024 apart: about 7% more vectors than KC
+// reach it (KC = 128), and one pass over 65,536 keys replaces three.  Where
+// fewer than KC threads hold an allowed vector, it is the KC-th largest key.
 __global__ __launch_bounds__(PS_THREADS) void pilot_select_kernel(PilotParams p) {
     constexpr int TV = 64 * WD_NG;                 // vectors per pilot tile
     extern __shared__ __attribute__((aligned(16))) uint16_t k16[];   // [npv], 0: absent
@@ -1848,12 +1938,14 @@ __global__ __launch_bounds__(PS_THREADS) void pilot_select_kernel(PilotParams p)
     if (tid == 0) {
         sh[4] = 0;
         sh[5] = 0;
+        sh[6] = 0;
     }
     __shared__ uint64_t allow_s[64];
     if (arow)
         for (int w = tid; w < p.W; w += PS_THREADS) allow_s[w] = arow[w];
     __syncthreads();
     int cnt = 0;
+    uint32_t best = 0;   // this thread's largest key
     // rounds of 16 loads per thread, all issued before any is used
     constexpr int R = 16;
     for (int e0 = 0; e0 < npv; e0 += R * PS_THREADS) {
@@ -1883,22 +1975,31 @@ __global__ __launch_bounds__(PS_THREADS) void pilot_select_kernel(PilotParams p)
                     const int64_t v = vec_of(e);
                     ok = ok && ((p.live[v < p.n ? v >> 6 : 0] >> (v & 63)) & 1ull);
                 }
-                k16[e] = ok ? (uint16_t)(ukey(val[u]) >> 16) : (uint16_t)0;   // a finite key's top half is >= 0x80
+                const uint32_t key = ok ? ukey(val[u]) >> 16 : 0u;   // a finite key's top half is >= 0x80
+                k16[e] = (uint16_t)key;
+                best = key > best ? key : best;
                 cnt += ok;
             }
         }
     }
     for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
+    const int some = __popcll(__ballot(best != 0u));
     __syncthreads();
-    if (lane == 0) atomicAdd(&sh[5], cnt);
+    if (lane == 0) {
+        atomicAdd(&sh[5], cnt);
+        atomicAdd(&sh[6], some);
+    }
     __syncthreads();
     const int allowed = sh[5];
     uint32_t thk = 1u;   // every present key
     if (allowed > p.KC) {
         int n_above;
-        thk = radix_kth<16>([&](auto fn) {
-            for (int e = tid; e < npv; e += PS_THREADS) fn((uint32_t)k16[e]);
-        }, p.KC, hist, sh, n_above);
+        if (sh[6] >= p.KC)
+            thk = radix_kth<16>([&](auto fn) { fn(best); }, p.KC, hist, sh, n_above);
+        else
+            thk = radix_kth<16>([&](auto fn) {
+                for (int e = tid; e < npv; e += PS_THREADS) fn((uint32_t)k16[e]);
+            }, p.KC, hist, sh, n_above);
     }
     if (tid == 0) p.theta[q] = allowed > p.KC ? ukey_value(thk << 16) : -INFINITY;
     for (int e = tid; e < npv; e += PS_THREADS) {
@@ -1928,6 +2029,7 @@ struct FinalParams {
     int nqt;
     Gate gate;
     int *top_i;                // [nqt][KC] (INT_MAX: none)
+    float *top_s;
     float *amin;
     int *state;
 };
@@ -1943,6 +2045,7 @@ __global__ __launch_bounds__(PS_THREADS) void final_select_kernel(FinalParams p)
     const int q = blockIdx.x, tid = threadIdx.x;
     if (scan_is_faster(p.gate, 0, p.nqt)) return;
     int *out = p.top_i + (int64_t)q * p.KC;
+    float *out_s = p.top_s + (int64_t)q * p.KC;
     __shared__ int goff[1025];                  // exclusive offsets of the workgroup lists
     __shared__ int wsum[PS_THREADS / 64];
     const int lane = tid & 63, wave = tid >> 6;
@@ -2007,7 +2110,10 @@ __global__ __launch_bounds__(PS_THREADS) void final_select_kernel(FinalParams p)
     if (tot <= p.KC) {
         // every candidate kept: all allowed vectors when theta = -inf, else
         // every vector below theta is outside
-        for (int i = tid; i < p.KC; i += PS_THREADS) out[i] = i < tot ? cv[i] : INT_MAX;
+        for (int i = tid; i < p.KC; i += PS_THREADS) {
+            out[i] = i < tot ? cv[i] : INT_MAX;
+            if (i < tot) out_s[i] = ukey_value(ck[i]);
+        }
         if (tid == 0) {
             p.amin[q] = theta;
             p.state[q] = theta == -INFINITY ? kSelAll : kSelBound;
@@ -2022,10 +2128,15 @@ __global__ __launch_bounds__(PS_THREADS) void final_select_kernel(FinalParams p)
     for (int i = tid; i < tot; i += PS_THREADS) {
         const uint32_t k = ck[i];
         if (k > thk) {
-            out[atomicAdd(&sh[4], 1)] = cv[i];
+            const int e = atomicAdd(&sh[4], 1);
+            out[e] = cv[i];
+            out_s[e] = ukey_value(k);
         } else if (k == thk) {
-            const int e = atomicAdd(&sh[5], 1);
-            if (e < need_eq) out[n_gt + e] = cv[i];
+            const int e = n_gt + atomicAdd(&sh[5], 1);
+            if (e < n_gt + need_eq) {
+                out[e] = cv[i];
+                out_s[e] = ukey_value(k);
+            }
         }
     }
     if (tid == 0) {
@@ -2076,11 +2187,11 @@ constexpr int kGroupTiles = 8;
 
 struct BatchLayout {
     int tiles;
-    size_t q16, info, approx, bmax, top_i, amin, state, tickets, count, rows, qc, tmask, list,
+    size_t q16, info, approx, bmax, top_i, top_s, amin, state, tickets, count, rows, qc, tmask, list,
         qconst_c, allow_c, lut, total;
     // wide passes
     size_t w_q16, w_info, w_qfrag, w_qf, w_pil, w_theta, w_pcn, w_pci, w_pcs, w_cs, w_ci, w_cn,
-        w_top, w_amin, w_state;
+        w_top, w_tops, w_amin, w_state;
 };
 
 // Geometry of a wide pass with NG blocks per tile.
@@ -2108,22 +2219,24 @@ WideGeom wide_geom(const ScanShape &s, int NG, int grid, int KC) {
     return w;
 }
 
-// Whether a pass over nq more queries takes the wide kernels: more queries
-// than two tiles, and an index of which the pilot (at most 65,536 vectors) is
+// Whether a pass over nq more queries takes the wide kernels: enough queries
+// and vectors, and an index of which the pilot (at most 65,536 vectors) is
 // large enough a part -- about KC ntiles / npil candidates per query must fit
 // the final selection and about 2 per + 16 a workgroup's list, with room for
 // chance; beyond that (N above 6.4M at k = 10, 1.6M at k = 100) most
 // queries would overflow and fall back.
 bool wide_pass(const ScanShape &s, int64_t nq, int KC, int grid) {
-    if (s.bits != 4 || nq <= kWideMinQ || s.chunks < kWideMinChunks || grid > PS_THREADS) return false;
+    // Six tiles or more and 1,000,000 vectors at 6 tiles, 500,000 at 7, 333,333
+    // at 8.  256 queries, tiles / wide, d = 1536: 188 / 231 us at 100,000
+    // vectors, 368 / 405 at 300,000, 1,214 / 982 at 1,000,000; d = 256: 75 / 100
+    // at 300,000, 330 / 255 at 1,000,000.  192 queries: 950 / 919 and 253 / 240
+    // at 1,000,000; 128: 617 / 635 and 133 / 158.
+    const int64_t tiles = (std::min<int64_t>(nq, kWideMaxQ) + kTile - 1) / kTile;
+    if (s.bits != 4 || tiles < 6 || s.n * (tiles - 5) < kWideWork || s.chunks < kWideMinChunks || grid > PS_THREADS) return false;
     const WideGeom w = wide_geom(s, WD_NG, grid, KC);
     const double part = (double)w.ntiles / (double)w.npil;
     return KC * part <= 0.8 * kFinalMax && 2.0 * KC * part / grid + 16.0 <= 512.0;
 }
-
-// Query slots of a wide pass of nqt > kWideMinQ queries.
-int wide_slots(int nqt) { return nqt <= 128 ? 128 : 256; }
-
 
 // Row length of the approximate-score matrix: whole 512-vector select units.
 int64_t approx_row(const ScanShape &s) { return (s.nblk * 64 + 511) / 512 * 512; }
@@ -2132,8 +2245,12 @@ BatchLayout batch_layout(const ScanShape &s, int64_t nq, int k, int grid) {
     BatchLayout L{};
     size_t o = align256((size_t)nq * s.d * sizeof(float));   // rotated queries
     const int64_t npad = approx_row(s);
-    // after wide passes at most kWideMinQ queries are left for tiles
-    const int64_t tile_q = wide_pass(s, nq, batch_candidates(k), grid) ? std::min<int64_t>(nq, kWideMinQ) : nq;
+    // after whole wide passes the rest, if it is not another one, is left for tiles
+    int64_t tile_q = nq;
+    if (wide_pass(s, nq, batch_candidates(k), grid)) {
+        tile_q = nq % kWideMaxQ;
+        if (tile_q == 0 || wide_pass(s, tile_q, batch_candidates(k), grid)) tile_q = 1;
+    }
     const int64_t need = (tile_q + kTile - 1) / kTile, fit = ((int64_t)256 << 20) / (kTile * npad * 2 + 1);
     L.tiles = (int)std::max<int64_t>(1, std::min<int64_t>({need, fit, kGroupTiles, grid}));
     const size_t gq = (size_t)L.tiles * kTile;   // queries of a group
@@ -2146,6 +2263,8 @@ BatchLayout batch_layout(const ScanShape &s, int64_t nq, int k, int grid) {
     L.bmax = o;
     o += align256(gq * s.nblk * 2);
     L.top_i = o;
+    o += align256(gq * kCandMax * 4);
+    L.top_s = o;
     o += align256(gq * kCandMax * 4);
     L.amin = o;
     o += align256(gq * 4);
@@ -2171,7 +2290,7 @@ BatchLayout batch_layout(const ScanShape &s, int64_t nq, int k, int grid) {
     o += lut_search_workspace_bytes(s, nq, k, grid);
     if (wide_pass(s, nq, batch_candidates(k), grid)) {
         const int KC = batch_candidates(k), PCM = 2 * KC;
-        const int QP = wide_slots((int)std::min<int64_t>(nq, kWideMaxQ));
+        constexpr int QP = kWideMaxQ;
         const WideGeom w = wide_geom(s, WD_NG, grid, KC);
         auto take = [&](size_t bytes) {
             const size_t at = o;
@@ -2191,6 +2310,7 @@ BatchLayout batch_layout(const ScanShape &s, int64_t nq, int k, int grid) {
         L.w_ci = take((size_t)grid * QP * w.S * 4);
         L.w_cn = take((size_t)grid * QP * 4);
         L.w_top = take((size_t)QP * KC * 4);
+        L.w_tops = take((size_t)QP * KC * 4);
         L.w_amin = take((size_t)QP * 4);
         L.w_state = take((size_t)QP * 4);
     }
@@ -2233,13 +2353,13 @@ hipError_t launch_scores(int bits, const ScoreParams &sp, int grid, hipStream_t 
     }
 }
 
-// LDS of the rescoring: the table, 16 floats, integer sums and sorted
-// (score, id) runs, four words.
+// LDS of the rescoring: the table (8 bits: and a run's chunk sums), 16
+// floats, integer sums, sorted (score, id) runs and the list, eight words.
 int rescore_lut_words(const ScanShape &s) {
-    return s.bits == 8 ? kByteRepWords + s.d : s.bits == 3 ? s.chunks * 320 : s.chunks * 512;
+    return s.bits == 8 ? kByteRepWords + s.d + 64 * s.chunks : s.bits == 3 ? s.chunks * 320 : s.chunks * 512;
 }
 size_t rescore_lds(const ScanShape &s, int KC) {
-    return (size_t)rescore_lut_words(s) * 4 + 16 * 4 + (size_t)KC * 12 + 16;
+    return (size_t)rescore_lut_words(s) * 4 + 16 * 4 + (size_t)KC * 16 + 32;
 }
 template <int MODE, int S>
 hipError_t launch_rescore_as(const RescoreParams &rp, int nqt, size_t lds, hipStream_t stream) {
@@ -2265,12 +2385,11 @@ hipError_t launch_rescore(const ScanShape &s, int KC, const RescoreParams &rp, i
     return e;
 }
 
-// Launches wide_scores_kernel for a pass of QP query slots (QP / 2 queries
-// per wave).
-hipError_t launch_wide_scores(int QP, const WideParams &wp, int grid, hipStream_t stream) {
+// Launches wide_scores_kernel (kWideMaxQ / 2 queries per wave).
+hipError_t launch_wide_scores(const WideParams &wp, int grid, hipStream_t stream) {
     hipError_t err = hipSuccess;
-    auto go = [&](auto qw, auto pilot, auto filt) {
-        constexpr int QW = decltype(qw)::value;
+    auto go = [&](auto pilot, auto filt) {
+        constexpr int QW = kWideMaxQ / WD_NH;
         constexpr bool P = decltype(pilot)::value, F = decltype(filt)::value;
         static bool attr = false;
         if (!attr) {
@@ -2283,13 +2402,9 @@ hipError_t launch_wide_scores(int QP, const WideParams &wp, int grid, hipStream_
                            stream, wp);
         err = hipGetLastError();
     };
-    auto go_width = [&](auto qw) {
-        if (wp.pilot) go(qw, std::true_type(), std::false_type());
-        else if (wp.tmask) go(qw, std::false_type(), std::true_type());
-        else go(qw, std::false_type(), std::false_type());
-    };
-    if (QP == 128) go_width(std::integral_constant<int, 64>());
-    else go_width(std::integral_constant<int, 128>());
+    if (wp.pilot) go(std::true_type(), std::false_type());
+    else if (wp.tmask) go(std::false_type(), std::true_type());
+    else go(std::false_type(), std::false_type());
     return err;
 }
 
@@ -2341,6 +2456,7 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
     _Float16 *approx = reinterpret_cast<_Float16 *>(w8 + L.approx);
     _Float16 *bmax = reinterpret_cast<_Float16 *>(w8 + L.bmax);
     int *top_i = reinterpret_cast<int *>(w8 + L.top_i);
+    float *top_s = reinterpret_cast<float *>(w8 + L.top_s);
     float *amin = reinterpret_cast<float *>(w8 + L.amin);
     int *state = reinterpret_cast<int *>(w8 + L.state);
     int *tickets = reinterpret_cast<int *>(w8 + L.tickets);
@@ -2381,7 +2497,7 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
             g.pass_us = (s.bits == 8 ? 83.f : 58.f) / tiles + (tiles > 1 ? 8.f : 0.f);
             g.read_us = g.block_us;
         } else {
-            g.pass_us = (float)(230.0 + (double)s.nblk * block_bytes / (QP == 256 ? 1.0e6 : 1.35e6));
+                g.pass_us = (float)(150.0 + (double)s.nblk * block_bytes / 1.0e6);
         }
         return g;
     };
@@ -2406,7 +2522,7 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
                            dim3((unsigned)(mask_wgs + (s.nblk + FK_THREADS - 1) / FK_THREADS), tiles),
                            dim3(FK_THREADS), 0, stream, fp);
     };
-    auto rescore = [&](int64_t q0, int nqt, const int *ti, const float *am, const int *st,
+    auto rescore = [&](int64_t q0, int nqt, const int *ti, const float *ts, const float *am, const int *st,
                        const QInfo *qi, const Gate &gate, int tile_q) {
         RescoreParams rp{};
         rp.codes = reinterpret_cast<const uint4 *>(blocked);
@@ -2415,6 +2531,7 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
         rp.qconst = qconst ? qconst + q0 : nullptr;
         rp.cents = cents32;
         rp.top_i = ti;
+        rp.top_s = ts;
         rp.amin = am;
         rp.state = st;
         rp.info = qi;
@@ -2443,7 +2560,7 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
         if (wide_pass(s, nq - q0, KC, grid)) {
             // a wide pass of up to kWideMaxQ queries
             const int nqt = (int)std::min<int64_t>(nq - q0, kWideMaxQ);
-            const int QP = wide_slots(nqt);
+            constexpr int QP = kWideMaxQ;
             const int PCM = 2 * KC;
             const WideGeom w = wide_geom(s, WD_NG, grid, KC);
             _Float16 *wq16 = reinterpret_cast<_Float16 *>(w8 + L.w_q16);
@@ -2459,6 +2576,7 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
             int *wci = reinterpret_cast<int *>(w8 + L.w_ci);
             int *wcn = reinterpret_cast<int *>(w8 + L.w_cn);
             int *wtop = reinterpret_cast<int *>(w8 + L.w_top);
+            float *wtops = reinterpret_cast<float *>(w8 + L.w_tops);
             float *wamin = reinterpret_cast<float *>(w8 + L.w_amin);
             int *wstate = reinterpret_cast<int *>(w8 + L.w_state);
             const uint64_t *allow_p = allow ? allow + q0 * s.W : nullptr;
@@ -2495,7 +2613,7 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
             wp.cand_n = wcn;
             wp.S = w.S;
             wp.pilot = 1;
-            hipError_t e = launch_wide_scores(QP, wp, grid, stream);
+            hipError_t e = launch_wide_scores(wp, grid, stream);
             if (e != hipSuccess) return e;
             PilotParams pp{};
             pp.pil = wpil;
@@ -2517,7 +2635,7 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
             hipLaunchKernelGGL(pilot_select_kernel, dim3(nqt), dim3(PS_THREADS), (size_t)pp.npv * 2, stream,
                                pp);
             wp.pilot = 0;
-            e = launch_wide_scores(QP, wp, grid, stream);
+            e = launch_wide_scores(wp, grid, stream);
             if (e != hipSuccess) return e;
             FinalParams fp{};
             fp.theta = wtheta;
@@ -2535,12 +2653,13 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
             fp.nqt = nqt;
             fp.gate = gate;
             fp.top_i = wtop;
+            fp.top_s = wtops;
             fp.amin = wamin;
             fp.state = wstate;
             hipLaunchKernelGGL(final_select_kernel, dim3(nqt), dim3(PS_THREADS),
                                (size_t)kFinalMax * 8, stream, fp);
             e = hipGetLastError();
-            if (e == hipSuccess) e = rescore(q0, nqt, wtop, wamin, wstate, winfo, gate, QP);
+            if (e == hipSuccess) e = rescore(q0, nqt, wtop, wtops, wamin, wstate, winfo, gate, QP);
             if (e != hipSuccess) return e;
             q0 += nqt;
             continue;
@@ -2588,6 +2707,7 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
         bp.approx = reinterpret_cast<const uint16_t *>(approx);
         bp.bmax = reinterpret_cast<const uint16_t *>(bmax);
         bp.top_i = top_i;
+        bp.top_s = top_s;
         bp.amin = amin;
         bp.state = state;
         bp.n = s.n;
@@ -2598,7 +2718,7 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
         bp.gate = gate;
         hipLaunchKernelGGL(block_select_kernel, dim3(nqt), dim3(BS_THREADS), 0, stream, bp);
         e = hipGetLastError();
-        if (e == hipSuccess) e = rescore(q0, nqt, top_i, amin, state, info, gate, kTile);
+        if (e == hipSuccess) e = rescore(q0, nqt, top_i, top_s, amin, state, info, gate, kTile);
         if (e != hipSuccess) return e;
         q0 += nqt;
     }

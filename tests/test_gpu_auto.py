@@ -3,6 +3,7 @@ path it takes, ids and scores are the scan's, bit for bit -- over sizes on
 both sides of the rule that chooses, with queries whose certificate fails
 (the scan answers them within the call), inside a captured graph, and with a
 workspace that only the scan fits."""
+import numpy as np
 import pytest
 
 import synth
@@ -164,3 +165,51 @@ def test_scan_workspace_is_enough():
     same(idx.search(Q, k, workspace=ws), idx.search(Q, k, path="lut"))
     with pytest.raises(tq.TQError):
         idx.search(Q, k, workspace=ws[:small // 2 // 256 * 256])
+
+
+@pytest.mark.parametrize("kind,k,nq", [("flat", 10, 256), ("flat", 100, 225), ("tenants", 10, 256),
+                                       ("deleted", 10, 250), ("plus", 20, 256), ("flat", 10, 487)])
+def test_wide_passes(kind, k, nq):
+    """340,000 vectors and more than 224 queries take a wide pass (and leave a
+    rest of 231 for another one); the ids and scores are the scan's."""
+    print("wide %s k=%d nq=%d" % (kind, k, nq), flush=True)
+    d, n, T = 256, 340_007, 10
+    g = torch.Generator(device="cuda").manual_seed(nq)
+    cb, rot = tq.Codebook(d, 4), tq.Rotation(d, 42)
+    c = torch.randn(500, d, generator=g, device="cuda")
+    X = torch.randn(n, d, generator=g, device="cuda") * 0.5 + c[torch.randint(500, (n,), generator=g, device="cuda")]
+    Q = torch.randn(nq, d, generator=g, device="cuda") * 0.5 + c[torch.randint(500, (nq,), generator=g, device="cuda")]
+    ten = torch.randint(T, (n,), generator=g, device="cuda").to(torch.int16)
+    idx = (tq.IdMapIndex if kind == "deleted" else tq.Index)(cb, rot, T)
+    if kind == "plus":
+        idx.calibrate(X[:5000])
+    if kind == "deleted":
+        idx.add(X, range(n), ten)
+        idx.remove(np.arange(0, n, 7))
+    else:
+        idx.add(X, ten)
+    allow = torch.randint(1, 1 << T, (nq, 1), generator=g, device="cuda") if kind == "tenants" else None
+    a_i, a_s = idx.search(Q, k, allow=allow)
+    b_i, b_s = idx.search(Q, k, allow=allow, path="lut")
+    assert torch.equal(a_i, b_i) and torch.equal(a_s, b_s)
+
+
+@pytest.mark.parametrize("bits,d,n,nq", [(4, 1536, 5000, 33), (4, 1536, 5000, 224), (2, 512, 4100, 257), (3, 128, 9001, 300),
+                                         (8, 640, 3001, 95), (8, 128, 700, 65)])
+@pytest.mark.parametrize("filt", [False, True])
+def test_groups_of_tiles(bits, d, n, nq, filt):
+    """More than one tile of 32 queries, whole and ragged, up to more than the
+    8 tiles of a group; the ids and scores are the scan's."""
+    print("groups b=%d d=%d n=%d nq=%d filt=%d" % (bits, d, n, nq, filt), flush=True)
+    T = 70
+    g = torch.Generator(device="cuda").manual_seed(n + nq)
+    cb, rot = tq.Codebook(d, bits), tq.Rotation(d, 42)
+    X = torch.randn(n, d, generator=g, device="cuda")
+    Q = torch.randn(nq, d, generator=g, device="cuda")
+    idx = tq.Index(cb, rot, T)
+    idx.add(X, torch.randint(T, (n,), generator=g, device="cuda").to(torch.int16))
+    allow = torch.randint(-(1 << 60), 1 << 60, (nq, 2), generator=g, device="cuda") if filt else None
+    for k in (1, 10, 100):
+        a_i, a_s = idx.search(Q, k, allow=allow)
+        b_i, b_s = idx.search(Q, k, allow=allow, path="lut")
+        assert torch.equal(a_i, b_i) and torch.equal(a_s, b_s), k
