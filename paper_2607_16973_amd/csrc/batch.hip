@@ -68,7 +68,6 @@ constexpr int kSelBound = 0;       // candidates + a bound amin on every other v
 constexpr int kSelOverflow = 1;    // no usable candidates: the query is not certified
 constexpr int kSelAll = 2;         // every vector is a candidate
 constexpr int MF_THREADS = 768;    // 12 waves: three per SIMD, 168 registers each
-constexpr int kTableBytes = 256 * 32 * 4;   // byte table, 32 replicas
 constexpr int SEL_THREADS = 256;
 constexpr int kTicketStride = 32;  // ints between two workgroups' ticket counters (own 128 B line)
 // Last word of a raw buffer resource (stride 0, byte offsets): 32-bit data
@@ -1316,7 +1315,13 @@ __global__ __launch_bounds__(kTableThreads) void rescore_kernel(RescoreParams p)
             __syncthreads();
             if (wave == 0) {
                 float facc = C;
-                for (int c = 0; c < p.chunks; ++c) facc += part[c * 64 + lane];
+                for (int c = 0; c < p.chunks; c += 4) {   // whole rings of 4 chunks
+                    float t[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) t[u] = part[(c + u) * 64 + lane];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) facc += t[u];
+                }
                 const bool in = vr != INT_MAX;
                 sort_run(r, in ? facc * p.scales[vr] : -INFINITY, vr);
             }
@@ -1497,24 +1502,27 @@ constexpr int WD_NH = WD_WAVES / WD_NG;        // query halves (wave w: half w /
 // Slab buffers in LDS per query-slot count.  A slab holds the chunk's QF
 // query pieces (pieces 0..QF-1) and the chunk of each of the tile's 4 blocks
 // (pieces QF..QF+3), 1 KiB each; piece i is loaded by wave i % 8 as its
-// (i / 8)-th load and stored at position (i % 8) DW + i / 8, so that each
-// wave's pieces are contiguous (one LDS base per wave and slab; DW = the
-// most loads a wave makes per slab).  NB buffers hold the slab being
+// (i / 8)-th load and stored among the wave's pieces, which are contiguous
+// (one LDS base per wave and slab).  NB buffers hold the slab being
 // multiplied, the next one (whose codes are turned into operands meanwhile)
-// and NB - 2 in flight.
+// and NB - 2 in flight; four of 20 KiB leave room for a table of 64 replicas,
+// whose lookups take one vector instruction instead of two.
 template <int QW>
 struct WideShape {
     static constexpr int QP = QW * WD_NH;
     static constexpr int QF = QP / 16;                 // query pieces of a slab
     static constexpr int NI = QF + WD_NG;              // 1 KiB pieces of a slab
-    static constexpr int DW = (NI + WD_WAVES - 1) / WD_WAVES;
-    static constexpr int SU = WD_WAVES * DW * 64;      // uint4 of a slab
-    static constexpr int NB = 5;                       // slab buffers
+    static constexpr int DW = (NI + WD_WAVES - 1) / WD_WAVES;   // most loads of a wave per slab
+    static constexpr int DH = NI - (DW - 1) * WD_WAVES;         // waves that make so many (the others one fewer)
+    static constexpr int SU = NI * 64;                 // uint4 of a slab
+    static constexpr int NB = 4;                       // slab buffers
+    static constexpr int NR = 64;                      // table replicas
     static constexpr int PD = NB - 1;                  // slabs requested ahead
-    static constexpr size_t lds = kTableBytes + (size_t)NB * SU * 16 + 2 * 1024 +
+    static constexpr size_t lds = 256 * NR * 4 + (size_t)NB * SU * 16 + 2 * 1024 +
                                   4 * (size_t)QP * 4;
     // uint4 offset of piece i within a slab
-    static constexpr int pos(int i) { return ((i % WD_WAVES) * DW + i / WD_WAVES) * 64; }
+    static constexpr __host__ __device__ int first(int wave) { return wave * (DW - 1) + (wave < DH ? wave : DH); }
+    static constexpr __host__ __device__ int pos(int i) { return (first(i % WD_WAVES) + i / WD_WAVES) * 64; }
 };
 
 template <int QW, bool PILOT, bool FILT>
@@ -1529,8 +1537,9 @@ __global__ __launch_bounds__(WD_THREADS) void wide_scores_kernel(WideParams p) {
     constexpr int DHI = (NI + WD_WAVES - 1) / WD_WAVES, NHI = NI - (DHI - 1) * WD_WAVES;
     static_assert(PD >= 2, "the next slab must be present a step ahead");
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    uint32_t *T = reinterpret_cast<uint32_t *>(smem);                 // byte table x 32
-    uint4 *slab = reinterpret_cast<uint4 *>(smem + kTableBytes);      // [NB][SU]
+    constexpr int NR = WS::NR;
+    uint32_t *T = reinterpret_cast<uint32_t *>(smem);                 // byte table x NR
+    uint4 *slab = reinterpret_cast<uint4 *>(smem + 256 * NR * 4);     // [NB][SU]
     float *sclv = reinterpret_cast<float *>(slab + NB * SU);           // [2][256] tile scales
     float *fq = sclv + 512;                                            // [QP]
     float *th = fq + QP;                                               // [QP]
@@ -1553,8 +1562,8 @@ __global__ __launch_bounds__(WD_THREADS) void wide_scores_kernel(WideParams p) {
         return (j / r) * p.pstride + 1 + j % r;
     };
 
-    for (int e = tid; e < 256 * 32; e += WD_THREADS) {
-        const int v = e >> 5;
+    for (int e = tid; e < 256 * NR; e += WD_THREADS) {
+        const int v = e / NR;
         const uint32_t lo = __builtin_bit_cast(uint16_t, (_Float16)p.cents[v & 15]);
         const uint32_t hi = __builtin_bit_cast(uint16_t, (_Float16)p.cents[v >> 4]);
         T[e] = lo | (hi << 16);
@@ -1566,7 +1575,8 @@ __global__ __launch_bounds__(WD_THREADS) void wide_scores_kernel(WideParams p) {
         cnt[q] = 0;
     }
     if (my_tiles > 0) {
-        const uint32_t lb = (uint32_t)(lane & 31) * 4;
+        const uint32_t lb = (uint32_t)(lane & (NR - 1)) * 4;
+        const uint32_t lo16 = (uint32_t)lane * 16;
         const uint32_t slab_lds = (uint32_t)(uintptr_t)slab;
         const uint32_t scl_lds = (uint32_t)(uintptr_t)sclv;
         // this wave's loads of a slab: DHI of them for waves below NHI
@@ -1578,18 +1588,18 @@ __global__ __launch_bounds__(WD_THREADS) void wide_scores_kernel(WideParams p) {
         // i = 8j + wave, stored at this wave's base + j KiB); request_base
         // first, once per slab
         auto request_base = [&]() {
-            set_lds_base(slab_lds + (uint32_t)ld_b * (SU * 16) + (uint32_t)(wave * WS::DW) * 1024);
+            set_lds_base(slab_lds + (uint32_t)ld_b * (SU * 16) + (uint32_t)WS::first(wave) * 1024);
         };
         auto request_part = [&](auto J) {
             constexpr int j = decltype(J)::value;
             const int i = j * WD_WAVES + wave;
             if (i < NI) {   // uniform
                 if (i < QF) {
-                    lds_dma16_at<j, false>(p.qfrag + (int64_t)ld_c * QU + i * 64 + lane);
+                    lds_dma16_s_at<j, false>(lo16, p.qfrag + (int64_t)ld_c * QU + i * 64);
                 } else {
                     int64_t b = ld_tile * NG + (i - QF);
                     b = b < p.nblk ? b : p.nblk - 1;
-                    lds_dma16_at<j, true>(p.codes + (b * CH + ld_c) * 64 + lane);
+                    lds_dma16_s_at<j, true>(lo16, p.codes + (b * CH + ld_c) * 64);
                 }
             }
         };
@@ -1628,21 +1638,21 @@ __global__ __launch_bounds__(WD_THREADS) void wide_scores_kernel(WideParams p) {
         // of vectors 0..31 in lanes 0..31 and word 1 of the same vectors in
         // lanes 32..63 (first result), and words 0, 1 of vectors 32..63 the
         // same way (second); likewise (w2, w3) for the second k-half.
-        half8 bcur[4];
+        half8 bop[2][4];   // of the current and the next step, in turn
         auto operands = [&](const uint4 *sb, half8 (&b)[4]) {
             const uint4 w = sb[WS::pos(QF + g) + lane];
             const auto k0 = __builtin_amdgcn_permlane32_swap(w.x, w.y, false, false);
             const auto k1 = __builtin_amdgcn_permlane32_swap(w.z, w.w, false, false);
-            b[0] = dequant8<32>(k0[0], lb);   // vectors 0..31, k-half 0
-            b[1] = dequant8<32>(k1[0], lb);   // vectors 0..31, k-half 1
-            b[2] = dequant8<32>(k0[1], lb);   // vectors 32..63, k-half 0
-            b[3] = dequant8<32>(k1[1], lb);   // vectors 32..63, k-half 1
+            b[0] = dequant8<NR>(k0[0], lb);   // vectors 0..31, k-half 0
+            b[1] = dequant8<NR>(k1[0], lb);   // vectors 0..31, k-half 1
+            b[2] = dequant8<NR>(k0[1], lb);   // vectors 32..63, k-half 0
+            b[3] = dequant8<NR>(k1[1], lb);   // vectors 32..63, k-half 1
         };
 #pragma unroll 1
         for (int x = 0; x < PD; ++x) request();
         wait_slabs(std::integral_constant<int, PD - 1>());
         lds_barrier();
-        operands(slab, bcur);
+        operands(slab, bop[0]);
         // this wave's A operands of a slab: fragment 2t + ks of its query half
         half8 acur[2 * QT];
         auto a_operands = [&](const uint4 *sb) {
@@ -1788,8 +1798,9 @@ __global__ __launch_bounds__(WD_THREADS) void wide_scores_kernel(WideParams p) {
             }
             clear_acc();
         };
-        for (;;) {
-            for (int c = 0; c < CH; ++c) {
+        // one step, with operands bcur; the next one's go to bnext
+        auto step = [&](const half8 (&bcur)[4], half8 (&bnext)[4]) {
+            {
                 // the next step's slab has landed (own loads), then everyone's;
                 // every wave is done with the buffer the new request overwrites
                 wait_slabs(std::integral_constant<int, PD - 2>());
@@ -1800,7 +1811,7 @@ __global__ __launch_bounds__(WD_THREADS) void wide_scores_kernel(WideParams p) {
                 // groups so that they overlap the matrix cores' work
                 buf = buf + 1 == NB ? 0 : buf + 1;
                 const uint4 wn = slab[buf * SU + WS::pos(QF + g) + lane];
-                half8 bnext[4];
+                const half8 *an = reinterpret_cast<const half8 *>(slab + buf * SU) + lane;
                 // k-half outer, so that the two products into one accumulator
                 // are 2 QT products apart (a product waits for the previous
                 // one into the same accumulator to finish)
@@ -1815,10 +1826,10 @@ __global__ __launch_bounds__(WD_THREADS) void wide_scores_kernel(WideParams p) {
                         if (grp == 0) {
                             const auto k0 = __builtin_amdgcn_permlane32_swap(wn.x, wn.y, false, false);
                             const auto k1 = __builtin_amdgcn_permlane32_swap(wn.z, wn.w, false, false);
-                            bnext[0] = dequant8<32>(k0[0], lb);
-                            bnext[1] = dequant8<32>(k1[0], lb);
-                            bnext[2] = dequant8<32>(k0[1], lb);
-                            bnext[3] = dequant8<32>(k1[1], lb);
+                            bnext[0] = dequant8<NR>(k0[0], lb);
+                            bnext[1] = dequant8<NR>(k1[0], lb);
+                            bnext[2] = dequant8<NR>(k0[1], lb);
+                            bnext[3] = dequant8<NR>(k1[1], lb);
                         }
                         if (grp == 1) {
                             request_base();
@@ -1828,17 +1839,24 @@ __global__ __launch_bounds__(WD_THREADS) void wide_scores_kernel(WideParams p) {
                             if (grp == 2) request_part(std::integral_constant<int, 1>());
                         if constexpr (DHI > 2)
                             if (grp == 3) request_part(std::integral_constant<int, 2>());
+                        // the next slab's A operands, as soon as the tile's
+                        // last product has been issued
+                        if (ks == 1) {
+                            acur[2 * t] = an[WS::pos(h * 2 * QT + 2 * t)];
+                            acur[2 * t + 1] = an[WS::pos(h * 2 * QT + 2 * t + 1)];
+                        }
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 // loads that found no group after them
                 if constexpr (DHI > 1 && 2 * QT <= 2) request_part(std::integral_constant<int, 1>());
                 if constexpr (DHI > 2 && 2 * QT <= 3) request_part(std::integral_constant<int, 2>());
                 request_done();
-                // the next slab's A operands, read now so that they arrive
-                // while this wave waits at the next barrier
-                a_operands(slab + buf * SU);
-#pragma unroll
-                for (int m = 0; m < 4; ++m) bcur[m] = bnext[m];
+            }
+        };
+        for (;;) {
+            for (int c = 0; c < CH; c += 2) {   // CH is even
+                step(bop[0], bop[1]);
+                step(bop[1], bop[0]);
             }
             epilogue();
             if (++ti == my_tiles) break;
@@ -1846,7 +1864,7 @@ __global__ __launch_bounds__(WD_THREADS) void wide_scores_kernel(WideParams p) {
             // the next step's operands again (its slab stays in place until the
             // next request): not held in registers across the epilogue
             a_operands(slab + buf * SU);
-            operands(slab + buf * SU, bcur);
+            operands(slab + buf * SU, bop[0]);
         }
     }
     if (!PILOT) {

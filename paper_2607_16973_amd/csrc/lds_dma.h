@@ -32,6 +32,15 @@ __device__ inline void lds_dma16_at(const void *src) {
     else
         asm volatile("global_load_lds_dwordx4 %0, off offset:%1" :: "v"(s), "i"(K * 1024) : "memory");
 }
+// The same with a uniform source base and a 32-bit lane byte offset.
+template <int K, bool NT>
+__device__ inline void lds_dma16_s_at(uint32_t voff, const void *sbase) {
+    const char *s = static_cast<const char *>(sbase) - K * 1024;
+    if constexpr (NT)
+        asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2 nt" :: "v"(voff), "s"(s), "i"(K * 1024) : "memory");
+    else
+        asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2" :: "v"(voff), "s"(s), "i"(K * 1024) : "memory");
+}
 // One load with a uniform source base and a 32-bit lane byte offset (the
 // scalar-base form: no 64-bit address arithmetic per lane); lane l's 16
 // bytes at sbase + voff go to LDS byte address lds_base + 16 l.
