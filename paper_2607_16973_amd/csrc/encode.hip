@@ -1,8 +1,8 @@
 // Rotation + quantisation of float32 rows on gfx950 (section II-B, steps 1-5).
 //
 // Pipeline per chunk of rows:
-//  0. split_rows_kernel: the exact row norm n = sqrt(sum_k x_k^2) (sequential
-//     float64 over k), a report of non-finite inputs, and every row scaled by
+//  0. split_rows_kernel: the row norm n = sqrt(sum_k x_k^2) (float64, see
+//     kSumEps), a report of non-finite inputs, and every row scaled by
 //     a power of two 2^e (n 2^e in [2^15, 2^16) / 1.02) and split into two
 //     float16 parts, x 2^e = xh + xl (1 + eps).  The rotation is split the
 //     same way once, R 2^15 = Rh + Rl (1 + eps).
@@ -34,8 +34,8 @@
 //     falls back to the sequential order where that decides the code, with
 //     many (b = 8, about 3% of coordinates) each tile stages its X and R
 //     slabs in LDS once for all of its flags.
-//  3. pack: per row, scale = n / sqrt(sum_j fl64(c_code_j^2)) (sequential
-//     float64 over j) and the codes are written in the canonical bitstream
+//  3. pack: per row, scale = n / sqrt(sum_j fl64(c_code_j^2)) (float64, as by
+//     sequential sums: kSumEps) and the codes are written in the canonical bitstream
 //     and/or the index's blocked layout.
 // With TQ+ calibration (section II-B) coordinate j is coded against its own
 // thresholds fl64(a_ij n), a_ij = fl64(mu_j + fl64(kappa_j t_i)), and the
@@ -259,16 +259,48 @@ __global__ __launch_bounds__(256) void split_rotation_kernel(const float *__rest
     split_store(src[0], src[1], kRotScale, planes, split_at(row, piece >> 1, piece & 1, 0, d));
 }
 
+// Norms.  The definition's norm n is the square root of the sum of squares
+// added in k order in float64, a chain of d dependent additions.  A sum in any
+// other order is within d 2^-53 (2.3e-13 at most) of the exact one like it (all
+// terms are positive), so the two norms are within 2.3e-13 of each other
+// relatively, and scales, with two such sums, within kSumEps.  The encoder works with parallel sums and
+// repeats the chains where a result could depend on it: a scale whose
+// float32 rounding differs within the margin (scale_of; about one row in
+// 60,000), a coordinate as close to a threshold (fixup).  The chains took 5 us
+// of latency per group of rows, 11 where one wave converted for them.
+constexpr double kSumEps = 5e-13;
+
+// The definition's norm of a row.
+__device__ inline double exact_norm(const float *__restrict__ x, int d) {
+    constexpr int B = 16;   // pieces of 4 loaded together (d is a multiple of 64)
+    double s2 = 0.0;
+    for (int k = 0; k < d; k += 4 * B) {
+        f4 v[B];
+#pragma unroll
+        for (int u = 0; u < B; ++u) v[u] = *reinterpret_cast<const f4 *>(x + k + 4 * u);
+#pragma unroll
+        for (int u = 0; u < B; ++u)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)   // the square is exact: fused or not
+                s2 = __builtin_fma((double)v[u][c], (double)v[u][c], s2);
+    }
+    return std::sqrt(s2);
+}
+// n / sqrt(h2) as float32, and whether every pair within kSumEps of these
+// rounds to the same.
+__device__ inline bool scale_of(double n, double h2, float &s) {
+    const double q = n / std::sqrt(h2);
+    s = (float)q;
+    return (float)(q * (1.0 - kSumEps)) == (float)(q * (1.0 + kSumEps));
+}
+
 // Norms and split panels of 8 rows per workgroup (rows m .. up to a multiple
 // of 32: zeros).  The rows are read once into LDS (padded by one 16-byte
-// piece, so that the 8 rows' pieces lie in distinct banks); two rows per
-// wave are summed in parallel for the row's exponent e, then lanes 0..7 of
-// wave 0 add the squares in k order in float64 (x^2 is exact in float64, so
-// the fused multiply-add rounds exactly as add(fl(x^2))) while the other
-// waves split.  Three workgroups fit a compute unit, so one workgroup's sequential
-// sums (about 5 us at d = 1536) overlap the others' loads.  A non-finite
-// input makes the sum non-finite (x^2 of a finite float32 cannot overflow
-// float64), which sets *status.
+// piece, so that the 8 rows' pieces lie in distinct banks), a wave sums two
+// rows, and all split: bound by the 8 bytes that are read and written per
+// coordinate (32,768 rows at d = 1536: 68 us, 5.9 TB/s; 110 us with the
+// norm's chain in the kernel).  A non-finite input makes the sum non-finite (x^2 of a finite
+// float32 cannot overflow float64), which sets *status.
 constexpr int SR_ROWS = 8;
 constexpr int SR_THREADS = 256;
 __global__ __launch_bounds__(SR_THREADS) void split_rows_kernel(
@@ -310,51 +342,22 @@ __global__ __launch_bounds__(SR_THREADS) void split_rows_kernel(
         }
         for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
         if (lane == 0) {
-            const double n = std::sqrt(s);   // within 1e-13 of the norm
+            const double n = std::sqrt(s);
             const bool ok = n > 0.0 && std::isfinite(n);
             const int e = ok ? 15 - ilogb(n * 1.02) : 0;
             exps[r] = e;
+            if (r0 + r < m) {
+                norms[r0 + r] = n;
+                if (!std::isfinite(s)) atomicOr(status, 1);
+            }
             if (r0 + r < m) inv[r0 + r] = ok ? (float)(1.0 / ldexp(n, e + kRotScale)) : 0.f;
         }
     }
     __syncthreads();
-    if (wave == 0) {
-        if (lane < SR_ROWS) {
-            const float *x = xs + lane * ps;
-            // 8 pieces in registers while the 8 before are summed (pq is a
-            // multiple of 16); the last read is of the last pieces again
-            f4 va[8], vb[8];
-            auto load = [&](int q, f4(&v)[8]) {
-#pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const f4 *>(x + 4 * (q + u));
-            };
-            double s2 = 0.0;
-            auto sum = [&](const f4(&v)[8]) {
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) s2 = __builtin_fma((double)v[u][c], (double)v[u][c], s2);
-            };
-            load(0, va);
-            for (int q = 0; q < pq; q += 16) {
-                load(q + 8, vb);
-                __builtin_amdgcn_sched_barrier(0);
-                sum(va);
-                load(q + 16 < pq ? q + 16 : q + 8, va);
-                __builtin_amdgcn_sched_barrier(0);
-                sum(vb);
-            }
-            if (r0 + lane < m) {
-                norms[r0 + lane] = std::sqrt(s2);
-                if (!std::isfinite(s2)) atomicOr(status, 1);
-            }
-        }
-    } else {
-        for (int e = tid - 64; e < SR_ROWS * (d / 8); e += SR_THREADS - 64) {
-            const int r = e & 7, piece = e >> 3;
-            const f4 *x = reinterpret_cast<const f4 *>(xs + r * ps + piece * 8);
-            split_store(x[0], x[1], exps[r], planes, split_at(r0 + r, piece >> 1, piece & 1, 0, d));
-        }
+    for (int e = tid; e < SR_ROWS * (d / 8); e += SR_THREADS) {
+        const int r = e & 7, piece = e >> 3;
+        const f4 *x = reinterpret_cast<const f4 *>(xs + r * ps + piece * 8);
+        split_store(x[0], x[1], exps[r], planes, split_at(r0 + r, piece >> 1, piece & 1, 0, d));
     }
 }
 
@@ -686,10 +689,10 @@ __device__ inline int exact_code(double S, double nrm, int j, int d, const doubl
 // Exact recomputation of flagged coordinates (b <= 4).  One wave per flag
 // (the list tile's flags w, w + 4, ... for wave w) adds the coordinate's
 // products in float64 in parallel: every product is exact, so that sum and
-// the definition's sequential one differ by at most 2 gamma_d n < 1e-12 n.
+// the definition's sequential one differ by at most 2 gamma_d n < kSumEps n.
 // If no threshold lies that close, both give the same code; otherwise (about
-// one flag in a million) the wave repeats the sum in k order from its
-// registers.  Bound by the 12 KiB of X and R a flag reads (68,000 flags of
+// one flag in a million) the wave repeats the sum, and the norm's, in k order
+// from its registers.  Bound by the 12 KiB of X and R a flag reads (68,000 flags of
 // 32,768 rows at d = 1536: 128 us, 6.4 TB/s); one lane per flag summing in k
 // order took 47 us for 400 flags, this takes 11.
 constexpr int FX_WAVES = 4;
@@ -727,27 +730,34 @@ __global__ __launch_bounds__(FX_WAVES * 64) void fixup_flag_kernel(
                 r[u] = *reinterpret_cast<const f4 *>(rr + 4 * q);
             }
         }
-        const double nrm = norms[row];
+        double nrm = norms[row];
         double S = 0.0;
 #pragma unroll
         for (int u = 0; u < FX_PC; ++u)
 #pragma unroll
             for (int c = 0; c < 4; ++c) S = __builtin_fma((double)r[u][c], (double)x[u][c], S);
         for (int o = 32; o > 0; o >>= 1) S += __shfl_xor(S, o, 64);
-        const double eps = 1e-12 * nrm;
+        const double eps = 2 * kSumEps * nrm;   // of S, and of the thresholds' norm
         int code = exact_code(S + eps, nrm, j, d, bounds, athr, levels);
         if (code != exact_code(S - eps, nrm, j, d, bounds, athr, levels) || !std::isfinite(S)) {
-            double T = 0.0;
+            double T = 0.0, T2 = 0.0;
 #pragma unroll
             for (int u = 0; u < FX_PC; ++u) {
-                double p[4];
+                double p[4], p2[4];
 #pragma unroll
-                for (int c = 0; c < 4; ++c) p[c] = (double)r[u][c] * (double)x[u][c];
+                for (int c = 0; c < 4; ++c) {
+                    p[c] = (double)r[u][c] * (double)x[u][c];
+                    p2[c] = (double)x[u][c] * (double)x[u][c];
+                }
                 const int nl = pq - 64 * u < 64 ? pq - 64 * u : 64;
                 for (int l = 0; l < nl; ++l)
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) T = T + __shfl(p[c], l, 64);
+                    for (int c = 0; c < 4; ++c) {
+                        T = T + __shfl(p[c], l, 64);
+                        T2 = T2 + __shfl(p2[c], l, 64);
+                    }
             }
+            nrm = std::sqrt(T2);
             code = exact_code(T, nrm, j, d, bounds, athr, levels);
         }
         if (lane == 0) codes_tmp[row * d + j] = (uint8_t)code;
@@ -815,23 +825,30 @@ __global__ __launch_bounds__(GEMM_THREADS) void fixup_tile_kernel(
         if (active) {
             const int64_t row = row0 + lr;
             const int j = col0 + lc;
-            codes_tmp[row * d + j] = (uint8_t)exact_code(S, norms[row], j, d, bounds, athr, levels);
+            const double nrm = norms[row], eps = kSumEps * nrm;
+            int code = exact_code(S + eps, nrm, j, d, bounds, athr, levels);
+            if (code != exact_code(S - eps, nrm, j, d, bounds, athr, levels))   // the norm's last bits decide
+                code = exact_code(S, exact_norm(X + row * d, d), j, d, bounds, athr, levels);
+            codes_tmp[row * d + j] = (uint8_t)code;
         }
     }
 }
 
-// Packs one row per thread, 64 rows per one-wave workgroup, for the bit
-// widths whose 16-byte blocked chunk holds 128 / BITS codes as 4 words of
-// 32 / BITS codes (BITS in {1, 2, 4, 8}; the canonical words are the same
-// words): each lane walks its row's chunks in j order, adds fl64(c_code^2)
-// (or the calibrated reconstruction's square) to the scale sum of the
-// definition in j order, and writes the chunk's 16 bytes to the canonical
-// and blocked layouts.  Every row of a chunk of rows is in flight at once,
-// so the sequential sums (one dependent float64 add per code) overlap; the
-// next 64 codes and more are loaded while as many are summed.
+// Packs 16 rows per workgroup, for the bit widths whose 16-byte blocked chunk
+// holds 128 / BITS codes as 4 words of 32 / BITS codes (BITS in {1, 2, 4, 8};
+// the canonical words are the same words): thread (row, c) takes the row's
+// chunks c, c + 16, ..., adds their part of the scale's sum of fl64(c_code^2)
+// (or the calibrated reconstruction's square) and writes each chunk's 16
+// bytes to the canonical and blocked layouts (there 16 rows are 256 adjacent
+// bytes).  The 16 parts are added in LDS.  For a row whose scale could depend
+// on the order the workgroup stages the terms in LDS and one thread each
+// repeats the definition's two chains.  257 rows at d = 1536 and 4 bits take
+// 8 us (22 us with a row's chain per thread); 32,768 rows 39, of which about 15
+// are such a row's chains in every second chunk of rows (30).
+constexpr int PR_ROWS = 16;
 template <int BITS>
-__global__ __launch_bounds__(64) void pack_rows_kernel(
-    const uint8_t *__restrict__ codes_tmp, int64_t m, int d,
+__global__ __launch_bounds__(256) void pack_rows_kernel(
+    const uint8_t *__restrict__ codes_tmp, const float *__restrict__ X, int64_t m, int d,
     const double *__restrict__ cent_sq, const double *__restrict__ ysq,
     const double *__restrict__ norms,
     uint8_t *__restrict__ canon, float *__restrict__ scales,
@@ -841,75 +858,93 @@ __global__ __launch_bounds__(64) void pack_rows_kernel(
     constexpr int CPC = 128 / BITS;   // codes per chunk
     constexpr int LPC = CPC / 16;     // 16-byte loads of one-byte codes per chunk
     constexpr int PER = 32 / BITS;    // codes per word
-    constexpr int G = LPC >= 4 ? 1 : 4 / LPC;
     __shared__ double csq_s[L];
-    const int lane = threadIdx.x;
-    for (int i = lane; i < L; i += 64) csq_s[i] = ysq ? 0.0 : cent_sq[i];
+    __shared__ double part[16][PR_ROWS];
+    __shared__ double sq_s[2048];   // a row's terms
+    __shared__ float x_s[2048];
+    __shared__ double chain_s[2];
+    __shared__ int nredo;
+    __shared__ int redo[PR_ROWS];
+    const int tid = threadIdx.x, rl = tid & (PR_ROWS - 1), cg = tid / PR_ROWS;
+    for (int i = tid; i < L; i += 256) csq_s[i] = ysq ? 0.0 : cent_sq[i];
     __syncthreads();
-    const int64_t r = (int64_t)blockIdx.x * 64 + lane;
-    if (r >= m) return;
-    const uint4 *src = reinterpret_cast<const uint4 *>(codes_tmp + r * d);
+    const int64_t r = (int64_t)blockIdx.x * PR_ROWS + rl;
+    const uint8_t *row = codes_tmp + (r < m ? r : 0) * d;
+    const uint4 *src = reinterpret_cast<const uint4 *>(row);
     const int64_t v = base + r;
-    uint8_t *bdst = blocked ? blocked + (v >> 6) * chunks * 1024 + (v & 63) * 16 : nullptr;
-    uint8_t *cdst = canon ? canon + r * (int64_t)(d * BITS / 8) : nullptr;
+    uint8_t *bdst = blocked && r < m ? blocked + (v >> 6) * chunks * 1024 + (v & 63) * 16 : nullptr;
+    uint8_t *cdst = canon && r < m ? canon + r * (int64_t)(d * BITS / 8) : nullptr;
     double h2 = 0.0;
-    auto run = [&](auto cal_t) {
-        constexpr bool CAL = decltype(cal_t)::value;
-        uint4 buf[2][G][LPC];   // a group of G chunks is loaded while one is summed
-        auto load = [&](int c0, uint4(&b)[G][LPC]) {
+    auto square = [&](int j, uint32_t code) { return ysq ? ysq[(int64_t)j * L + code] : csq_s[code]; };
+    for (int ch = cg; ch < chunks; ch += 16) {
+        uint4 cur[LPC];
 #pragma unroll
-            for (int g = 0; g < G; ++g) {
-                const int c = c0 + g < chunks ? c0 + g : chunks - 1;
+        for (int i = 0; i < LPC; ++i) cur[i] = src[ch * LPC + i];
+        uint32_t w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-                for (int i = 0; i < LPC; ++i) b[g][i] = src[c * LPC + i];
-            }
-        };
-        auto chunk = [&](int ch, const uint4(&cur)[LPC]) {
-            uint32_t w[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-            for (int t = 0; t < CPC; ++t) {
-                const uint4 &q = cur[t >> 4];
-                const int u = (t >> 2) & 3;
-                const uint32_t word = u == 0 ? q.x : u == 1 ? q.y : u == 2 ? q.z : q.w;
-                const uint32_t code = (word >> (8 * (t & 3))) & 255u;
-                w[t / PER] |= code << (BITS * (t % PER));
-                double sq;
-                if constexpr (CAL)
-                    sq = ysq[(int64_t)(ch * CPC + t) * L + code];
-                else
-                    sq = csq_s[code];
-                h2 = h2 + sq;
-            }
-            if (cdst) *reinterpret_cast<uint4 *>(cdst + ch * 16) = make_uint4(w[0], w[1], w[2], w[3]);
-            if (bdst) {
-                if (blocked_rotated(BITS))
-                    for (int u = 0; u < 4; ++u) w[u] = rotl2(w[u]);
-                *reinterpret_cast<uint4 *>(bdst + ch * 1024) = make_uint4(w[0], w[1], w[2], w[3]);
-            }
-        };
-        auto group = [&](int c0, const uint4(&b)[G][LPC]) {
-#pragma unroll
-            for (int g = 0; g < G; ++g)
-                if (c0 + g < chunks) chunk(c0 + g, b[g]);
-        };
-        load(0, buf[0]);
-        for (int c0 = 0; c0 < chunks; c0 += 2 * G) {
-            load(c0 + G, buf[1]);
-            __builtin_amdgcn_sched_barrier(0);
-            group(c0, buf[0]);
-            load(c0 + 2 * G, buf[0]);
-            __builtin_amdgcn_sched_barrier(0);
-            group(c0 + G, buf[1]);
+        for (int t = 0; t < CPC; ++t) {
+            const uint4 &q = cur[t >> 4];
+            const int u = (t >> 2) & 3;
+            const uint32_t word = u == 0 ? q.x : u == 1 ? q.y : u == 2 ? q.z : q.w;
+            const uint32_t code = (word >> (8 * (t & 3))) & 255u;
+            w[t / PER] |= code << (BITS * (t % PER));
+            h2 = h2 + square(ch * CPC + t, code);
         }
+        if (cdst) *reinterpret_cast<uint4 *>(cdst + ch * 16) = make_uint4(w[0], w[1], w[2], w[3]);
+        if (bdst) {
+            if (blocked_rotated(BITS))
+                for (int u = 0; u < 4; ++u) w[u] = rotl2(w[u]);
+            *reinterpret_cast<uint4 *>(bdst + ch * 1024) = make_uint4(w[0], w[1], w[2], w[3]);
+        }
+    }
+    part[cg][rl] = h2;
+    if (tid == 0) nredo = 0;
+    __syncthreads();
+    auto put = [&](int64_t row_, float s) {
+        if (scales) scales[row_] = s;
+        if (blocked_scales) blocked_scales[base + row_] = s;
     };
-    if (ysq)
-        run(std::true_type{});
-    else
-        run(std::false_type{});
-    const double nrm = norms[r];
-    const float s = (nrm == 0.0) ? 0.0f : (float)(nrm / std::sqrt(h2));
-    if (scales) scales[r] = s;
-    if (blocked_scales) blocked_scales[base + r] = s;
+    if (cg == 0 && r < m) {
+        for (int c = 1; c < 16; ++c) h2 += part[c][rl];
+        const double nrm = norms[r];
+        float s = 0.f;
+        if (nrm != 0.0 && !scale_of(nrm, h2, s)) redo[atomicAdd(&nredo, 1)] = rl;
+        else put(r, s);
+    }
+    __syncthreads();
+    const int nr = nredo;
+    for (int i = 0; i < nr; ++i) {
+        const int64_t rr = (int64_t)blockIdx.x * PR_ROWS + redo[i];
+        for (int j = tid; j < d; j += 256) {
+            x_s[j] = X[rr * d + j];
+            sq_s[j] = square(j, codes_tmp[rr * d + j]);
+        }
+        __syncthreads();
+        if (tid == 0) {
+            double s2 = 0.0;
+            for (int j = 0; j < d; j += 32) {   // 32 terms read together (d is a multiple of 64)
+                float t[32];
+#pragma unroll
+                for (int u = 0; u < 32; ++u) t[u] = x_s[j + u];
+#pragma unroll
+                for (int u = 0; u < 32; ++u) s2 = __builtin_fma((double)t[u], (double)t[u], s2);
+            }
+            chain_s[0] = std::sqrt(s2);
+        }
+        if (tid == 64) {
+            double s2 = 0.0;
+            for (int j = 0; j < d; j += 16) {
+                double t[16];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) t[u] = sq_s[j + u];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) s2 = s2 + t[u];
+            }
+            chain_s[1] = std::sqrt(s2);
+        }
+        __syncthreads();
+        if (tid == 0) put(rr, (float)(chain_s[0] / chain_s[1]));
+    }
 }
 
 // Packs PACK_ROWS rows per workgroup (3-bit codes): scale, canonical
@@ -920,7 +955,7 @@ __global__ __launch_bounds__(64) void pack_rows_kernel(
 constexpr int PACK_ROWS = 32;   // PACK_ROWS * (d + 16) bytes of LDS (66 KiB at d = 2048)
 
 __global__ __launch_bounds__(256) void pack_kernel(
-    const uint8_t *__restrict__ codes_tmp, int64_t m, int d, int bits,
+    const uint8_t *__restrict__ codes_tmp, const float *__restrict__ X, int64_t m, int d, int bits,
     const double *__restrict__ cent_sq, const double *__restrict__ ysq,
     const double *__restrict__ norms,
     uint8_t *__restrict__ canon, float *__restrict__ scales,
@@ -977,7 +1012,9 @@ __global__ __launch_bounds__(256) void pack_kernel(
             }
         }
         const double nrm = norms[r0 + tid];
-        const float s = (nrm == 0.0) ? 0.0f : (float)(nrm / std::sqrt(h2));
+        float s = 0.f;
+        if (nrm != 0.0 && !scale_of(nrm, h2, s))
+            s = (float)(exact_norm(X + (r0 + tid) * d, d) / std::sqrt(h2));
         if (scales) scales[r0 + tid] = s;
         if (blocked_scales) blocked_scales[base + r0 + tid] = s;
     }
@@ -1328,26 +1365,26 @@ hipError_t encode_rows(const float *X, int64_t n, int d, const float *R, const v
         if (e != hipSuccess) return e;
         uint8_t *canon_p = out.canonical ? out.canonical + r0 * (int64_t)(d * cb.bits / 8) : nullptr;
         float *scales_p = out.scales ? out.scales + r0 : nullptr;
-        const dim3 prow((unsigned)((m + 63) / 64));
+        const dim3 prow((unsigned)((m + PR_ROWS - 1) / PR_ROWS));
         if (cb.bits == 3) {
             const int packs = (int)((m + PACK_ROWS - 1) / PACK_ROWS);
             hipLaunchKernelGGL(pack_kernel, dim3(packs), dim3(256), PACK_ROWS * (d + 16), stream,
-                               codes_tmp, m, d, cb.bits, cent_sq, calib.ysq, norms, canon_p, scales_p,
+                               codes_tmp, X + r0 * d, m, d, cb.bits, cent_sq, calib.ysq, norms, canon_p, scales_p,
                                out.blocked, out.blocked_scales, out.base + r0, chunks);
         } else if (cb.bits == 1) {
-            hipLaunchKernelGGL(pack_rows_kernel<1>, prow, dim3(64), 0, stream, codes_tmp, m, d, cent_sq,
+            hipLaunchKernelGGL(pack_rows_kernel<1>, prow, dim3(256), 0, stream, codes_tmp, X + r0 * d, m, d, cent_sq,
                                calib.ysq, norms, canon_p, scales_p, out.blocked, out.blocked_scales,
                                out.base + r0, chunks);
         } else if (cb.bits == 2) {
-            hipLaunchKernelGGL(pack_rows_kernel<2>, prow, dim3(64), 0, stream, codes_tmp, m, d, cent_sq,
+            hipLaunchKernelGGL(pack_rows_kernel<2>, prow, dim3(256), 0, stream, codes_tmp, X + r0 * d, m, d, cent_sq,
                                calib.ysq, norms, canon_p, scales_p, out.blocked, out.blocked_scales,
                                out.base + r0, chunks);
         } else if (cb.bits == 4) {
-            hipLaunchKernelGGL(pack_rows_kernel<4>, prow, dim3(64), 0, stream, codes_tmp, m, d, cent_sq,
+            hipLaunchKernelGGL(pack_rows_kernel<4>, prow, dim3(256), 0, stream, codes_tmp, X + r0 * d, m, d, cent_sq,
                                calib.ysq, norms, canon_p, scales_p, out.blocked, out.blocked_scales,
                                out.base + r0, chunks);
         } else {
-            hipLaunchKernelGGL(pack_rows_kernel<8>, prow, dim3(64), 0, stream, codes_tmp, m, d, cent_sq,
+            hipLaunchKernelGGL(pack_rows_kernel<8>, prow, dim3(256), 0, stream, codes_tmp, X + r0 * d, m, d, cent_sq,
                                calib.ysq, norms, canon_p, scales_p, out.blocked, out.blocked_scales,
                                out.base + r0, chunks);
         }

@@ -237,3 +237,24 @@ def test_codes_do_not_depend_on_the_chunks(n):
     for a in range(0, n, 5000):
         c, s = tq.rotate_quantize(cb, rot, X[a:a + 5000].contiguous())
         assert torch.equal(c, codes[a:a + 5000]) and torch.equal(s, scales[a:a + 5000]), a
+
+
+@pytest.mark.parametrize("bits", [4, 3])
+def test_scales_where_the_order_of_sums_decides(rot_pair, bits):
+    """Among 300,000 rows about five have a scale whose float32 rounding
+    hangs on the order of the float64 sums; every scale is that of the
+    sequential sums, computed here by a sequential cumulative sum."""
+    print("scales by sequential sums bits=%d" % bits, flush=True)
+    d, n = 128, 300_000
+    rot, cb = tq.Rotation(d, 3), tq.Codebook(d, bits)
+    X = np.random.default_rng(bits).standard_normal((n, d)).astype(np.float32)
+    codes, scales = tq.rotate_quantize(cb, rot, torch.from_numpy(X).cuda())
+    c = oracle.unpack_codes(codes.cpu().numpy(), d, bits)
+    sq = (cb.cents * cb.cents)[c]
+    x2 = X.astype(np.float64) ** 2
+    n2, h2 = np.zeros(n), np.zeros(n)
+    for k in range(d):
+        n2 += x2[:, k]
+        h2 += sq[:, k]
+    want = (np.sqrt(n2) / np.sqrt(h2)).astype(np.float32)
+    assert np.array_equal(scales.cpu().numpy(), want)
