@@ -1140,7 +1140,8 @@ struct RescoreParams {
 //     order-free): bit-identical to the single-query scan's scores.  8-bit
 //     codes are summed in float32 chunk by chunk: for one run after the
 //     other, the waves compute the sums of every sixteenth chunk, which wave 0
-//     then adds in the scan's order (a wave per run over all chunks took 41 us).
+//     then adds in the scan's order.  A run takes 12 us of LDS reads, so the
+//     64 best come first, and their k-th exact score can end the loop.
 //  3. Waves 0..R-1 sort their 64 exact scores; an entry's rank is its lane
 //     plus, in every other sorted run, the number of entries ahead of it
 //     (binary search); ranks below k are written.
@@ -1181,7 +1182,8 @@ __global__ __launch_bounds__(kTableThreads) void rescore_kernel(RescoreParams p)
     int *run_i = reinterpret_cast<int *>(run_s + KC);
     int *kept = run_i + KC;                 // [KC] candidates that may be in the top k
     // [0] sorted entries, [1] k-th exact score, [2] certified, [3] list slot,
-    // [4] key of the k-th largest stored score, [5] kept, [6] candidates
+    // [4] key of the k-th largest stored score, [5] kept, [6] candidates,
+    // [7] 8 bits: key of the largest stored score after the first 64
     int *sh = kept + KC;
     const int q = blockIdx.x;
     if (scan_is_faster_for(p.gate, q, p.nqt, p.tile_q)) {
@@ -1215,6 +1217,7 @@ __global__ __launch_bounds__(kTableThreads) void rescore_kernel(RescoreParams p)
         sh[4] = INT_MAX;
         sh[5] = 0;
         sh[6] = 0;
+        sh[7] = fkey(-INFINITY);
     }
     __syncthreads();
     {
@@ -1222,7 +1225,10 @@ __global__ __launch_bounds__(kTableThreads) void rescore_kernel(RescoreParams p)
         const int j0 = tid / KC * LEN;
         int ahead = 0;
 #pragma unroll 4
-        for (int j = 0; j < LEN; ++j) ahead += run_s[j0 + j] > own;
+        for (int j = 0; j < LEN; ++j) {   // ranks without ties: stored scores often agree
+            const float o = run_s[j0 + j];
+            ahead += o > own || (o == own && j0 + j < ce);
+        }
         if (ahead) atomicAdd(&sums[ce], ahead);
     }
     __syncthreads();
@@ -1236,22 +1242,44 @@ __global__ __launch_bounds__(kTableThreads) void rescore_kernel(RescoreParams p)
     auto stored_err = [&](double x) {
         return ldexp(1.0, -11) * fabs(x) + ldexp(1.0, -25) * qi.norm + (double)qi.err;
     };
+    bool rest = false;
     if (tid < KC) {
         bool keep = cv != INT_MAX;
         if (qi.err < INFINITY && sh[6] >= p.k) {
             const double kth = (double)unfkey(sh[4]) * qi.norm, x = (double)own * qi.norm;
             keep = keep && x + stored_err(x) >= kth - stored_err(kth);
         }
-        const uint64_t m = __ballot(keep);
-        int at = 0;
-        if (lane == 0 && m) at = atomicAdd(&sh[5], (int)__popcll(m));
-        at = __shfl(at, 0) + (int)__popcll(m & ((1ull << lane) - 1));
-        if (keep) kept[at] = cv;
+        auto take = [&](bool in) {
+            const uint64_t m = __ballot(in);
+            int at = 0;
+            if (lane == 0 && m) at = atomicAdd(&sh[5], (int)__popcll(m));
+            at = __shfl(at, 0) + (int)__popcll(m & ((1ull << lane) - 1));
+            if (in) kept[at] = cv;
+        };
+        if constexpr (MODE == BYTE) {
+            // the 64 best first; [7]: the largest of the others
+            const bool first = keep && sums[ce] < 64;
+            take(first);
+            rest = keep && !first;
+            if (rest) atomicMax(&sh[7], fkey(own));
+        } else {
+            take(keep);
+        }
         sums[ce] = 0;
         run_s[ce] = -INFINITY;
         run_i[ce] = INT_MAX;
     }
     __syncthreads();
+    if constexpr (MODE == BYTE) {
+        if (tid < KC) {
+            const uint64_t m = __ballot(rest);
+            int at = 0;
+            if (lane == 0 && m) at = atomicAdd(&sh[5], (int)__popcll(m));
+            at = __shfl(at, 0) + (int)__popcll(m & ((1ull << lane) - 1));
+            if (rest) kept[at] = cv;
+        }
+        __syncthreads();
+    }
     const int nk = sh[5];
     int R = 1;                             // runs of 64 kept candidates
     while (R < S && 64 * R < nk) R *= 2;
@@ -1301,6 +1329,11 @@ __global__ __launch_bounds__(kTableThreads) void rescore_kernel(RescoreParams p)
     if constexpr (MODE == BYTE) {
         float *part = lds + kByteRepWords + p.d;   // [chunk][64]
         for (int r = 0; r < R; ++r) {
+            // the first run's k-th exact score may put all others out
+            if (r == 1 && p.k <= 64 && qi.err < INFINITY) {
+                const double x = (double)unfkey(sh[7]) * qi.norm;
+                if (x + stored_err(x) < (double)run_s[p.k - 1]) break;
+            }
             const int vr = r == 0 ? v : take_run(r);
             if (c0 < c1) {
                 if (r > 0) load_chunks(c0);

@@ -168,7 +168,7 @@ def test_scan_workspace_is_enough():
 
 
 @pytest.mark.parametrize("kind,k,nq", [("flat", 10, 256), ("flat", 100, 225), ("tenants", 10, 256),
-                                       ("deleted", 10, 250), ("plus", 20, 256), ("flat", 10, 487)])
+                                       ("deleted", 10, 250), ("plus", 20, 256), ("flat", 10, 487), ("ties", 10, 225)])
 def test_wide_passes(kind, k, nq):
     """340,000 vectors and more than 224 queries take a wide pass (and leave a
     rest of 231 for another one); the ids and scores are the scan's."""
@@ -179,6 +179,8 @@ def test_wide_passes(kind, k, nq):
     c = torch.randn(500, d, generator=g, device="cuda")
     X = torch.randn(n, d, generator=g, device="cuda") * 0.5 + c[torch.randint(500, (n,), generator=g, device="cuda")]
     Q = torch.randn(nq, d, generator=g, device="cuda") * 0.5 + c[torch.randint(500, (nq,), generator=g, device="cuda")]
+    if kind == "ties":      # more equal scores than any list holds: every query goes back to the scan
+        X = X[:1].expand(n, d).contiguous()
     ten = torch.randint(T, (n,), generator=g, device="cuda").to(torch.int16)
     idx = (tq.IdMapIndex if kind == "deleted" else tq.Index)(cb, rot, T)
     if kind == "plus":
@@ -213,3 +215,18 @@ def test_groups_of_tiles(bits, d, n, nq, filt):
         a_i, a_s = idx.search(Q, k, allow=allow)
         b_i, b_s = idx.search(Q, k, allow=allow, path="lut")
         assert torch.equal(a_i, b_i) and torch.equal(a_s, b_s), k
+
+
+def test_eight_bit_close_candidates():
+    """Clusters so tight that more than 64 candidates of a query lie within
+    the error of its tenth best, many with equal stored scores."""
+    print("8-bit close candidates", flush=True)
+    d, n, nq = 768, 60_000, 256
+    g = torch.Generator(device="cuda").manual_seed(8)
+    c = torch.randn(40, d, generator=g, device="cuda")
+    near = lambda m: torch.randn(m, d, generator=g, device="cuda") * 0.08 + c[torch.randint(40, (m,), generator=g, device="cuda")]
+    idx = tq.Index(tq.Codebook(d, 8), rotation(d))
+    idx.add(near(n))
+    Q = near(nq)
+    for k in (1, 5, 10, 64, 65):
+        same(idx.search(Q, k), idx.search(Q, k, path="lut"))
