@@ -8,7 +8,8 @@
 namespace tq {
 
 // Loads of 16 bytes per lane straight into LDS: set_lds_base(b), then
-// lds_dma16_at<K, NT>(src) puts lane l's 16 bytes from src at LDS byte
+// lds_dma16_s_at<K, NT>(voff, sbase) puts lane l's 16 bytes at sbase + voff (a
+// uniform base, a lane's byte offset) at LDS byte
 // address b + K KiB + 16 l (b wave-uniform).  The instruction offset moves
 // both addresses, so it is taken off the source first.  Setting the base
 // once per group of loads matters: a load must read M0 before it may change
@@ -24,15 +25,6 @@ __device__ inline void lds_dma16(const void *src, uint32_t lds_base) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
                  :: "s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(src) : "memory");
 }
-template <int K, bool NT>
-__device__ inline void lds_dma16_at(const void *src) {
-    const char *s = static_cast<const char *>(src) - K * 1024;
-    if constexpr (NT)
-        asm volatile("global_load_lds_dwordx4 %0, off offset:%1 nt" :: "v"(s), "i"(K * 1024) : "memory");
-    else
-        asm volatile("global_load_lds_dwordx4 %0, off offset:%1" :: "v"(s), "i"(K * 1024) : "memory");
-}
-// The same with a uniform source base and a 32-bit lane byte offset.
 template <int K, bool NT>
 __device__ inline void lds_dma16_s_at(uint32_t voff, const void *sbase) {
     const char *s = static_cast<const char *>(sbase) - K * 1024;
