@@ -1246,8 +1246,11 @@ __global__ __launch_bounds__(kTableThreads) void rescore_kernel(RescoreParams p)
     if (tid < KC) {
         bool keep = cv != INT_MAX;
         if (qi.err < INFINITY && sh[6] >= p.k) {
+            // only a comparison that holds puts a candidate out: stored scores
+            // past the float16 range (a TQ+ constant term far larger than the
+            // rest) are infinite, and with one of those as kth nothing is known
             const double kth = (double)unfkey(sh[4]) * qi.norm, x = (double)own * qi.norm;
-            keep = keep && x + stored_err(x) >= kth - stored_err(kth);
+            keep = keep && !(x + stored_err(x) < kth - stored_err(kth));
         }
         auto take = [&](bool in) {
             const uint64_t m = __ballot(in);
@@ -1422,8 +1425,8 @@ __global__ __launch_bounds__(kTableThreads) void rescore_kernel(RescoreParams p)
         const double amin = (double)amin_s * qi.norm;
         const double reach = amin + stored_err(amin);
         // an error bound that is not finite (scales or queries that are not)
-        // proves nothing
-        const bool cert = qi.err < INFINITY &&
+        // proves nothing, nor does a list shorter than the candidates allow
+        const bool cert = qi.err < INFINITY && nv >= (sh[6] < p.k ? sh[6] : p.k) &&
                           (st == kSelAll || (st == kSelBound && reach < (double)ek));
         sh[2] = cert;
     }

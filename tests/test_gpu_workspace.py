@@ -1,0 +1,45 @@
+"""Workspaces that are not the size the call would ask for: made for more
+queries, or for another path."""
+import pytest
+
+from tests.conftest import gpu_available
+
+pytestmark = pytest.mark.gpu
+if not gpu_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+import torch  # noqa: E402
+
+import paper_2607_16973_amd as tq  # noqa: E402
+
+D, N, K = 256, 340_007, 10   # from 333,334 vectors on 256 queries are a wide pass
+
+
+def rows(n, d, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    return torch.randn(n, d, generator=g, device="cuda")
+
+
+@pytest.fixture(scope="module")
+def index():
+    idx = tq.Index(tq.Codebook(D, 4), tq.Rotation(D, 42))
+    idx.add(rows(N, D, 1))
+    return idx
+
+
+@pytest.mark.parametrize("made_for", [256, 1000])
+@pytest.mark.parametrize("path", ["auto", "mfma"])
+def test_workspace_made_for_more_queries(index, made_for, path):
+    """One workspace for the largest batch serves every smaller one, on the
+    batched path (which writes past the room of the scan)."""
+    ws = torch.empty(index.workspace_bytes(made_for, K, path=path), dtype=torch.uint8, device="cuda")
+    Q = rows(256, D, 2)
+    for nq in (2, 33, 64, 65, 96, 97, 128, 160, 161, 224, 225, 256):
+        print("workspace for %d, %d queries, %s" % (made_for, nq, path), flush=True)
+        q = Q[:nq].contiguous()
+        lut = index.workspace_bytes(nq, K, path="lut")
+        ws.fill_(0xAB)
+        ids, scores = index.search(q, K, path=path, workspace=ws)
+        assert (ws[lut:] != 0xAB).any()
+        want = index.search(q, K, path="lut")
+        assert torch.equal(ids, want[0]) and torch.equal(scores, want[1])
