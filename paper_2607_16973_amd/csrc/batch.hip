@@ -118,7 +118,10 @@ struct QInfo {
 // The sum of all terms times s_max is the error before storage (the factor
 // 1.1 is margin only); the float16 storage of the approximate score adds at
 // most 2^-11 of its magnitude plus 2^-25 norm, accounted for where the
-// certificate is checked.
+// certificate is checked.  Relative errors say nothing about subnormal
+// results: a query whose norm is not within 2^+-100 (and not 0, where every
+// score is the exact 0 or s_v C) has an infinite bound, proves nothing and is
+// answered by the scan.
 __global__ void prep_kernel(const float *__restrict__ Q, const float *__restrict__ qconst, int nq,
                             int d, int bits, const float *smax_p,
                             float cmax16, float dmax, _Float16 *__restrict__ q16,
@@ -178,6 +181,9 @@ __global__ void prep_kernel(const float *__restrict__ Q, const float *__restrict
         for (int w = 0; w < SEL_THREADS / 64; ++w) se += red_1[w];
         const double smax = (double)*smax_p;
         double norm = smax * sqrt(s2);
+        // Below and above these the bounds do not hold as derived: subnormal
+        // scores are rounded to multiples of 2^-149, largest ones overflow
+        const bool in_range = norm == 0.0 || (norm >= ldexp(1.0, -100) && norm <= ldexp(1.0, 100));
         if (!(norm > 0.0)) norm = 1.0;
         const double u = ldexp(1.0, -24);
         const double gd = d * u / (1.0 - d * u);
@@ -192,7 +198,7 @@ __global__ void prep_kernel(const float *__restrict__ Q, const float *__restrict
         QInfo qi;
         qi.f = (float)(1.0 / ((double)alpha * norm));
         qi.norm = (float)norm;
-        qi.err = (float)(1.1 * smax * E);
+        qi.err = in_range ? (float)(1.1 * smax * E) : INFINITY;
         qi.c = (float)(C / norm);
         info[q] = qi;
     }

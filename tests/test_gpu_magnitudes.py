@@ -83,3 +83,19 @@ def test_narrow_calibration_small_tenants(bits):
     allow = torch.zeros(nq, words, dtype=torch.int64, device="cuda")
     allow[torch.arange(nq, device="cuda"), t >> 6] = torch.ones_like(t) << (t & 63)
     check(idx, rows(nq, d, 9), 10, allow=allow)
+
+
+# Scores that are subnormal (rounded to multiples of 2^-149, many equal), tiny
+# queries on tiny scales, and s_max ||q'|| above the largest float32.
+@pytest.mark.parametrize("bits", [2, 3, 4, 8])
+@pytest.mark.parametrize("n", [100, 20_011])
+@pytest.mark.parametrize("s,q", [(1e-43, 1.0), (3e-45, 1.0), (1e-11, 1e-32), (1e-30, 1.0), (1.0, 1e-36), (100.0, 1e37),
+                                 (1e30, 1e7), (0.0, 1.0)])
+def test_scales_and_queries(bits, n, s, q):
+    print("magnitudes b=%d n=%d s=%g q=%g" % (bits, n, s, q), flush=True)
+    d = 256
+    cb = tq.Codebook(d, bits)
+    codes, scales = tq.rotate_quantize(cb, rotation(d), rows(n, d, 11))
+    idx = tq.Index(cb, rotation(d))
+    idx.add_codes(codes, scales * s)
+    check(idx, rows(40, d, 12) * q, 10)
