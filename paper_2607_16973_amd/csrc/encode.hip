@@ -1415,7 +1415,9 @@ hipError_t rotate_rows_f32(const float *X, int64_t m, int d, const float *R, flo
         if (e != hipSuccess) return e;
     }
     if (m <= 0) return hipSuccess;
-    if (m <= kMidRows) {
+    // the direct loads into LDS want rows on 16-byte boundaries (d is a multiple
+    // of 64); rows elsewhere take the ordinary loads of rot_gemm
+    if (m <= kMidRows && (reinterpret_cast<uintptr_t>(X) & 15) == 0) {
         hipLaunchKernelGGL(rot_mid_kernel, dim3((unsigned)(d / 32), (unsigned)((m + 31) / 32)), dim3(256), 0,
                            stream, X, m, R, d, Y);
         return hipGetLastError();

@@ -195,6 +195,21 @@ def test_codes_of_rows_built_on_thresholds(rot_pair, bits):
     assert_scales_close(scales.cpu().numpy(), s_or)
 
 
+@pytest.mark.parametrize("n", [33, 65, 300, 2100])
+def test_query_rotation_of_rows_off_16_byte_boundaries(n):
+    print("query rotation, shifted rows n=%d" % n, flush=True)
+    d = 192
+    rot = tq.Rotation(d, 9)
+    Q = torch.from_numpy(np.random.default_rng(n).standard_normal((n, d)).astype(np.float32)).cuda()
+    want = tq.rotate_queries(rot, Q)
+    for shift in (1, 2, 3):
+        buf = torch.zeros(n * d + 4, device="cuda")
+        q = buf[shift:shift + n * d].view(n, d)
+        q.copy_(Q)
+        assert q.data_ptr() % 16 == 4 * shift
+        assert torch.equal(tq.rotate_queries(rot, q), want), shift
+
+
 @pytest.fixture(scope="module")
 def edge_rows(rot_pair):
     """2,200 rows with special ones among them, and the oracle's codes."""
