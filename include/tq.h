@@ -357,12 +357,14 @@ typedef enum {
  * skipped before their codes are read. */
 #define TQ_FLAG_SLOT_ALLOW 0x200
 
-/* Workspace size in bytes needed by tq_search_ex for (nq, k, path). */
+/* Workspace size in bytes with which tq_search_ex is fastest for (nq, k,
+ * path).  A workspace of the size for some nq serves every smaller nq on the
+ * same path too; the size itself need not grow with nq. */
 tq_status tq_search_workspace_size(const tq_index *idx, int64_t nq, int32_t k,
                                    int32_t path, size_t *bytes_out);
 
 /* tq_search with an explicit path and a caller-provided device workspace of
- * at least tq_search_workspace_size() bytes (256-byte aligned).  Allocates no
+ * tq_search_workspace_size() bytes (256-byte aligned; see there).  Allocates no
  * device memory.  Calls sharing one workspace must not overlap in time. */
 tq_status tq_search_ex(const tq_index *idx, const float *Q_dev, int64_t nq,
                        int32_t k, const uint64_t *allow_dev, int32_t path,

@@ -1135,27 +1135,13 @@ static bool auto_batch(const ScanShape &sh, int64_t nq, int k) {
     return batch_search_supported(sh, k) && batch_matrix_fits(sh) && batch_pays(sh, nq);
 }
 
-static bool use_mfma(const ScanShape &sh, int k, int base) {
-    return base == TQ_PATH_MFMA && mfma_search_supported(sh, k);
-}
-
 // Workspace of a search; a calibrated index adds the queries' constant
 // terms at the end (calib_offset).
 static size_t calib_offset(const ScanShape &sh, int64_t nq, int k) {
     return (lut_search_workspace_bytes(sh, nq, k, scan_grid()) + 255) & ~(size_t)255;
 }
 
-// The same for the batched path.
-static size_t batch_calib_offset(const ScanShape &sh, int64_t nq, int k) {
-    return (mfma_search_workspace_bytes(sh, nq, k, scan_grid()) + 255) & ~(size_t)255;
-}
-
-static size_t batch_bytes(const ScanShape &sh, int64_t nq, int k, bool calibrated) {
-    return batch_calib_offset(sh, nq, k) + (calibrated ? (size_t)nq * sizeof(float) : 0);
-}
-
-static size_t search_bytes(const ScanShape &sh, int64_t nq, int k, int base, bool calibrated) {
-    if (use_mfma(sh, k, base)) return mfma_search_workspace_bytes(sh, nq, k, scan_grid());
+static size_t scan_bytes(const ScanShape &sh, int64_t nq, int k, bool calibrated) {
     if (calibrated) return calib_offset(sh, nq, k) + (size_t)nq * sizeof(float);
     return lut_search_workspace_bytes(sh, nq, k, scan_grid());
 }
@@ -1198,9 +1184,9 @@ tq_status tq_search_workspace_size(const tq_index *idx, int64_t nq, int32_t k, i
     tq_status st = device_ready();
     if (st != TQ_OK) return st;
     const ScanShape sh = shape_of(idx);
-    size_t bytes = search_bytes(sh, nq, k, base, idx->calibrated);
-    if (base == TQ_PATH_AUTO && auto_batch(sh, nq, k))
-        bytes = std::max(bytes, batch_bytes(sh, nq, k, idx->calibrated));
+    size_t bytes = base == TQ_PATH_MFMA ? 0 : scan_bytes(sh, nq, k, idx->calibrated);
+    if (base == TQ_PATH_MFMA || (base == TQ_PATH_AUTO && auto_batch(sh, nq, k)))
+        bytes = std::max(bytes, batch_plan(sh, nq, k, scan_grid(), idx->calibrated).bytes);
     *bytes_out = bytes;
     return TQ_OK;
 }
@@ -1240,14 +1226,17 @@ tq_status tq_search_ex(const tq_index *idx, const float *Q_dev, int64_t nq, int3
     if (base == TQ_PATH_MFMA && idx->calibrated)
         return fail(TQ_EUNSUPPORTED, "matrix-core path does not take a TQ+ calibrated index");
     const int grid = scan_grid();
-    const size_t need = search_bytes(sh, nq, k, base, idx->calibrated);
-    if (workspace_bytes < need)
+    // the batched path takes any workspace from its smallest form's up; on the
+    // default path one that is too small for it still serves the scan
+    const bool want_batch = base == TQ_PATH_MFMA ||
+                            (base == TQ_PATH_AUTO && !filter.slot_allow &&
+                             (!filter.allow || nq >= kBatchFiltered) && auto_batch(sh, nq, k));
+    BatchPlan plan;
+    if (want_batch) plan = batch_plan(sh, nq, k, grid, idx->calibrated, workspace_bytes);
+    const bool batched = plan.fits;
+    const size_t need = base == TQ_PATH_MFMA ? plan.bytes : scan_bytes(sh, nq, k, idx->calibrated);
+    if (!batched && workspace_bytes < need)
         return fail(TQ_EINVAL, "workspace too small: need " + std::to_string(need) + " bytes");
-    // a workspace sized for the scan alone is still taken (by the scan)
-    const bool batched = use_mfma(sh, k, base) ||
-                         (base == TQ_PATH_AUTO && !filter.slot_allow &&
-                          (!filter.allow || nq >= kBatchFiltered) && auto_batch(sh, nq, k) &&
-                          workspace_bytes >= batch_bytes(sh, nq, k, idx->calibrated));
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (idx->n == 0) {
         // nothing indexed: every slot is padding
@@ -1279,8 +1268,7 @@ tq_status tq_search_ex(const tq_index *idx, const float *Q_dev, int64_t nq, int3
     float *qconst = nullptr;
     if (idx->calibrated) {
         uint8_t *w8 = static_cast<uint8_t *>(workspace_dev);
-        qconst = reinterpret_cast<float *>(
-            w8 + (batched ? batch_calib_offset(sh, nq, k) : calib_offset(sh, nq, k)));
+        qconst = reinterpret_cast<float *>(w8 + (batched ? plan.qconst : calib_offset(sh, nq, k)));
         float *qr = static_cast<float *>(workspace_dev);
         st = prepare_calibrated(idx, Qrot, nq, qr, qconst, s);
         if (st != TQ_OK) return st;
@@ -1292,7 +1280,7 @@ tq_status tq_search_ex(const tq_index *idx, const float *Q_dev, int64_t nq, int3
         centroid_half_bounds(idx, &cmax16, &dmax);
         hipError_t e = mfma_search(sh, idx->codes, idx->scales, scale_max_dev(idx), idx->tenants,
                                    idx->summ, idx->cents_dev, cmax16, dmax, Qrot, qconst, nq, k,
-                                   filter, grid, workspace_dev, ids_dev, scores_dev,
+                                   filter, grid, plan, workspace_dev, ids_dev, scores_dev,
                                    base == TQ_PATH_MFMA ? &n_fallback : nullptr, s);
         if (e != hipSuccess) return hip_fail(e, "matrix-core search");
         if (idx->idmap && (e = map_ids(ids_dev, nq * k, idx->ext, s)) != hipSuccess)
@@ -1337,7 +1325,7 @@ tq_status tq_search_postfilter(const tq_index *idx, const float *Q_dev, int64_t 
     const ScanShape sh = shape_of(idx);
     const int grid = scan_grid();
     const size_t sbytes =
-        (search_bytes(sh, nq, kk, TQ_PATH_LUT, idx->calibrated) + 255) & ~(size_t)255;
+        (scan_bytes(sh, nq, kk, idx->calibrated) + 255) & ~(size_t)255;
     const size_t tbytes = (size_t)nq * kk * (sizeof(int64_t) + sizeof(float));
     AsyncBuf ws;
     hipError_t e = ws.alloc(sbytes + tbytes, s);

@@ -2246,9 +2246,10 @@ void with_slots(int KC, Fn fn) {
 constexpr int kGroupTiles = 8;
 
 struct BatchLayout {
-    int tiles;
+    bool wide;   // whole passes of wide_pass take the wide kernels
+    int tiles;   // of a group
     size_t q16, info, approx, bmax, top_i, top_s, amin, state, tickets, count, rows, qc, tmask, list,
-        qconst_c, allow_c, lut, total;
+        qconst_c, allow_c, qconst, lut, total;
     // wide passes
     size_t w_q16, w_info, w_qfrag, w_qf, w_pil, w_theta, w_pcn, w_pci, w_pcs, w_cs, w_ci, w_cn,
         w_top, w_tops, w_amin, w_state;
@@ -2301,18 +2302,24 @@ bool wide_pass(const ScanShape &s, int64_t nq, int KC, int grid) {
 // Row length of the approximate-score matrix: whole 512-vector select units.
 int64_t approx_row(const ScanShape &s) { return (s.nblk * 64 + 511) / 512 * 512; }
 
-BatchLayout batch_layout(const ScanShape &s, int64_t nq, int k, int grid) {
-    BatchLayout L{};
-    size_t o = align256((size_t)nq * s.d * sizeof(float));   // rotated queries
-    const int64_t npad = approx_row(s);
+// Tiles of the largest group that a search of nq queries is given.
+int group_tiles(const ScanShape &s, int64_t nq, int k, int grid, bool wide) {
     // after whole wide passes the rest, if it is not another one, is left for tiles
     int64_t tile_q = nq;
-    if (wide_pass(s, nq, batch_candidates(k), grid)) {
+    if (wide) {
         tile_q = nq % kWideMaxQ;
         if (tile_q == 0 || wide_pass(s, tile_q, batch_candidates(k), grid)) tile_q = 1;
     }
-    const int64_t need = (tile_q + kTile - 1) / kTile, fit = ((int64_t)256 << 20) / (kTile * npad * 2 + 1);
-    L.tiles = (int)std::max<int64_t>(1, std::min<int64_t>({need, fit, kGroupTiles, grid}));
+    const int64_t need = (tile_q + kTile - 1) / kTile, fit = ((int64_t)256 << 20) / (kTile * approx_row(s) * 2 + 1);
+    return (int)std::max<int64_t>(1, std::min<int64_t>({need, fit, kGroupTiles, grid}));
+}
+
+BatchLayout batch_layout(const ScanShape &s, int64_t nq, int k, int grid, bool calibrated, bool wide, int tiles) {
+    BatchLayout L{};
+    size_t o = align256((size_t)nq * s.d * sizeof(float));   // rotated queries
+    const int64_t npad = approx_row(s);
+    L.wide = wide;
+    L.tiles = tiles;
     const size_t gq = (size_t)L.tiles * kTile;   // queries of a group
     L.q16 = o;
     o += align256(gq * s.d * 2);
@@ -2346,9 +2353,11 @@ BatchLayout batch_layout(const ScanShape &s, int64_t nq, int k, int grid) {
     o += align256((size_t)nq * sizeof(float));
     L.allow_c = o;
     o += align256((size_t)nq * s.W * sizeof(uint64_t));
+    L.qconst = o;
+    o += calibrated ? align256((size_t)nq * sizeof(float)) : 0;
     L.lut = o;
     o += lut_search_workspace_bytes(s, nq, k, grid);
-    if (wide_pass(s, nq, batch_candidates(k), grid)) {
+    if (wide) {
         const int KC = batch_candidates(k), PCM = 2 * KC;
         constexpr int QP = kWideMaxQ;
         const WideGeom w = wide_geom(s, WD_NG, grid, KC);
@@ -2488,8 +2497,21 @@ bool batch_matrix_fits(const ScanShape &s) {
     return (size_t)kTile * approx_row(s) * 2 <= (size_t)1 << 30;
 }
 
-size_t mfma_search_workspace_bytes(const ScanShape &s, int64_t nq, int k, int grid) {
-    return batch_layout(s, nq, k, grid).total;
+BatchPlan batch_plan(const ScanShape &s, int64_t nq, int k, int grid, bool calibrated, size_t room) {
+    BatchPlan p;
+    for (bool wide = wide_pass(s, nq, batch_candidates(k), grid);; wide = false) {
+        for (int tiles = group_tiles(s, nq, k, grid, wide); tiles >= 1; --tiles) {
+            const BatchLayout L = batch_layout(s, nq, k, grid, calibrated, wide, tiles);
+            p.bytes = L.total;
+            if (L.total > room) continue;
+            p.fits = true;
+            p.wide = wide;
+            p.tiles = tiles;
+            p.qconst = L.qconst;
+            return p;
+        }
+        if (!wide) return p;
+    }
 }
 
 hipError_t update_scale_max(const float *scales, int64_t n, float *smax, hipStream_t stream) {
@@ -2505,11 +2527,11 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
                        const float *smax, const uint16_t *tenants, const uint64_t *summaries,
                        const float *cents32, float cmax16, float dmax, const float *Qrot,
                        const float *qconst, int64_t nq, int k,
-                       const SearchFilter &filter, int grid, void *ws, int64_t *ids, float *scores,
-                       int *n_fallback, hipStream_t stream) {
+                       const SearchFilter &filter, int grid, const BatchPlan &plan, void *ws, int64_t *ids,
+                       float *scores, int *n_fallback, hipStream_t stream) {
     const uint64_t *allow = filter.allow, *live = filter.live;
     const bool filtered = filter.any();
-    const BatchLayout L = batch_layout(s, nq, k, grid);
+    const BatchLayout L = batch_layout(s, nq, k, grid, qconst != nullptr, plan.wide, plan.tiles);
     uint8_t *w8 = static_cast<uint8_t *>(ws);
     _Float16 *q16 = reinterpret_cast<_Float16 *>(w8 + L.q16);
     QInfo *info = reinterpret_cast<QInfo *>(w8 + L.info);
@@ -2617,7 +2639,7 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
         return launch_rescore(s, KC, rp, nqt, stream);
     };
     for (int64_t q0 = 0; q0 < nq;) {
-        if (wide_pass(s, nq - q0, KC, grid)) {
+        if (L.wide && wide_pass(s, nq - q0, KC, grid)) {
             // a wide pass of up to kWideMaxQ queries
             const int nqt = (int)std::min<int64_t>(nq - q0, kWideMaxQ);
             constexpr int QP = kWideMaxQ;

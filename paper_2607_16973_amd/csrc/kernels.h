@@ -192,13 +192,24 @@ bool batch_search_supported(const ScanShape &s, int k);
 bool mfma_search_supported(const ScanShape &s, int k);
 // Whether the workspace of the batched path stays moderate (about 1.1 GiB).
 bool batch_matrix_fits(const ScanShape &s);
-size_t mfma_search_workspace_bytes(const ScanShape &s, int64_t nq, int k, int grid);
+// How a search uses `room` bytes of workspace: with wide passes and the
+// largest groups of tiles if they fit, else with smaller groups, else without
+// wide passes.  The smallest form grows with nq and k, so that a workspace made
+// for more queries holds every search of fewer.
+struct BatchPlan {
+    bool fits = false;
+    bool wide = false;
+    int tiles = 0;       // of a group
+    size_t bytes = 0;    // of the workspace; the smallest form's if nothing fits
+    size_t qconst = 0;   // where a calibrated search's constant terms go
+};
+BatchPlan batch_plan(const ScanShape &s, int64_t nq, int k, int grid, bool calibrated, size_t room = SIZE_MAX);
 hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *scales,
                        const float *smax, const uint16_t *tenants, const uint64_t *summaries,
                        const float *cents32, float cmax16, float dmax, const float *Qrot,
                        const float *qconst, int64_t nq, int k,
-                       const SearchFilter &filter, int grid, void *ws, int64_t *ids, float *scores,
-                       int *n_fallback, hipStream_t stream);
+                       const SearchFilter &filter, int grid, const BatchPlan &plan, void *ws, int64_t *ids,
+                       float *scores, int *n_fallback, hipStream_t stream);
 // *smax = max(*smax, max of |scales[0..n)|).
 hipError_t update_scale_max(const float *scales, int64_t n, float *smax, hipStream_t stream);
 

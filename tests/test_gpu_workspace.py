@@ -34,7 +34,7 @@ def test_workspace_made_for_more_queries(index, made_for, path):
     batched path (which writes past the room of the scan)."""
     ws = torch.empty(index.workspace_bytes(made_for, K, path=path), dtype=torch.uint8, device="cuda")
     Q = rows(256, D, 2)
-    for nq in (2, 33, 64, 65, 96, 97, 128, 160, 161, 224, 225, 256):
+    for nq in (4, 33, 64, 65, 96, 97, 128, 160, 161, 224, 225, 256):
         print("workspace for %d, %d queries, %s" % (made_for, nq, path), flush=True)
         q = Q[:nq].contiguous()
         lut = index.workspace_bytes(nq, K, path="lut")
@@ -43,3 +43,26 @@ def test_workspace_made_for_more_queries(index, made_for, path):
         assert (ws[lut:] != 0xAB).any()
         want = index.search(q, K, path="lut")
         assert torch.equal(ids, want[0]) and torch.equal(scores, want[1])
+
+
+@pytest.mark.parametrize("plus", [False, True])
+def test_smallest_workspaces(plus):
+    """Every size from the scan's up is taken, results do not depend on it,
+    and nothing past its end is written."""
+    d, n, nq, k = 256, 60_013, 200, 10
+    X = rows(n, d, 3)
+    idx = tq.Index(tq.Codebook(d, 4), tq.Rotation(d, 42))
+    if plus:
+        idx.calibrate(X[:2000])
+    idx.add(X)
+    Q = rows(nq, d, 4)
+    want = idx.search(Q, k, path="lut")
+    lo, hi = idx.workspace_bytes(nq, k, path="lut"), idx.workspace_bytes(nq, k)
+    buf = torch.empty(hi + 4096, dtype=torch.uint8, device="cuda")
+    for i in range(17):
+        size = lo + (hi - lo) * i // 16
+        print("workspace of %d bytes" % size, flush=True)
+        buf.fill_(0xAB)
+        ids, scores = idx.search(Q, k, workspace=buf[:size])
+        assert torch.equal(ids, want[0]) and torch.equal(scores, want[1])
+        assert (buf[size:] == 0xAB).all()
