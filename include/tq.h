@@ -298,7 +298,9 @@ tq_status tq_slot_allowlist(const tq_index *idx, const uint64_t *ids_host,
  * descending, id ascending) in ids_dev [nq][k] int64 and scores_dev [nq][k]
  * float32; unused slots hold id -1 and score -inf.
  * The search needs a device workspace; tq_search allocates it on `stream`
- * (stream-ordered allocation) and releases it before returning. */
+ * (stream-ordered allocation) and releases it before returning.  If there is
+ * no room for the one it would like (up to about 256 MiB, 1 GiB for the largest
+ * indexes) it takes the single-query scan's, a small part of that. */
 tq_status tq_search(const tq_index *idx, const float *Q_dev, int64_t nq,
                     int32_t k, const uint64_t *allow_dev, int64_t *ids_dev,
                     float *scores_dev, void *stream);
@@ -357,8 +359,12 @@ typedef enum {
  * skipped before their codes are read. */
 #define TQ_FLAG_SLOT_ALLOW 0x200
 
+/* With tenant allowlists TQ_PATH_AUTO is the single-query scan for fewer
+ * queries than this (a workspace of the size of TQ_PATH_LUT is all they use). */
+#define TQ_AUTO_FILTERED_QUERIES 6
+
 /* Workspace size in bytes with which tq_search_ex is fastest for (nq, k,
- * path).  A workspace of the size for some nq serves every smaller nq on the
+ * path; TQ_FLAG_SLOT_ALLOW may be in it).  A workspace of the size for some nq serves every smaller nq on the
  * same path too; the size itself need not grow with nq. */
 tq_status tq_search_workspace_size(const tq_index *idx, int64_t nq, int32_t k,
                                    int32_t path, size_t *bytes_out);

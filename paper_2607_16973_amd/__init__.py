@@ -16,7 +16,8 @@ import os
 
 import numpy as np
 
-from ._lib import FLAG_PREROTATED, FLAG_SLOT_ALLOW, PATHS, TQError, check, lib
+from ._lib import (AUTO_FILTERED_QUERIES, FLAG_PREROTATED, FLAG_SLOT_ALLOW, PATHS, TQError, check,
+                   lib)
 
 __all__ = ["Codebook", "Rotation", "Index", "IdMapIndex", "TQError", "rotate_quantize",
            "rotate_queries", "version", "last_search_fallbacks"]
@@ -287,6 +288,20 @@ class Index:
         check(lib.tq_search_workspace_size(self._h, nq, k, PATHS[path], ctypes.byref(b)))
         return b.value
 
+    def _workspace(self, nq, k, path, device):
+        """The workspace that the index keeps, grown to the call's size; if
+        there is no room for that, the scan's serves the default path."""
+        torch = _torch()
+        need = self.workspace_bytes(nq, k, path)
+        if self._ws is None or self._ws.numel() < need:
+            try:
+                self._ws = torch.empty((need,), dtype=torch.uint8, device=device)
+            except torch.OutOfMemoryError:
+                if path != "auto":
+                    raise
+                return self._workspace(nq, k, "lut", device)
+        return self._ws
+
     def search(self, Q, k: int, allow=None, path: str = "auto", ids=None, scores=None,
                workspace=None, prerotated: bool = False, slot_allow=None):
         """Top-k per query row of Q (cuda float32 [nq, d]).  allow: cuda int64
@@ -314,10 +329,9 @@ class Index:
             scores = torch.empty((nq, k), dtype=torch.float32, device=Q.device)
         if workspace is None:
             # a workspace the caller passes is checked by the library itself
-            need = self.workspace_bytes(nq, k, path)
-            if self._ws is None or self._ws.numel() < need:
-                self._ws = torch.empty((need,), dtype=torch.uint8, device=Q.device)
-            workspace = self._ws
+            scan = path == "auto" and (slot_allow is not None or
+                                       (allow is not None and nq < AUTO_FILTERED_QUERIES))
+            workspace = self._workspace(nq, k, "lut" if scan else path, Q.device)
         check(lib.tq_search_ex(self._h, _dev_ptr(Q, torch.float32, "Q", 2), nq, k,
                                _dev_ptr(allow, torch.int64, "allow") if allow is not None else None,
                                PATHS[path] | flags,

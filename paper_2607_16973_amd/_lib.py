@@ -19,6 +19,7 @@ TQ_OK, TQ_EINVAL, TQ_ENOMEM, TQ_EDEVICE, TQ_EUNSUPPORTED = 0, -1, -2, -3, -4
 PATHS = {"auto": 0, "lut": 1, "mfma": 2}
 FLAG_PREROTATED = 0x100
 FLAG_SLOT_ALLOW = 0x200
+AUTO_FILTERED_QUERIES = 6   # TQ_AUTO_FILTERED_QUERIES
 _STATUS = {TQ_EINVAL: "TQ_EINVAL", TQ_ENOMEM: "TQ_ENOMEM", TQ_EDEVICE: "TQ_EDEVICE",
            TQ_EUNSUPPORTED: "TQ_EUNSUPPORTED"}
 

@@ -1129,7 +1129,7 @@ static bool batch_pays(const ScanShape &sh, int64_t nq) {
 // pass has been the faster one even for the most selective lists: one tenant
 // of 1,000 per query, 1,000,000 vectors, scan / batched 82 / 91 us for 4
 // queries, 124 / 98 for 8, 410 / 170 for 32 (one of 10: 1,082 / 250 for 8).
-constexpr int64_t kBatchFiltered = 6;
+constexpr int64_t kBatchFiltered = TQ_AUTO_FILTERED_QUERIES;
 
 static bool auto_batch(const ScanShape &sh, int64_t nq, int k) {
     return batch_search_supported(sh, k) && batch_matrix_fits(sh) && batch_pays(sh, nq);
@@ -1185,7 +1185,8 @@ tq_status tq_search_workspace_size(const tq_index *idx, int64_t nq, int32_t k, i
     if (st != TQ_OK) return st;
     const ScanShape sh = shape_of(idx);
     size_t bytes = base == TQ_PATH_MFMA ? 0 : scan_bytes(sh, nq, k, idx->calibrated);
-    if (base == TQ_PATH_MFMA || (base == TQ_PATH_AUTO && auto_batch(sh, nq, k)))
+    const bool slot_allow = (path & TQ_FLAG_SLOT_ALLOW) != 0;   // the scan's
+    if (base == TQ_PATH_MFMA || (base == TQ_PATH_AUTO && !slot_allow && auto_batch(sh, nq, k)))
         bytes = std::max(bytes, batch_plan(sh, nq, k, scan_grid(), idx->calibrated).bytes);
     *bytes_out = bytes;
     return TQ_OK;
@@ -1361,13 +1362,25 @@ tq_status tq_search_postfilter(const tq_index *idx, const float *Q_dev, int64_t 
 
 tq_status tq_search(const tq_index *idx, const float *Q_dev, int64_t nq, int32_t k,
                     const uint64_t *allow_dev, int64_t *ids_dev, float *scores_dev, void *stream) {
-    size_t bytes = 0;
-    tq_status st = tq_search_workspace_size(idx, nq, k, TQ_PATH_AUTO, &bytes);
+    // few queries with allowlists are the scan's
+    const bool scan = allow_dev && nq < TQ_AUTO_FILTERED_QUERIES;
+    size_t bytes = 0, scan_need = 0;
+    tq_status st = tq_search_workspace_size(idx, nq, k, scan ? TQ_PATH_LUT : TQ_PATH_AUTO, &bytes);
     if (st != TQ_OK) return st;
     if (nq == 0) return TQ_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
     AsyncBuf ws;
     hipError_t e = ws.alloc(bytes, s);
+    if (e != hipSuccess) {
+        // the scan makes do with far less
+        st = tq_search_workspace_size(idx, nq, k, TQ_PATH_LUT, &scan_need);
+        if (st != TQ_OK) return st;
+        if (scan_need < bytes) {
+            (void)hipGetLastError();   // launches look at the last error
+            bytes = scan_need;
+            e = ws.alloc(bytes, s);
+        }
+    }
     if (e != hipSuccess) return hip_fail(e, "hipMallocAsync(search workspace)");
     return tq_search_ex(idx, Q_dev, nq, k, allow_dev, TQ_PATH_AUTO, ws.p, bytes, ids_dev,
                         scores_dev, stream);

@@ -66,3 +66,51 @@ def test_smallest_workspaces(plus):
         ids, scores = idx.search(Q, k, workspace=buf[:size])
         assert torch.equal(ids, want[0]) and torch.equal(scores, want[1])
         assert (buf[size:] == 0xAB).all()
+
+
+def big_index(n=14_000_000, d=128):
+    """Codes as they come: a tile's scores alone take 0.9 GB."""
+    idx = tq.Index(tq.Codebook(d, 4), tq.Rotation(d, 42), 4)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    codes = torch.randint(256, (n, d // 2), generator=g, device="cuda", dtype=torch.uint8)
+    idx.add_codes(codes, torch.rand(n, generator=g, device="cuda") + 0.5)
+    return idx
+
+
+def test_search_where_the_batched_workspace_does_not_fit():
+    """100 MiB left on the GPU: the default search of four queries takes the
+    scan's workspace instead of failing, in the library and in the binding."""
+    print("little memory left", flush=True)
+    idx = big_index()
+    Q = rows(4, 128, 6)
+    assert idx.workspace_bytes(4, K) > 800 << 20
+    want = idx.search(Q, K, path="lut")
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    hog = torch.empty(torch.cuda.mem_get_info()[0] - (100 << 20), dtype=torch.uint8, device="cuda")
+    try:
+        for search in (idx.search_alloc, idx.search):
+            print(search.__name__, flush=True)
+            ids, scores = search(Q, K)
+            assert torch.equal(ids, want[0]) and torch.equal(scores, want[1])
+    finally:
+        del hog
+        torch.cuda.empty_cache()
+
+
+def test_workspace_kept_is_that_of_the_scan_where_the_scan_runs(index):
+    """Slot allowlists, and tenant allowlists of few queries, never take the
+    batched path: the workspace that the index keeps is the scan's."""
+    idx = tq.Index(tq.Codebook(D, 4), tq.Rotation(D, 42))
+    idx.add(rows(200_000, D, 7))
+    Q = rows(40, D, 8)
+    slots = torch.full((40, (200_000 + 63) // 64), -1, dtype=torch.int64, device="cuda")
+    idx.search(Q, K, slot_allow=slots)
+    assert idx._ws.numel() == idx.workspace_bytes(40, K, path="lut") < idx.workspace_bytes(40, K)
+    idx._ws = None
+    few = tq.AUTO_FILTERED_QUERIES - 1
+    allow = torch.ones(40, 1, dtype=torch.int64, device="cuda")
+    idx.search(Q[:few].contiguous(), K, allow=allow[:few].contiguous())
+    assert idx._ws.numel() == idx.workspace_bytes(few, K, path="lut") < idx.workspace_bytes(few, K)
+    idx.search(Q, K, allow=allow)
+    assert idx._ws.numel() == idx.workspace_bytes(40, K)

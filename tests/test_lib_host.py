@@ -34,6 +34,14 @@ def test_exports_every_declared_symbol():
     assert set(names) == set(_lib.EXPORTED)
 
 
+def test_constants_of_the_header():
+    text = open(os.path.join(ROOT, "include", "tq.h")).read()
+    c = {m[0]: int(m[1], 0) for m in re.findall(r"#define (TQ_[A-Z_]+) (\w+)\n", text)}
+    assert c["TQ_FLAG_PREROTATED"] == _lib.FLAG_PREROTATED
+    assert c["TQ_FLAG_SLOT_ALLOW"] == _lib.FLAG_SLOT_ALLOW
+    assert c["TQ_AUTO_FILTERED_QUERIES"] == _lib.AUTO_FILTERED_QUERIES
+
+
 @pytest.mark.parametrize("d,bits", [(64, 4), (1536, 4), (1536, 2), (1536, 1), (1536, 3), (1536, 8),
                                     (768, 4), (2048, 4), (128, 8)])
 def test_codebook_matches_oracle(d, bits):
