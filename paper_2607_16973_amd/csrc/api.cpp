@@ -384,6 +384,16 @@ void tq_rotation_free(tq_rotation *rot) {
     delete rot;
 }
 
+// The encoder's workspace for n rows and `extra` bytes: about 7 d bytes for each
+// row of a chunk, whose rows go down where the memory is not there.
+static hipError_t alloc_encode(AsyncBuf *ws, int64_t n, int d, size_t extra, hipStream_t s, int *chunk) {
+    for (*chunk = kEncodeChunkRows;; *chunk /= 4) {
+        const hipError_t e = ws->alloc(encode_workspace_bytes(n, d, *chunk) + extra, s);
+        if (e == hipSuccess || *chunk / 4 < kEncodeChunkLeast) return e;
+        (void)hipGetLastError();   // launches look at the last error
+    }
+}
+
 tq_status tq_rotate_quantize(const tq_codebook *cb, const tq_rotation *rot, const float *X_dev,
                              int64_t n, uint8_t *codes_dev, float *scales_dev, void *stream) {
     if (!cb || !rot) return fail(TQ_EINVAL, "NULL codebook or rotation");
@@ -401,13 +411,14 @@ tq_status tq_rotate_quantize(const tq_codebook *cb, const tq_rotation *rot, cons
     fill_codebook_dev(cb->t, &cd);
     const int d = rot->d;
     AsyncBuf ws;
-    hipError_t e = ws.alloc(encode_workspace_bytes(n, d) + 256, s);
+    int chunk = 0;
+    hipError_t e = alloc_encode(&ws, n, d, 256, s, &chunk);
     if (e != hipSuccess) return hip_fail(e, "hipMallocAsync(encode workspace)");
-    int *status = reinterpret_cast<int *>(static_cast<uint8_t *>(ws.p) + encode_workspace_bytes(n, d));
+    int *status = reinterpret_cast<int *>(static_cast<uint8_t *>(ws.p) + encode_workspace_bytes(n, d, chunk));
     EncodeOut out;
     out.canonical = codes_dev;
     out.scales = scales_dev;
-    e = encode_rows(X_dev, n, d, R, R + (size_t)d * d, cd, out, ws.p, status, s);
+    e = encode_rows(X_dev, n, d, R, R + (size_t)d * d, cd, out, ws.p, status, s, chunk);
     if (e != hipSuccess) return hip_fail(e, "encode");
     int h = 0;
     st = read_status(status, s, &h);
@@ -492,7 +503,8 @@ static tq_status add_vectors(tq_index *idx, const float *X_dev, const uint16_t *
     st = rotation_dev(&idx->rot, &R);
     if (st != TQ_OK) return st;
     AsyncBuf ws;
-    hipError_t e = ws.alloc(encode_workspace_bytes(n, idx->d), s);
+    int chunk = 0;
+    hipError_t e = alloc_encode(&ws, n, idx->d, 0, s, &chunk);
     if (e != hipSuccess) return hip_fail(e, "hipMallocAsync(encode workspace)");
     EncodeOut out;
     out.blocked = idx->codes;
@@ -503,7 +515,8 @@ static tq_status add_vectors(tq_index *idx, const float *X_dev, const uint16_t *
         cal.athr = idx->athr;
         cal.ysq = idx->ysq;
     }
-    e = encode_rows(X_dev, n, idx->d, R, R + (size_t)idx->d * idx->d, idx->cbdev, out, ws.p, idx->status, s, cal);
+    e = encode_rows(X_dev, n, idx->d, R, R + (size_t)idx->d * idx->d, idx->cbdev, out, ws.p, idx->status, s,
+                    chunk, cal);
     if (e != hipSuccess) return hip_fail(e, "encode");
     int h = 0;
     st = read_status(idx->status, s, &h);

@@ -1235,17 +1235,17 @@ static EncodeLayout encode_layout(int64_t rows, int d) {
 // Rows of the next chunk of n: a last chunk of few rows, which would leave
 // most compute units idle through five launches (113 us for 1,696 rows at
 // d = 1536, 34 a thousand for full ones), joins the one before.
-static int64_t chunk_rows(int64_t n) {
-    return n <= kEncodeChunkRows + kEncodeChunkSlack ? n : kEncodeChunkRows;
+static int64_t chunk_rows(int64_t n, int chunk) {
+    return n <= chunk + kEncodeChunkSlack ? n : chunk;
 }
 
 // Rows that any chunk of n holds at most.
-static int64_t layout_rows(int64_t n) {
-    return n <= kEncodeChunkRows ? n : kEncodeChunkRows + kEncodeChunkSlack;
+static int64_t layout_rows(int64_t n, int chunk) {
+    return n <= chunk ? n : chunk + kEncodeChunkSlack;
 }
 
-size_t encode_workspace_bytes(int64_t n, int d) {
-    return encode_layout(layout_rows(n), d).total;
+size_t encode_workspace_bytes(int64_t n, int d, int chunk) {
+    return encode_layout(layout_rows(n, chunk), d).total;
 }
 
 size_t split_rotation_bytes(int d) { return (size_t)d * d * 4; }
@@ -1297,8 +1297,8 @@ static hipError_t launch_encode_gemm(const uint4 *Xp, int64_t m, const uint4 *Rp
 
 hipError_t encode_rows(const float *X, int64_t n, int d, const float *R, const void *Rsplit,
                        const CodebookDev &cb, const EncodeOut &out, void *ws,
-                       int *status_dev, hipStream_t stream, const CalibDev &calib) {
-    const EncodeLayout L = encode_layout(layout_rows(n), d);
+                       int *status_dev, hipStream_t stream, int chunk, const CalibDev &calib) {
+    const EncodeLayout L = encode_layout(layout_rows(n, chunk), d);
     uint8_t *p = static_cast<uint8_t *>(ws);
     uint8_t *codes_tmp = p + L.codes;
     uint4 *planes = reinterpret_cast<uint4 *>(p + L.planes);
@@ -1335,7 +1335,7 @@ hipError_t encode_rows(const float *X, int64_t n, int d, const float *R, const v
         attr = true;
     }
     for (int64_t r0 = 0, m; r0 < n; r0 += m) {
-        m = chunk_rows(n - r0);
+        m = chunk_rows(n - r0, chunk);
         // every list tile of the chunk's rows gets its flag count
         QuantArgs qa{bounds, calib.athr, cb.levels, codes_tmp, inv, (float)tau_rel(d),
                      (cb.bounds[cb.levels - 2] - cb.bounds[0]) / EG_BINS, flags, tile_count};

@@ -18,10 +18,12 @@ struct CodebookDev {
 };
 
 // ------------------------------------------------------------------ encode
-// Rows per encode chunk and the workspace it needs.
+// Rows per encode chunk (the fewest: where memory is short) and the workspace
+// of n rows in such chunks.
 constexpr int kEncodeChunkRows = 32768;
+constexpr int kEncodeChunkLeast = 2048;
 constexpr int kEncodeChunkSlack = 4096;   // more rows that the last chunk may take
-size_t encode_workspace_bytes(int64_t n, int d);
+size_t encode_workspace_bytes(int64_t n, int d, int chunk);
 // The rotation's float16 parts in the encoder's operand order, made once
 // from R [d][d] on the device.
 size_t split_rotation_bytes(int d);
@@ -37,7 +39,8 @@ struct EncodeOut {
 };
 
 // Encodes X [n][d] (float32, row-major) with R [d][d] and its parts on
-// `stream`.  `ws` must hold encode_workspace_bytes(n, d); `status_dev` is an int32 that the
+// `stream`, in chunks of `chunk` rows.  `ws` must hold encode_workspace_bytes(n,
+// d, chunk); `status_dev` is an int32 that the
 // kernels set to zero, or non-zero on a non-finite input.
 // TQ+ calibration tables on the device (null: plain TurboQuant):
 // athr [(levels-1)][d] per-coordinate thresholds mu_j + kappa_j t_i and ysq
@@ -49,7 +52,7 @@ struct CalibDev {
 
 hipError_t encode_rows(const float *X, int64_t n, int d, const float *R, const void *Rsplit,
                        const CodebookDev &cb, const EncodeOut &out, void *ws,
-                       int *status_dev, hipStream_t stream,
+                       int *status_dev, hipStream_t stream, int chunk = kEncodeChunkRows,
                        const CalibDev &calib = CalibDev());
 
 // Y = X R^T in float32 (query rotation), X [m][d], Y [m][d].  With fill,

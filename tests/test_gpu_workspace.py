@@ -68,6 +68,19 @@ def test_smallest_workspaces(plus):
         assert (buf[size:] == 0xAB).all()
 
 
+def take_memory(leave):
+    """Tensors that hold all of the GPU's memory but about `leave` bytes."""
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    held = []
+    for _ in range(20):
+        free = torch.cuda.mem_get_info()[0]
+        if free < leave + (16 << 20):
+            break
+        held.append(torch.empty(free - leave, dtype=torch.uint8, device="cuda"))
+    return held
+
+
 def big_index(n=14_000_000, d=128):
     """Codes as they come: a tile's scores alone take 0.9 GB."""
     idx = tq.Index(tq.Codebook(d, 4), tq.Rotation(d, 42), 4)
@@ -85,16 +98,14 @@ def test_search_where_the_batched_workspace_does_not_fit():
     Q = rows(4, 128, 6)
     assert idx.workspace_bytes(4, K) > 800 << 20
     want = idx.search(Q, K, path="lut")
-    torch.cuda.synchronize()
-    torch.cuda.empty_cache()
-    hog = torch.empty(torch.cuda.mem_get_info()[0] - (100 << 20), dtype=torch.uint8, device="cuda")
+    held = take_memory(100 << 20)
     try:
         for search in (idx.search_alloc, idx.search):
             print(search.__name__, flush=True)
             ids, scores = search(Q, K)
             assert torch.equal(ids, want[0]) and torch.equal(scores, want[1])
     finally:
-        del hog
+        del held
         torch.cuda.empty_cache()
 
 
@@ -114,3 +125,26 @@ def test_workspace_kept_is_that_of_the_scan_where_the_scan_runs(index):
     assert idx._ws.numel() == idx.workspace_bytes(few, K, path="lut") < idx.workspace_bytes(few, K)
     idx.search(Q, K, allow=allow)
     assert idx._ws.numel() == idx.workspace_bytes(40, K)
+
+
+def test_encode_where_the_workspace_of_large_chunks_does_not_fit():
+    """40,000 rows at d = 1536 take 410 MB in chunks of 32,768; with 300 MiB
+    left they are encoded in smaller ones, to the same codes."""
+    print("encode with little memory left", flush=True)
+    d, n = 1536, 40_000
+    cb, rot = tq.Codebook(d, 4), tq.Rotation(d, 42)
+    X = rows(n, d, 9)
+    want = tq.rotate_quantize(cb, rot, X)
+    got = tuple(torch.empty_like(t) for t in want)
+    idx = tq.Index(cb, rot)
+    idx.reserve(n)
+    held = take_memory(300 << 20)
+    try:
+        tq.rotate_quantize(cb, rot, X, codes=got[0], scales=got[1])
+        idx.add(X)
+        torch.cuda.synchronize()
+    finally:
+        del held
+        torch.cuda.empty_cache()
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    assert torch.equal(idx.export()[0], want[0])
