@@ -1452,10 +1452,9 @@ __global__ __launch_bounds__(kTableThreads) void rescore_kernel(RescoreParams p)
 //  2. wide_scores_kernel, pilot launch: tiles of NG blocks (every pstride-th
 //     tile of the store, at most one per workgroup); every approximate score
 //     of their vectors is written, [query][pilot vector].
-//  3. pilot_select_kernel: per query, theta = the KC-th largest allowed
-//     pilot score (-inf when at most KC pilot vectors are allowed), and the
-//     allowed pilot vectors that reach it as candidates.  At least KC
-//     vectors of the store score theta or more.
+//  3. pilot_select_kernel: per query, theta = about the KC-th largest allowed
+//     pilot score (see pilot_rank; -inf when no more pilot vectors are
+//     allowed), and the allowed pilot vectors that reach it as candidates.
 //  4. wide_scores_kernel, main launch: every other tile; a vector whose
 //     score reaches its query's theta (and that is live and whose tenant the
 //     query allows) is appended to the workgroup's list for that query.
@@ -1969,7 +1968,10 @@ struct PilotParams {
     const uint64_t *live;      // [nblk] or null
     Gate gate;
     int nqt;
-    int W, KC, PCM;
+    int W, PCM;
+    int rank;                  // see pilot_rank
+    int groups;                // maxima per thread: 1, 2 or 4
+    int most;                  // pilot candidates that need no exact threshold
     float *theta;              // [nqt]
     int *pc_n;                 // [nqt] pilot candidates (may exceed PCM: overflow)
     int *pc_i;                 // [nqt][PCM]
@@ -1978,12 +1980,17 @@ struct PilotParams {
 
 // One workgroup per query.  The selection runs on 16-bit keys, the top half
 // of the order-preserving key of each allowed pilot score, held in LDS: with
-// kt a key that at least KC allowed pilot vectors reach, theta = the smallest
-// float whose key starts with kt, and a pilot vector reaches theta exactly when
-// its 16-bit key reaches kt.  kt is the KC-th largest of the threads' largest
-// keys, each over up to 64 vectors 1024 apart: about 7% more vectors than KC
-// reach it (KC = 128), and one pass over 65,536 keys replaces three.  Where
-// fewer than KC threads hold an allowed vector, it is the KC-th largest key.
+// kt a key that at least `rank` allowed pilot vectors reach, theta = the
+// smallest float whose key starts with kt, and a pilot vector reaches theta
+// exactly when its 16-bit key reaches kt.  kt is the rank-th largest of the
+// largest keys of G = 1,024, 2,048 or 4,096 groups (G / rank at least 8), each
+// of up to 65,536 / G vectors: where scores lie at random G ln(G / (G - rank))
+// vectors reach it, at most 7% more than rank, and one pass over the keys
+// replaces three.  (With one group per thread also at rank 512 it was 39%
+// more, and a call of 256 queries at 1,500,000 vectors, d = 256, k = 100 took
+// 14.6 ms for the queries that overflowed, 0.51 now.)  Where more than `most`
+// reach it, or fewer than `rank` groups hold an allowed vector, kt is the
+// rank-th largest key itself.
 __global__ __launch_bounds__(PS_THREADS) void pilot_select_kernel(PilotParams p) {
     constexpr int TV = 64 * WD_NG;                 // vectors per pilot tile
     extern __shared__ __attribute__((aligned(16))) uint16_t k16[];   // [npv], 0: absent
@@ -2005,7 +2012,7 @@ __global__ __launch_bounds__(PS_THREADS) void pilot_select_kernel(PilotParams p)
         for (int w = tid; w < p.W; w += PS_THREADS) allow_s[w] = arow[w];
     __syncthreads();
     int cnt = 0;
-    uint32_t best = 0;   // this thread's largest key
+    uint32_t best[4] = {0u, 0u, 0u, 0u};   // the largest keys of this thread's groups
     // rounds of 16 loads per thread, all issued before any is used
     constexpr int R = 16;
     for (int e0 = 0; e0 < npv; e0 += R * PS_THREADS) {
@@ -2037,13 +2044,18 @@ __global__ __launch_bounds__(PS_THREADS) void pilot_select_kernel(PilotParams p)
                 }
                 const uint32_t key = ok ? ukey(val[u]) >> 16 : 0u;   // a finite key's top half is >= 0x80
                 k16[e] = (uint16_t)key;
-                best = key > best ? key : best;
+                best[u & 3] = key > best[u & 3] ? key : best[u & 3];
                 cnt += ok;
             }
         }
     }
     for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
-    const int some = __popcll(__ballot(best != 0u));
+    if (p.groups < 4)
+        for (int i = 0; i < 2; ++i) best[i] = best[i] > best[i + 2] ? best[i] : best[i + 2];
+    if (p.groups < 2) best[0] = best[0] > best[1] ? best[0] : best[1];
+    int some = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) some += __popcll(__ballot(i < p.groups && best[i] != 0u));
     __syncthreads();
     if (lane == 0) {
         atomicAdd(&sh[5], cnt);
@@ -2052,26 +2064,39 @@ __global__ __launch_bounds__(PS_THREADS) void pilot_select_kernel(PilotParams p)
     __syncthreads();
     const int allowed = sh[5];
     uint32_t thk = 1u;   // every present key
-    if (allowed > p.KC) {
-        int n_above;
-        if (sh[6] >= p.KC)
-            thk = radix_kth<16>([&](auto fn) { fn(best); }, p.KC, hist, sh, n_above);
-        else
-            thk = radix_kth<16>([&](auto fn) {
-                for (int e = tid; e < npv; e += PS_THREADS) fn((uint32_t)k16[e]);
-            }, p.KC, hist, sh, n_above);
-    }
-    if (tid == 0) p.theta[q] = allowed > p.KC ? ukey_value(thk << 16) : -INFINITY;
-    for (int e = tid; e < npv; e += PS_THREADS) {
-        const uint32_t k = k16[e];
-        if (k != 0u && k >= thk) {
-            const int pos = atomicAdd(&sh[4], 1);
-            if (pos < p.PCM) {
-                p.pc_i[(int64_t)q * p.PCM + pos] = (int)vec_of(e);
-                p.pc_s[(int64_t)q * p.PCM + pos] = row[e];
+    auto take_from = [&](uint32_t key) {
+        for (int e = tid; e < npv; e += PS_THREADS) {
+            const uint32_t k = k16[e];
+            if (k != 0u && k >= key) {
+                const int pos = atomicAdd(&sh[4], 1);
+                if (pos < p.PCM) {
+                    p.pc_i[(int64_t)q * p.PCM + pos] = (int)vec_of(e);
+                    p.pc_s[(int64_t)q * p.PCM + pos] = row[e];
+                }
             }
         }
+    };
+    bool taken = false;
+    int n_above;
+    if (allowed > p.rank && sh[6] >= p.rank) {
+        thk = radix_kth<16>([&](auto fn) {
+            for (int i = 0; i < p.groups; ++i) fn(best[i]);
+        }, p.rank, hist, sh, n_above);
+        take_from(thk);
+        __syncthreads();
+        taken = sh[4] <= p.most;
+        __syncthreads();
+        if (!taken && tid == 0) sh[4] = 0;
     }
+    if (!taken) {
+        if (allowed > p.rank)
+            thk = radix_kth<16>([&](auto fn) {
+                for (int e = tid; e < npv; e += PS_THREADS) fn((uint32_t)k16[e]);
+            }, p.rank, hist, sh, n_above);
+        __syncthreads();
+        take_from(thk);
+    }
+    if (tid == 0) p.theta[q] = allowed > p.rank ? ukey_value(thk << 16) : -INFINITY;
     __syncthreads();
     if (tid == 0) p.pc_n[q] = sh[4];
 }
@@ -2280,12 +2305,25 @@ WideGeom wide_geom(const ScanShape &s, int NG, int grid, int KC) {
     return w;
 }
 
+// Pilot candidates of a query up to which its candidates in the whole store,
+// `part` times the pilot's, fit the final selection but for chance: the store's
+// share above a threshold that KC pilot vectors reach has a standard deviation
+// of about 1 / sqrt(KC) of it, of which four and a half are left as room (one query in
+// 300,000; a query that overflows costs the call a scan, 0.35 ms at 1,800,000
+// vectors, d = 256, k = 100).
+double pilot_most(double part, int KC) {
+    return kFinalMax / (part * (1.0 + 4.5 / std::sqrt((double)KC)));
+}
+// The rank of the pilot score that is the threshold: KC, or fewer where that
+// many (and 2% that share a 16-bit key) would be too many.  The store has
+// `part` times as many vectors above it, far more than KC either way.
+int pilot_rank(double part, int KC) { return std::min(KC, (int)(pilot_most(part, KC) / 1.02)); }
+
 // Whether a pass over nq more queries takes the wide kernels: enough queries
 // and vectors, and an index of which the pilot (at most 65,536 vectors) is
-// large enough a part -- about KC ntiles / npil candidates per query must fit
-// the final selection and about 2 per + 16 a workgroup's list, with room for
-// chance; beyond that (N above 6.4M at k = 10, 1.6M at k = 100) most
-// queries would overflow and fall back.
+// large enough a part, so that the threshold's rank is still three quarters of KC
+// (N up to 7.8M at k = 10, 2.2M at k = 100) and about 2 per + 16 candidates fit
+// a workgroup's list.
 bool wide_pass(const ScanShape &s, int64_t nq, int KC, int grid) {
     // Six tiles or more and 1,000,000 vectors at 6 tiles, 500,000 at 7, 333,333
     // at 8.  256 queries, tiles / wide, d = 1536: 188 / 231 us at 100,000
@@ -2296,7 +2334,7 @@ bool wide_pass(const ScanShape &s, int64_t nq, int KC, int grid) {
     if (s.bits != 4 || tiles < 6 || s.n * (tiles - 5) < kWideWork || s.chunks < kWideMinChunks || grid > PS_THREADS) return false;
     const WideGeom w = wide_geom(s, WD_NG, grid, KC);
     const double part = (double)w.ntiles / (double)w.npil;
-    return KC * part <= 0.8 * kFinalMax && 2.0 * KC * part / grid + 16.0 <= 512.0;
+    return 4 * pilot_rank(part, KC) >= 3 * KC && 2.0 * KC * part / grid + 16.0 <= 512.0;
 }
 
 // Row length of the approximate-score matrix: whole 512-vector select units.
@@ -2708,8 +2746,11 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
             pp.gate = gate;
             pp.nqt = nqt;
             pp.W = s.W;
-            pp.KC = KC;
             pp.PCM = PCM;
+            const double part = (double)w.ntiles / (double)w.npil;
+            pp.rank = pilot_rank(part, KC);
+            pp.groups = KC <= 128 ? 1 : KC / 128;
+            pp.most = (int)std::min(1.25 * pp.rank, pilot_most(part, KC));
             pp.theta = wtheta;
             pp.pc_n = wpcn;
             pp.pc_i = wpci;
