@@ -1,21 +1,18 @@
-"""GPU parity of the batched matrix-core path in passes of 65 to 256 queries
-(one pass over the code store per pass, no score matrix: a pilot launch
-scores every vector of some tiles, the KC-th best allowed pilot score per
-query is its threshold, the main launch keeps only vectors that reach it,
-then the KC best candidates are rescored exactly and certified).
+"""GPU parity of the batched matrix-core path at 64 to 300 queries, in groups
+of up to eight tiles of 32 (wide passes begin at larger corpora:
+test_gpu_wide_passes.py).
 
 Against the oracle's brute force over the whole corpus (section II-B step 5
 scores, section IV-A ground truth) and against the single-query path's
 scores for the same ids:
 
-* the 10,000-row workload, where every tile is a pilot tile, in passes of
-  65, 100, 200 and 300 (a pass of 256, then 44 queries in tiles of 32) at
-  k = 10 and 100;
-* a 70,037-row corpus (274 tiles: pilot and main launches both work, the
-  last block is partial) in passes of 65, 128 and 256 queries, k = 10 and
-  100, and filtered by Zipf tenants (section V-C), selective and broad;
-* forced failures (all scores tied) in a pass of 64 queries, re-run on the
-  single-query path."""
+* the 10,000-row workload at 65, 100, 200 and 300 queries (the last a group of
+  256 and one of 44), k = 10 and 100;
+* a 70,037-row corpus (the last block is partial) at 65, 128 and 256 queries,
+  k = 10 and 100, and filtered by Zipf tenants (section V-C), selective and
+  broad;
+* forced failures (all scores tied) of 80 queries, re-run on the single-query
+  path, and fewer vectors than candidate slots."""
 import numpy as np
 import pytest
 
@@ -128,17 +125,16 @@ def test_filtered_pass(mid, mode):
 
 
 def test_tied_scores_fall_back(small_env):
-    """200,000 copies of one vector: every score ties, the pilot keeps more
-    tied vectors than its candidate room and the main launch overflows its
-    lists, so every query of the pass is re-run on the single-query path
-    (ties resolved by the lowest ids)."""
+    """200,000 copies of one vector: every score ties, more vectors than
+    candidates reach any threshold and no list is proven, so every query is
+    re-run on the single-query path (ties resolved by the lowest ids)."""
     e = small_env
     n = 200_000
     one = oracle.pack_codes(e.codes[:1], 4)
     idx = tq.Index(e.cb, e.rot, n_tenants=1)
     idx.add_codes(torch.from_numpy(one).cuda().expand(n, -1).contiguous(),
                   torch.from_numpy(e.scales[:1]).cuda().expand(n).contiguous())
-    Q = torch.cat([e.Qd, e.Qd[:16]]).contiguous()   # 80 queries: one wide pass
+    Q = torch.cat([e.Qd, e.Qd[:16]]).contiguous()   # 80 queries: three tiles
     ids, sc = idx.search(Q, 10, path="mfma")
     assert tq.last_search_fallbacks() == 80
     li, ls = idx.search(Q, 10, path="lut")
