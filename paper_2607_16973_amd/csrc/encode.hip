@@ -17,16 +17,17 @@
 //     unit roundoff, for additions that truncate), ||R_j|| <= 1 + 1e-6 and
 //     A = sum_k |R_jk x_k| <= n (1 + 1e-6), relative to n:
 //       xh Rh: 32 products per slab, added from 0 in any order: 33 u A
-//              (1 + 2^-10)^2; rounded to the integer unit, at most 2^-30 n,
-//              once per slab: d/32 2^-31;
+//              (1 + 2^-10)^2; rounded to the integer unit, at most 1.02 2^-30 n
+//              (n 2^e may be as small as 2^15 / 1.02), once per slab: d/32 1.02 2^-31;
 //       xh Rl + xl Rh: 2d products of which the absolute sum is at most
 //              2^-10 A (1 + 2^-10), in any order: (2d + 1) u 2^-10 (1 + 2^-9);
 //       xl Rl left out, and xl and Rl rounded: 2^-22 A each;
 //       parts below the smallest normal float16 (2^-14, 2^-29 relative to
-//              the scales) if the matrix cores flush them: 4 sqrt(d) 2^-29;
+//              the scales, 1.02 2^-29 for x) if the matrix cores flush them: 4.08
+//              sqrt(d) 2^-29;
 //       the float64 reference itself: < 3e-13; the float32 arithmetic of
 //              the epilogue: 5 2^-24.
-//     tau_rel sums these: 5.7e-6 at d = 1536.
+//     tau_rel sums these: 5.6e-6 at d = 1536.
 //  2. fixup: every flagged coordinate is recomputed as the sequential float64
 //     sum sum_{k=0}^{d-1} R[j][k] x_k (every product of two float32 values is
 //     exact in float64) and re-coded.  Flags are kept per list tile; with
@@ -67,9 +68,9 @@ constexpr int RC_PANEL = 32;            // rows of a split panel (an MFMA tile)
 double tau_rel(int d) {
     const double u = std::ldexp(1.0, -23);
     const double hh = 33 * u * (1 + std::ldexp(1.0, -10)) * (1 + std::ldexp(1.0, -10)) +
-                      (d / 32) * std::ldexp(1.0, -31);
+                      (d / 32) * 1.02 * std::ldexp(1.0, -31);
     const double small = (2 * d + 1) * u * std::ldexp(1.0, -10) * (1 + std::ldexp(1.0, -9));
-    const double rest = 3 * std::ldexp(1.0, -22) + 4 * std::sqrt((double)d) * std::ldexp(1.0, -29) + 3e-13 +
+    const double rest = 3 * std::ldexp(1.0, -22) + 4.08 * std::sqrt((double)d) * std::ldexp(1.0, -29) + 3e-13 +
                         5 * std::ldexp(1.0, -24);
     return (hh + small + rest) * (1 + 3e-6);
 }
