@@ -1658,12 +1658,12 @@ __global__ __launch_bounds__(WD_THREADS) void wide_scores_kernel(WideParams p) {
                 if (ld_i + 1 < my_tiles) ld_tile = tile_of(++ld_i);
             }
         };
+        static_assert(DHI == 3 && 2 * QT >= 4, "a wave's loads of a slab follow product groups 1, 2 and 3");
         auto request = [&]() {
             request_base();
             request_part(std::integral_constant<int, 0>());
-            if constexpr (DHI > 1) request_part(std::integral_constant<int, 1>());
-            if constexpr (DHI > 2) request_part(std::integral_constant<int, 2>());
-            static_assert(DHI <= 3, "at most three loads per wave and slab");
+            request_part(std::integral_constant<int, 1>());
+            request_part(std::integral_constant<int, 2>());
             request_done();
         };
         // until the oldest requested slab but `ahead` has landed
@@ -1876,10 +1876,8 @@ __global__ __launch_bounds__(WD_THREADS) void wide_scores_kernel(WideParams p) {
                             request_base();
                             request_part(std::integral_constant<int, 0>());
                         }
-                        if constexpr (DHI > 1)
-                            if (grp == 2) request_part(std::integral_constant<int, 1>());
-                        if constexpr (DHI > 2)
-                            if (grp == 3) request_part(std::integral_constant<int, 2>());
+                        if (grp == 2) request_part(std::integral_constant<int, 1>());
+                        if (grp == 3) request_part(std::integral_constant<int, 2>());
                         // the next slab's A operands, as soon as the tile's
                         // last product has been issued
                         if (ks == 1) {
@@ -1888,9 +1886,6 @@ __global__ __launch_bounds__(WD_THREADS) void wide_scores_kernel(WideParams p) {
                         }
                         __builtin_amdgcn_sched_barrier(0);
                     }
-                // loads that found no group after them
-                if constexpr (DHI > 1 && 2 * QT <= 2) request_part(std::integral_constant<int, 1>());
-                if constexpr (DHI > 2 && 2 * QT <= 3) request_part(std::integral_constant<int, 2>());
                 request_done();
             }
         };

@@ -366,7 +366,7 @@ __global__ __launch_bounds__(SR_THREADS) void split_rows_kernel(
 // Y = X R^T with the quantiser epilogue, for the encode.  WR x WC waves of TM
 // x TN tiles of 32 x 32 outputs:
 //  - both operands are split panels, staged by direct global -> LDS loads of
-//    1 KiB pieces into a ring of ST k-steps of 16, four k-steps ahead,
+//    1 KiB pieces into a ring of ST k-steps of 16, ST - 1 k-steps ahead,
 //    one barrier per k-step; operand reads are 16 bytes per lane at
 //    consecutive addresses;
 //  - three products per tile and k-step.  The integer fold of the previous
@@ -408,8 +408,8 @@ struct EgShape {
     static constexpr int PIECES = 2 * (RP + CP);         // 1 KiB pieces of a k-step
     static constexpr int PW = PIECES / WAVES;            // of which a wave loads
     static constexpr int STEP_B = PIECES * 1024;
-    static constexpr int SIDE = COLS;                    // list tiles are COLS x COLS
-    static constexpr int LISTS = ROWS / SIDE;            // of a workgroup
+    static constexpr int SIDE = COLS;                    // of a workgroup's outputs and list
+    static_assert(ROWS == COLS, "square tiles");
     static constexpr size_t lds = (size_t)ST * STEP_B + ROWS * 4 + EG_BINS * 8 + 8;
     static_assert(PIECES % WAVES == 0, "whole pieces per wave");
 };
@@ -426,7 +426,7 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void encode_gemm(
     char *stg = smem;
     float *inv_s = reinterpret_cast<float *>(smem + ST * S::STEP_B);      // [ROWS]
     float2 *bin_s = reinterpret_cast<float2 *>(inv_s + S::ROWS);                 // [EG_BINS]
-    unsigned int *nflag_s = reinterpret_cast<unsigned int *>(bin_s + EG_BINS);   // [LISTS]
+    unsigned int *nflag_s = reinterpret_cast<unsigned int *>(bin_s + EG_BINS);
 
     const int ncol = (d + S::COLS - 1) / S::COLS;
     int rt, ct;
@@ -479,7 +479,7 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void encode_gemm(
             const int i = up ? c : c - 1;
             bin_s[e] = make_float2((float)qa.bounds[i], __int_as_float(i));
         }
-    if (tid < S::LISTS) nflag_s[tid] = 0;
+    if (tid == 0) *nflag_s = 0;
     for (int r = tid; r < S::ROWS; r += S::THREADS) inv_s[r] = row0 + r < m ? qa.inv[row0 + r] : 0.f;
     wait_vmem<0>();   // the counts below are of the pieces alone
 #pragma unroll
@@ -536,7 +536,7 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void encode_gemm(
                                                           0, 0, 0);
     };
     // Publishes the k-step after the current one (own pieces landed, then
-    // everyone's) and requests the k-step five ahead into the stage of the
+    // everyone's) and requests the k-step ST - 1 ahead into the stage of the
     // previous one, which every wave is past.  Operand reads in flight need
     // not complete here: their stage is not written before the next
     // publication but one.
@@ -606,8 +606,7 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void encode_gemm(
     }
 
     const int lrow = wr * 32 * TM;                 // the wave's first row in the workgroup's tile
-    const int list = lrow / S::SIDE;
-    const int64_t tile = ((int64_t)rt * S::LISTS + list) * ncol + ct;
+    const int64_t tile = (int64_t)rt * ncol + ct;
     uint16_t *tflags = qa.flags + tile * (S::SIDE * S::SIDE);
     // Code and flag of the lane's 16 outputs of a tile (one column, 16 rows),
     // from z = y / n in float32: the float32 rounding of the two sums, of
@@ -639,7 +638,7 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void encode_gemm(
             if (inv_s[r] == 0.f)   // a zero row
                 cbase[(uint32_t)(r * d + lc)] = (uint8_t)(L / 2);
             else
-                tflags[atomicAdd(&nflag_s[list], 1u)] = (uint16_t)(((r - list * S::SIDE) << 7) | lc);
+                tflags[atomicAdd(nflag_s, 1u)] = (uint16_t)((r << 7) | lc);
         }
     };
     if (!qa.athr) {
@@ -672,8 +671,7 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void encode_gemm(
             for (int tj = 0; tj < TN; ++tj) epilogue(ti, tj, find);
     }
     __syncthreads();
-    if (tid < S::LISTS && row0 + tid * S::SIDE < m)
-        qa.tile_count[((int64_t)rt * S::LISTS + tid) * ncol + ct] = nflag_s[tid];
+    if (tid == 0) qa.tile_count[tile] = *nflag_s;
 }
 
 // The code of coordinate j of a row with norm nrm whose exact sum is S.
@@ -956,18 +954,18 @@ __global__ __launch_bounds__(256) void pack_rows_kernel(
 constexpr int PACK_ROWS = 32;   // PACK_ROWS * (d + 16) bytes of LDS (66 KiB at d = 2048)
 
 __global__ __launch_bounds__(256) void pack_kernel(
-    const uint8_t *__restrict__ codes_tmp, const float *__restrict__ X, int64_t m, int d, int bits,
+    const uint8_t *__restrict__ codes_tmp, const float *__restrict__ X, int64_t m, int d,
     const double *__restrict__ cent_sq, const double *__restrict__ ysq,
     const double *__restrict__ norms,
     uint8_t *__restrict__ canon, float *__restrict__ scales,
     uint8_t *__restrict__ blocked, float *__restrict__ blocked_scales, int64_t base,
     int chunks) {
     extern __shared__ __attribute__((aligned(16))) uint8_t cs_raw[];   // [PACK_ROWS][d + 16]
-    __shared__ double csq_s[256];
+    __shared__ double csq_s[8];
     const int64_t r0 = (int64_t)blockIdx.x * PACK_ROWS;
     const int rows = (int)((m - r0) < PACK_ROWS ? (m - r0) : PACK_ROWS);
     const int tid = threadIdx.x;
-    const int L = 1 << bits;
+    constexpr int L = 8;
     const int ps = d + 16;           // LDS row stride
     if (!ysq)
         for (int i = tid; i < L; i += blockDim.x) csq_s[i] = cent_sq[i];
@@ -1020,24 +1018,19 @@ __global__ __launch_bounds__(256) void pack_kernel(
         if (blocked_scales) blocked_scales[base + r0 + tid] = s;
     }
     // canonical rows: 32-bit words, bits LSB-first
-    const int wpr = d * bits / 32;   // words per canonical row
+    const int wpr = d * 3 / 32;   // words per canonical row
     if (canon) {
         for (int e = tid; e < rows * wpr; e += blockDim.x) {
             const int r = e / wpr, w = e % wpr;
             const uint8_t *c = cs_raw + r * ps;
             uint32_t word = 0;
-            if (bits == 3) {
-                const int b0 = w * 32;
-                for (int t = 0; t < 32; ++t) {
-                    const int bit = b0 + t;
-                    const int j = bit / 3, sh = bit % 3;
-                    word |= (uint32_t)((c[j] >> sh) & 1) << t;
-                }
-            } else {
-                const int per = 32 / bits;
-                for (int t = 0; t < per; ++t) word |= (uint32_t)c[w * per + t] << (t * bits);
+            const int b0 = w * 32;
+            for (int t = 0; t < 32; ++t) {
+                const int bit = b0 + t;
+                const int j = bit / 3, sh = bit % 3;
+                word |= (uint32_t)((c[j] >> sh) & 1) << t;
             }
-            reinterpret_cast<uint32_t *>(canon + (r0 + r) * (int64_t)(d * bits / 8))[w] = word;
+            reinterpret_cast<uint32_t *>(canon + (r0 + r) * (int64_t)(d * 3 / 8))[w] = word;
         }
     }
     // blocked layout: 16-byte chunk ch of vector v at ((v/64)*chunks + ch)*1024 + (v%64)*16
@@ -1047,17 +1040,10 @@ __global__ __launch_bounds__(256) void pack_kernel(
             const int ch = rem >> 2, wq = rem & 3;
             const uint8_t *c = cs_raw + r * ps;
             uint32_t word = 0;
-            if (bits == 3) {
-                const int j0 = (ch * 4 + wq) * 10;
-                for (int t = 0; t < 10; ++t) {
-                    const int j = j0 + t;
-                    if (j < d) word |= (uint32_t)c[j] << (3 * t);
-                }
-            } else {
-                const int per = 32 / bits;
-                const int j0 = (ch * 4 + wq) * per;
-                for (int t = 0; t < per; ++t) word |= (uint32_t)c[j0 + t] << (t * bits);
-                if (blocked_rotated(bits)) word = rotl2(word);
+            const int j0 = (ch * 4 + wq) * 10;
+            for (int t = 0; t < 10; ++t) {
+                const int j = j0 + t;
+                if (j < d) word |= (uint32_t)c[j] << (3 * t);
             }
             const int64_t v = base + r0 + r;
             uint8_t *dst = blocked + ((v >> 6) * chunks + ch) * 1024 + (v & 63) * 16;
@@ -1142,7 +1128,7 @@ __global__ __launch_bounds__(SPLIT_WAVES * 64) void rot_small_kernel(
 // Tiles of 32 x 32 outputs, four waves with a 16 x 16 block each, so that a few
 // hundred rows fill the chip: 256 rows at d = 1536 are 384 workgroups instead
 // of 24.  Slabs of 32 k come by direct global -> LDS loads into a ring of
-// RM_STAGES, four slabs ahead, one barrier per slab.  A 1 KiB piece holds 8
+// RM_STAGES, five slabs ahead, one barrier per slab.  A 1 KiB piece holds 8
 // rows of 8 16-byte quads, quad q of row r at place q ^ r, so that a read of
 // one quad of 8 consecutive rows meets distinct banks.
 constexpr int kMidRows = 2048;
@@ -1370,7 +1356,7 @@ hipError_t encode_rows(const float *X, int64_t n, int d, const float *R, const v
         if (cb.bits == 3) {
             const int packs = (int)((m + PACK_ROWS - 1) / PACK_ROWS);
             hipLaunchKernelGGL(pack_kernel, dim3(packs), dim3(256), PACK_ROWS * (d + 16), stream,
-                               codes_tmp, X + r0 * d, m, d, cb.bits, cent_sq, calib.ysq, norms, canon_p, scales_p,
+                               codes_tmp, X + r0 * d, m, d, cent_sq, calib.ysq, norms, canon_p, scales_p,
                                out.blocked, out.blocked_scales, out.base + r0, chunks);
         } else if (cb.bits == 1) {
             hipLaunchKernelGGL(pack_rows_kernel<1>, prow, dim3(256), 0, stream, codes_tmp, X + r0 * d, m, d, cent_sq,
