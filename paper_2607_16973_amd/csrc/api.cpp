@@ -1119,15 +1119,18 @@ static int scan_grid() {
 // Whether TQ_PATH_AUTO answers nq queries on the batched path (same scores
 // and lists as the scan's, queries without a certificate re-run on the scan
 // within the call's launches).  Both read the codes at about 5 TB/s: the scan
-// once per query, with 9 us (8 bits: 15 us) of table build and merge each and
-// about 20 us more for the first; the batched path once per tile of 32
-// queries, with 55 us of query preparation, selection and rescoring for a
-// group of 8 tiles.  Measured at k = 10 in us a call, scan / batched: d =
+// once per query, with 9 us of table build and merge each (7 measured; 8 bits:
+// 8 at d = 256 to 25 at d = 1536, 15 taken) and about 20 us more for the first;
+// the batched path once per tile of 32 queries, with 55 us of query preparation,
+// selection and rescoring for a group of 8 tiles (256 MiB of scores; the groups
+// are smaller above 500,000 vectors, where the reading decides).  Measured
+// at k = 10 in us a call, scan / batched: d =
 // 1536, 4 bits, 20,000 vectors 58 / 65 for 3 queries, 69 / 65 for 4; 100,000
 // vectors 82 / 77 for 2, 102 / 77 for 3; 1,000,000 vectors 170 / 231 for 1,
 // 300 / 229 for 2.  d = 256, 30,000 vectors 44 / 49 for 3, 67 / 49 for 6.
 // 2 bits, 500,000 vectors 160 / 114 for 2; 3 bits, d = 256, 350,000 vectors
-// 116 / 58 for 2.
+// 116 / 58 for 2.  8 bits, 16,000 vectors, 16 queries 154 / 48 at d = 256, 508 /
+// 72 at d = 1536.
 static bool batch_pays(const ScanShape &sh, int64_t nq) {
     const double pass_us = (double)sh.nblk * sh.chunks * 1024.0 / 5.0e6;
     const double tiles = (double)((nq + 31) / 32);

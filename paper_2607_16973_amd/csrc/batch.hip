@@ -2598,9 +2598,19 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    // the scan of a pass's queries against the pass (see Gate; the explicit
-    // path always runs the pass): the scan reads at about 5 TB/s, a tile too
-    // (unions only), a wide pass multiplies 1.0 to 1.35 MB of codes a us
+    // The scan of a pass's queries against the pass (see Gate; the explicit
+    // path always runs the pass).  Both read 5 MB a us, a tile the union's
+    // blocks only.  Measured at 16,000 vectors, d = 1536, k = 10, in us:
+    //  - the scan, a query: 12 (8 bits 31) where every workgroup has a block of
+    //    it and builds its table, 2.5 and 5 of that reading; 6 (2.8) where few
+    //    have one, one tenant of 16 neighbours.  9 and 30 lean to the pass,
+    //    which costs the same whatever the allowlists;
+    //  - the tiles of 32, 64 and 256 queries with one tenant each: 73, 80 and 90
+    //    (8 bits 95, 101, 112), 15 of them for the rotation and the scan's own
+    //    launches.  58 (83) shared by the tiles of the group and 8 a tile more
+    //    are 4 a tile too many;
+    //  - a wide pass: 930 and 255 a call of 256 queries at 1,000,000 vectors, d =
+    //    1536 (768 MB) and 256 (128 MB): 150 and 1 a MB.
     const double block_bytes = s.chunks * 1024.0;
     auto gate_of = [&](int QP, int tiles) {
         Gate g{};
@@ -2612,7 +2622,7 @@ hipError_t mfma_search(const ScanShape &s, const uint8_t *blocked, const float *
             g.pass_us = (s.bits == 8 ? 83.f : 58.f) / tiles + (tiles > 1 ? 8.f : 0.f);
             g.read_us = g.block_us;
         } else {
-                g.pass_us = (float)(150.0 + (double)s.nblk * block_bytes / 1.0e6);
+            g.pass_us = (float)(150.0 + (double)s.nblk * block_bytes / 1.0e6);
         }
         return g;
     };
