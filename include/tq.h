@@ -106,10 +106,9 @@ void tq_rotation_free(tq_rotation *rot);
  *            a boundary goes to the upper cell; a zero row codes to L/2);
  *   scale  = n_x / ||c[code]|| (float64, stored float32): the per-vector
  *            length-renormalisation scalar; 0 for a zero row.
- * The rotation runs on the matrix cores (float32 MFMA with float64
- * accumulation); coordinates whose MFMA value lies within a proven error
- * bound of a boundary are recomputed exactly, so the codes equal the
- * definition above bit for bit.
+ * The rotation runs on the matrix cores (products of float16 parts); coordinates
+ * whose value there lies within a proven error bound of a boundary are
+ * recomputed exactly, so the codes equal the definition above bit for bit.
  * Outputs: codes_dev [n][d*bits/8] bytes in the canonical layout (one
  * little-endian bitstream per row, coordinate j at bits [bits*j, bits*j +
  * bits), least significant bit first); scales_dev [n] float32.
@@ -196,8 +195,7 @@ tq_status tq_index_info(const tq_index *idx, int32_t *d, int32_t *bits,
  * on an index with no vectors.
  * calibration(): copies the installed values to mu_host, kappa_host (either
  * may be NULL) and sets *calibrated to 1, or sets it to 0 and copies nothing.
- * A calibrated index is searched by the scans only: TQ_PATH_MFMA is
- * TQ_EUNSUPPORTED on it. */
+ * TQ_PATH_MFMA is TQ_EUNSUPPORTED on a calibrated index. */
 tq_status tq_index_calibrate(tq_index *idx, const float *X_dev, int64_t m, void *stream);
 tq_status tq_index_set_calibration(tq_index *idx, const float *mu_host, const float *kappa_host);
 tq_status tq_index_calibration(const tq_index *idx, float *mu_host, float *kappa_host,
@@ -238,9 +236,9 @@ void tq_index_free(tq_index *idx);
  * scan (section III-B).  Searches return the external ids (uint64 bit
  * patterns in the int64 output; 2^64-1 is reserved, so -1 still marks
  * padding).  tq_index_add / tq_index_add_codes are TQ_EINVAL on it.  The
- * search, export, save and load calls work on both index types; an id-map
- * index with deleted vectors, or a search with a slot allowlist, always runs
- * the single-query scan (TQ_PATH_MFMA is TQ_EUNSUPPORTED then). */
+ * search, export, save and load calls work on both index types.  A search with
+ * a slot allowlist always runs the single-query scan; with one, or on an id-map
+ * index with deleted vectors, TQ_PATH_MFMA is TQ_EUNSUPPORTED. */
 tq_status tq_idmap_create(const tq_codebook *cb, const tq_rotation *rot,
                           int32_t n_tenants, tq_index **out);
 
@@ -331,10 +329,11 @@ tq_status tq_search_postfilter(const tq_index *idx, const float *Q_dev,
  *                TQ_PATH_LUT) is accepted and selects it.
  *  TQ_PATH_LUT   one pass over the code store per query, with the query's
  *                lookup table in LDS.
- *  TQ_PATH_MFMA  one pass per tile of 32 queries: approximate float16 scores
- *                on the matrix cores select 256 candidates per query (512
- *                for k > 64), which are rescored exactly (the same scores as
- *                TQ_PATH_LUT).  A
+ *  TQ_PATH_MFMA  one pass per tile of 32 queries, or per 256 queries over a
+ *                large index: approximate float16 scores on the matrix cores
+ *                select 64 to 512 candidates per query (eight per result), of
+ *                which those that can be in the top k are rescored exactly
+ *                (the same scores as TQ_PATH_LUT).  A
  *                per-query certificate -- a rigorous bound on the
  *                approximation error -- proves that the exact top k lies
  *                among the candidates; queries without one are re-run on the
@@ -380,7 +379,8 @@ tq_status tq_search_ex(const tq_index *idx, const float *Q_dev, int64_t nq,
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): tq_search
  * with the same arguments, meaning, layout and results (the single-query
- * scan), whose workspace is a device array of TQ_NOALLOC_SCRATCH_BYTES held
+ * scan), whose workspace is a device array of TQ_NOALLOC_SCRATCH_BYTES (and, for
+ * k > 256, 96 KiB for one query's selection that are not counted) held
  * by the library (one per GPU, kept until the process ends) instead of a
  * per-call allocation.  It calls no device allocation or free.
  * Queries are taken in as many consecutive launches as the array needs; a
